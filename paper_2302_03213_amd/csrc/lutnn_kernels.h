@@ -68,6 +68,13 @@ hipError_t launch_softpq_backward(const float* P, int C, int K, int V, float t, 
                                   int64_t ldx, const float* Z, int64_t ldz, float* dP, float* dX,
                                   int64_t lddx, float* dt, float* workspace, hipStream_t s);
 
+// The same on the fp32 matrix instructions (softpq_matrix.hip), for the sub-vector lengths where that is faster.
+bool softpq_matrix_preferred(int K, int V);
+size_t softpq_matrix_workspace_bytes(int C, int K, int V, int64_t N);
+hipError_t launch_softpq_matrix(const float* P, int C, int K, int V, float t, const float* X, int64_t N, int64_t ldx,
+                                const float* Z, int64_t ldz, float* dP, float* dX, int64_t lddx, float* dt,
+                                float* workspace, hipStream_t s);
+
 hipError_t launch_encode_tree_conv(const int32_t* split_dim, const float* threshold, int C, int levels,
                                    int V, const float* input, int64_t B, const ConvGeom& g, uint8_t* idx,
                                    hipStream_t s);

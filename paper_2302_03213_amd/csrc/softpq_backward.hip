@@ -1,4 +1,5 @@
-// Soft-PQ backward pass (arXiv 2302.03213, Sec. 3.1-3.2, Eq. 5-6) for gfx950.
+// Soft-PQ backward pass (arXiv 2302.03213, Sec. 3.1-3.2, Eq. 5-6) for gfx950: the form on the vector units, for short
+// sub-vectors and K = 8 (softpq_matrix.hip has the rest).
 //
 // Training replaces the one-hot arg-min encoding by a softmax over the same K squared distances
 // (Eq. 5) in the backward pass only (Eq. 6: value of the hard output, gradient of the soft one):
@@ -360,11 +361,13 @@ auto by_v(int V, F&& f) {
         case 1: return f(std::integral_constant<int, 1>{});
         case 2: return f(std::integral_constant<int, 2>{});
         case 3: return f(std::integral_constant<int, 3>{});
-        case 4: return f(std::integral_constant<int, 4>{});
-        case 8: return f(std::integral_constant<int, 8>{});
-        case 9: return f(std::integral_constant<int, 9>{});
-        case 16: return f(std::integral_constant<int, 16>{});
-        default: return f(std::integral_constant<int, 32>{});
+        case 8:
+            if constexpr (K_T == 8) return f(std::integral_constant<int, 8>{});
+            [[fallthrough]];
+        case 9:
+            if constexpr (K_T == 8) return f(std::integral_constant<int, 9>{});
+            [[fallthrough]];
+        default: return f(std::integral_constant<int, 4>{});
     }
 }
 
@@ -375,6 +378,7 @@ bool softpq_supported(int K, int V) { return (K == 8 || K == 16) && enc_tile_cod
 
 size_t softpq_workspace_bytes(int C, int K, int V, int64_t N) {
     if (!softpq_supported(K, V) || C <= 0 || N <= 0) return 0;
+    if (softpq_matrix_preferred(K, V)) return softpq_matrix_workspace_bytes(C, K, V, N);
     if (K == 16) return by_v<16>(V, [&](auto v) { return workspace_bytes_for<decltype(v)::value, 16>(C, N); });
     return by_v<8>(V, [&](auto v) { return workspace_bytes_for<decltype(v)::value, 8>(C, N); });
 }
@@ -383,6 +387,8 @@ hipError_t launch_softpq_backward(const float* P, int C, int K, int V, float t, 
                                   int64_t ldx, const float* Z, int64_t ldz, float* dP, float* dX,
                                   int64_t lddx, float* dt, float* workspace, hipStream_t s) {
     if (!softpq_supported(K, V)) return hipErrorInvalidValue;
+    if (softpq_matrix_preferred(K, V))
+        return launch_softpq_matrix(P, C, K, V, t, X, N, ldx, Z, ldz, dP, dX, lddx, dt, workspace, s);
     if (K == 16)
         return by_v<16>(V, [&](auto v) {
             return launch_softpq<decltype(v)::value, 16>(P, C, t, X, N, ldx, Z, ldz, dP, dX, lddx, dt, workspace, s);

@@ -269,3 +269,27 @@ def test_softpq_backward_on_a_random_shape(lut, seed):
     N, C, K, V, M, t = draw_softpq_shape(seed)
     print("seed %d: N=%d C=%d K=%d V=%d M=%d t=%.3f" % (seed, N, C, K, V, M, t), file=sys.stderr, flush=True)
     run_case(lut, N, C, K, V, M, t, seed=900 + seed, strided=bool(seed & 1))
+
+
+@pytest.mark.parametrize("N,C,K,V,M,t", [
+    # the matrix form: rows and codebooks at the edges of its 64-row, four-codebook tiles, both K, every V
+    (65, 5, 16, 9, 7, 1.0), (1, 1, 16, 32, 3, 4.0), (129, 6, 8, 16, 5, 2.0), (63, 3, 16, 8, 6, 1.0),
+    (191, 9, 8, 32, 4, 8.0), (16, 4, 16, 16, 5, 1.0),
+    # more row tiles than chunks: several tiles per chunk, the last chunk shorter
+    (19300, 4, 16, 8, 4, 1.0), (16500, 3, 8, 16, 4, 2.0),
+])
+@pytest.mark.parametrize("offset", [0.0, 30.0])
+def test_matrix_form_tile_edges(lut, N, C, K, V, M, t, offset):
+    """A common offset of activations and centroids changes no gradient but dL/dW's; the bar stays that of the file
+    although the values are thirty times the differences, because only differences enter the sums: the distances
+    directly, the products after the codebook's mean is taken off (one rounding of 2^-24 of a difference)."""
+    w = wl.make_layer("t", N, C, K, V, M, "f32", seed=N)
+    X, P = (w.X + np.float32(offset)).astype(np.float32), (w.P + np.float32(offset)).astype(np.float32)
+    G = np.random.default_rng(N).standard_normal((N, M))
+    Z = (G @ w.W.astype(np.float64).T).astype(np.float32)
+    dP_ref, dX_ref, _ = osp.backward(P, w.W, X, t, G)
+    layer = lut.LutLayer(dev(P), None, lut.TABLE_F32, M)
+    dP, dX, _ = lut.softpq_backward(layer, t, dev(X), dev(Z))
+    # the oracle's A = z . P carries the offset exactly (fp64); the kernel's does not see it
+    close(host(dP), dP_ref)
+    close(host(dX), dX_ref)
