@@ -365,6 +365,27 @@ LUTNN_API lutnn_status lutnn_conv2d(const lutnn_layer* layer, const float* input
                                     int32_t variant, uint8_t* idx_workspace, void* stream);
 
 /*
+ * lutnn_softpq_backward for a convolution, on the rows of the im2col matrix of `input`, which is never written:
+ * gradients of the soft output for the centroids, the temperature and the image.
+ *
+ *   input   [B][Cin][H][W] fp32, dense (the forward pass's input)
+ *   W       [D][M] fp32 row-major, row stride ldw >= M, D = Cin*kh*kw (as lutnn_build_table)
+ *   G       [B][M][Ho][Wo] fp32, dense: dL/dY
+ *   Z       [B][D][Ho*Wo] fp32 device scratch: receives W . G per image, the im2col gradient of the ordinary
+ *           convolution, and then dL/dX of the rows; contents unspecified afterwards
+ *   dP      [C][K][V] fp32, overwritten
+ *   dinput  [B][Cin][H][W] fp32, overwritten; NULL to skip it
+ *   dt      one fp32, overwritten; NULL to skip it
+ *   workspace  at least lutnn_softpq_workspace_bytes(C, K, V, N) bytes, N = lutnn_conv2d_rows(geom, B)
+ * Needs Cin*kh*kw == C*V, V in {1, 2, 3, 4, 8, 9, 16} and K = 8 or 16.
+ * Errors: as lutnn_softpq_backward and lutnn_encode_conv2d.
+ */
+LUTNN_API lutnn_status lutnn_softpq_backward_conv2d(const lutnn_layer* layer, float temperature, const float* input,
+                                                    int64_t B, const lutnn_conv2d_geom* geom, const float* W,
+                                                    int64_t ldw, const float* G, float* Z, float* dP, float* dinput,
+                                                    float* dt, void* workspace, size_t workspace_bytes, void* stream);
+
+/*
  * The hash encoder on a convolution's rows (lutnn_encode_tree on the im2col matrix of `input`,
  * which is never written; row and column order as for lutnn_encode_conv2d), and the whole
  * convolution with it: lutnn_encode_tree_conv2d into idx_workspace, then lutnn_lookup.

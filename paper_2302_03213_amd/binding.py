@@ -30,7 +30,7 @@ VARIANTS = {"auto": VARIANT_AUTO, "lds": VARIANT_LDS, "mfma": VARIANT_MFMA, "fus
 EXPORTS = ["lutnn_softpq_backward_static", "lutnn_set_tunable", "lutnn_encode_tree16", "lutnn_lookup16",
            "lutnn_linear_tree16", "lutnn_table_bytes", "lutnn_packed_bytes", "lutnn_build_table", "lutnn_encode",
            "lutnn_lookup", "lutnn_linear", "lutnn_encode_tree", "lutnn_linear_tree",
-           "lutnn_softpq_backward", "lutnn_softpq_workspace_bytes",
+           "lutnn_softpq_backward", "lutnn_softpq_backward_conv2d", "lutnn_softpq_workspace_bytes",
            "lutnn_encode_tree_conv2d", "lutnn_conv2d_tree", "lutnn_conv2d_rows", "lutnn_encode_conv2d", "lutnn_conv2d",
            "lutnn_auto_variant", "lutnn_linear_auto_variant", "lutnn_status_string", "lutnn_last_error", "lutnn_version",
            "lutnn_probe_smfmac_stream"]
@@ -110,6 +110,10 @@ def _load():
     lib.lutnn_softpq_backward_static.restype = i32
     lib.lutnn_softpq_backward_static.argtypes = [ctypes.POINTER(_CLayer), ctypes.c_float, vp, i64, i64, vp, i64,
                                                  vp, vp, i64, vp, vp]
+    lib.lutnn_softpq_backward_conv2d.restype = i32
+    lib.lutnn_softpq_backward_conv2d.argtypes = [ctypes.POINTER(_CLayer), ctypes.c_float, vp, i64,
+                                                 ctypes.POINTER(_CConvGeom), vp, i64, vp, vp, vp, vp, vp, vp, ctypes.c_size_t,
+                                                 vp]
     lib.lutnn_encode_tree_conv2d.restype = i32
     lib.lutnn_encode_tree_conv2d.argtypes = [ctypes.POINTER(_CTree), vp, i64, ctypes.POINTER(_CConvGeom), vp, vp]
     lib.lutnn_conv2d_tree.restype = i32
@@ -403,6 +407,28 @@ def conv_geom(inp, kernel, stride=1, pad=0):
 
 def conv2d_rows(geom, B):
     return int(LIB.lutnn_conv2d_rows(ctypes.byref(geom), B))
+
+
+def softpq_backward_conv2d(layer, temperature, inp, W, G, kernel, stride=1, pad=0, need_dx=True):
+    """lutnn_softpq_backward_conv2d: the gradients for a convolution from the image batch, the weights W [D, M] and
+    G = dL/dY [B, M, Ho, Wo].  Returns (dP [C, K, V], dinput like inp or None, dt [1])."""
+    assert inp.is_cuda and inp.dtype == torch.float32 and inp.is_contiguous() and inp.dim() == 4
+    assert W.is_cuda and W.dtype == torch.float32 and W.stride(1) == 1 and W.shape == (layer.D, layer.M)
+    geom = conv_geom(inp, kernel, stride, pad)
+    N = conv2d_rows(geom, inp.shape[0])
+    if N < 0:
+        raise ValueError("invalid convolution geometry")
+    assert G.is_cuda and G.dtype == torch.float32 and G.is_contiguous() and G.numel() == N * layer.M
+    dP = torch.empty((layer.C, layer.K, layer.V), dtype=torch.float32, device=inp.device)
+    dinp = torch.empty_like(inp) if need_dx else None
+    dt = torch.empty(1, dtype=torch.float32, device=inp.device)
+    Z = torch.empty(N * layer.D, dtype=torch.float32, device=inp.device)
+    workspace = torch.empty(max(softpq_workspace_bytes(layer.C, layer.K, layer.V, N), 4), dtype=torch.uint8,
+                            device=inp.device)
+    _check(LIB.lutnn_softpq_backward_conv2d(ctypes.byref(layer.c), float(temperature), _ptr(inp), inp.shape[0],
+                                            ctypes.byref(geom), _ptr(W), W.stride(0), _ptr(G), _ptr(Z), _ptr(dP),
+                                            _ptr(dinp), _ptr(dt), _ptr(workspace), workspace.numel(), _stream()))
+    return dP, dinp, dt
 
 
 def encode_conv2d(layer, inp, kernel, stride=1, pad=0, out=None):

@@ -395,10 +395,9 @@ lutnn_status softpq_backward_checked(const lutnn_layer* layer, float temperature
         return fail(LUTNN_E_ALIGN, "Z, dP, dX, dt and workspace must be 4-byte aligned");
     hipStream_t s = static_cast<hipStream_t>(stream);
     // N == 0: the launcher only writes the zeros of the empty sums
-    return hip_result(lutnn::launch_softpq_backward(layer->centroids, layer->C, layer->K, layer->V, temperature,
-                                                    X, N, ldx, Z, ldz, dP, dX, lddx, dt,
-                                                    static_cast<float*>(workspace), s),
-                      "soft-PQ backward launch");
+    const lutnn::SoftPqCall call = {layer->centroids, layer->C, layer->K, layer->V, temperature, X, N, ldx, Z, ldz,
+                                    dP, dX, lddx, dt, static_cast<float*>(workspace), nullptr};
+    return hip_result(lutnn::launch_softpq_backward(call, s), "soft-PQ backward launch");
 }
 
 }  // namespace
@@ -797,6 +796,45 @@ lutnn_status lutnn_conv2d_tree(const lutnn_layer* layer, const lutnn_tree* tree,
     if (lutnn_status st = check_lookup(layer, v, idx_workspace, Y, N, ldy)) return st;
     if (lutnn_status st = lutnn_encode_tree_conv2d(tree, input, B, geom, idx_workspace, stream)) return st;
     return do_lookup(layer, v, idx_workspace, N, Y, ldy, static_cast<hipStream_t>(stream));
+}
+
+lutnn_status lutnn_softpq_backward_conv2d(const lutnn_layer* layer, float temperature, const float* input, int64_t B,
+                                          const lutnn_conv2d_geom* geom, const float* W, int64_t ldw, const float* G,
+                                          float* Z, float* dP, float* dinput, float* dt, void* workspace,
+                                          size_t workspace_bytes, void* stream) {
+    if (lutnn_status st = check_layer(layer)) return st;
+    lutnn::ConvGeom g;
+    int64_t N = 0;
+    if (lutnn_status st = check_conv(layer, geom, B, &g, &N)) return st;
+    if (!(temperature > 0.0f) || !std::isfinite(temperature))
+        return fail(LUTNN_E_SHAPE, "temperature must be positive and finite (got %g)", (double)temperature);
+    if (!lutnn::softpq_supported(layer->K, layer->V))
+        return fail(LUTNN_E_UNSUPPORTED, "soft-PQ backward supports K in {8,16} (got K=%d V=%d)", layer->K, layer->V);
+    if (!dP) return fail(LUTNN_E_NULL, "dP is NULL");
+    if (N > 0) {
+        if (lutnn_status st = check_conv_input(layer, input)) return st;
+        if (!W || !G || !Z) return fail(LUTNN_E_NULL, "W, G or Z is NULL");
+        if (ldw < layer->M) return fail(LUTNN_E_SHAPE, "ldw=%lld is smaller than M=%d", (long long)ldw, layer->M);
+        if (!workspace) return fail(LUTNN_E_NULL, "workspace is NULL");
+        const size_t need = lutnn::softpq_workspace_bytes(layer->C, layer->K, layer->V, N);
+        if (workspace_bytes < need)
+            return fail(LUTNN_E_SHAPE, "workspace of %zu bytes is smaller than the %zu this shape needs", workspace_bytes, need);
+    }
+    if (!aligned(W, 4) || !aligned(G, 4) || !aligned(Z, 4) || !aligned(dP, 4) || !aligned(dinput, 4) || !aligned(dt, 4) || !aligned(workspace, 4))
+        return fail(LUTNN_E_ALIGN, "W, G, Z, dP, dinput, dt and workspace must be 4-byte aligned");
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    // one tap at stride 1 without padding: the columns are the image's channels, and nothing has to be folded
+    const bool plain = g.kh * g.kw == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0;
+    float* columns = !dinput ? nullptr : plain ? dinput : Z;
+    if (N > 0)
+        if (lutnn_status st = hip_result(lutnn::launch_conv_z(W, ldw, G, B, layer->C * layer->V, layer->M, g, Z, s),
+                                         "convolution gradient launch"))
+            return st;
+    const lutnn::SoftPqCall call = {layer->centroids, layer->C, layer->K, layer->V, temperature, input, N, 0, Z, 0,
+                                    dP, columns, 0, dt, static_cast<float*>(workspace), &g};
+    if (lutnn_status st = hip_result(lutnn::launch_softpq_backward(call, s), "soft-PQ backward launch")) return st;
+    if (!dinput || plain || N == 0) return LUTNN_OK;
+    return hip_result(lutnn::launch_fold(Z, B, g, dinput, s), "fold launch");
 }
 
 lutnn_status lutnn_conv2d(const lutnn_layer* layer, const float* input, int64_t B,

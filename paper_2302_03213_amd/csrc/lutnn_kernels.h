@@ -64,16 +64,32 @@ hipError_t launch_lookup_wide_f32(const float* T, const float* bias, int C, int 
 // input and the temperature, from Z = dL/dY . W^T.  workspace: softpq_workspace_bytes() bytes.
 bool softpq_supported(int K, int V);
 size_t softpq_workspace_bytes(int C, int K, int V, int64_t N);
-hipError_t launch_softpq_backward(const float* P, int C, int K, int V, float t, const float* X, int64_t N,
-                                  int64_t ldx, const float* Z, int64_t ldz, float* dP, float* dX,
-                                  int64_t lddx, float* dt, float* workspace, hipStream_t s);
+struct SoftPqCall {
+    const float* P;
+    int C, K, V;
+    float t;
+    const float* X;  // [N][D] rows - or, with geom, the NCHW batch whose im2col rows they are
+    int64_t N, ldx;
+    const float* Z;  // [N][D] rows; with geom [B][D][Ho*Wo]
+    int64_t ldz;
+    float *dP, *dX;  // dX as Z (and with geom it may be Z), or NULL
+    int64_t lddx;
+    float *dt, *workspace;
+    const ConvGeom* geom;
+};
+hipError_t launch_softpq_backward(const SoftPqCall& a, hipStream_t s);
+
+// Z[b][d][l] = sum_m W[d][m] G[b][m][l]: the im2col gradient of the ordinary convolution with weights W.
+hipError_t launch_conv_z(const float* W, int64_t ldw, const float* G, int64_t B, int D, int M, const ConvGeom& g, float* Z,
+                         hipStream_t s);
+
+// [B][D][Ho*Wo] gradients of the im2col rows back onto the image: every input element sums its taps in order.
+hipError_t launch_fold(const float* columns, int64_t B, const ConvGeom& g, float* image, hipStream_t s);
 
 // The same on the fp32 matrix instructions (softpq_matrix.hip), for the sub-vector lengths where that is faster.
 bool softpq_matrix_preferred(int K, int V);
 size_t softpq_matrix_workspace_bytes(int C, int K, int V, int64_t N);
-hipError_t launch_softpq_matrix(const float* P, int C, int K, int V, float t, const float* X, int64_t N, int64_t ldx,
-                                const float* Z, int64_t ldz, float* dP, float* dX, int64_t lddx, float* dt,
-                                float* workspace, hipStream_t s);
+hipError_t launch_softpq_matrix(const SoftPqCall& a, hipStream_t s);
 
 hipError_t launch_encode_tree_conv(const int32_t* split_dim, const float* threshold, int C, int levels,
                                    int V, const float* input, int64_t B, const ConvGeom& g, uint8_t* idx,

@@ -30,7 +30,7 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "encode_tile.h"
+#include "conv_rows.h"
 #include "lutnn_kernels.h"
 
 namespace lutnn {
@@ -102,12 +102,13 @@ struct SoftPq {
 // grid: chunks * col_tiles workgroups, column tile fastest.
 //   partial    [chunks][C][NG*64] sums of the dP contributions over the chunk's rows
 //   partial_dt [gridDim.x] one sum of dz_k * d_k per workgroup
-template <int V, int K_T>
+//   CONV != 0  X is an NCHW image batch (CONV filter taps, -1 = any filter), Z and dX are [B][D][Ho*Wo] arrays,
+//              which may be the same one
+template <int V, int K_T, int CONV>
 __global__ __launch_bounds__(kEncThreads) void softpq_backward_kernel(
-    const float* __restrict__ X, int64_t ldx, const float* __restrict__ Z, int64_t ldz,
-    const float* __restrict__ P, float inv_t, float* __restrict__ dX, int64_t lddx,
-    float* __restrict__ partial, float* __restrict__ partial_dt, int64_t N, int C, int tiles_per_chunk,
-    int vec4_x, int vec4_z, int vec4_dx) {
+    const float* __restrict__ X, int64_t ldx, const float* Z, int64_t ldz, const float* __restrict__ P,
+    float inv_t, float* dX, int64_t lddx, float* __restrict__ partial, float* __restrict__ partial_dt, int64_t N,
+    int C, int tiles_per_chunk, int vec4_x, int vec4_z, int vec4_dx, ConvGeom geom) {
     using S = SoftPq<V, K_T>;
     constexpr int CT = S::CT;
     using E = EncTile<V, CT>;
@@ -135,8 +136,23 @@ __global__ __launch_bounds__(kEncThreads) void softpq_backward_kernel(
 
     for (int64_t tile = tile_begin; tile < tile_end; ++tile) {
         const int64_t row0 = tile * kEncRows;
-        stage_x<V, CT>(X, ldx, N, C * V, row0, c0, xs, vec4_x, tid);
-        stage_x<V, CT>(Z, ldz, N, C * V, row0, c0, zs, vec4_z, tid);
+        constexpr int COLS = E::CPW * V;  // a wavefront's own columns
+        ConvRow cr;
+        if constexpr (CONV != 0) {
+            cr = conv_row(geom, (uint32_t)row0 + lane, (uint32_t)N, C * V);
+#pragma unroll 1
+            for (int j = 0; j < E::CPW; ++j) {
+                float xv[V], zv[V];
+                const int col = (w * E::CPW + j) * V;
+                load_patch<V, CONV>(X, geom, cr, c0 * V + col, C * V, xv);
+                load_columns<V>(Z, geom, cr, c0 * V + col, C * V, zv);
+#pragma unroll
+                for (int v = 0; v < V; ++v) xs[lane * E::LS + col + v] = xv[v], zs[lane * E::LS + col + v] = zv[v];
+            }
+        } else {
+            stage_x<V, CT>(X, ldx, N, C * V, row0, c0, xs, vec4_x, tid);
+            stage_x<V, CT>(Z, ldz, N, C * V, row0, c0, zs, vec4_z, tid);
+        }
         __syncthreads();
 
         // one codebook at a time (rolled: a codebook's K*V centroid values fill the scalar registers)
@@ -221,8 +237,10 @@ __global__ __launch_bounds__(kEncThreads) void softpq_backward_kernel(
         }
         __syncthreads();
 
-        if (dX) {  // the X tile now holds dL/dX: out as coalesced row segments
-            if (vec4_dx) {
+        if (dX) {  // the X tile now holds dL/dX: out as coalesced row (CONV: column) segments
+            if constexpr (CONV != 0) {
+                store_columns<COLS>(dX, geom, cr, c0 * V + w * COLS, C * V, xs + lane * E::LS + w * COLS);
+            } else if (vec4_dx) {
                 constexpr int Q = E::TW / 4;
                 for (int i = tid; i < kEncRows * Q; i += kEncThreads) {
                     const int r = i / Q, col = (i % Q) * 4;
@@ -328,45 +346,51 @@ inline int vec4_ok(const float* A, int64_t ld, int C, int V, int CT) {
            ((reinterpret_cast<uintptr_t>(A) & 15) == 0);
 }
 
-template <int V, int K_T>
-hipError_t launch_softpq(const float* P, int C, float t, const float* X, int64_t N, int64_t ldx,
-                         const float* Z, int64_t ldz, float* dP, float* dX, int64_t lddx, float* dt,
-                         float* workspace, hipStream_t s) {
+template <int V, int K_T, int CONV>
+hipError_t launch_softpq(const SoftPqCall& a, hipStream_t s) {
     constexpr int CT = SoftPq<V, K_T>::CT;
-    const float inv_t = 1.0f / t;
-    const int64_t total = (int64_t)C * K_T * V;
-    if (N == 0) {  // empty sums: the reduction over zero chunks writes the zeros
+    const float inv_t = 1.0f / a.t;
+    const int64_t total = (int64_t)a.C * K_T * V;
+    if (a.N == 0) {  // empty sums: the reduction over zero chunks writes the zeros
         hipLaunchKernelGGL((softpq_reduce_kernel<V, K_T>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0,
-                           s, workspace, workspace, 0, 0, C, inv_t, dP, dt);
+                           s, a.workspace, a.workspace, 0, 0, a.C, inv_t, a.dP, a.dt);
         return hipGetLastError();
     }
-    const Plan p = make_plan<V, K_T>(C, N);
+    const Plan p = make_plan<V, K_T>(a.C, a.N);
     const int64_t blocks = (int64_t)p.chunks * p.col_tiles;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    float* partial = workspace;
-    float* partial_dt = workspace + (size_t)p.chunks * C * SoftPq<V, K_T>::GROUP_FLOATS;
-    hipLaunchKernelGGL((softpq_backward_kernel<V, K_T>), dim3((unsigned)blocks), dim3(kEncThreads), 0, s, X,
-                       ldx, Z, ldz, P, inv_t, dX, lddx, partial, partial_dt, N, C, p.tiles_per_chunk,
-                       vec4_ok(X, ldx, C, V, CT), vec4_ok(Z, ldz, C, V, CT),
-                       dX ? vec4_ok(dX, lddx, C, V, CT) : 0);
+    float* partial = a.workspace;
+    float* partial_dt = a.workspace + (size_t)p.chunks * a.C * SoftPq<V, K_T>::GROUP_FLOATS;
+    hipLaunchKernelGGL((softpq_backward_kernel<V, K_T, CONV>), dim3((unsigned)blocks), dim3(kEncThreads), 0, s, a.X,
+                       a.ldx, a.Z, a.ldz, a.P, inv_t, a.dX, a.lddx, partial, partial_dt, a.N, a.C, p.tiles_per_chunk,
+                       vec4_ok(a.X, a.ldx, a.C, V, CT), vec4_ok(a.Z, a.ldz, a.C, V, CT),
+                       a.dX ? vec4_ok(a.dX, a.lddx, a.C, V, CT) : 0, a.geom ? *a.geom : ConvGeom{});
     if (hipError_t e = hipGetLastError()) return e;
     hipLaunchKernelGGL((softpq_reduce_kernel<V, K_T>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s,
-                       partial, partial_dt, p.chunks, (int)blocks, C, inv_t, dP, dt);
+                       partial, partial_dt, p.chunks, (int)blocks, a.C, inv_t, a.dP, a.dt);
     return hipGetLastError();
+}
+
+template <int V, int K_T>
+hipError_t launch_source(const SoftPqCall& a, hipStream_t s) {
+    if (!a.geom) return launch_softpq<V, K_T, 0>(a, s);
+    const int taps = a.geom->kh * a.geom->kw;
+    if (taps == 1) return launch_softpq<V, K_T, 1>(a, s);
+    if constexpr (V == 9)
+        if (taps == 9) return launch_softpq<V, K_T, 9>(a, s);
+    return launch_softpq<V, K_T, -1>(a, s);
 }
 
 template <int K_T, class F>
 auto by_v(int V, F&& f) {
+    if constexpr (K_T == 8) {
+        if (V == 8) return f(std::integral_constant<int, 8>{});
+        if (V == 9) return f(std::integral_constant<int, 9>{});
+    }
     switch (V) {
         case 1: return f(std::integral_constant<int, 1>{});
         case 2: return f(std::integral_constant<int, 2>{});
         case 3: return f(std::integral_constant<int, 3>{});
-        case 8:
-            if constexpr (K_T == 8) return f(std::integral_constant<int, 8>{});
-            [[fallthrough]];
-        case 9:
-            if constexpr (K_T == 8) return f(std::integral_constant<int, 9>{});
-            [[fallthrough]];
         default: return f(std::integral_constant<int, 4>{});
     }
 }
@@ -383,19 +407,11 @@ size_t softpq_workspace_bytes(int C, int K, int V, int64_t N) {
     return by_v<8>(V, [&](auto v) { return workspace_bytes_for<decltype(v)::value, 8>(C, N); });
 }
 
-hipError_t launch_softpq_backward(const float* P, int C, int K, int V, float t, const float* X, int64_t N,
-                                  int64_t ldx, const float* Z, int64_t ldz, float* dP, float* dX,
-                                  int64_t lddx, float* dt, float* workspace, hipStream_t s) {
-    if (!softpq_supported(K, V)) return hipErrorInvalidValue;
-    if (softpq_matrix_preferred(K, V))
-        return launch_softpq_matrix(P, C, K, V, t, X, N, ldx, Z, ldz, dP, dX, lddx, dt, workspace, s);
-    if (K == 16)
-        return by_v<16>(V, [&](auto v) {
-            return launch_softpq<decltype(v)::value, 16>(P, C, t, X, N, ldx, Z, ldz, dP, dX, lddx, dt, workspace, s);
-        });
-    return by_v<8>(V, [&](auto v) {
-        return launch_softpq<decltype(v)::value, 8>(P, C, t, X, N, ldx, Z, ldz, dP, dX, lddx, dt, workspace, s);
-    });
+hipError_t launch_softpq_backward(const SoftPqCall& a, hipStream_t s) {
+    if (!softpq_supported(a.K, a.V)) return hipErrorInvalidValue;
+    if (softpq_matrix_preferred(a.K, a.V)) return launch_softpq_matrix(a, s);
+    if (a.K == 16) return by_v<16>(a.V, [&](auto v) { return launch_source<decltype(v)::value, 16>(a, s); });
+    return by_v<8>(a.V, [&](auto v) { return launch_source<decltype(v)::value, 8>(a, s); });
 }
 
 }  // namespace lutnn

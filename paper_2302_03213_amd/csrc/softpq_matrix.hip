@@ -27,7 +27,7 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "encode_tile.h"
+#include "conv_rows.h"
 #include "lutnn_kernels.h"
 
 namespace lutnn {
@@ -149,11 +149,13 @@ __device__ __forceinline__ void store_rows(const float* __restrict__ src, float*
 // grid: chunks * col_tiles workgroups, column tile fastest.
 //   partial    [chunks][C][group_floats(V, K)], element k*V + v: the sums of the dP contributions over the chunk's rows
 //   partial_dt [blocks] one sum of dz_k * d_k per workgroup
-template <int V, int K_T>
+//   CONV != 0  X is an NCHW image batch (CONV filter taps, -1 = any filter), Z and dX are [B][D][Ho*Wo] arrays, which
+//              may be the same one; a wavefront then stages its own codebook's columns with lane = row
+template <int V, int K_T, int CONV>
 __global__ __launch_bounds__(kEncThreads, per_cu(V, K_T)) void softpq_matrix_kernel(
-    const float* __restrict__ X, int64_t ldx, const float* __restrict__ Z, int64_t ldz, const float* __restrict__ P,
-    float inv_t, float* __restrict__ dX, int64_t lddx, float* __restrict__ partial, float* __restrict__ partial_dt,
-    int64_t N, int C, int tiles_per_chunk, int blocks, int vec4_x, int vec4_z, int vec4_dx) {
+    const float* __restrict__ X, int64_t ldx, const float* Z, int64_t ldz, const float* __restrict__ P, float inv_t,
+    float* dX, int64_t lddx, float* __restrict__ partial, float* __restrict__ partial_dt, int64_t N, int C,
+    int tiles_per_chunk, int blocks, int vec4_x, int vec4_z, int vec4_dx, ConvGeom geom) {
     using S = Soft<V, K_T>;
     using E = typename S::E;
     constexpr int VB = S::VB, VQ = S::VQ, H = S::H, TS = S::TS;
@@ -166,7 +168,7 @@ __global__ __launch_bounds__(kEncThreads, per_cu(V, K_T)) void softpq_matrix_ker
 
     // Workgroups go round the eight XCDs; each XCD takes a contiguous run of the work, so that neighbouring column
     // tiles - which share the cache lines at their common edge where 4V floats are no whole number of lines - meet
-    // in one L2 (V = 9, 50176 rows x 64 codebooks: xxx us).
+    // in one L2 (V = 9, 50176 rows x 64 codebooks: 159 -> 152 us).
     const int block = (int)(blockIdx.x % 8) * (int)(gridDim.x / 8) + (int)(blockIdx.x / 8);
     if (block >= blocks) return;
     const int col_tiles = (C + kCT - 1) / kCT;
@@ -231,9 +233,22 @@ __global__ __launch_bounds__(kEncThreads, per_cu(V, K_T)) void softpq_matrix_ker
 
     for (int64_t tile = tile_begin; tile < tile_end; ++tile) {
         const int64_t row0 = tile * kEncRows;
-        stage_rows<V>(X, ldx, N, C * V, row0, c0, xs, vec4_x, tid);
-        stage_rows<V>(Z, ldz, N, C * V, row0, c0, zs, vec4_z, tid);
-        __syncthreads();
+        ConvRow cr;
+        if constexpr (CONV != 0) {
+            if (live) {
+                cr = conv_row(geom, (uint32_t)row0 + lane, (uint32_t)N, C * V);
+                float xv[V], zv[V];
+                load_patch<V, CONV>(X, geom, cr, c * V, C * V, xv);
+                load_columns<V>(Z, geom, cr, c * V, C * V, zv);
+#pragma unroll
+                for (int v = 0; v < V; ++v) xs[lane * E::LS + w * V + v] = xv[v], zs[lane * E::LS + w * V + v] = zv[v];
+                wave_lds_fence();
+            }
+        } else {
+            stage_rows<V>(X, ldx, N, C * V, row0, c0, xs, vec4_x, tid);
+            stage_rows<V>(Z, ldz, N, C * V, row0, c0, zs, vec4_z, tid);
+            __syncthreads();
+        }
         if (live) {
 #pragma unroll 1
             for (int g = 0; g < 4; g += H) {
@@ -324,9 +339,14 @@ __global__ __launch_bounds__(kEncThreads, per_cu(V, K_T)) void softpq_matrix_ker
                 wave_lds_fence();
             }
         }
-        __syncthreads();
-        if (dX) store_rows<V>(xs, dX, lddx, N, C * V, row0, c0, vec4_dx, tid);
-        __syncthreads();  // the tiles are restaged next
+        if constexpr (CONV != 0) {
+            if (dX && live) store_columns<V>(dX, geom, cr, c * V, C * V, xs + lane * E::LS + w * V);
+            wave_lds_fence();
+        } else {
+            __syncthreads();
+            if (dX) store_rows<V>(xs, dX, lddx, N, C * V, row0, c0, vec4_dx, tid);
+            __syncthreads();  // the tiles are restaged next
+        }
     }
 
     if (live) {
@@ -411,39 +431,54 @@ inline int vec4_ok(const float* A, int64_t ld, int C, int V) {
     return (((int64_t)C * V) % 4 == 0) && (ld % 4 == 0) && ((reinterpret_cast<uintptr_t>(A) & 15) == 0);
 }
 
-template <int V, int K_T>
-hipError_t launch(const float* P, int C, float t, const float* X, int64_t N, int64_t ldx, const float* Z, int64_t ldz,
-                  float* dP, float* dX, int64_t lddx, float* dt, float* workspace, hipStream_t s) {
-    constexpr int G = group_floats(V, K_T);
-    const float inv_t = 1.0f / t;
+template <int V, int K_T, int CONV>
+hipError_t launch(const SoftPqCall& a, hipStream_t s) {
+    const float inv_t = 1.0f / a.t;
     Plan p = {0, 0, 0};
-    float *partial = workspace, *partial_dt = workspace;
+    float *partial = a.workspace, *partial_dt = a.workspace;
     int64_t blocks = 0;
-    if (N > 0) {
-        p = make_plan(C, N, per_cu(V, K_T));
+    if (a.N > 0) {
+        p = make_plan(a.C, a.N, per_cu(V, K_T));
         blocks = (int64_t)p.chunks * p.col_tiles;
         if (blocks > 0x7ffffff0LL) return hipErrorInvalidValue;
-        partial_dt = workspace + (size_t)p.chunks * C * G;
-        hipLaunchKernelGGL((softpq_matrix_kernel<V, K_T>), dim3((unsigned)(blocks + 7) / 8 * 8), dim3(kEncThreads), 0, s, X, ldx, Z,
-                           ldz, P, inv_t, dX, lddx, partial, partial_dt, N, C, p.tiles_per_chunk, (int)blocks,
-                           vec4_ok(X, ldx, C, V), vec4_ok(Z, ldz, C, V), dX ? vec4_ok(dX, lddx, C, V) : 0);
+        partial_dt = a.workspace + (size_t)p.chunks * a.C * group_floats(V, K_T);
+        hipLaunchKernelGGL((softpq_matrix_kernel<V, K_T, CONV>), dim3((unsigned)(blocks + 7) / 8 * 8), dim3(kEncThreads), 0,
+                           s, a.X, a.ldx, a.Z, a.ldz, a.P, inv_t, a.dX, a.lddx, partial, partial_dt, a.N, a.C,
+                           p.tiles_per_chunk, (int)blocks, vec4_ok(a.X, a.ldx, a.C, V), vec4_ok(a.Z, a.ldz, a.C, V),
+                           a.dX ? vec4_ok(a.dX, a.lddx, a.C, V) : 0, a.geom ? *a.geom : ConvGeom{});
         if (hipError_t e = hipGetLastError()) return e;
     }
     // an empty batch: the reduction over zero chunks writes the zeros
-    const int64_t total = (int64_t)C * K_T * V;
+    const int64_t total = (int64_t)a.C * K_T * V;
     hipLaunchKernelGGL(softpq_chunks_kernel, dim3((unsigned)((total + 63) / 64)), dim3(256), 0, s, partial, partial_dt,
-                       p.chunks, (int)blocks, C, K_T * V, G, inv_t, dP, dt);
+                       p.chunks, (int)blocks, a.C, K_T * V, group_floats(V, K_T), inv_t, a.dP, a.dt);
     return hipGetLastError();
+}
+
+template <int V, int K_T>
+hipError_t launch_source(const SoftPqCall& a, hipStream_t s) {
+    if (!a.geom) return launch<V, K_T, 0>(a, s);
+    if constexpr (V < 32) {
+        const int taps = a.geom->kh * a.geom->kw;
+        if (taps == 1) return launch<V, K_T, 1>(a, s);
+        if constexpr (V == 9)
+            if (taps == 9) return launch<V, K_T, 9>(a, s);
+        return launch<V, K_T, -1>(a, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 template <int K_T, class F>
 auto by_v(int V, F&& f) {
-    if constexpr (K_T == 8) return V == 16 ? f(std::integral_constant<int, 16>{}) : f(std::integral_constant<int, 32>{});
-    switch (V) {
-        case 8: return f(std::integral_constant<int, 8>{});
-        case 9: return f(std::integral_constant<int, 9>{});
-        case 16: return f(std::integral_constant<int, 16>{});
-        default: return f(std::integral_constant<int, 32>{});
+    if constexpr (K_T == 8) {
+        return V == 16 ? f(std::integral_constant<int, 16>{}) : f(std::integral_constant<int, 32>{});
+    } else {
+        switch (V) {
+            case 8: return f(std::integral_constant<int, 8>{});
+            case 9: return f(std::integral_constant<int, 9>{});
+            case 16: return f(std::integral_constant<int, 16>{});
+            default: return f(std::integral_constant<int, 32>{});
+        }
     }
 }
 
@@ -458,16 +493,9 @@ size_t softpq_matrix_workspace_bytes(int C, int K, int V, int64_t N) {
     return ((size_t)p.chunks * C * group_floats(V, K) + (size_t)p.chunks * p.col_tiles) * sizeof(float);
 }
 
-hipError_t launch_softpq_matrix(const float* P, int C, int K, int V, float t, const float* X, int64_t N, int64_t ldx,
-                                const float* Z, int64_t ldz, float* dP, float* dX, int64_t lddx, float* dt,
-                                float* workspace, hipStream_t s) {
-    if (K == 16)
-        return by_v<16>(V, [&](auto v) {
-            return launch<decltype(v)::value, 16>(P, C, t, X, N, ldx, Z, ldz, dP, dX, lddx, dt, workspace, s);
-        });
-    return by_v<8>(V, [&](auto v) {
-        return launch<decltype(v)::value, 8>(P, C, t, X, N, ldx, Z, ldz, dP, dX, lddx, dt, workspace, s);
-    });
+hipError_t launch_softpq_matrix(const SoftPqCall& a, hipStream_t s) {
+    if (a.K == 16) return by_v<16>(a.V, [&](auto v) { return launch_source<decltype(v)::value, 16>(a, s); });
+    return by_v<8>(a.V, [&](auto v) { return launch_source<decltype(v)::value, 8>(a, s); });
 }
 
 }  // namespace lutnn

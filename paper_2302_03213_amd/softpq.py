@@ -52,9 +52,8 @@ class SoftPQLinear(torch.nn.Module):
 
 class _SoftPQConv2dFn(torch.autograd.Function):
     """The same operator for a convolution (Sec. 4: a convolution is the linear operator on the rows
-    of its im2col matrix).  Forward reads the NCHW batch directly (lutnn_conv2d); backward
-    materialises the rows with torch's unfold - training can afford the matrix the inference path
-    avoids - and folds the row gradients back onto the image."""
+    of its im2col matrix).  Forward (lutnn_conv2d) and backward (lutnn_softpq_backward_conv2d) read the
+    NCHW batch directly; nothing is unfolded, transposed or copied around them."""
 
     @staticmethod
     def forward(ctx, inp, centroids, temperature, W, bias, table_dtype, kernel, stride, pad):
@@ -66,27 +65,18 @@ class _SoftPQConv2dFn(torch.autograd.Function):
         Wo = (Wd + 2 * geom.pad_w - geom.kw) // geom.stride_w + 1
         ctx.save_for_backward(inp, centroids, temperature, W)
         ctx.has_bias = bias is not None
-        ctx.conv = (kernel, stride, pad, Ho, Wo)
+        ctx.conv = (kernel, stride, pad)
         return Y.view(B, Ho, Wo, -1).permute(0, 3, 1, 2)  # NCHW view of the row-major output
 
     @staticmethod
     def backward(ctx, G):
         inp, centroids, temperature, W = ctx.saved_tensors
-        kernel, stride, pad, Ho, Wo = ctx.conv
-        B, Cin, H, Wd = inp.shape
-        M = W.shape[1]
-        G2 = G.permute(0, 2, 3, 1).reshape(-1, M).contiguous()  # rows (b, ho, wo)
-        cols = torch.nn.functional.unfold(inp.detach(), kernel, padding=pad, stride=stride)  # [B, D, Ho*Wo]
-        X = cols.permute(0, 2, 1).reshape(-1, cols.shape[1]).contiguous()
-        Z = G2 @ W.t()
-        layer = _b.LutLayer(centroids.detach().contiguous(), None, _b.TABLE_F32, M)
-        need_dx = ctx.needs_input_grad[0]
-        dP, dX, dt = _b.softpq_backward(layer, float(temperature), X, Z, need_dx=need_dx)
-        dinp = None
-        if need_dx:
-            dcols = dX.view(B, Ho * Wo, -1).permute(0, 2, 1)
-            dinp = torch.nn.functional.fold(dcols, (H, Wd), kernel, padding=pad, stride=stride)
-        dbias = G2.sum(dim=0) if ctx.has_bias and ctx.needs_input_grad[4] else None
+        kernel, stride, pad = ctx.conv
+        G = G.contiguous()
+        layer = _b.LutLayer(centroids.detach().contiguous(), None, _b.TABLE_F32, W.shape[1])
+        dP, dinp, dt = _b.softpq_backward_conv2d(layer, float(temperature), inp.detach().contiguous(), W, G, kernel,
+                                                 stride, pad, need_dx=ctx.needs_input_grad[0])
+        dbias = G.sum(dim=(0, 2, 3)) if ctx.has_bias and ctx.needs_input_grad[4] else None
         return dinp, dP, dt.reshape(temperature.shape), None, dbias, None, None, None, None
 
 

@@ -293,3 +293,39 @@ def test_matrix_form_tile_edges(lut, N, C, K, V, M, t, offset):
     # the oracle's A = z . P carries the offset exactly (fp64); the kernel's does not see it
     close(host(dP), dP_ref)
     close(host(dX), dX_ref)
+
+
+@pytest.mark.parametrize("B,Cin,H,W,kernel,stride,pad,K,V,M", [
+    (3, 7, 9, 11, 3, 1, 1, 16, 9, 17),            # one channel per codebook, ragged image, codebooks and outputs
+    (2, 6, 13, 8, 3, 2, 1, 8, 9, 70),             # K = 8, stride 2, more than one tile of W's rows
+    (1, 16, 15, 15, 1, 1, 0, 16, 4, 33),          # 1x1: the gradient is written to the image directly
+    (2, 8, 10, 7, 1, 2, 0, 16, 8, 5),             # 1x1 at stride 2: pixels that no filter reads get zero
+    (2, 8, 6, 9, (3, 2), (1, 2), (0, 1), 16, 16, 8),  # a filter that no instance is made for
+    (1, 4, 5, 70, (1, 3), 1, (0, 1), 8, 4, 1),
+    (5, 4, 3, 3, 3, 1, 0, 16, 9, 16),             # one output pixel per image
+])
+def test_softpq_backward_of_a_convolution(lut, B, Cin, H, W, kernel, stride, pad, K, V, M):
+    """lutnn_softpq_backward_conv2d against the oracle on torch's unfolded rows.  Z = W . G is summed in fp32 over M
+    terms here (relative error about sqrt(M) * 2^-24, below 1e-6) where the oracle has it exactly: the bar of the file
+    covers it ten times over."""
+    rng = np.random.default_rng(Cin * H + K)
+    inp = rng.standard_normal((B, Cin, H, W)).astype(np.float32)
+    cols = torch.nn.functional.unfold(torch.from_numpy(inp), kernel, padding=pad, stride=stride)
+    X = cols.permute(0, 2, 1).reshape(-1, cols.shape[1]).contiguous().numpy()
+    D = X.shape[1]
+    w = wl.make_layer("t", 1, D // V, K, V, M, "f32", seed=77)
+    G = rng.standard_normal((B, M, cols.shape[2])).astype(np.float32)
+    G2 = np.ascontiguousarray(G.transpose(0, 2, 1).reshape(-1, M)).astype(np.float64)
+    dP_ref, dX_ref, dt_ref = osp.backward(w.P, w.W, X, 1.5, G2)
+    fold = torch.from_numpy(dX_ref).view(B, -1, D).permute(0, 2, 1)
+    dinp_ref = torch.nn.functional.fold(fold, (H, W), kernel, padding=pad, stride=stride).numpy()
+    layer = lut.LutLayer(dev(w.P), None, lut.TABLE_F32, M)
+    dP, dinp, dt = lut.softpq_backward_conv2d(layer, 1.5, dev(inp), dev(w.W), dev(G), kernel, stride, pad)
+    close(host(dP), dP_ref)
+    close(host(dinp), dinp_ref)
+    w.X = X
+    check_dt(host(dt)[0], dt_ref, dt_magnitude(w, 1.5, G2))
+    dP2, none, dt2 = lut.softpq_backward_conv2d(layer, 1.5, dev(inp), dev(w.W), dev(G), kernel, stride, pad, need_dx=False)
+    assert none is None
+    np.testing.assert_array_equal(host(dP2), host(dP))
+    np.testing.assert_array_equal(host(dt2), host(dt))
