@@ -11,9 +11,30 @@ import torch
 from . import binding as _b
 
 
+class _HostTemperature:
+    """The temperature's value for the backward pass, which the C ABI takes by value.  The copy to the host starts in
+    the forward pass, ahead of its kernels: when the backward pass asks for the value it has long arrived, instead of
+    being waited for behind everything that the stream has been given by then."""
+
+    def __init__(self, temperature):
+        self.event = None
+        self.value = temperature.detach()
+        if temperature.is_cuda and not torch.cuda.is_current_stream_capturing():
+            self.value = torch.empty(temperature.shape, dtype=temperature.dtype, pin_memory=True)
+            self.value.copy_(temperature.detach(), non_blocking=True)
+            self.event = torch.cuda.Event()
+            self.event.record()
+
+    def get(self):
+        if self.event is not None:
+            self.event.synchronize()
+        return float(self.value)
+
+
 class _SoftPQLinearFn(torch.autograd.Function):
     @staticmethod
     def forward(ctx, X, centroids, temperature, W, bias, table_dtype):
+        ctx.temperature = _HostTemperature(temperature) if any(ctx.needs_input_grad) else None
         layer = _b.build_table(centroids.detach(), W, table_dtype, bias=bias)
         Y = _b.linear(layer, X.detach())
         ctx.save_for_backward(X, centroids, temperature, W)
@@ -28,7 +49,7 @@ class _SoftPQLinearFn(torch.autograd.Function):
         Z = G @ W.t()  # input gradient of the ordinary linear layer: a plain library GEMM
         C, K, V = centroids.shape
         layer = _b.LutLayer(centroids.detach().contiguous(), None, _b.TABLE_F32, W.shape[1])
-        dP, dX, dt = _b.softpq_backward(layer, float(temperature), X.detach(), Z,
+        dP, dX, dt = _b.softpq_backward(layer, ctx.temperature.get(), X.detach(), Z,
                                         need_dx=ctx.needs_input_grad[0])
         dbias = G.sum(dim=0) if ctx.has_bias and ctx.needs_input_grad[4] else None
         return dX, dP, dt.reshape(temperature.shape), None, dbias, None
@@ -57,6 +78,7 @@ class _SoftPQConv2dFn(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, inp, centroids, temperature, W, bias, table_dtype, kernel, stride, pad):
+        ctx.temperature = _HostTemperature(temperature) if any(ctx.needs_input_grad) else None
         layer = _b.build_table(centroids.detach(), W, table_dtype, bias=bias)
         B, _, H, Wd = inp.shape
         Y = _b.conv2d(layer, inp.detach().contiguous(), kernel, stride, pad)  # [B*Ho*Wo, M]
@@ -74,7 +96,7 @@ class _SoftPQConv2dFn(torch.autograd.Function):
         kernel, stride, pad = ctx.conv
         G = G.contiguous()
         layer = _b.LutLayer(centroids.detach().contiguous(), None, _b.TABLE_F32, W.shape[1])
-        dP, dinp, dt = _b.softpq_backward_conv2d(layer, float(temperature), inp.detach().contiguous(), W, G, kernel,
+        dP, dinp, dt = _b.softpq_backward_conv2d(layer, ctx.temperature.get(), inp.detach().contiguous(), W, G, kernel,
                                                  stride, pad, need_dx=ctx.needs_input_grad[0])
         dbias = G.sum(dim=(0, 2, 3)) if ctx.has_bias and ctx.needs_input_grad[4] else None
         return dinp, dP, dt.reshape(temperature.shape), None, dbias, None, None, None, None
