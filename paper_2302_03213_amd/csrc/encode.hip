@@ -294,6 +294,8 @@ hipError_t launch_conv_v(const float* P, int C, int K, const float* input, int64
     if (taps == 1) return launch_tile<V, 1>(P, C, K, input, N, 0, idx, s, g);
     if constexpr (V == 9) {
         if (taps == 9) {
+            if (const int64_t chunks = encode_conv9_filter_chunks(C, K, B, g))
+                return launch_encode_conv9_filter(P, C, K, input, B, g, idx, chunks, s);
             // rows of the input staged once, if the widest band fits 48 KiB of LDS
             constexpr int CT = enc_tile_codebooks(9), CT_SMALL = 4;
             const int64_t bs = conv_band_floats(g);

@@ -41,6 +41,14 @@ bool encode_conv_supported(int V);
 hipError_t launch_encode_conv(const float* P, int C, int K, int V, const float* input, int64_t B,
                               const ConvGeom& g, uint8_t* idx, hipStream_t s);
 
+// A 3x3 convolution with V = 9, the matrix cores as a filter (encode_conv9.hip), over `chunks` chunks of pixel tiles:
+// encode_conv9_filter_chunks gives their number, 0 where the direct search is to be taken.  conv_band_floats: the
+// largest band of input rows (floats per channel) of any 64-pixel tile.
+int64_t conv_band_floats(const ConvGeom& g);
+int64_t encode_conv9_filter_chunks(int C, int K, int64_t B, const ConvGeom& g);
+hipError_t launch_encode_conv9_filter(const float* P, int C, int K, const float* input, int64_t B, const ConvGeom& g,
+                                      uint8_t* idx, int64_t chunks, hipStream_t s);
+
 // Eq. 2.
 hipError_t launch_encode(const float* P, int C, int K, int V, const float* X, int64_t N, int64_t ldx,
                          uint8_t* idx, hipStream_t s);

@@ -1,0 +1,77 @@
+"""The matrix-core filter of the 3x3 convolution's encoder (encode_conv9.hip): indices equal to the oracle's on the unfolded
+rows, including where the filter must step aside - ties, near-ties, values beyond fp16's range, zeros, values that
+are not finite.  Launches larger than a workgroup per CU, where the filter is taken."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import dev, host
+
+pytestmark = pytest.mark.gpu
+
+
+def unfolded(inp, kernel, stride, pad):
+    cols = torch.nn.functional.unfold(torch.from_numpy(inp), kernel, padding=pad, stride=stride)
+    return np.ascontiguousarray(cols.permute(0, 2, 1).reshape(-1, cols.shape[1]).numpy())
+
+
+def check(P, inp, kernel, stride, pad, finite=True):
+    import paper_2302_03213_amd as lut
+    layer = lut.LutLayer(dev(P), None, lut.TABLE_F32, 8)
+    got = host(lut.encode_conv2d(layer, dev(inp), kernel, stride, pad))
+    X = unfolded(inp, kernel, stride, pad)
+    if finite:
+        np.testing.assert_array_equal(got, oracle.encode(P, X))
+    else:  # what is not finite is the direct kernel's to decide: the same as on materialised rows
+        np.testing.assert_array_equal(got, host(lut.encode(layer, dev(X))))
+        assert got.max() < P.shape[1]
+    return got
+
+
+@pytest.mark.parametrize("B,C,H,W,kernel,stride,pad,K", [
+    (6, 64, 56, 56, 3, 1, 1, 16),      # five pieces of band, chunks of one and two tiles
+    (9, 37, 28, 28, 3, 1, 1, 16),      # three pieces; codebooks that fill neither a wavefront nor a dword
+    (2, 18, 100, 90, 3, 1, 1, 8),      # eight pieces, K = 8
+    (70, 64, 7, 7, 3, 1, 1, 16),       # images smaller than a tile
+    (5, 66, 57, 41, 3, 2, 1, 16),      # stride 2
+    (3, 50, 9, 130, 3, 1, 0, 16),      # tiles within one row and across two: the band's width changes
+    (40, 30, 21, 13, (1, 9), 1, (0, 4), 16),  # nine taps in a row
+])
+def test_indices_equal_the_oracles(B, C, H, W, kernel, stride, pad, K):
+    rng = np.random.default_rng(B * C)
+    inp = rng.standard_normal((B, C, H, W)).astype(np.float32)
+    inp[rng.random(inp.shape) < 0.01] *= 10
+    check(rng.standard_normal((C, K, 9)).astype(np.float32), inp, kernel, stride, pad)
+
+
+def test_doubtful_rows():
+    rng = np.random.default_rng(5)
+    B, C = 8, 48
+    P = rng.standard_normal((C, 16, 9)).astype(np.float32)
+    P[0, 9] = P[0, 3]                       # equal centroids: the lower index
+    P[1, 12] = np.nextafter(P[1, 4], 9)     # one unit in the last place apart
+    P[2] = np.round(P[2])                   # small integers: exact ties between different centroids
+    P[3] = 0                                # all equal
+    P[4] *= 1e-5                            # too small for the parts
+    P[5] *= 1e4                             # too large
+    inp = rng.standard_normal((B, C, 30, 30)).astype(np.float32)
+    inp[:, 2] = np.round(inp[:, 2])
+    inp[:, 4] *= 1e-5
+    inp[:, 5] *= 1e4
+    inp[:, 6] *= 1e30                       # activations beyond fp16 against ordinary centroids
+    inp[:, 7] *= 1e-30
+    inp[:, 8] = np.maximum(inp[:, 8], 0)
+    inp[0, 9] = 0
+    inp[:, 10, ::7] *= 30000
+    got = check(P, inp, 3, 1, 1)
+    assert not (got[:, 0] == 9).any() and not got[:, 3].any()
+
+
+def test_values_that_are_not_finite():
+    rng = np.random.default_rng(6)
+    inp = rng.standard_normal((8, 32, 30, 30)).astype(np.float32)
+    inp[rng.random(inp.shape) < 0.01] = np.nan
+    inp[rng.random(inp.shape) < 0.01] = np.inf
+    inp[rng.random(inp.shape) < 0.01] = -np.inf
+    check(rng.standard_normal((32, 16, 9)).astype(np.float32), inp, 3, 1, 1, finite=False)
