@@ -151,11 +151,12 @@ def _check(status):
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """Handle of the current stream of the current device, without the Stream object around it (3 us)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _variant(v):
@@ -214,6 +215,7 @@ class LutLayer:
             centroids, table, packed, scale, bias
         self.c = _CLayer(self.C, self.K, self.V, self.M, self.table_dtype, 0, _ptr(centroids),
                          _ptr(table), _ptr(packed), _ptr(scale), _ptr(bias))
+        self.ref = ctypes.byref(self.c)
 
     @property
     def D(self):
@@ -254,7 +256,7 @@ def encode(layer, X, out=None):
     if out is None:
         out = torch.empty((N, layer.C), dtype=torch.uint8, device=X.device)
     assert out.is_contiguous() and out.shape == (N, layer.C) and out.dtype == torch.uint8
-    _check(LIB.lutnn_encode(ctypes.byref(layer.c), _ptr(X), N, X.stride(0), _ptr(out), _stream()))
+    _check(LIB.lutnn_encode(layer.ref, _ptr(X), N, X.stride(0), _ptr(out), _stream()))
     return out
 
 
@@ -265,7 +267,7 @@ def lookup(layer, idx, variant="auto", out=None):
     if out is None:
         out = torch.empty((N, layer.M), dtype=torch.float32, device=idx.device)
     assert out.dtype == torch.float32 and out.stride(1) == 1 and out.shape == (N, layer.M)
-    _check(LIB.lutnn_lookup(ctypes.byref(layer.c), _ptr(idx), N, _ptr(out), out.stride(0),
+    _check(LIB.lutnn_lookup(layer.ref, _ptr(idx), N, _ptr(out), out.stride(0),
                             _variant(variant), _stream()))
     return out
 
@@ -285,6 +287,7 @@ class LutTree:
         self.split_dim = split_dim.contiguous()
         self.threshold = threshold.contiguous()
         self.c = _CTree(self.C, self.V, levels, 0, self.split_dim.data_ptr(), self.threshold.data_ptr())
+        self.ref = ctypes.byref(self.c)
 
 
 def encode_tree(tree, X, out=None):
@@ -294,7 +297,7 @@ def encode_tree(tree, X, out=None):
     if out is None:
         out = torch.empty((N, tree.C), dtype=torch.uint8, device=X.device)
     assert out.is_contiguous() and out.shape == (N, tree.C) and out.dtype == torch.uint8
-    _check(LIB.lutnn_encode_tree(ctypes.byref(tree.c), _ptr(X), N, X.stride(0), _ptr(out), _stream()))
+    _check(LIB.lutnn_encode_tree(tree.ref, _ptr(X), N, X.stride(0), _ptr(out), _stream()))
     return out
 
 
@@ -306,9 +309,9 @@ def linear_tree(layer, tree, X, variant="auto", out=None, idx_workspace=None):
         out = torch.empty((N, layer.M), dtype=torch.float32, device=X.device)
     assert out.dtype == torch.float32 and out.stride(1) == 1 and out.shape == (N, layer.M)
     v = _variant(variant)
-    if idx_workspace is None and v != VARIANT_FUSED:
+    if idx_workspace is None and not _one_launch(layer, N, v):
         idx_workspace = torch.empty((N, layer.C), dtype=torch.uint8, device=X.device)
-    _check(LIB.lutnn_linear_tree(ctypes.byref(layer.c), ctypes.byref(tree.c), _ptr(X), N, X.stride(0),
+    _check(LIB.lutnn_linear_tree(layer.ref, tree.ref, _ptr(X), N, X.stride(0),
                                  _ptr(out), out.stride(0), v, _ptr(idx_workspace), _stream()))
     return out
 
@@ -320,7 +323,7 @@ def encode_tree16(tree, X, out=None):
     if out is None:
         out = torch.empty((N, tree.C), dtype=torch.int16, device=X.device)
     assert out.dtype == torch.int16 and out.is_contiguous() and out.shape == (N, tree.C)
-    _check(LIB.lutnn_encode_tree16(ctypes.byref(tree.c), _ptr(X), N, X.stride(0), _ptr(out), _stream()))
+    _check(LIB.lutnn_encode_tree16(tree.ref, _ptr(X), N, X.stride(0), _ptr(out), _stream()))
     return out
 
 
@@ -333,7 +336,7 @@ def lookup16(layer, idx, out=None):
     if out is None:
         out = torch.empty((N, layer.M), dtype=torch.float32, device=idx.device)
     assert out.dtype == torch.float32 and out.stride(1) == 1 and out.shape == (N, layer.M)
-    _check(LIB.lutnn_lookup16(ctypes.byref(layer.c), _ptr(idx), N, _ptr(out), out.stride(0), _stream()))
+    _check(LIB.lutnn_lookup16(layer.ref, _ptr(idx), N, _ptr(out), out.stride(0), _stream()))
     return out
 
 
@@ -346,7 +349,7 @@ def linear_tree16(layer, tree, X, out=None, idx_workspace=None):
     if idx_workspace is None:
         idx_workspace = torch.empty((N, layer.C), dtype=torch.int16, device=X.device)
     assert out.dtype == torch.float32 and out.stride(1) == 1 and out.shape == (N, layer.M)
-    _check(LIB.lutnn_linear_tree16(ctypes.byref(layer.c), ctypes.byref(tree.c), _ptr(X), N, X.stride(0),
+    _check(LIB.lutnn_linear_tree16(layer.ref, tree.ref, _ptr(X), N, X.stride(0),
                                    _ptr(out), out.stride(0), _ptr(idx_workspace), _stream()))
     return out
 
@@ -368,7 +371,7 @@ def softpq_backward(layer, temperature, X, Z, need_dx=True, workspace=None):
     if workspace is None:
         workspace = torch.empty(max(need, 4), dtype=torch.uint8, device=X.device)
     assert workspace.is_cuda and workspace.is_contiguous()
-    _check(LIB.lutnn_softpq_backward(ctypes.byref(layer.c), float(temperature), _ptr(X), N, X.stride(0),
+    _check(LIB.lutnn_softpq_backward(layer.ref, float(temperature), _ptr(X), N, X.stride(0),
                                      _ptr(Z), Z.stride(0), _ptr(dP), _ptr(dX),
                                      dX.stride(0) if need_dx else 0, _ptr(dt), _ptr(workspace),
                                      workspace.numel() * workspace.element_size(), _stream()))
@@ -389,7 +392,7 @@ def softpq_backward_static(layer, temperature, X, Z, need_dx=True, dP=None, dX=N
         dt = torch.empty(1, dtype=torch.float32, device=X.device)
     assert dP.is_contiguous() and dP.shape == (layer.C, layer.K, layer.V) and dt.numel() == 1
     assert not need_dx or (dX.stride(1) == 1 and dX.shape == (N, layer.C * layer.V))
-    _check(LIB.lutnn_softpq_backward_static(ctypes.byref(layer.c), float(temperature), _ptr(X), N, X.stride(0),
+    _check(LIB.lutnn_softpq_backward_static(layer.ref, float(temperature), _ptr(X), N, X.stride(0),
                                             _ptr(Z), Z.stride(0), _ptr(dP), _ptr(dX) if need_dx else None,
                                             dX.stride(0) if need_dx else 0, _ptr(dt), _stream()))
     return dP, (dX if need_dx else None), dt
@@ -425,7 +428,7 @@ def softpq_backward_conv2d(layer, temperature, inp, W, G, kernel, stride=1, pad=
     Z = torch.empty(N * layer.D, dtype=torch.float32, device=inp.device)
     workspace = torch.empty(max(softpq_workspace_bytes(layer.C, layer.K, layer.V, N), 4), dtype=torch.uint8,
                             device=inp.device)
-    _check(LIB.lutnn_softpq_backward_conv2d(ctypes.byref(layer.c), float(temperature), _ptr(inp), inp.shape[0],
+    _check(LIB.lutnn_softpq_backward_conv2d(layer.ref, float(temperature), _ptr(inp), inp.shape[0],
                                             ctypes.byref(geom), _ptr(W), W.stride(0), _ptr(G), _ptr(Z), _ptr(dP),
                                             _ptr(dinp), _ptr(dt), _ptr(workspace), workspace.numel(), _stream()))
     return dP, dinp, dt
@@ -442,7 +445,7 @@ def encode_conv2d(layer, inp, kernel, stride=1, pad=0, out=None):
     if out is None:
         out = torch.empty((N, layer.C), dtype=torch.uint8, device=inp.device)
     assert out.is_contiguous() and out.shape == (N, layer.C) and out.dtype == torch.uint8
-    _check(LIB.lutnn_encode_conv2d(ctypes.byref(layer.c), _ptr(inp), inp.shape[0], ctypes.byref(geom),
+    _check(LIB.lutnn_encode_conv2d(layer.ref, _ptr(inp), inp.shape[0], ctypes.byref(geom),
                                    _ptr(out), _stream()))
     return out
 
@@ -459,7 +462,7 @@ def conv2d(layer, inp, kernel, stride=1, pad=0, variant="auto", out=None, idx_wo
     assert out.dtype == torch.float32 and out.stride(1) == 1 and out.shape == (N, layer.M)
     if idx_workspace is None:
         idx_workspace = torch.empty((N, layer.C), dtype=torch.uint8, device=inp.device)
-    _check(LIB.lutnn_conv2d(ctypes.byref(layer.c), _ptr(inp), inp.shape[0], ctypes.byref(geom), _ptr(out),
+    _check(LIB.lutnn_conv2d(layer.ref, _ptr(inp), inp.shape[0], ctypes.byref(geom), _ptr(out),
                             out.stride(0), _variant(variant), _ptr(idx_workspace), _stream()))
     return out
 
@@ -474,7 +477,7 @@ def encode_tree_conv2d(tree, inp, kernel, stride=1, pad=0, out=None):
     if out is None:
         out = torch.empty((N, tree.C), dtype=torch.uint8, device=inp.device)
     assert out.is_contiguous() and out.shape == (N, tree.C) and out.dtype == torch.uint8
-    _check(LIB.lutnn_encode_tree_conv2d(ctypes.byref(tree.c), _ptr(inp), inp.shape[0], ctypes.byref(geom),
+    _check(LIB.lutnn_encode_tree_conv2d(tree.ref, _ptr(inp), inp.shape[0], ctypes.byref(geom),
                                         _ptr(out), _stream()))
     return out
 
@@ -491,22 +494,29 @@ def conv2d_tree(layer, tree, inp, kernel, stride=1, pad=0, variant="auto", out=N
     assert out.dtype == torch.float32 and out.stride(1) == 1 and out.shape == (N, layer.M)
     if idx_workspace is None:
         idx_workspace = torch.empty((N, layer.C), dtype=torch.uint8, device=inp.device)
-    _check(LIB.lutnn_conv2d_tree(ctypes.byref(layer.c), ctypes.byref(tree.c), _ptr(inp), inp.shape[0],
+    _check(LIB.lutnn_conv2d_tree(layer.ref, tree.ref, _ptr(inp), inp.shape[0],
                                  ctypes.byref(geom), _ptr(out), out.stride(0), _variant(variant),
                                  _ptr(idx_workspace), _stream()))
     return out
 
 
+def _one_launch(layer, N, variant):
+    """Whether the call runs as one launch, which has no use for an index workspace (lutnn_linear_auto_variant with
+    the alignment that torch's allocations have)."""
+    return variant == VARIANT_FUSED or (variant == VARIANT_AUTO and
+                                        LIB.lutnn_linear_auto_variant(layer.ref, 256, N) == VARIANT_FUSED)
+
+
 def auto_variant(layer, N, idx=None):
     """lutnn_auto_variant: name of the lookup variant that "auto" stands for at this shape."""
-    code = LIB.lutnn_auto_variant(ctypes.byref(layer.c), _ptr(idx), N)
+    code = LIB.lutnn_auto_variant(layer.ref, _ptr(idx), N)
     return {v: k for k, v in VARIANTS.items()}[code]
 
 
 def linear_auto_variant(layer, N, idx_workspace=None):
     """lutnn_linear_auto_variant: name of what lutnn_linear runs for "auto" at this shape ("fused" =
     one launch does both steps)."""
-    code = LIB.lutnn_linear_auto_variant(ctypes.byref(layer.c), _ptr(idx_workspace), N)
+    code = LIB.lutnn_linear_auto_variant(layer.ref, _ptr(idx_workspace), N)
     return {v: k for k, v in VARIANTS.items()}[code]
 
 
@@ -518,8 +528,8 @@ def linear(layer, X, variant="auto", out=None, idx_workspace=None):
         out = torch.empty((N, layer.M), dtype=torch.float32, device=X.device)
     assert out.dtype == torch.float32 and out.stride(1) == 1 and out.shape == (N, layer.M)
     v = _variant(variant)
-    if idx_workspace is None and v != VARIANT_FUSED:
+    if idx_workspace is None and not _one_launch(layer, N, v):
         idx_workspace = torch.empty((N, layer.C), dtype=torch.uint8, device=X.device)
-    _check(LIB.lutnn_linear(ctypes.byref(layer.c), _ptr(X), N, X.stride(0), _ptr(out),
+    _check(LIB.lutnn_linear(layer.ref, _ptr(X), N, X.stride(0), _ptr(out),
                             out.stride(0), v, _ptr(idx_workspace), _stream()))
     return out
