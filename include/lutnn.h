@@ -365,6 +365,23 @@ LUTNN_API lutnn_status lutnn_conv2d(const lutnn_layer* layer, const float* input
                                     int32_t variant, uint8_t* idx_workspace, void* stream);
 
 /*
+ * Z = G . W^T in fp32: the input gradient of the ordinary linear layer with weights W, which lutnn_softpq_backward
+ * takes as its Z.
+ *
+ *   G  [N][M] fp32, row stride ldg >= M: dL/dY
+ *   W  [D][M] fp32, row stride ldw >= M (as lutnn_build_table)
+ *   Z  [N][D] fp32, row stride ldz >= D, overwritten
+ * Row strides of G and W up to 2^20.  Errors: E_NULL, E_SHAPE, E_ALIGN, E_HIP.
+ */
+LUTNN_API lutnn_status lutnn_linear_gradient(const float* G, int64_t N, int64_t ldg, const float* W, int64_t ldw,
+                                             int32_t D, int32_t M, float* Z, int64_t ldz, void* stream);
+
+/* Host: 1 where lutnn_linear_gradient is faster than a library's fp32 matrix product for these operands, 0 elsewhere
+ * (few tiles of a long sum, rows that are not whole 16-byte vectors) and for shapes it refuses. */
+LUTNN_API int32_t lutnn_linear_gradient_preferred(const float* G, int64_t N, int64_t ldg, const float* W, int64_t ldw,
+                                                  int32_t D, int32_t M);
+
+/*
  * lutnn_softpq_backward for a convolution, on the rows of the im2col matrix of `input`, which is never written:
  * gradients of the soft output for the centroids, the temperature and the image.
  *

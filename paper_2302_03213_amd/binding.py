@@ -30,7 +30,7 @@ VARIANTS = {"auto": VARIANT_AUTO, "lds": VARIANT_LDS, "mfma": VARIANT_MFMA, "fus
 EXPORTS = ["lutnn_softpq_backward_static", "lutnn_set_tunable", "lutnn_encode_tree16", "lutnn_lookup16",
            "lutnn_linear_tree16", "lutnn_table_bytes", "lutnn_packed_bytes", "lutnn_build_table", "lutnn_encode",
            "lutnn_lookup", "lutnn_linear", "lutnn_encode_tree", "lutnn_linear_tree",
-           "lutnn_softpq_backward", "lutnn_softpq_backward_conv2d", "lutnn_softpq_workspace_bytes",
+           "lutnn_softpq_backward", "lutnn_softpq_backward_conv2d", "lutnn_linear_gradient", "lutnn_linear_gradient_preferred", "lutnn_softpq_workspace_bytes",
            "lutnn_encode_tree_conv2d", "lutnn_conv2d_tree", "lutnn_conv2d_rows", "lutnn_encode_conv2d", "lutnn_conv2d",
            "lutnn_auto_variant", "lutnn_linear_auto_variant", "lutnn_status_string", "lutnn_last_error", "lutnn_version",
            "lutnn_probe_smfmac_stream"]
@@ -110,6 +110,10 @@ def _load():
     lib.lutnn_softpq_backward_static.restype = i32
     lib.lutnn_softpq_backward_static.argtypes = [ctypes.POINTER(_CLayer), ctypes.c_float, vp, i64, i64, vp, i64,
                                                  vp, vp, i64, vp, vp]
+    lib.lutnn_linear_gradient.restype = i32
+    lib.lutnn_linear_gradient.argtypes = [vp, i64, i64, vp, i64, i32, i32, vp, i64, vp]
+    lib.lutnn_linear_gradient_preferred.restype = i32
+    lib.lutnn_linear_gradient_preferred.argtypes = [vp, i64, i64, vp, i64, i32, i32]
     lib.lutnn_softpq_backward_conv2d.restype = i32
     lib.lutnn_softpq_backward_conv2d.argtypes = [ctypes.POINTER(_CLayer), ctypes.c_float, vp, i64,
                                                  ctypes.POINTER(_CConvGeom), vp, i64, vp, vp, vp, vp, vp, vp, ctypes.c_size_t,
@@ -356,6 +360,24 @@ def linear_tree16(layer, tree, X, out=None, idx_workspace=None):
 
 def softpq_workspace_bytes(C, K, V, N):
     return int(LIB.lutnn_softpq_workspace_bytes(C, K, V, N))
+
+
+def linear_gradient(G, W, out=None):
+    """lutnn_linear_gradient: Z = G @ W^T, G [N, M] and W [D, M]; Z [N, D] as softpq_backward takes it."""
+    assert G.is_cuda and W.is_cuda and G.dtype == torch.float32 and W.dtype == torch.float32
+    assert G.dim() == 2 and W.dim() == 2 and G.stride(1) == 1 and W.stride(1) == 1 and G.shape[1] == W.shape[1]
+    if out is None:
+        out = torch.empty((G.shape[0], W.shape[0]), dtype=torch.float32, device=G.device)
+    assert out.is_cuda and out.dtype == torch.float32 and out.stride(1) == 1 and out.shape == (G.shape[0], W.shape[0])
+    _check(LIB.lutnn_linear_gradient(_ptr(G), G.shape[0], G.stride(0), _ptr(W), W.stride(0), W.shape[0], W.shape[1],
+                                     _ptr(out), out.stride(0), _stream()))
+    return out
+
+
+def linear_gradient_preferred(G, W):
+    """Whether linear_gradient is faster than G @ W.t() for these operands (lutnn_linear_gradient_preferred)."""
+    return bool(LIB.lutnn_linear_gradient_preferred(_ptr(G), G.shape[0], G.stride(0), _ptr(W), W.stride(0), W.shape[0],
+                                                    W.shape[1]))
 
 
 def softpq_backward(layer, temperature, X, Z, need_dx=True, workspace=None):

@@ -798,6 +798,28 @@ lutnn_status lutnn_conv2d_tree(const lutnn_layer* layer, const lutnn_tree* tree,
     return do_lookup(layer, v, idx_workspace, N, Y, ldy, static_cast<hipStream_t>(stream));
 }
 
+lutnn_status lutnn_linear_gradient(const float* G, int64_t N, int64_t ldg, const float* W, int64_t ldw, int32_t D, int32_t M,
+                                   float* Z, int64_t ldz, void* stream) {
+    if (D <= 0 || M <= 0) return fail(LUTNN_E_SHAPE, "D=%d and M=%d must be positive", D, M);
+    if (N < 0 || N >= kMaxRows) return fail(LUTNN_E_SHAPE, "N=%lld out of range", (long long)N);
+    if (N == 0) return LUTNN_OK;
+    if (!G || !W || !Z) return fail(LUTNN_E_NULL, "G, W or Z is NULL");
+    if (ldg < M || ldw < M || ldz < D)
+        return fail(LUTNN_E_SHAPE, "ldg=%lld, ldw=%lld or ldz=%lld is smaller than M=%d or D=%d", (long long)ldg, (long long)ldw,
+                    (long long)ldz, M, D);
+    if (ldg > (1 << 20) || ldw > (1 << 20))
+        return fail(LUTNN_E_SHAPE, "ldg=%lld or ldw=%lld is larger than 2^20", (long long)ldg, (long long)ldw);
+    if (!aligned(G, 4) || !aligned(W, 4) || !aligned(Z, 4)) return fail(LUTNN_E_ALIGN, "G, W and Z must be 4-byte aligned");
+    return hip_result(lutnn::launch_matmul_split(G, N, ldg, W, ldw, D, M, Z, ldz, static_cast<hipStream_t>(stream)),
+                      "gradient product launch");
+}
+
+int32_t lutnn_linear_gradient_preferred(const float* G, int64_t N, int64_t ldg, const float* W, int64_t ldw, int32_t D,
+                                        int32_t M) {
+    if (D <= 0 || M <= 0 || N <= 0 || N >= kMaxRows || ldg < M || ldw < M) return 0;
+    return lutnn::matmul_split_preferred(G, N, ldg, W, ldw, D, M);
+}
+
 lutnn_status lutnn_softpq_backward_conv2d(const lutnn_layer* layer, float temperature, const float* input, int64_t B,
                                           const lutnn_conv2d_geom* geom, const float* W, int64_t ldw, const float* G,
                                           float* Z, float* dP, float* dinput, float* dt, void* workspace,

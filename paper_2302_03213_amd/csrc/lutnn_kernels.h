@@ -87,6 +87,12 @@ struct SoftPqCall {
 };
 hipError_t launch_softpq_backward(const SoftPqCall& a, hipStream_t s);
 
+// Z[n][d] = sum_m G[n][m] W[d][m] in fp32 (matmul_split.hip); rows of up to 2^20 floats.  preferred: whether it is
+// faster than the library's product.
+bool matmul_split_preferred(const float* G, int64_t N, int64_t ldg, const float* W, int64_t ldw, int D, int M);
+hipError_t launch_matmul_split(const float* G, int64_t N, int64_t ldg, const float* W, int64_t ldw, int D, int M, float* Z,
+                               int64_t ldz, hipStream_t s);
+
 // Z[b][d][l] = sum_m W[d][m] G[b][m][l]: the im2col gradient of the ordinary convolution with weights W.
 hipError_t launch_conv_z(const float* W, int64_t ldw, const float* G, int64_t B, int D, int M, const ConvGeom& g, float* Z,
                          hipStream_t s);

@@ -4,7 +4,7 @@ Forward: the hard operator (arg-min encoding + table lookup, lutnn_build_table +
 with the table quantised as in inference when `table_dtype` is TABLE_I8 / TABLE_I4 (Sec. 3.3: the
 forward pass of training uses the quantised table).  Backward: the gradient of the soft output of
 Eq. 5-6 (lutnn_softpq_backward) for the centroids, the temperature and the layer input; the weights
-W are fixed, as in the paper, and only the GEMM Z = dL/dY @ W^T is left to torch.
+W are fixed, as in the paper.  The product Z = dL/dY @ W^T is lutnn_linear_gradient's, or torch's where that is faster.
 """
 import torch
 
@@ -46,7 +46,8 @@ class _SoftPQLinearFn(torch.autograd.Function):
     def backward(ctx, G):
         X, centroids, temperature, W = ctx.saved_tensors
         G = G.contiguous()
-        Z = G @ W.t()  # input gradient of the ordinary linear layer: a plain library GEMM
+        # input gradient of the ordinary linear layer
+        Z = _b.linear_gradient(G, W) if _b.linear_gradient_preferred(G, W) else G @ W.t()
         C, K, V = centroids.shape
         layer = _b.LutLayer(centroids.detach().contiguous(), None, _b.TABLE_F32, W.shape[1])
         dP, dX, dt = _b.softpq_backward(layer, ctx.temperature.get(), X.detach(), Z,

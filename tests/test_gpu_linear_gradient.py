@@ -1,0 +1,86 @@
+"""lutnn_linear_gradient (matmul_split.hip): Z = G . W^T from bf16 parts, against 64-bit sums.
+
+Bar: |Z - ref| <= 2^-20 sum_m |G W| elementwise.  A product loses at most 3 * 2^-22 of itself to the parts left out (the
+middle and low parts are below 2^-7 and 2^-15 of the value).  Each slice of 32 m ends in a few cut fp32 sums (2^-23 of the
+slice's magnitude each, two of them at full size) and one rounded addition to the running sum (2^-24): together below
+2^-20 of the sum of magnitudes.  Observed: 2-norm error 8e-8 to 1.6e-7 of the result (library fp32: 1.4e-7 to 1e-6)."""
+import pytest
+import torch
+
+import paper_2302_03213_amd as lut
+
+pytestmark = pytest.mark.gpu
+
+
+def operands(N, D, M, ldg=0, ldw=0, shift=0, seed=0):
+    gen = torch.Generator(device="cuda").manual_seed(seed + N * 7 + D * 3 + M)
+    def one(rows, ld):
+        flat = torch.full((rows * ld + shift,), float("nan"), device="cuda")  # what lies between the rows is not read
+        view = flat[shift:].view(rows, ld)[:, :M]
+        view.copy_(torch.randn(rows, M, generator=gen, device="cuda"))
+        return view
+    return one(N, max(ldg, M)), one(D, max(ldw, M))
+
+
+def check(G, W, Z):
+    ref = G.double() @ W.double().t()
+    bound = G.double().abs() @ W.double().abs().t() * 2.0 ** -20
+    assert bool(((Z.double() - ref).abs() <= bound).all())
+
+
+def error(G, W, Z):
+    ref = G.double() @ W.double().t()
+    return float((Z.double() - ref).norm() / ref.norm())
+
+
+@pytest.mark.parametrize("N,D,M,ldg,ldw,shift", [
+    (1, 1, 1, 0, 0, 0), (64, 64, 64, 0, 0, 0), (65, 63, 4, 0, 0, 0), (33, 97, 65, 0, 0, 0), (200, 130, 1001, 0, 0, 0),
+    (256, 256, 96, 100, 128, 0),             # strides; the second group's last slice is empty
+    (300, 77, 64, 0, 0, 1),                  # not 16-byte aligned
+    (4096, 768, 160, 0, 0, 0),               # 128 x 96 tiles
+    (8192, 2048, 36, 0, 0, 0), (4090, 1999, 68, 0, 0, 0),  # 128 x 128, whole and not
+    (1100, 1030, 132, 0, 0, 0), (600, 1800, 404, 0, 0, 0),  # 64 x 64 and 96 x 64
+])
+def test_against_64_bit_sums(N, D, M, ldg, ldw, shift):
+    G, W = operands(N, D, M, ldg, ldw, shift)
+    out = torch.full((N, D + 5), 7.0, device="cuda")
+    check(G, W, lut.linear_gradient(G, W))
+    check(G, W, lut.linear_gradient(G, W, out=out[:, :D]))
+    assert bool((out[:, D:] == 7.0).all())
+
+
+@pytest.mark.parametrize("scale_g,scale_w", [(1e-30, 1e20), (1e30, 1e-20), (3e37, 1e-3), (1e-25, 1.0)])
+def test_the_range_of_the_exponent(scale_g, scale_w):
+    G, W = operands(200, 100, 200)
+    check(G * scale_g, W * scale_w, lut.linear_gradient(G * scale_g, W * scale_w))
+
+
+def test_error_is_no_larger_than_the_librarys():
+    for N, D, M, same_sign in [(4096, 768, 3072, False), (4096, 256, 256, False), (8192, 96, 64, False), (2048, 512, 2048, True)]:
+        G, W = operands(N, D, M)
+        if same_sign:
+            G, W = G.abs(), W.abs()
+        assert error(G, W, lut.linear_gradient(G, W)) <= error(G, W, G @ W.t())
+
+
+def test_values_that_are_not_finite_stay_in_their_row():
+    G, W = operands(300, 200, 128)
+    G[17, 5], G[200, 100], W[33, 7] = float("inf"), float("nan"), float("-inf")
+    Z = lut.linear_gradient(G, W)
+    bad = ~torch.isfinite(Z)
+    expect = torch.zeros_like(bad)
+    expect[17], expect[200], expect[:, 33] = True, True, True
+    assert torch.equal(bad, expect)
+
+
+def test_refusals():
+    G, W = operands(8, 8, 8)
+    Z = torch.empty(8, 8, device="cuda")
+    call = lut.LIB.lutnn_linear_gradient
+    p = lambda t: t.data_ptr()  # noqa: E731
+    assert call(p(G), 0, 8, p(W), 8, 8, 8, p(Z), 8, None) == 0
+    for args in [(None, 8, 8, p(W), 8, 8, 8, p(Z), 8), (p(G), 8, 7, p(W), 8, 8, 8, p(Z), 8), (p(G), 8, 8, p(W), 8, 8, 8, p(Z), 7),
+                 (p(G), 8, 8, p(W), 8, 0, 8, p(Z), 8), (p(G), 8, 8, p(W), (1 << 20) + 1, 8, 8, p(Z), 8),
+                 (p(G) + 2, 8, 8, p(W), 8, 8, 8, p(Z), 8)]:
+        assert call(*args, None) != 0
+    assert not lut.LIB.lutnn_linear_gradient_preferred(p(G) + 4, 4096, 3072, p(W), 3072, 768, 3072)
