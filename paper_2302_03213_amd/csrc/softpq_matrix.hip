@@ -199,28 +199,24 @@ __global__ __launch_bounds__(kEncThreads, per_cu(V, K_T)) void softpq_matrix_ker
     __syncthreads();
     const int kq = q % (4 / H), hb = q / (4 / H);  // this lane's block of four centroids and of 16 rows
     float p[4][V];        // direct distances: centroids 4kq .. 4kq+3
-    float pA[H][VQ];      // A operand of A_k:   P'[k = i16 % K][4j + q] in the rows of D that belong to row block h
-    float pT[H][VB][4];   // A operand of dL/dx: -P'[k = 4kq + j][v = 16b + i16] in the lanes that hold row block h's e
+    float pA[VQ];     // A operand of A_k:   P'[k = i16 % K][4j + q]
+    float pT[VB][4];  // A operand of dL/dx: -P'[k = 4kq + j][v = 16b + i16]
     float my[VB];
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
         for (int v = 0; v < V; ++v) p[r][v] = pc[(4 * kq + r) * V + v];
 #pragma unroll
-    for (int h = 0; h < H; ++h)
-#pragma unroll
-        for (int j = 0; j < VQ; ++j) {
-            const int v = 4 * j + q;
-            pA[h][j] = i16 / K_T == h && v < V ? pc[i16 % K_T * V + v] - mean[w][v] : 0.f;
-        }
+    for (int j = 0; j < VQ; ++j) {
+        const int v = 4 * j + q;
+        pA[j] = v < V ? pc[i16 % K_T * V + v] - mean[w][v] : 0.f;
+    }
 #pragma unroll
     for (int b = 0; b < VB; ++b) {
         const int v = 16 * b + i16;
         my[b] = mean[w][v];
 #pragma unroll
-        for (int h = 0; h < H; ++h)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) pT[h][b][j] = hb == h && v < V ? my[b] - pc[(4 * kq + j) * V + v] : 0.f;
+        for (int j = 0; j < 4; ++j) pT[b][j] = v < V ? my[b] - pc[(4 * kq + j) * V + v] : 0.f;
     }
 
     f32x4 acc_z[VB], acc_y[VB];
@@ -254,16 +250,20 @@ __global__ __launch_bounds__(kEncThreads, per_cu(V, K_T)) void softpq_matrix_ker
             for (int g = 0; g < 4; g += H) {
                 float* const xg = xs + g * 16 * E::LS + w * V;
                 const float* const zg = zs + g * 16 * E::LS + w * V;
-                // A_k on the matrix pipe, beside the distances on the vector units
-                f32x4 a = {0.f, 0.f, 0.f, 0.f};
+                // A_k on the matrix pipe, beside the distances on the vector units.  With K = 8 each row block has a
+                // product of its own, so that a value that is not finite stays in its row.
+                f32x4 a_of[H];
 #pragma unroll
-                for (int h = 0; h < H; ++h)
+                for (int h = 0; h < H; ++h) {
+                    a_of[h] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int j = 0; j < VQ; ++j) {
                         float z = zg[(16 * h + i16) * E::LS + 4 * j + q];
                         if (4 * j + 3 >= V && 4 * j + q >= V) z = 0.f;
-                        a = __builtin_amdgcn_mfma_f32_16x16x4f32(pA[h][j], z, a, 0, 0, 0);
+                        a_of[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(pA[j], z, a_of[h], 0, 0, 0);
                     }
+                }
+                const f32x4 a = hb == 0 ? a_of[0] : a_of[H - 1];
                 const int row = i16 + (H == 1 ? 0 : 16 * hb);  // this lane's row of the step
                 float d[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -325,7 +325,7 @@ __global__ __launch_bounds__(kEncThreads, per_cu(V, K_T)) void softpq_matrix_ker
                         f32x4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                         for (int j = 0; j < 4; ++j)
-                            o = __builtin_amdgcn_mfma_f32_16x16x4f32(pT[h][b][j], e[j], o, 0, 0, 0);
+                            o = __builtin_amdgcn_mfma_f32_16x16x4f32(pT[b][j], H == 1 || hb == h ? e[j] : 0.f, o, 0, 0, 0);
                         float* const dst = xg + (16 * h + i16) * E::LS + 16 * b + 4 * q;
                         if constexpr (V % 4 == 0) {
                             if (16 * b + 4 * q < V) *reinterpret_cast<f32x4*>(dst) = o;
@@ -359,7 +359,7 @@ __global__ __launch_bounds__(kEncThreads, per_cu(V, K_T)) void softpq_matrix_ker
             for (int b = 0; b < VB; ++b) {
                 const int v = 16 * b + i16;
                 if (4 * q + r < K_T && v < V)
-                    dst[(4 * q + r) * V + v] = __fmaf_rn(-pT[0][b][r], es, acc_z[b][r] - acc_y[b][r]);
+                    dst[(4 * q + r) * V + v] = __fmaf_rn(-pT[b][r], es, acc_z[b][r] - acc_y[b][r]);
             }
         }
     }

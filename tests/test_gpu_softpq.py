@@ -329,3 +329,16 @@ def test_softpq_backward_of_a_convolution(lut, B, Cin, H, W, kernel, stride, pad
     assert none is None
     np.testing.assert_array_equal(host(dP2), host(dP))
     np.testing.assert_array_equal(host(dt2), host(dt))
+
+
+@pytest.mark.parametrize("K,V", [(8, 16), (8, 32), (16, 8), (16, 9), (16, 16), (16, 32), (8, 8)])
+def test_a_row_that_is_not_finite_spoils_no_other_rows_input_gradient(lut, K, V):
+    w = wl.make_layer("t", 100, 6, K, V, 4, "f32", seed=K + V)
+    Z = np.random.default_rng(K * V).standard_normal((100, 6 * V)).astype(np.float32)
+    layer = lut.LutLayer(dev(w.P), None, lut.TABLE_F32, 4)
+    _, clean, _ = lut.softpq_backward(layer, 1.0, dev(w.X), dev(Z))
+    Z[21, 3 * V + 1], Z[70, 0] = np.nan, np.inf
+    _, dX, _ = lut.softpq_backward(layer, 1.0, dev(w.X), dev(Z))
+    others = np.setdiff1d(np.arange(100), (21, 70))
+    np.testing.assert_array_equal(host(dX)[others], host(clean)[others])
+    assert np.isnan(host(dX)[21, 3 * V:4 * V]).all()
