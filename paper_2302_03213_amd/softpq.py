@@ -31,10 +31,17 @@ class _HostTemperature:
         return float(self.value)
 
 
+def _host_temperature(*inputs):
+    """For a call whose backward pass may follow, before autograd.Function.forward hides the grad mode."""
+    if torch.is_grad_enabled() and any(t is not None and t.requires_grad for t in inputs):
+        return _HostTemperature(inputs[2])
+    return None
+
+
 class _SoftPQLinearFn(torch.autograd.Function):
     @staticmethod
-    def forward(ctx, X, centroids, temperature, W, bias, table_dtype):
-        ctx.temperature = _HostTemperature(temperature) if any(ctx.needs_input_grad) else None
+    def forward(ctx, X, centroids, temperature, W, bias, table_dtype, host_temperature):
+        ctx.temperature = host_temperature
         layer = _b.build_table(centroids.detach(), W, table_dtype, bias=bias)
         Y = _b.linear(layer, X.detach())
         ctx.save_for_backward(X, centroids, temperature, W)
@@ -53,7 +60,7 @@ class _SoftPQLinearFn(torch.autograd.Function):
         dP, dX, dt = _b.softpq_backward(layer, ctx.temperature.get(), X.detach(), Z,
                                         need_dx=ctx.needs_input_grad[0])
         dbias = G.sum(dim=0) if ctx.has_bias and ctx.needs_input_grad[4] else None
-        return dX, dP, dt.reshape(temperature.shape), None, dbias, None
+        return dX, dP, dt.reshape(temperature.shape), None, dbias, None, None
 
 
 class SoftPQLinear(torch.nn.Module):
@@ -69,7 +76,8 @@ class SoftPQLinear(torch.nn.Module):
         self.table_dtype = table_dtype
 
     def forward(self, X):
-        return _SoftPQLinearFn.apply(X, self.centroids, self.temperature, self.W, self.bias, self.table_dtype)
+        return _SoftPQLinearFn.apply(X, self.centroids, self.temperature, self.W, self.bias, self.table_dtype,
+                                     _host_temperature(X, self.centroids, self.temperature, self.W, self.bias))
 
 
 class _SoftPQConv2dFn(torch.autograd.Function):
@@ -78,8 +86,8 @@ class _SoftPQConv2dFn(torch.autograd.Function):
     NCHW batch directly; nothing is unfolded, transposed or copied around them."""
 
     @staticmethod
-    def forward(ctx, inp, centroids, temperature, W, bias, table_dtype, kernel, stride, pad):
-        ctx.temperature = _HostTemperature(temperature) if any(ctx.needs_input_grad) else None
+    def forward(ctx, inp, centroids, temperature, W, bias, table_dtype, kernel, stride, pad, host_temperature):
+        ctx.temperature = host_temperature
         layer = _b.build_table(centroids.detach(), W, table_dtype, bias=bias)
         B, _, H, Wd = inp.shape
         Y = _b.conv2d(layer, inp.detach().contiguous(), kernel, stride, pad)  # [B*Ho*Wo, M]
@@ -100,7 +108,7 @@ class _SoftPQConv2dFn(torch.autograd.Function):
         dP, dinp, dt = _b.softpq_backward_conv2d(layer, ctx.temperature.get(), inp.detach().contiguous(), W, G, kernel,
                                                  stride, pad, need_dx=ctx.needs_input_grad[0])
         dbias = G.sum(dim=(0, 2, 3)) if ctx.has_bias and ctx.needs_input_grad[4] else None
-        return dinp, dP, dt.reshape(temperature.shape), None, dbias, None, None, None, None
+        return dinp, dP, dt.reshape(temperature.shape), None, dbias, None, None, None, None, None
 
 
 class SoftPQConv2d(torch.nn.Module):
@@ -119,4 +127,5 @@ class SoftPQConv2d(torch.nn.Module):
 
     def forward(self, inp):
         return _SoftPQConv2dFn.apply(inp, self.centroids, self.temperature, self.W, self.bias,
-                                     self.table_dtype, self.kernel, self.stride, self.pad)
+                                     self.table_dtype, self.kernel, self.stride, self.pad,
+                                     _host_temperature(inp, self.centroids, self.temperature, self.W, self.bias))
