@@ -29,23 +29,17 @@
 #include <algorithm>
 
 #include "lutnn_kernels.h"
+#include "split_bf16.h"
 
 namespace lutnn {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kSlice = 32;     // m per slice
-constexpr int kRowBytes = 64;  // of a row's 32 bf16 in LDS
 constexpr int64_t kMaxStride = 1 << 20;  // floats: a tile's rows within 32-bit offsets
 constexpr uint32_t kNowhere = 0xc0000000u;  // an offset beyond any resource: the load returns zero
-
-// Where the q-th 16 bytes of a row lie in it: rows of 64 bytes start at every fourth bank, and this spreads the same q
-// of eight neighbouring rows over all of them, for the 16-byte reads and for the 8-byte writes.
-__device__ __forceinline__ int unit(int row, int q) { return (q ^ ((row >> 1) & 3)) * 16; }
 
 __device__ __forceinline__ f32x4 product(bf16x8 a, bf16x8 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
@@ -81,21 +75,13 @@ __device__ __forceinline__ u32x4 load4(const Rows& a, uint32_t row_off, int m, i
     return r;
 }
 
-// The upper halves of two words: two values cut to bf16.
-__device__ __forceinline__ uint32_t upper(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
-
 template <int PLANE>  // bytes between the parts
 __device__ __forceinline__ void store_parts(u32x4 v, char* to) {
-    uint32_t mid[4], low[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const float r = __uint_as_float(v[i]) - __uint_as_float(v[i] & 0xffff0000u);
-        mid[i] = __float_as_uint(r);
-        low[i] = __float_as_uint(r - __uint_as_float(mid[i] & 0xffff0000u));
-    }
-    *reinterpret_cast<u32x2*>(to) = u32x2{upper(v[0], v[1]), upper(v[2], v[3])};
-    *reinterpret_cast<u32x2*>(to + PLANE) = u32x2{upper(mid[0], mid[1]), upper(mid[2], mid[3])};
-    *reinterpret_cast<u32x2*>(to + 2 * PLANE) = u32x2{upper(low[0], low[1]), upper(low[2], low[3])};
+    uint32_t high[2], mid[2], low[2];
+    cut<2>({v[0], v[1], v[2], v[3]}, high, mid, low);
+    *reinterpret_cast<u32x2*>(to) = u32x2{high[0], high[1]};
+    *reinterpret_cast<u32x2*>(to + PLANE) = u32x2{mid[0], mid[1]};
+    *reinterpret_cast<u32x2*>(to + 2 * PLANE) = u32x2{low[0], low[1]};
 }
 
 // grid: tiles of Z, column tile fastest.

@@ -4,26 +4,42 @@
 #include <algorithm>
 
 #include "lutnn_kernels.h"
+#include "split_bf16.h"
 
 namespace lutnn {
 namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int kTD = 64, kTN = 256, kTM = 16;  // workgroup tile: rows of W, output pixels; m per stage
-constexpr int kAS = kTD + 4, kBS = kTN + 4;
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
-// Z[b][d][l] = sum_m W[d][m] * G[b][m][l] on v_mfma_f32_32x32x2_f32 (fp32 products and sums, m ascending in steps of
-// two).  A workgroup owns 64 rows d and 256 columns n = (b, l), a wavefront a 64 x 64 part; a thread copies one column of
-// G, so that the column's image is found once and images need not be multiples of anything.
-// Bound by the write of Z.  50176 columns, D = 576, M = 64: 54 us for 128 MB and 3.7 GFLOP (a library batched product:
-// 99 us; the same library's plain product 60 us, but from a transposed copy of G and into rows that then had to be
-// transposed back).
-__global__ __launch_bounds__(256, 4) void conv_z_kernel(const float* __restrict__ W, int64_t ldw,
+constexpr int kTD = 64, kTN = 256;  // workgroup tile: rows of W, output pixels
+constexpr int kPlane = (kTD + kTN) * kRowBytes;
+
+__device__ __forceinline__ f32x16 product(bf16x8 a, bf16x8 b, f32x16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+// 16 bytes of each part of a row, eight values.
+__device__ __forceinline__ void store_parts(const uint32_t (&v)[8], char* to) {
+    uint32_t high[4], mid[4], low[4];
+    cut<4>(v, high, mid, low);
+    *reinterpret_cast<u32x4*>(to) = u32x4{high[0], high[1], high[2], high[3]};
+    *reinterpret_cast<u32x4*>(to + kPlane) = u32x4{mid[0], mid[1], mid[2], mid[3]};
+    *reinterpret_cast<u32x4*>(to + 2 * kPlane) = u32x4{low[0], low[1], low[2], low[3]};
+}
+
+// Z[b][d][l] = sum_m W[d][m] * G[b][m][l] from bf16 parts, as matmul_split.hip forms G . W^T (the parts, the six products
+// and the sums are described there).  A workgroup owns 64 rows d and 256 columns n = (b, l), a wavefront a 64 x 64 part; a
+// thread copies one column of G, so that the column's image is found once and images need not be multiples of anything.
+// On the fp32 matrix instructions it was bound by them wherever M is not small; the whole backward pass of a 3x3
+// convolution, with those and with this: 16 x 256 channels 14 x 14, M = 512: 171 -> 130 us; 4 x 128, 28 x 28, M = 256: 84
+// -> 72; 16 x 64, 56 x 56, M = 64: 228 -> 220, where the write of Z bounds it (53 us for 128 MB, 55 before; a library
+// batched product: 99).
+__global__ __launch_bounds__(256, 2) void conv_z_kernel(const float* __restrict__ W, int64_t ldw,
                                                         const float* __restrict__ G, float* __restrict__ Z, int D, int M,
                                                         uint32_t L, uint32_t N, int d_tiles, int blocks) {
-    __shared__ float as[kTM * kAS];
-    __shared__ float bs[kTM * kBS];
+    __shared__ __align__(16) char lds[3 * kPlane];
     // row tiles of W fastest, and neighbouring blocks on one XCD: the columns of G are then in its L2
     const int block = (int)(blockIdx.x % 8) * (int)(gridDim.x / 8) + (int)(blockIdx.x / 8);
     if (block >= blocks) return;
@@ -35,41 +51,78 @@ __global__ __launch_bounds__(256, 4) void conv_z_kernel(const float* __restrict_
     const bool n_ok = n < N;
     const uint32_t b = n_ok ? n / L : 0u;
     const float* __restrict__ g = G + (int64_t)b * M * L + (n_ok ? n - b * L : 0u);
-    const int ad = tid >> 2, am = (tid & 3) * 4;
+    const int ad = tid >> 2, aq = tid & 3;
     const float* __restrict__ wr = W + (int64_t)(d0 + ad < D ? d0 + ad : 0) * ldw;
+    uint32_t gv[kSlice], wv[8];
+    const auto load = [&](int m0) {
+        const float* at = g + (int64_t)m0 * L;
+        int64_t step = L;
+        asm volatile("" : "+s"(step));  // one pointer that walks: the compiler kept 32 of them across the loop, and spilled
+#pragma unroll
+        for (int i = 0; i < kSlice; ++i, at += step) gv[i] = __float_as_uint(n_ok && m0 + i < M ? *at : 0.f);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int m = m0 + 8 * aq + i;
+            wv[i] = __float_as_uint(d0 + ad < D && m < M ? wr[m] : 0.f);
+        }
+    };
+    char* const to_n = lds + (kTD + tid) * kRowBytes;
+    char* const to_d = lds + ad * kRowBytes + unit(ad, aq);
+    const char* const from_d = lds + j32 * kRowBytes;
+    const char* const from_n = lds + (kTD + 64 * w + j32) * kRowBytes;
 
     f32x16 acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{};
 
-    for (int m0 = 0; m0 < M; m0 += kTM) {
-        float gv[kTM], wv[4];
-#pragma unroll
-        for (int i = 0; i < kTM; ++i) gv[i] = n_ok && m0 + i < M ? g[(int64_t)(m0 + i) * L] : 0.f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) wv[i] = d0 + ad < D && m0 + am + i < M ? wr[m0 + am + i] : 0.f;
+    load(0);
+    for (int m0 = 0; m0 < M; m0 += kSlice) {
         __syncthreads();
 #pragma unroll
-        for (int i = 0; i < kTM; ++i) bs[i * kBS + tid] = gv[i];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) as[(am + i) * kAS + ad] = wv[i];
+        for (int q = 0; q < 4; ++q)
+            store_parts({gv[8 * q], gv[8 * q + 1], gv[8 * q + 2], gv[8 * q + 3], gv[8 * q + 4], gv[8 * q + 5], gv[8 * q + 6],
+                         gv[8 * q + 7]}, to_n + unit(tid, q));
+        store_parts(wv, to_d);
         __syncthreads();
+        if (m0 + kSlice < M) load(m0 + kSlice);
 #pragma unroll
-        for (int k = 0; k < kTM; k += 2) {
-            float a[2], bb[2];
+        for (int j = 0; j < 2; ++j) {  // 32 columns at a time: the registers of both at once are not there
+            f32x16 s[2] = {f32x16{}, f32x16{}};
+            bf16x8 dh[2][2], nh[2];  // high parts, for the last products of the slice
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                a[i] = as[(k + half) * kAS + 32 * i + j32];
-                bb[i] = bs[(k + half) * kBS + 64 * w + 32 * i + j32];
+            for (int k = 0; k < 2; ++k) {
+                const int u = unit(j32, 2 * k + half);
+                const char* const at_n = from_n + j * 32 * kRowBytes + u;
+                nh[k] = *reinterpret_cast<const bf16x8*>(at_n);
+                const bf16x8 nm = *reinterpret_cast<const bf16x8*>(at_n + kPlane);
+                const bf16x8 nl = *reinterpret_cast<const bf16x8*>(at_n + 2 * kPlane);
+                bf16x8 dm[2], dl[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const char* const at = from_d + i * 32 * kRowBytes + u;
+                    dh[k][i] = *reinterpret_cast<const bf16x8*>(at);
+                    dm[i] = *reinterpret_cast<const bf16x8*>(at + kPlane);
+                    dl[i] = *reinterpret_cast<const bf16x8*>(at + 2 * kPlane);
+                }
+#pragma unroll
+                for (int i = 0; i < 2; ++i) s[i] = product(dl[i], nh[k], s[i]);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) s[i] = product(dh[k][i], nl, s[i]);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) s[i] = product(dm[i], nm, s[i]);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) s[i] = product(dm[i], nh[k], s[i]);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) s[i] = product(dh[k][i], nm, s[i]);
             }
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+            for (int k = 0; k < 2; ++k)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], bb[j], acc[i][j], 0, 0, 0);
+                for (int i = 0; i < 2; ++i) s[i] = product(dh[k][i], nh[k], s[i]);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) acc[i][j] += s[i];
         }
     }
 #pragma unroll

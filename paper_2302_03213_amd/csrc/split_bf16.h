@@ -1,0 +1,40 @@
+// fp32 values as sums of three bf16 parts for the bf16 matrix instructions (matmul_split.hip says why and how exactly),
+// and the LDS layout that both kernels keep them in: rows of 32 values, 64 bytes, one plane per part.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace lutnn {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+constexpr int kSlice = 32;     // values of a row in LDS
+constexpr int kRowBytes = 64;  // of one part
+
+// Where the q-th 16 bytes of a row lie in it: rows of 64 bytes start at every fourth bank, and this spreads the same q
+// of eight neighbouring rows over all of them, for the 16-byte reads and for the writes.
+__device__ __forceinline__ int unit(int row, int q) { return (q ^ ((row >> 1) & 3)) * 16; }
+
+// The upper halves of two words: two values cut to bf16.
+__device__ __forceinline__ uint32_t upper(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+
+// 2 n values into n words of each part: the top eight significant bits, the next eight, the rest.
+template <int n>
+__device__ __forceinline__ void cut(const uint32_t (&v)[2 * n], uint32_t (&high)[n], uint32_t (&mid)[n], uint32_t (&low)[n]) {
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+        uint32_t m[2], l[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const uint32_t x = v[2 * i + j];
+            const float r = __uint_as_float(x) - __uint_as_float(x & 0xffff0000u);
+            m[j] = __float_as_uint(r);
+            l[j] = __float_as_uint(r - __uint_as_float(m[j] & 0xffff0000u));
+        }
+        high[i] = upper(v[2 * i], v[2 * i + 1]);
+        mid[i] = upper(m[0], m[1]);
+        low[i] = upper(l[0], l[1]);
+    }
+}
+
+}  // namespace lutnn
