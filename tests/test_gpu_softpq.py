@@ -342,3 +342,51 @@ def test_a_row_that_is_not_finite_spoils_no_other_rows_input_gradient(lut, K, V)
     others = np.setdiff1d(np.arange(100), (21, 70))
     np.testing.assert_array_equal(host(dX)[others], host(clean)[others])
     assert np.isnan(host(dX)[21, 3 * V:4 * V]).all()
+
+
+def spread_codebook(kind, rng, N, C, K, V):
+    """Centroids that are not one cloud, and activations of the clouds that are in use; values that fp32 holds."""
+    P, X = rng.standard_normal((C, K, V)), rng.standard_normal((N, C, V))
+    if kind.startswith("one far"):          # a centroid that no row is near
+        P[:, 3] = float(kind.split()[-1])
+    elif kind == "most far":                # K/2 + 1 of them: fewer than half are in use
+        P[:, K // 2 - 1:] = 1e4
+    elif kind == "most zero":               # the same, parked at zero beside a cloud that is not there
+        P += 100.0
+        X += 100.0
+        P[:, 5:] = 0.0
+    elif kind == "two clouds":
+        P[:, K // 2:] += 100.0
+        X[1::2] += 100.0
+    elif kind == "opposite clouds":         # no offset of either sign can be taken off
+        P += np.where(np.arange(K) % 2, 50.0, -50.0)[:, None]
+        X += np.where(np.arange(N) % 2, 50.0, -50.0)[:, None, None]
+    else:
+        assert kind == "one axis far"
+        P[:, :, 1] += 1000.0
+        X[:, :, 1] += 1000.0
+    return P.astype(np.float32), X.astype(np.float32).reshape(N, C * V)
+
+
+@pytest.mark.parametrize("K,V", [(16, 8), (16, 9), (16, 16), (16, 32), (8, 16), (8, 32)])
+@pytest.mark.parametrize("kind", ["one far 100", "one far 1e4", "one far -1e6", "one far 1e20", "most far", "most zero", "two clouds",
+                                  "opposite clouds", "one axis far"])
+def test_codebooks_whose_centroids_are_spread(lut, kind, K, V):
+    """The bar of the file holds where centroids are no single cloud, too.  A = z . P is rounded at about 2^-24 |z| |P_k|, and an
+    error of A reaches dL/dx times 2 s |x - P| / t: with values of 100 beside differences of one, some 100 * 2^-24 = 6e-6 of
+    the gradient in the 2-norm and a few times that in the largest element (1.2e-5 and 4e-5 at most, computed in fp32); far
+    centroids that no row is near add nothing.  Sums about the centroids' mean miss the bar by orders of magnitude."""
+    N, C, M, t = 200, 5, 6, V / 2
+    rng = np.random.default_rng(K * 100 + V)
+    w = wl.make_layer("t", N, C, K, V, M, "f32", seed=V)
+    w.P, w.X = spread_codebook(kind, rng, N, C, K, V)
+    G = rng.standard_normal((N, M))
+    Z = (G @ w.W.astype(np.float64).T).astype(np.float32)
+    dP_ref, dX_ref, dt_ref = osp.backward(w.P, w.W, w.X, t, G)
+    layer = lut.LutLayer(dev(w.P), None, lut.TABLE_F32, M)
+    dP, dX, dt = lut.softpq_backward(layer, t, dev(w.X), dev(Z))
+    print("normalised errors dP %.2e dX %.2e" % (close(host(dP), dP_ref, 1e9), close(host(dX), dX_ref, 1e9)))
+    close(host(dP), dP_ref)
+    close(host(dX), dX_ref)
+    if kind != "one far 1e20":  # the distance to it is infinite in fp32, and 0 * inf has no place in a magnitude
+        check_dt(host(dt)[0], dt_ref, dt_magnitude(w, t, G))
