@@ -227,9 +227,9 @@ __global__ __launch_bounds__(kEncThreads, per_cu(V, K_T)) void softpq_matrix_ker
         for (int j = 0; j < 4; ++j) pT[b][j] = v < V ? my[b] - pc[(4 * kq + j) * V + v] : 0.f;
     }
 
-    f32x4 acc_z[VB], acc_y[VB];
+    f32x4 sum[VB];
 #pragma unroll
-    for (int b = 0; b < VB; ++b) acc_z[b] = acc_y[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int b = 0; b < VB; ++b) sum[b] = f32x4{0.f, 0.f, 0.f, 0.f};
     float esum[4] = {0.f, 0.f, 0.f, 0.f};
     float dt_acc = 0.f;
     float* __restrict__ ts = tr[w][0];
@@ -319,7 +319,11 @@ __global__ __launch_bounds__(kEncThreads, per_cu(V, K_T)) void softpq_matrix_ker
                 *reinterpret_cast<f32x4*>(ts + row * TS + 4 * kq) = f32x4{s[0], s[1], s[2], s[3]};
                 *reinterpret_cast<f32x4*>(te + row * TS + 4 * kq) = f32x4{e[0], e[1], e[2], e[3]};
                 wave_lds_fence();
-                // dL/dP: rows 4q + j of a block are contracted in step j (rows K .. of the result are not used)
+                // dL/dP: rows 4q + j of a block are contracted in step j (rows K .. of the result are not used).  Each step of
+                // 16 rows is summed from zero and added to the running sum, so that no chain is long.
+                f32x4 acc_z[VB], acc_y[VB];
+#pragma unroll
+                for (int b = 0; b < VB; ++b) acc_z[b] = acc_y[b] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int hj = 0; hj < 4 * H; ++hj) {
                     const int n = hj / 4 * 16 + 4 * q + hj % 4;
@@ -351,6 +355,8 @@ __global__ __launch_bounds__(kEncThreads, per_cu(V, K_T)) void softpq_matrix_ker
                         }
                     }
                 }
+#pragma unroll
+                for (int b = 0; b < VB; ++b) sum[b] += acc_z[b] - acc_y[b];
                 wave_lds_fence();
             }
         }
@@ -374,7 +380,7 @@ __global__ __launch_bounds__(kEncThreads, per_cu(V, K_T)) void softpq_matrix_ker
             for (int b = 0; b < VB; ++b) {
                 const int v = 16 * b + i16;
                 if (4 * q + r < K_T && v < V)
-                    dst[(4 * q + r) * V + v] = __fmaf_rn(-pT[b][r], es, acc_z[b][r] - acc_y[b][r]);
+                    dst[(4 * q + r) * V + v] = __fmaf_rn(-pT[b][r], es, sum[b][r]);
             }
         }
     }
@@ -386,7 +392,7 @@ __global__ __launch_bounds__(kEncThreads, per_cu(V, K_T)) void softpq_matrix_ker
 }
 
 // dP[c][k][v] = sum over chunks of partial[chunk][c][k*V + v]: four wavefronts take a quarter of the chunks each, in
-// ascending order, and the quarters are added in ascending order (reproducible run to run).  Block 0 also folds
+// ascending order, and the quarters are added in ascending order (reproducible run to run; no chain is long).  Block 0 also folds
 // the workgroups' temperature sums.
 __global__ __launch_bounds__(256) void softpq_chunks_kernel(const float* __restrict__ partial,
                                                             const float* __restrict__ partial_dt, int chunks, int n_dt,
@@ -403,12 +409,11 @@ __global__ __launch_bounds__(256) void softpq_chunks_kernel(const float* __restr
         const int per = (chunks + 3) / 4;
         const int end = min(chunks, (w + 1) * per);
         int ch = w * per;
-        for (; ch + 8 <= end; ch += 8) {  // eight independent loads, added in ascending chunk order
+        for (; ch + 8 <= end; ch += 8) {  // eight independent loads, added in pairs
             float t[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) t[u] = partial[(size_t)(ch + u) * stride + e];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) sum += t[u];
+            sum += ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
         }
         for (; ch < end; ++ch) sum += partial[(size_t)ch * stride + e];
     }

@@ -390,3 +390,32 @@ def test_codebooks_whose_centroids_are_spread(lut, kind, K, V):
     close(host(dX), dX_ref)
     if kind != "one far 1e20":  # the distance to it is infinite in fp32, and 0 * inf has no place in a magnitude
         check_dt(host(dt)[0], dt_ref, dt_magnitude(w, t, G))
+
+
+def gradient_in_64_bits(P, X, Z, t):
+    """dL/dP of the soft output on the GPU, in slices of rows."""
+    C, K, V = P.shape
+    P, total = P.double(), 0.0
+    for x, z in zip(X.split(2048), Z.split(2048)):
+        x, z = x.double().view(-1, C, 1, V), z.double().view(-1, C, 1, V)
+        s = torch.softmax(-((x - P) ** 2).sum(-1) / t, -1)
+        a = (z * P).sum(-1)
+        e = -2.0 / t * s * (a - (s * a).sum(-1, keepdim=True))
+        total = total + (s[..., None] * z - e[..., None] * (x - P)).sum(0)
+    return total
+
+
+@pytest.mark.parametrize("C,K,V", [(64, 16, 9), (64, 16, 16), (64, 8, 32)])
+def test_centroid_gradient_over_many_rows(lut, C, K, V):
+    """Nothing long is summed in one fp32 chain: terms that nearly cancel over 50176 rows.  A term is known to about 2^-22
+    (softmax weights of a few ulp), and behind it come some hundred additions of 2^-24, each of a part of the sum: observed
+    2.5e-7, 2.9e-7 and 3.3e-7 of the result in the 2-norm.  One chain over a chunk's 800 to 1600 rows makes it 5.9e-7 to
+    7.5e-7."""
+    gen = torch.Generator(device="cuda").manual_seed(C * K * V)
+    P = torch.randn(C, K, V, generator=gen, device="cuda")
+    X, Z = (torch.randn(50176, C * V, generator=gen, device="cuda") for _ in range(2))
+    dP, _, _ = lut.softpq_backward(lut.LutLayer(P, None, lut.TABLE_F32, 4), V / 2, X, Z)
+    ref = gradient_in_64_bits(P, X, Z, V / 2)
+    error = float((dP.double() - ref).norm() / ref.norm())
+    print("error of dP %.2e" % error)
+    assert error <= 4e-7
