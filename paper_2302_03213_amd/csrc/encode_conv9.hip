@@ -31,8 +31,8 @@
 //   index bits 2^-19 of the score
 // and the direct form by (V + 2) 2^-24 d_k, d_k = score + |x|^2.  Summed for the two scores that are compared, and
 // doubled for good measure, this is  tx |x| + t2 |x|^2 + t0 + tm (|m1| + |m2|)  with tx and t0 per codebook.
-// Sub-vectors with |x|^2 > 2^28 (the parts may overflow), and codebooks with values outside 2^-10 .. 2^12, are not
-// filtered.
+// Sub-vectors with |x|^2 > 2^28 (the parts may overflow), and codebooks whose largest value lies outside 2^-10 .. 2^12 or
+// that hold a value that is not finite, are not filtered.
 #include <algorithm>
 
 #include "encode_tile.h"
@@ -79,6 +79,7 @@ __device__ __forceinline__ void load_codebook(const float* __restrict__ pc, int 
         nn = __fmaf_rn(p[v], p[v], nn);
         pm = fmaxf(pm, fabsf(p[v]));
     }
+    if (!(nn <= 3.0e38f)) pm = __builtin_inff();  // a maximum passes NaN by
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         const float x = q == 3 ? (j < 3 ? -2.f * p[8] : 0.f) : -2.f * p[j];  // high, low, high of the ninth
@@ -272,8 +273,9 @@ __device__ __forceinline__ uint32_t search_rows(uint64_t rows, uint32_t best, co
             const float t = taps[at + toff[v]] - p[v];
             d = __fmaf_rn(t, t, d);
         }
-        // not negative: ordered like its bits (NaN, from activations that are not finite, is the largest)
-        const uint32_t bits = k < K_T ? __float_as_uint(d) : 0xffffffffu;
+        // not negative: ordered like its bits, NaN being the largest - but in centroid 0, where the direct search starts
+        // and which nothing is below then
+        const uint32_t bits = k >= K_T ? 0xffffffffu : k == 0 && d != d ? 0u : __float_as_uint(d);
         const uint32_t least = min_ror<0x121>(min_ror<0x122>(min_ror<0x124>(min_ror<0x128>(bits))));
         const uint64_t hit = __ballot(bits == least);
 #pragma unroll

@@ -75,3 +75,16 @@ def test_values_that_are_not_finite():
     inp[rng.random(inp.shape) < 0.01] = np.inf
     inp[rng.random(inp.shape) < 0.01] = -np.inf
     check(rng.standard_normal((32, 16, 9)).astype(np.float32), inp, 3, 1, 1, finite=False)
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("k", [0, 5, 15])
+def test_centroids_that_are_not_finite(value, k):
+    """A distance that is not a number loses against any other but in centroid 0, which nothing is below then."""
+    rng = np.random.default_rng(7)
+    P = rng.standard_normal((32, 16, 9)).astype(np.float32)
+    P[::3, k, 4] = value
+    inp = rng.standard_normal((40, 32, 30, 30)).astype(np.float32)
+    inp[rng.random(inp.shape) < 0.01] = np.inf
+    inp[rng.random(inp.shape) < 0.01] = np.nan
+    check(P, inp, 3, 1, 1, finite=False)
