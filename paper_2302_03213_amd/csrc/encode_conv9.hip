@@ -188,7 +188,7 @@ struct Band {
 __device__ __forceinline__ Band band_of(const ConvGeom& g, int b, int pt) {  // image, pixel tile
     Band t;
     const int pix = g.Ho * g.Wo;
-    t.image = b * g.Cin * (int64_t)g.H * g.W;
+    t.image = (int64_t)b * g.Cin * g.H * g.W;
     t.p0 = pt * kEncRows;
     t.p1 = min(t.p0 + kEncRows - 1, pix - 1);
     t.ho0 = t.p0 / g.Wo;

@@ -88,3 +88,16 @@ def test_centroids_that_are_not_finite(value, k):
     inp[rng.random(inp.shape) < 0.01] = np.inf
     inp[rng.random(inp.shape) < 0.01] = np.nan
     check(P, inp, 3, 1, 1, finite=False)
+
+
+def test_channels_of_all_images_beyond_31_bits():
+    """B * Cin above 2^31, with images of one pixel: the last images equal the oracle's indices on their rows."""
+    B, C, last = (1 << 23) + 70, 256, 64
+    P = np.random.default_rng(8).standard_normal((C, 16, 9)).astype(np.float32)
+    inp = torch.randn(B, C, 1, 1, generator=torch.Generator(device="cuda").manual_seed(8), device="cuda")
+    import paper_2302_03213_amd as lut
+    got = lut.encode_conv2d(lut.LutLayer(dev(P), None, lut.TABLE_F32, 8), inp, 3, 1, 1)
+    for part in (slice(0, last), slice(B - last, B)):
+        np.testing.assert_array_equal(host(got[part]), oracle.encode(P, unfolded(host(inp[part]), 3, 1, 1)))
+    del got, inp
+    torch.cuda.empty_cache()
