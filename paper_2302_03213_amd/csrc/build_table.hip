@@ -248,7 +248,8 @@ struct Tables {
 template <int V_T, int CPT>
 hipError_t launch_columns(const Tables& t, hipStream_t s) {
     const int Kb = kblocks(t.K), Mp = (int)packed_cols(t.M);
-    const int threads = CPT == 4 && t.M >= 4096 ? 256 : 64;
+    // the grid's second dimension stops at 65535
+    const int threads = (CPT == 4 && t.M >= 4096) || Mp > 64 * 65535 ? kThreads : 64;
     const auto grid = [&](int cols) {
         return dim3((unsigned)t.C * Kb, (unsigned)((cols + threads * CPT - 1) / (threads * CPT)));
     };
@@ -290,7 +291,8 @@ hipError_t launch_tables(const Tables& t, hipStream_t s) {
 
 }  // namespace
 
-// Callers guarantee C*K < 2^31 (grid.x) and M <= 2^24 (grid.y <= 65536).
+// Callers guarantee C*K < 2^31 (grid.x) and M <= 2^24 - 512: padded to the packed width, up to 65535 blocks of 256 columns
+// (grid.y).
 hipError_t launch_build_table_f32(const float* P, const float* W, int64_t ldw, int C, int K, int V,
                                   int M, float* T, hipStream_t s) {
     return launch_tables(Tables{P, W, ldw, C, K, V, M, T, nullptr, nullptr, nullptr, false}, s);

@@ -39,3 +39,22 @@ def test_table_shares(C, K, V, M, strided):
     assert host(zero.scale)[0] == 1.0 and not host(zero.table).any()
     scales = [host(lut.build_table(dev(w.P), W, lut.TABLE_I4, packed=p).scale)[0] for p in (True, False)]
     assert scales == [np.float32(np.abs(Tf).max() / np.float32(7))] * 2
+
+
+@pytest.mark.parametrize("C,K,V,M", [(1, 2, 3, (1 << 24) - 512), (1, 3, 2, 4194305), (1, 2, 9, 4194239), (2, 2, 9, 4194241)])
+def test_widest_tables(C, K, V, M):
+    """One column per thread, at widths where workgroups of 64 would not fit the grid's second dimension."""
+    import paper_2302_03213_amd as lut
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    P = torch.randn(C, K, V, generator=gen, device="cuda")
+    W = torch.randn(C * V, M, generator=gen, device="cuda")
+    f32 = lut.build_table(P, W, lut.TABLE_F32).table
+    for part in (slice(0, 1000), slice(M - 1000, M)):
+        np.testing.assert_array_equal(host(f32[:, :, part]), oracle.build_table_f32(host(P), host(W[:, part].contiguous())))
+    layer = lut.build_table(P, W, lut.TABLE_I8)
+    q, s = oracle.quantize_i8(host(f32))
+    assert host(layer.scale)[0] == np.float32(s)
+    np.testing.assert_array_equal(host(layer.table), q)
+    packed = host(layer.packed).reshape(C, -1, 16)
+    np.testing.assert_array_equal(packed[:, :M, :K], q.transpose(0, 2, 1))
+    assert not packed[:, :, K:].any() and not packed[:, M:].any()
