@@ -376,8 +376,9 @@ LUTNN_API lutnn_status lutnn_conv2d(const lutnn_layer* layer, const float* input
 LUTNN_API lutnn_status lutnn_linear_gradient(const float* G, int64_t N, int64_t ldg, const float* W, int64_t ldw,
                                              int32_t D, int32_t M, float* Z, int64_t ldz, void* stream);
 
-/* Host: 1 where lutnn_linear_gradient is faster than a library's fp32 matrix product for these operands, 0 elsewhere
- * (few tiles of a long sum, rows that are not whole 16-byte vectors) and for shapes it refuses. */
+/* Host: 1 where lutnn_linear_gradient is faster than a library's fp32 matrix product for these operands and no less exact,
+ * 0 elsewhere (few tiles of a long sum, rows that are not whole 16-byte vectors, fewer than 16 terms) and for shapes it
+ * refuses. */
 LUTNN_API int32_t lutnn_linear_gradient_preferred(const float* G, int64_t N, int64_t ldg, const float* W, int64_t ldw,
                                                   int32_t D, int32_t M);
 

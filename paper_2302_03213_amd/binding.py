@@ -375,7 +375,8 @@ def linear_gradient(G, W, out=None):
 
 
 def linear_gradient_preferred(G, W):
-    """Whether linear_gradient is faster than G @ W.t() for these operands (lutnn_linear_gradient_preferred)."""
+    """Whether linear_gradient is faster than G @ W.t() for these operands and no less exact
+    (lutnn_linear_gradient_preferred)."""
     return bool(LIB.lutnn_linear_gradient_preferred(_ptr(G), G.shape[0], G.stride(0), _ptr(W), W.stride(0), W.shape[0],
                                                     W.shape[1]))
 

@@ -12,7 +12,7 @@
 // and low.low, is 2^-24 of a product on average and 2^-21 at most.  The matrix instruction cuts its result where an fp32
 // addition rounds, so nothing long is summed in it: each slice of 32 m starts from zero, small products first, and is
 // added to the running sum by a vector addition.  Against 64-bit sums the error is below that of the library's fp32
-// product, which adds all M in one fp32 chain: tests/test_gpu_linear_gradient.py states both.
+// product, which adds all M in one fp32 chain, from 16 terms on: tests/test_gpu_linear_gradient.py states both.
 //
 // Mapping.  A workgroup is two groups of four wavefronts, a wavefront of each per SIMD.  Both own the same tile of Z, 32
 // RB rows n by 32 CB columns d, and every other slice of m.  They take turns: while one group reads its slice's parts
@@ -237,8 +237,10 @@ int best_tile(int64_t N, int D, int M) {
 // 142 -> 121; 8192 x 768, M = 768: 84 -> 60; 8192 x 2048, M = 1024: 244 -> 196; 1024 x 1024, M = 1024: 21 -> 20; 5000 x
 // 300, M = 700: 30 -> 21; 4096 x 256, M = 256: 19 -> 8.  Rows that are not whole 16-byte vectors load value by value (3000
 // x 1000, M = 1001: 81 -> 73 at best, and behind at others): the library.
+// Below 16 terms the parts are less exact than one fp32 chain (7e-8 of the result at any length, against 2.5e-8 at one term,
+// 6.4e-8 at 12 and 7.4e-8 at 16): the library.
 bool matmul_split_preferred(const float* G, int64_t N, int64_t ldg, const float* W, int64_t ldw, int D, int M) {
-    if (N <= 0 || !vec4_ok(G, ldg, M) || !vec4_ok(W, ldw, M) || ldg > kMaxStride || ldw > kMaxStride) return false;
+    if (N <= 0 || M < 16 || !vec4_ok(G, ldg, M) || !vec4_ok(W, ldw, M) || ldg > kMaxStride || ldw > kMaxStride) return false;
     const float library_us = 2.f * N * D * M / 130e6f + 8.f;
     return predicted_us(kTiles[best_tile(N, D, M)], N, D, M) < library_us;
 }

@@ -84,3 +84,24 @@ def test_refusals():
                  (p(G) + 2, 8, 8, p(W), 8, 8, 8, p(Z), 8)]:
         assert call(*args, None) != 0
     assert not lut.LIB.lutnn_linear_gradient_preferred(p(G) + 4, 4096, 3072, p(W), 3072, 768, 3072)
+
+
+@pytest.mark.parametrize("M", [1, 2, 4, 8, 12, 16, 20, 32, 48])
+def test_short_sums_are_no_less_exact_than_an_fp32_chain(M):
+    """What training forms Z with: for a linear layer where linear_gradient is preferred, for a convolution always.  With all
+    centroids equal the soft encoding is 1/16 each and no other term is left: dL/dP of a single pixel is Z / 16."""
+    def chain(G, W):
+        sums = torch.zeros(G.shape[0], W.shape[0], device="cuda")
+        for m in range(M):  # one rounding a term: the product of two fp32 values is exact in 64 bits
+            sums = (sums.double() + G[:, m:m + 1].double() * W[:, m].double()).float()
+        return sums
+    G, W = operands(8192, 1024, M)
+    if lut.linear_gradient_preferred(G, W):
+        assert error(G, W, lut.linear_gradient(G, W)) <= error(G, W, chain(G, W))
+    C, pixels = 1000, 200
+    G, W = operands(pixels, 9 * C, M)
+    layer = lut.LutLayer(torch.zeros(C, 16, 9, device="cuda"), None, lut.TABLE_F32, M)
+    image = torch.ones(1, C, 3, 3, device="cuda")
+    Z = [lut.softpq_backward_conv2d(layer, 1.0, image, W, G[n].reshape(1, M, 1, 1), 3)[0][:, 7].reshape(-1) * 16
+         for n in range(pixels)]
+    assert error(G, W, torch.stack(Z)) <= error(G, W, chain(G, W))
