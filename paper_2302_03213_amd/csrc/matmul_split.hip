@@ -14,6 +14,8 @@
 // added to the running sum by a vector addition.  Against 64-bit sums the error is below that of the library's fp32
 // product, which adds all M in one fp32 chain, from 16 terms on: tests/test_gpu_linear_gradient.py states both.
 //
+// Sums that are not finite are formed again as one fp32 chain, by the thread that has them: an infinite value has no parts.
+//
 // Mapping.  A workgroup is two groups of four wavefronts, a wavefront of each per SIMD.  Both own the same tile of Z, 32
 // RB rows n by 32 CB columns d, and every other slice of m.  They take turns: while one group reads its slice's parts
 // from LDS and multiplies, the other cuts its next slice into parts, writes those to its own LDS, and loads the one after
@@ -172,6 +174,7 @@ __global__ __launch_bounds__(512, RB * CB > 4 ? 2 : 4) void matmul_split_kernel(
     }
     lds_barrier();
     if (group == 1) return;
+    float probe = 0.f;  // NaN once a sum is not finite
 #pragma unroll
     for (int b = 0; b < RB; ++b) {
         const int64_t n = n0 + wn * 16 * RB + 16 * b + i16;
@@ -181,6 +184,8 @@ __global__ __launch_bounds__(512, RB * CB > 4 ? 2 : 4) void matmul_split_kernel(
         for (int a = 0; a < CB; ++a) {
             const f32x4 r = sum[a][b] + other[(a * RB + b) * 64];
             const int d = d0 + wd * 16 * CB + 16 * a + 4 * q;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) probe = __fmaf_rn(r[j], 0.f, probe);
             if (vec4_z && d + 3 < D) {
                 *reinterpret_cast<f32x4*>(z + d) = r;
             } else {
@@ -189,6 +194,12 @@ __global__ __launch_bounds__(512, RB * CB > 4 ? 2 : 4) void matmul_split_kernel(
                     if (d + j < D) z[d + j] = r[j];
             }
         }
+    }
+    if (probe == 0.f) return;
+    for (int i = 0; i < RB * CB * 4; ++i) {
+        const int64_t n = n0 + wn * 16 * RB + i / (CB * 4) * 16 + i16;
+        const int d = d0 + wd * 16 * CB + i / 4 % CB * 16 + 4 * q + i % 4;
+        if (n < N && d < D && !is_finite(Z[n * ldz + d])) Z[n * ldz + d] = fp32_chain(G + n * ldg, 1, W + d * ldw, M);
     }
 }
 

@@ -125,6 +125,7 @@ __global__ __launch_bounds__(256, 2) void conv_z_kernel(const float* __restrict_
             for (int i = 0; i < 2; ++i) acc[i][j] += s[i];
         }
     }
+    float probe = 0.f;  // NaN once a sum is not finite
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
         const uint32_t no = n0 + 64 * w + 32 * j + j32;
@@ -136,8 +137,18 @@ __global__ __launch_bounds__(256, 2) void conv_z_kernel(const float* __restrict_
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int d = 32 * i + 8 * (r / 4) + 4 * half + r % 4;
+                probe = __fmaf_rn(acc[i][j][r], 0.f, probe);
                 if (d0 + d < D) z[(int64_t)d * L] = acc[i][j][r];
             }
+    }
+    if (probe == 0.f) return;
+    for (int i = 0; i < 64; ++i) {  // as in matmul_split.hip
+        const uint32_t no = n0 + 64 * w + i / 32 * 32 + j32;
+        const int d = d0 + i / 16 % 2 * 32 + i / 4 % 4 * 8 + 4 * half + i % 4;
+        if (no >= N || d >= D) continue;
+        const uint32_t bo = no / L, l = no - bo * L;
+        float* __restrict__ z = Z + ((int64_t)bo * D + d) * L + l;
+        if (!is_finite(*z)) *z = fp32_chain(G + (int64_t)bo * M * L + l, L, W + d * ldw, M);
     }
 }
 

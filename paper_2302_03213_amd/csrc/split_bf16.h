@@ -37,4 +37,20 @@ __device__ __forceinline__ void cut(const uint32_t (&v)[2 * n], uint32_t (&high)
     }
 }
 
+// For sums from parts that are not finite: an infinite value has none.  g: consecutive values `step` apart.
+__device__ __forceinline__ bool is_finite(float x) { return fabsf(x) <= 3.402823466e38f; }
+__device__ __forceinline__ float fp32_chain(const float* __restrict__ g, int64_t step, const float* __restrict__ w, int M) {
+    float sum = 0.f;
+    int m = 0;
+    for (; m + 8 <= M && sum == sum; m += 8) {  // nothing changes a NaN
+        float a[8], b[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) a[i] = g[(m + i) * step], b[i] = w[m + i];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) sum = __fmaf_rn(a[i], b[i], sum);
+    }
+    for (; m < M && sum == sum; ++m) sum = __fmaf_rn(g[m * step], w[m], sum);
+    return sum;
+}
+
 }  // namespace lutnn

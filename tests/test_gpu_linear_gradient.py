@@ -63,7 +63,7 @@ def test_error_is_no_larger_than_the_librarys():
         assert error(G, W, lut.linear_gradient(G, W)) <= error(G, W, G @ W.t())
 
 
-def test_values_that_are_not_finite_stay_in_their_row():
+def test_values_that_are_not_finite_stay_in_their_row_and_column():
     G, W = operands(300, 200, 128)
     G[17, 5], G[200, 100], W[33, 7] = float("inf"), float("nan"), float("-inf")
     Z = lut.linear_gradient(G, W)
@@ -105,3 +105,17 @@ def test_short_sums_are_no_less_exact_than_an_fp32_chain(M):
     Z = [lut.softpq_backward_conv2d(layer, 1.0, image, W, G[n].reshape(1, M, 1, 1), 3)[0][:, 7].reshape(-1) * 16
          for n in range(pixels)]
     assert error(G, W, torch.stack(Z)) <= error(G, W, chain(G, W))
+
+
+def test_infinite_values_and_overflow_as_in_an_fp32_product():
+    """All terms of a sum have one sign: whether it is finite does not hang on the order of the sum."""
+    G, W = operands(300, 200, 128)
+    G, W = G.abs() + 0.1, W.abs() + 0.1
+    W[50:60] *= -1
+    G[17, 5], G[200, 100], W[33, 7], W[34, 9] = float("inf"), float("nan"), float("-inf"), 0.0
+    G[34], W[34, 100] = G[34] * 3e38, 1.0  # sums beyond the largest value
+    W[40, 5] = 0.0  # times an infinite value
+    assert torch.equal(torch.isfinite(lut.linear_gradient(G, W)), torch.isfinite(G @ W.t()))
+    bad = ~torch.isfinite(G @ W.t())
+    torch.testing.assert_close(lut.linear_gradient(G, W)[bad], (G @ W.t())[bad], rtol=0, atol=0, equal_nan=True)
+    assert bool((lut.linear_gradient(G, W)[17, 50:60] == float("-inf")).all())
