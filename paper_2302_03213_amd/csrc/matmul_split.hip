@@ -5,7 +5,7 @@
 //
 // What bounds it.  The fp32 matrix instructions do 157 TFLOP/s, the bf16 ones sixteen times that.  An fp32 value is
 // exactly the sum of three bf16 values (its top eight significant bits, the next eight, the rest; cut off, never
-// rounded, so that nothing overflows), and of the nine products of two such sums six reach 2^-21 of the whole or more:
+// rounded, and scaled so that the last has its bits), and of the nine products of two such sums six reach 2^-21 of the whole or more:
 // six sixteenths of the fp32 instructions' time.
 //
 // Precision.  The products are exact in the matrix instructions' fp32 sums.  What is left out, middle.low, low.middle
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(512, RB * CB > 4 ? 2 : 4) void matmul_split_kernel(
         float* const z = Z + n * ldz;
 #pragma unroll
         for (int a = 0; a < CB; ++a) {
-            const f32x4 r = sum[a][b] + other[(a * RB + b) * 64];
+            const f32x4 r = (sum[a][b] + other[(a * RB + b) * 64]) * kUnscale;
             const int d = d0 + wd * 16 * CB + 16 * a + 4 * q;
 #pragma unroll
             for (int j = 0; j < 4; ++j) probe = __fmaf_rn(r[j], 0.f, probe);

@@ -137,8 +137,9 @@ __global__ __launch_bounds__(256, 2) void conv_z_kernel(const float* __restrict_
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int d = 32 * i + 8 * (r / 4) + 4 * half + r % 4;
-                probe = __fmaf_rn(acc[i][j][r], 0.f, probe);
-                if (d0 + d < D) z[(int64_t)d * L] = acc[i][j][r];
+                const float sum = acc[i][j][r] * kUnscale;
+                probe = __fmaf_rn(sum, 0.f, probe);
+                if (d0 + d < D) z[(int64_t)d * L] = sum;
             }
     }
     if (probe == 0.f) return;

@@ -18,20 +18,27 @@ __device__ __forceinline__ int unit(int row, int q) { return (q ^ ((row >> 1) & 
 // The upper halves of two words: two values cut to bf16.
 __device__ __forceinline__ uint32_t upper(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
 
+// Operands are scaled up before they are cut, and sums down: the lowest part of a value reaches 2^-16 to 2^-24 of it, and
+// bf16 has nothing below 2^-133, so that values under 2^-110 (7e-34) would lose bits that fp32 has.  Values from 2^104 and
+// products from 2^80 on leave the range that way; such sums are not finite, and formed again.  One instruction more per
+// value: 4096 x 768, M = 3072: 115 -> 119 us; 8192 x 768, M = 768: 60.5 -> 62.8.
+constexpr float kScale = 1 << 24, kUnscale = 1.f / kScale / kScale;
+
 // 2 n values into n words of each part: the top eight significant bits, the next eight, the rest.
 template <int n>
 __device__ __forceinline__ void cut(const uint32_t (&v)[2 * n], uint32_t (&high)[n], uint32_t (&mid)[n], uint32_t (&low)[n]) {
 #pragma unroll
     for (int i = 0; i < n; ++i) {
-        uint32_t m[2], l[2];
+        uint32_t top[2], m[2], l[2];
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            const uint32_t x = v[2 * i + j];
+            const uint32_t x = __float_as_uint(__uint_as_float(v[2 * i + j]) * kScale);
+            top[j] = x;
             const float r = __uint_as_float(x) - __uint_as_float(x & 0xffff0000u);
             m[j] = __float_as_uint(r);
             l[j] = __float_as_uint(r - __uint_as_float(m[j] & 0xffff0000u));
         }
-        high[i] = upper(v[2 * i], v[2 * i + 1]);
+        high[i] = upper(top[0], top[1]);
         mid[i] = upper(m[0], m[1]);
         low[i] = upper(l[0], l[1]);
     }

@@ -119,3 +119,19 @@ def test_infinite_values_and_overflow_as_in_an_fp32_product():
     bad = ~torch.isfinite(G @ W.t())
     torch.testing.assert_close(lut.linear_gradient(G, W)[bad], (G @ W.t())[bad], rtol=0, atol=0, equal_nan=True)
     assert bool((lut.linear_gradient(G, W)[17, 50:60] == float("-inf")).all())
+
+
+@pytest.mark.parametrize("scale_g,scale_w", [(1e-34, 1.0), (1e-36, 1.0), (1e-37, 1e20), (1e-20, 1e-16), (1.0, 1e-36), (1e20, 1e-36),
+                                             (1e19, 1e10), (1e37, 1e-36)])
+def test_small_and_large_values_keep_their_bits(scale_g, scale_w):
+    """Both kernels, at the ends of the range: the parts of small values, the fp32 chains of large ones (whose error is the
+    library's but for the spread of an estimate)."""
+    G, W = operands(300, 200, 128)
+    G, W = G * scale_g, W * scale_w
+    assert error(G, W, lut.linear_gradient(G, W)) <= 1.02 * error(G, W, G @ W.t())
+    C = 1000
+    G, W = operands(1, 9 * C, 128)
+    G, W = G * scale_g, W * scale_w
+    layer = lut.LutLayer(torch.zeros(C, 16, 9, device="cuda"), None, lut.TABLE_F32, 128)  # equal centroids: dL/dP = Z / 16
+    dP, _, _ = lut.softpq_backward_conv2d(layer, 1.0, torch.ones(1, C, 3, 3, device="cuda"), W, G.reshape(1, 128, 1, 1), 3)
+    assert error(G, W, dP[:, 7].reshape(1, -1) * 16) <= 2.5e-7  # 9e-8 from parts, 2e-7 from an fp32 chain of 128 terms
