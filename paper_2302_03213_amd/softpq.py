@@ -19,11 +19,13 @@ class _HostTemperature:
     def __init__(self, temperature):
         self.event = None
         self.value = temperature.detach()
-        if temperature.is_cuda and not torch.cuda.is_current_stream_capturing():
-            self.value = torch.empty(temperature.shape, dtype=temperature.dtype, pin_memory=True)
-            self.value.copy_(temperature.detach(), non_blocking=True)
-            self.event = torch.cuda.Event()
-            self.event.record()
+        if temperature.is_cuda:
+            with torch.cuda.device(temperature.device):  # whose stream the copy runs on, and the event after it
+                if not torch.cuda.is_current_stream_capturing():
+                    self.value = torch.empty(temperature.shape, dtype=temperature.dtype, pin_memory=True)
+                    self.value.copy_(temperature.detach(), non_blocking=True)
+                    self.event = torch.cuda.Event()
+                    self.event.record()
 
     def get(self):
         if self.event is not None:
