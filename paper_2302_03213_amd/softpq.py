@@ -29,6 +29,8 @@ class _HostTemperature:
 
     def get(self):
         if self.event is not None:
+            if torch.cuda.is_current_stream_capturing():  # replays would keep the value of this pass
+                raise RuntimeError("a soft-PQ backward pass cannot be captured: the temperature is read on the host")
             self.event.synchronize()
         return float(self.value)
 

@@ -60,6 +60,15 @@ def test_event_follows_the_copy_on_the_temperatures_device(monkeypatch, index):
     assert host.get() == 2.5 and device.log[-1][0] == "synchronize"
 
 
+def test_a_capture_is_refused(monkeypatch):
+    """A graph would keep the value that the temperature had when it was captured."""
+    device = Device(monkeypatch)
+    host = softpq._HostTemperature(Temperature(0))
+    device.capturing = True
+    with pytest.raises(RuntimeError, match="captured"):
+        host.get()
+
+
 def test_on_the_host_it_is_the_parameter_itself():
     temperature = torch.tensor(1.25)
     host = softpq._HostTemperature(temperature)
