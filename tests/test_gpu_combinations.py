@@ -318,3 +318,16 @@ def test_stream_probe_runs_and_fills_its_sink(lut):
         torch.cuda.synchronize()
     with pytest.raises(lut.LutnnError):
         lut.probe_smfmac_stream(1, 10, sink[:100])
+
+
+@pytest.mark.parametrize("N", [0, 1, 9, 64, 600, 5000])
+@pytest.mark.parametrize("C,M,dtype", [(40, 512, "i8"), (64, 64, "i8"), (128, 512, "f32"), (75, 1001, "i4"), (96, 1024, "i8")])
+def test_auto_takes_the_same_path_with_and_without_a_workspace(lut, N, C, M, dtype):
+    """The binding allocates no index workspace where it expects one launch; the library decides by the same rule."""
+    w = wl.make_layer("t", N or 1, C, 16, 4, M, "f32", seed=C + N)
+    layer = lut.build_table(dev(w.P), dev(w.W), {"i8": lut.TABLE_I8, "i4": lut.TABLE_I4, "f32": lut.TABLE_F32}[dtype], bias=dev(w.bias))
+    dims, thr = wl.random_tree(C, 4, 4, seed=C)
+    tree = lut.LutTree(dev(dims), dev(thr), 4)
+    X, workspace = dev(w.X)[:N], torch.empty((N, C), dtype=torch.uint8, device="cuda")
+    np.testing.assert_array_equal(host(lut.linear(layer, X)), host(lut.linear(layer, X, idx_workspace=workspace)))
+    np.testing.assert_array_equal(host(lut.linear_tree(layer, tree, X)), host(lut.linear_tree(layer, tree, X, idx_workspace=workspace)))

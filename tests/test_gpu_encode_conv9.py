@@ -16,11 +16,21 @@ def unfolded(inp, kernel, stride, pad):
     return np.ascontiguousarray(cols.permute(0, 2, 1).reshape(-1, cols.shape[1]).numpy())
 
 
-def check(P, inp, kernel, stride, pad, finite=True):
+def tiles_per_chunk(rows_an_image, B, C):
+    """Tiles of 64 pixels that a workgroup of the filter goes through, as encode_conv9_filter_chunks deals them out; fails
+    where that rule takes the direct search."""
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    tiles, columns = B * -(-rows_an_image // 64), -(-C // 16)
+    assert tiles * columns > units, "these sizes take the direct search"
+    return -(-tiles // min(max(4 * units // columns, 1), tiles))
+
+
+def check(P, inp, kernel, stride, pad, finite=True, tiles=1):
     import paper_2302_03213_amd as lut
     layer = lut.LutLayer(dev(P), None, lut.TABLE_F32, 8)
     got = host(lut.encode_conv2d(layer, dev(inp), kernel, stride, pad))
     X = unfolded(inp, kernel, stride, pad)
+    assert tiles_per_chunk(X.shape[0] // inp.shape[0], *inp.shape[:2]) == tiles
     if finite:
         np.testing.assert_array_equal(got, oracle.encode(P, X))
     else:  # what is not finite is the direct kernel's to decide: the same as on materialised rows
@@ -29,20 +39,22 @@ def check(P, inp, kernel, stride, pad, finite=True):
     return got
 
 
-@pytest.mark.parametrize("B,C,H,W,kernel,stride,pad,K", [
-    (6, 64, 56, 56, 3, 1, 1, 16),      # five pieces of band, chunks of one and two tiles
-    (9, 37, 28, 28, 3, 1, 1, 16),      # three pieces; codebooks that fill neither a wavefront nor a dword
-    (2, 18, 100, 90, 3, 1, 1, 8),      # eight pieces, K = 8
-    (70, 64, 7, 7, 3, 1, 1, 16),       # images smaller than a tile
-    (5, 66, 57, 41, 3, 2, 1, 16),      # stride 2
-    (3, 50, 9, 130, 3, 1, 0, 16),      # tiles within one row and across two: the band's width changes
-    (40, 30, 21, 13, (1, 9), 1, (0, 4), 16),  # nine taps in a row
+@pytest.mark.parametrize("B,C,H,W,kernel,stride,pad,K,tiles", [
+    (6, 64, 56, 56, 3, 1, 1, 16, 2),      # five pieces of band, chunks of one and two tiles
+    (9, 37, 28, 28, 3, 1, 1, 16, 1),      # three pieces; codebooks that fill neither a wavefront nor a dword
+    (4, 18, 100, 90, 3, 1, 1, 8, 2),      # eight pieces, K = 8; the band's width changes from tile to tile of a chunk
+    (80, 64, 7, 7, 3, 1, 1, 16, 1),       # images smaller than a tile
+    (600, 64, 7, 7, 3, 1, 1, 16, 3),      # a chunk goes from image to image
+    (9, 66, 57, 41, 3, 2, 1, 16, 1),      # stride 2
+    (30, 66, 57, 41, 3, 2, 1, 16, 2),
+    (30, 50, 9, 120, 3, 1, 0, 16, 2),     # tiles within one row and across two: the band's width changes
+    (40, 30, 21, 13, (1, 9), 1, (0, 4), 16, 1),  # nine taps in a row
 ])
-def test_indices_equal_the_oracles(B, C, H, W, kernel, stride, pad, K):
+def test_indices_equal_the_oracles(B, C, H, W, kernel, stride, pad, K, tiles):
     rng = np.random.default_rng(B * C)
     inp = rng.standard_normal((B, C, H, W)).astype(np.float32)
     inp[rng.random(inp.shape) < 0.01] *= 10
-    check(rng.standard_normal((C, K, 9)).astype(np.float32), inp, kernel, stride, pad)
+    check(rng.standard_normal((C, K, 9)).astype(np.float32), inp, kernel, stride, pad, tiles=tiles)
 
 
 def test_doubtful_rows():
@@ -70,11 +82,11 @@ def test_doubtful_rows():
 
 def test_values_that_are_not_finite():
     rng = np.random.default_rng(6)
-    inp = rng.standard_normal((8, 32, 30, 30)).astype(np.float32)
+    inp = rng.standard_normal((40, 32, 30, 30)).astype(np.float32)
     inp[rng.random(inp.shape) < 0.01] = np.nan
     inp[rng.random(inp.shape) < 0.01] = np.inf
     inp[rng.random(inp.shape) < 0.01] = -np.inf
-    check(rng.standard_normal((32, 16, 9)).astype(np.float32), inp, 3, 1, 1, finite=False)
+    check(rng.standard_normal((32, 16, 9)).astype(np.float32), inp, 3, 1, 1, finite=False, tiles=2)
 
 
 @pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
@@ -87,7 +99,7 @@ def test_centroids_that_are_not_finite(value, k):
     inp = rng.standard_normal((40, 32, 30, 30)).astype(np.float32)
     inp[rng.random(inp.shape) < 0.01] = np.inf
     inp[rng.random(inp.shape) < 0.01] = np.nan
-    check(P, inp, 3, 1, 1, finite=False)
+    check(P, inp, 3, 1, 1, finite=False, tiles=2)
 
 
 def test_channels_of_all_images_beyond_31_bits():

@@ -248,6 +248,12 @@ def test_autograd_conv2d_module_matches_oracle_on_unfolded_rows(lut):
     w.X = X
     check_dt(mod.temperature.grad.item(), dt_ref, dt_magnitude(w, t, G2))
     np.testing.assert_allclose(host(mod.bias.grad), G2.sum(axis=0), rtol=1e-4, atol=1e-5)
+    # the gradient in the layout of Y itself, as elementwise layers behind it return it
+    as_y = dev(G).contiguous(memory_format=torch.channels_last)
+    assert as_y.stride() == Y.stride() and not as_y.is_contiguous()
+    inputs = (x, mod.centroids, mod.temperature, mod.bias)
+    for got, want in zip(torch.autograd.grad(mod(x), inputs, as_y), torch.autograd.grad(mod(x), inputs, dev(G))):
+        np.testing.assert_array_equal(host(got), host(want))
 
 
 def draw_softpq_shape(seed):
@@ -275,8 +281,8 @@ def test_softpq_backward_on_a_random_shape(lut, seed):
     # the matrix form: rows and codebooks at the edges of its 64-row, four-codebook tiles, both K, every V
     (65, 5, 16, 9, 7, 1.0), (1, 1, 16, 32, 3, 4.0), (129, 6, 8, 16, 5, 2.0), (63, 3, 16, 8, 6, 1.0),
     (191, 9, 8, 32, 4, 8.0), (16, 4, 16, 16, 5, 1.0),
-    # more row tiles than chunks: several tiles per chunk, the last chunk shorter
-    (19300, 4, 16, 8, 4, 1.0), (16500, 3, 8, 16, 4, 2.0),
+    # more row tiles than the 256 chunks: two tiles per chunk, one in the last
+    (19333, 4, 16, 8, 4, 1.0), (16405, 3, 8, 16, 4, 2.0),
 ])
 @pytest.mark.parametrize("offset", [0.0, 30.0])
 def test_matrix_form_tile_edges(lut, N, C, K, V, M, t, offset):
@@ -303,6 +309,9 @@ def test_matrix_form_tile_edges(lut, N, C, K, V, M, t, offset):
     (2, 8, 6, 9, (3, 2), (1, 2), (0, 1), 16, 16, 8),  # a filter that no instance is made for
     (1, 4, 5, 70, (1, 3), 1, (0, 1), 8, 4, 1),
     (5, 4, 3, 3, 3, 1, 0, 16, 9, 16),             # one output pixel per image
+    (11, 5, 40, 44, 3, 1, 1, 16, 9, 6),           # 303 row tiles: two per chunk, one in the last (both forms of the kernel,
+    (4, 9, 41, 44, 3, 1, 1, 8, 9, 20),            # 113 row tiles for this one, of at most 64 chunks)
+    (11, 6, 40, 44, 1, 1, 0, 16, 2, 40),          # the same where the gradient goes to the image directly
 ])
 def test_softpq_backward_of_a_convolution(lut, B, Cin, H, W, kernel, stride, pad, K, V, M):
     """lutnn_softpq_backward_conv2d against the oracle on torch's unfolded rows.  Z = W . G is summed in fp32 over M
