@@ -242,9 +242,9 @@ struct Tables {
 
 // Four columns per thread where rows of W (and of an fp32 table) can be moved 16 bytes at a time and there are columns
 // enough to fill the chip's workgroups that way (from 1024 on); wavefronts of their own below, so that a narrow layer
-// (64 columns) still spreads its codebooks over the CUs.  Both passes of 48 codebooks x 3072 columns, V = 16, with the
-// launch of the fill: 64.5 -> 26.9 us (the weights were read once per centroid, a byte stored at a time); 1024 x 4096,
-// V = 4: 221 -> 102; 64 x 64, V = 9: 29.0 -> 20.4, which is three launches.
+// (64 columns) still spreads its codebooks over the CUs.  A call's three launches at 48 codebooks x 3072 columns, V
+// = 16: 64.5 -> 26 us (the weights were read once per centroid, a byte stored at a time); 1024 x 4096, V = 4: 221 -> 88;
+// 64 x 64, V = 9: 29 -> 18.
 template <int V_T, int CPT>
 hipError_t launch_columns(const Tables& t, hipStream_t s) {
     const int Kb = kblocks(t.K), Mp = (int)packed_cols(t.M);

@@ -430,8 +430,8 @@ hipError_t launch_k(const float* P, int C, const float* input, int64_t B, const 
 
 // Pixel tiles are shared out over as many chunks as are resident at once (four workgroups per CU; a chunk of several
 // tiles prepares its operands once).  Against the direct search (64 channels, K = 16, 56 x 56, with the launch): 32
-// images 59.5 -> 35.8 us, 16 32.8 -> 21.8, 8 20.8 -> 15.6, 2 10.0 -> 9.8; 32 x 128 channels 28 x 28 36.2 -> 21.6;
-// 32 x 512, 7 x 7 17.0 -> 10.9; K = 8, 12 images 19.5 -> 19.0.  With less than a workgroup per CU a wavefront prepares
+// images 59.5 -> 37 us, 16 32.8 -> 22, 8 20.8 -> 14.5, 2 10.0 -> 8.2; 32 x 128 channels 28 x 28 36.2 -> 21.6;
+// 32 x 512, 7 x 7 17.0 -> 11; K = 8, 12 images 19.5 -> 19.0.  With less than a workgroup per CU a wavefront prepares
 // its operands for one tile and waits for them: the direct search with its narrower tiles (one image: 6.3 us against
 // 7.6 for the kernel alone).
 int64_t encode_conv9_filter_chunks(int C, int K, int64_t B, const ConvGeom& g) {

@@ -34,8 +34,8 @@ __device__ __forceinline__ void store_parts(const uint32_t (&v)[8], char* to) {
 // thread copies one column of G, so that the column's image is found once and images need not be multiples of anything.
 // On the fp32 matrix instructions it was bound by them wherever M is not small; the whole backward pass of a 3x3
 // convolution, with those and with this: 16 x 256 channels 14 x 14, M = 512: 171 -> 130 us; 4 x 128, 28 x 28, M = 256: 84
-// -> 72; 16 x 64, 56 x 56, M = 64: 228 -> 220, where the write of Z bounds it (53 us for 128 MB, 55 before; a library
-// batched product: 99).
+// -> 72; 16 x 64, 56 x 56, M = 64: 228 -> 213, where the write of Z bounds it (53 us for 128 MB, 55 before; a library
+// batched product: 99).  With softpq_matrix.hip's shorter sums 135, 75 and 220.
 __global__ __launch_bounds__(256, 2) void conv_z_kernel(const float* __restrict__ W, int64_t ldw,
                                                         const float* __restrict__ G, float* __restrict__ Z, int D, int M,
                                                         uint32_t L, uint32_t N, int d_tiles, int blocks) {

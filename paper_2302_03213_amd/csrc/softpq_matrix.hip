@@ -28,9 +28,10 @@
 // lanes q = 2, 3 take another 16 rows (H = 2 row blocks at a time): the vector work halves, the matrix work does not.
 //
 // Measured against the vector form (both with the reduction over the chunks): 8192 rows x 192 codebooks, V = 16: 331 ->
-// 93 us (60 us for its bytes at 5 TB/s); 8192 x 96, V = 32: 353 -> 103; 4096 x 48, V = 16: 52 -> 22; 8192 x 384, V = 8:
-// 187 -> 128; 50176 x 64, V = 9: 305 -> 152 (of which distances and dL/dP products take about 20 us each when left
-// out, staging rows of 36 floats most of the rest).  Two steps in flight per wavefront, for latency, cost a
+// 102 us (60 us for its bytes at 5 TB/s); 8192 x 96, V = 32: 353 -> 106; 4096 x 48, V = 16: 52 -> 24; 8192 x 384, V = 8:
+// 187 -> 136; 50176 x 64, V = 9: 305 -> 155 (of which distances and dL/dP products take about 20 us each when left
+// out, staging rows of 36 floats most of the rest).  What precision asks for, the remainder taken off dz and the short
+// sums of dL/dP, is 1-7 us of these.  Two steps in flight per wavefront, for latency, cost a
 // workgroup of registers and gained nothing.
 #include <algorithm>
 #include <type_traits>
@@ -176,7 +177,7 @@ __global__ __launch_bounds__(kEncThreads, per_cu(V, K_T)) void softpq_matrix_ker
 
     // Workgroups go round the eight XCDs; each XCD takes a contiguous run of the work, so that neighbouring column
     // tiles - which share the cache lines at their common edge where 4V floats are no whole number of lines - meet
-    // in one L2 (V = 9, 50176 rows x 64 codebooks: 159 -> 152 us).
+    // in one L2 (V = 9, 50176 rows x 64 codebooks: 4 % of the time).
     const int block = (int)(blockIdx.x % 8) * (int)(gridDim.x / 8) + (int)(blockIdx.x / 8);
     if (block >= blocks) return;
     const int col_tiles = (C + kCT - 1) / kCT;
