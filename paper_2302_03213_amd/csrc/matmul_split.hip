@@ -24,10 +24,11 @@
 // go to the first through LDS.
 //
 // 4096 x 768, M = 3072 (128 x 96 tiles, one per compute unit): 113-119 us by machine, 162-171 TFLOP/s of fp32 results, the
-// matrix cores busy for half of it (124 us under a profiler).  Timed with parts left out, before values were scaled (112
+// matrix cores busy for half of it (128 us under a profiler).  Timed with parts left out, before values were scaled (112
 // us): without the matrix instructions 78, without cutting 99, without loads 102, operand reads alone 41 - no single one of
-// them bounds it, and the clock is down to 1.8 GHz under the products.  Slower were the 32 x 32 instruction (125), two slices in flight per wavefront (123), both groups on halves of one slice with a
-// double buffer (131), rows of 80 instead of swizzled 64 bytes (118); wave priorities change nothing.
+// them bounds it, and the clock is down to 1.8 GHz under the products.  Slower were the 32 x 32 instruction (125), two
+// slices in flight per wavefront (123), both groups on halves of one slice with a double buffer (131), rows of 80 instead
+// of swizzled 64 bytes (118); wave priorities change nothing.
 #include <algorithm>
 
 #include "lutnn_kernels.h"
@@ -246,9 +247,9 @@ int best_tile(int64_t N, int D, int M) {
 // at least, and it shares a long sum out over workgroups where there are few tiles, which this does not (256 x 256, M =
 // 3072: 23 us against 57).  Measured, library against this: 4096 x 768, M = 3072: 143 -> 113 us; 4096 x 3072, M = 768: 144
 // -> 127; 8192 x 768, M = 768: 78 -> 63; 8192 x 2048, M = 1024: 245 -> 206; 4096 x 256, M = 256: 19 -> 10; 5000 x 300, M =
-// 700: 30 -> 22.  Of 80 shapes that take it, four are behind the library, by 3-9 % (1000 x 1024 and 512 x 2048, M = 1024;
-// 1000 x 2048 and 2048 x 1024, M = 3072).  Rows that are not whole 16-byte vectors load value by value (3000 x 1000, M = 1001: 81 -> 73 at
-// best, and behind at others): the library.
+// 700: 30 -> 22.  Of 129 shapes that take it, four are behind the library, by 3-9 % (1000 x 1024 and 512 x 2048, M =
+// 1024; 1000 x 2048 and 2048 x 1024, M = 3072).  Rows that are not whole 16-byte vectors load value by value (3000 x 1000,
+// M = 1001: 81 -> 73 at best, and behind at others): the library.
 // Below 16 terms the parts are less exact than one fp32 chain (7e-8 of the result at any length, against 2.5e-8 at one term,
 // 6.4e-8 at 12 and 7.4e-8 at 16): the library.
 bool matmul_split_preferred(const float* G, int64_t N, int64_t ldg, const float* W, int64_t ldw, int D, int M) {
