@@ -6,7 +6,8 @@
 // but the K distances are computed that way for few rows only.  For all rows the matrix cores give
 // score_k = |P_k|^2 - 2 x.P_k, to about 18 bits; where the best score is ahead of the second by more than both forms'
 // errors can be, its k is the arg-min of the direct form too, and where it is not (one sub-vector in a few thousand
-// on random data) the wavefront takes the direct search for that codebook.
+// on random data) the wavefront searches that row directly - all its rows where they are many, and then without the
+// filter for the rest of its chunk.
 //
 // What bounds it.  A convolution's activations arrive nine times faster than its rows are searched: the direct search is
 // 334 vector instructions per 64 sub-vectors, half of them with a scalar operand at twice the price, and all of the
@@ -49,6 +50,7 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kRowBytes = 48;  // of a row in the operand buffer: 32 used (48 with V = 9), conflict-free for 16-byte reads
 
 constexpr int kV = 9, kCT = 16, kCPW = 4;
+constexpr int kFewRows = 16;
 
 struct Threshold {  // wave-uniform
     float tx, t0;
@@ -247,7 +249,9 @@ __device__ __forceinline__ uint32_t min_ror(uint32_t x) {
     return min(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, false));
 }
 
-// The direct search for the rows of `rows` (lanes), four at a time: 16 lanes take a row, one centroid each.  `taps`
+// The direct search for the rows of `rows` (lanes), four at a time: 16 lanes take a row, one centroid each.  Up to kFewRows
+// rows; more of them cost less in the form of encode.hip, lane = row (all 64 rows this way: 3 to 4.5 times the direct
+// kernel's time, for data or centroids that the filter can do nothing with).  `taps`
 // points at the codebook's channel in LDS, `base` is each lane's patch in it, toff the taps; returns `best` with
 // those lanes' bits replaced.
 template <int K_T>
@@ -365,9 +369,13 @@ __global__ __launch_bounds__(kEncThreads, NI > 5 ? 3 : 4) void encode_conv9_filt
                 }
             }
         }
-        uint32_t packed = 0;
+        uint32_t packed = 0, direct = 0;  // direct: codebooks whose 64 rows are searched directly
 #pragma unroll
         for (int j = 0; j < kCPW; ++j) {
+            if (!th[j].filter) {
+                direct |= 1u << j;
+                continue;
+            }
             float x[kV];
 #pragma unroll
             for (int v = 0; v < kV; ++v) x[v] = tap[v][j * BS];
@@ -385,10 +393,24 @@ __global__ __launch_bounds__(kEncThreads, NI > 5 ? 3 : 4) void encode_conv9_filt
             wave_lds_order();
             bool unsure;
             uint32_t best = best_of(d, k0, xx, th[j], unsure);
-            const uint64_t rows = th[j].filter ? __ballot(unsure) : ~0ull;
-            if (rows && channel + j < C)
-                best = search_rows<K_T>(rows, best, mine + j * BS, base, toff, P + (size_t)(channel + j) * K_T * kV, lane);
+            const uint64_t rows = __ballot(unsure);
+            if (__builtin_popcountll(rows) > kFewRows) {
+                direct |= 1u << j;
+                th[j].filter = false;  // for the rest of the chunk, which is more of the same image
+            } else if (rows)
+                best = search_rows<K_T>(rows, best, mine + j * BS, base, toff, P + (size_t)min(channel + j, C - 1) * K_T * kV, lane);
             packed |= index_byte(best, j);
+        }
+        direct &= (1u << max(0, min(kCPW, C - channel))) - 1;
+        while (direct) {  // wave-uniform
+            const int j = __builtin_amdgcn_readfirstlane(__builtin_ctz(direct));
+            direct &= direct - 1;
+            const float* __restrict__ ch = mine + j * BS + base;
+            float x[kV];
+#pragma unroll
+            for (int v = 0; v < kV; ++v) x[v] = ch[toff[v]];
+            const uint32_t best = nearest_centroid<kV, K_T>(x, P + (size_t)(channel + j) * K_T * kV, K_T);
+            packed = (packed & ~(0xffu << (8 * j))) | best << (8 * j);
         }
         // each lane stores its row's four bytes
         if (now.p0 + lane <= now.p1) {
@@ -430,10 +452,11 @@ hipError_t launch_k(const float* P, int C, const float* input, int64_t B, const 
 
 // Pixel tiles are shared out over as many chunks as are resident at once (four workgroups per CU; a chunk of several
 // tiles prepares its operands once).  Against the direct search (64 channels, K = 16, 56 x 56, with the launch): 32
-// images 59.5 -> 37 us, 16 32.8 -> 22, 8 20.8 -> 14.5, 2 10.0 -> 8.2; 32 x 128 channels 28 x 28 36.2 -> 21.6;
-// 32 x 512, 7 x 7 17.0 -> 11; K = 8, 12 images 19.5 -> 19.0.  With less than a workgroup per CU a wavefront prepares
-// its operands for one tile and waits for them: the direct search with its narrower tiles (one image: 6.3 us against
-// 7.6 for the kernel alone).
+// images 59.5 -> 37 us, 16 33.4 -> 23, 8 20.1 -> 15.2, 4 12.9 -> 11.8; 32 x 128 channels 28 x 28 36.5 -> 22.5; 32 x 512, 7
+// x 7 17.4 -> 12.  With less than a workgroup per CU a wavefront prepares its operands for one tile and waits for them:
+// the direct search with its narrower tiles (one image: 6.3 us against 7.6 for the kernel alone).
+// Where the filter can do nothing (all codebooks too small for it, or every row a tie between equal centroids): 32 images
+// 59.4 -> 59 and 63, 8 20 -> 20.7 and 24, 4 12.6 -> 15.2 and 19.
 int64_t encode_conv9_filter_chunks(int C, int K, int64_t B, const ConvGeom& g) {
     if (K != 8 && K != 16) return 0;
     // bands of up to 512 floats, and a wavefront's four channels within a resource's 32-bit offsets

@@ -80,6 +80,31 @@ def test_doubtful_rows():
     assert not (got[:, 0] == 9).any() and not got[:, 3].any()
 
 
+@pytest.mark.parametrize("kind", ["small", "equal centroids", "nearly equal centroids", "no image in half the tiles", "all zero"])
+@pytest.mark.parametrize("K", [8, 16])
+def test_whole_tiles_without_the_filter(kind, K):
+    """Codebooks outside its range, and tiles with more doubtful rows than are searched one by one: 64 rows at once, and the
+    rest of the chunk, too; 37 codebooks end within a wavefront's four."""
+    rng = np.random.default_rng(K)
+    P = rng.standard_normal((37, K, 9)).astype(np.float32)
+    inp = rng.standard_normal((120, 37, 30, 30)).astype(np.float32)
+    if kind == "small":
+        P, inp = P * np.float32(1e-5), inp * np.float32(1e-5)
+    elif kind == "equal centroids":
+        P[:, K // 2:] = P[:, :K // 2]
+    elif kind == "nearly equal centroids":
+        P[::2, K // 2:] = P[::2, :K // 2] * np.float32(1 + 1e-6)
+    elif kind == "no image in half the tiles":
+        P[::2, 3], P[1::2, 5] = -P[::2, 1], -P[1::2, 2]  # as far from zero as each other, and near it
+        P[:, (1, 2, 3, 5)] *= np.float32(0.25)
+        inp[:, :, 10:20] = 0
+    else:
+        P *= 0
+    got = check(P, inp, 3, 1, 1, tiles=6)
+    if kind == "equal centroids":
+        assert got.max() < K // 2
+
+
 def test_values_that_are_not_finite():
     rng = np.random.default_rng(6)
     inp = rng.standard_normal((40, 32, 30, 30)).astype(np.float32)
