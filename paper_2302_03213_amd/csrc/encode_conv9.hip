@@ -454,7 +454,9 @@ hipError_t launch_k(const float* P, int C, const float* input, int64_t B, const 
 // tiles prepares its operands once).  Against the direct search (64 channels, K = 16, 56 x 56, with the launch): 32
 // images 59.5 -> 37 us, 16 33.4 -> 23, 8 20.1 -> 15.2, 4 12.9 -> 11.8; 32 x 128 channels 28 x 28 36.5 -> 22.5; 32 x 512, 7
 // x 7 17.4 -> 12.  With less than a workgroup per CU a wavefront prepares its operands for one tile and waits for them:
-// the direct search with its narrower tiles (one image: 6.3 us against 7.6 for the kernel alone).
+// the direct search with its narrower tiles (one image: 6.3 us against 7.6 for the kernel alone).  With K = 8 the direct
+// search is half as long, and the filter pays from four workgroups per CU on: 32 images 47 -> 41, 8 15.7 -> 15, 32 x 512, 7
+// x 7 14.6 -> 12; 4 images 10.8 against 12.5.
 // Where the filter can do nothing (all codebooks too small for it, or every row a tie between equal centroids): 32 images
 // 59.4 -> 59 and 63, 8 20 -> 20.7 and 24, 4 12.6 -> 15.2 and 19.
 int64_t encode_conv9_filter_chunks(int C, int K, int64_t B, const ConvGeom& g) {
@@ -463,7 +465,7 @@ int64_t encode_conv9_filter_chunks(int C, int K, int64_t B, const ConvGeom& g) {
     if (conv_band_floats(g) > 512 || (int64_t)g.H * g.W >= 1 << 26 || g.Wo > 1 << 19) return 0;
     const int64_t tiles = B * (((int64_t)g.Ho * g.Wo + kEncRows - 1) / kEncRows);
     const int64_t resident = (int64_t)compute_units() * 4, col_tiles = (C + kCT - 1) / kCT;
-    if (tiles * col_tiles <= compute_units()) return 0;
+    if (K == 16 ? tiles * col_tiles <= compute_units() : tiles * col_tiles < resident) return 0;
     return std::min(std::max<int64_t>(resident / col_tiles, 1), tiles);
 }
 

@@ -16,12 +16,12 @@ def unfolded(inp, kernel, stride, pad):
     return np.ascontiguousarray(cols.permute(0, 2, 1).reshape(-1, cols.shape[1]).numpy())
 
 
-def tiles_per_chunk(rows_an_image, B, C):
+def tiles_per_chunk(rows_an_image, B, C, K):
     """Tiles of 64 pixels that a workgroup of the filter goes through, as encode_conv9_filter_chunks deals them out; fails
     where that rule takes the direct search."""
     units = torch.cuda.get_device_properties(0).multi_processor_count
     tiles, columns = B * -(-rows_an_image // 64), -(-C // 16)
-    assert tiles * columns > units, "these sizes take the direct search"
+    assert tiles * columns > units if K == 16 else tiles * columns >= 4 * units, "these sizes take the direct search"
     return -(-tiles // min(max(4 * units // columns, 1), tiles))
 
 
@@ -30,7 +30,7 @@ def check(P, inp, kernel, stride, pad, finite=True, tiles=1):
     layer = lut.LutLayer(dev(P), None, lut.TABLE_F32, 8)
     got = host(lut.encode_conv2d(layer, dev(inp), kernel, stride, pad))
     X = unfolded(inp, kernel, stride, pad)
-    assert tiles_per_chunk(X.shape[0] // inp.shape[0], *inp.shape[:2]) == tiles
+    assert tiles_per_chunk(X.shape[0] // inp.shape[0], *inp.shape[:2], P.shape[1]) == tiles
     if finite:
         np.testing.assert_array_equal(got, oracle.encode(P, X))
     else:  # what is not finite is the direct kernel's to decide: the same as on materialised rows
