@@ -56,13 +56,27 @@ __global__ void fill_u32_kernel(uint32_t* p, uint32_t v) {
 }
 
 // A thread's share of a codebook: CPT neighbouring columns of it, whose V weights it loads once and uses for all K
-// centroids (scalar operands).  V_T = 0: V is a run-time value and the weights are read again for every centroid.
+// centroids (scalar operands).  V_T = 0: V is a run-time value; one column, whose weights come one after another, each for
+// all 16 centroids of a block (read again for every centroid, 64 codebooks x 1000 columns of fp32, V = 64, took 103 us;
+// this way 17, and 41 with a thread per entry).
 template <int V_T, int CPT>
 struct Columns {
-    float w[V_T ? V_T : 1][CPT];
+    float w[V_T ? V_T : 16][CPT];  // V_T = 0: the 16 sums
 
-    __device__ __forceinline__ void load(const float* __restrict__ W, int64_t ldw, int c, int m, int M) {
-        if constexpr (V_T != 0) {
+    __device__ __forceinline__ void load(const float* __restrict__ P, const float* __restrict__ W, int64_t ldw, int K, int V,
+                                         int c, int kb, int m, int M) {
+        if constexpr (V_T == 0) {
+#pragma unroll
+            for (int k = 0; k < 16; ++k) w[k][0] = 0.f;
+            const float* __restrict__ src = W + (size_t)c * V * ldw + (m < M ? m : 0);  // past the last column the first again
+            const float* __restrict__ p = P + (size_t)c * K * V;
+#pragma unroll 2
+            for (int v = 0; v < V; ++v) {
+                const float weight = src[(size_t)v * ldw];
+#pragma unroll
+                for (int k = 0; k < 16; ++k) w[k][0] = __fmaf_rn(p[(size_t)min(kb * 16 + k, K - 1) * V + v], weight, w[k][0]);
+            }
+        } else {
             const float* __restrict__ src = W + (size_t)c * V_T * ldw + m;
 #pragma unroll
             for (int v = 0; v < V_T; ++v) {
@@ -76,11 +90,10 @@ struct Columns {
             }
         }
     }
-    // T[c][k][m + j] of every column, v ascending, one fma per term
-    __device__ __forceinline__ void entries(const float* __restrict__ P, const float* __restrict__ W, int64_t ldw, int K,
-                                            int V, int c, int k, int m, int M, float (&t)[CPT]) const {
+    // T[c][16 kb + kk][m + j] of every column, v ascending, one fma per term
+    __device__ __forceinline__ void entries(const float* __restrict__ P, int K, int c, int kb, int kk, float (&t)[CPT]) const {
         if constexpr (V_T != 0) {
-            const float* __restrict__ p = P + ((size_t)c * K + k) * V_T;
+            const float* __restrict__ p = P + ((size_t)c * K + kb * 16 + kk) * V_T;
 #pragma unroll
             for (int j = 0; j < CPT; ++j) t[j] = 0.f;
 #pragma unroll
@@ -88,7 +101,7 @@ struct Columns {
 #pragma unroll
                 for (int j = 0; j < CPT; ++j) t[j] = __fmaf_rn(p[v], w[v][j], t[j]);
         } else {
-            t[0] = m < M ? table_entry(P, W, ldw, K, V, c, k, m) : 0.f;
+            t[0] = w[kk][0];
         }
     }
 };
@@ -106,13 +119,14 @@ __global__ __launch_bounds__(kThreads) void table_amax_kernel(const float* __res
     const int m = (blockIdx.y * blockDim.x + threadIdx.x) * CPT;
     const int c = blockIdx.x / Kb, kb = blockIdx.x % Kb;
     Columns<V_T, CPT> col;
-    col.load(W, ldw, c, m, M);
+    col.load(P, W, ldw, K, V, c, kb, m, M);
     float a = 0.f;
     const int k_end = min(16, K - kb * 16);
-#pragma unroll 4
-    for (int kk = 0; kk < k_end; ++kk) {
+#pragma unroll V_T ? 4 : 16
+    for (int kk = 0; kk < (V_T ? k_end : 16); ++kk) {
+        if (V_T == 0 && kk >= k_end) continue;
         float t[CPT];
-        col.entries(P, W, ldw, K, V, c, kb * 16 + kk, m, M, t);
+        col.entries(P, K, c, kb, kk, t);
 #pragma unroll
         for (int j = 0; j < CPT; ++j) a = fmaxf(a, fabsf(t[j]));
     }
@@ -137,7 +151,7 @@ __global__ __launch_bounds__(kThreads) void table_quant_pack_kernel(
     finish_scale(scale, s);
     if (m >= Mp) return;
     Columns<V_T, CPT> col;
-    col.load(W, ldw, c, m, M);
+    col.load(P, W, ldw, K, V, c, kb, m, M);
     uint32_t w[CPT][4];
 #pragma unroll
     for (int j = 0; j < CPT; ++j) w[j][0] = w[j][1] = w[j][2] = w[j][3] = 0u;
@@ -148,7 +162,7 @@ __global__ __launch_bounds__(kThreads) void table_quant_pack_kernel(
             const int k = kb * 16 + 4 * kq + kk;
             if (k >= K || m >= M) break;
             float t[CPT];
-            col.entries(P, W, ldw, K, V, c, k, m, M, t);
+            col.entries(P, K, c, kb, 4 * kq + kk, t);
             uint32_t row = 0;
 #pragma unroll
             for (int j = 0; j < CPT; ++j) {
@@ -175,12 +189,13 @@ __global__ __launch_bounds__(kThreads) void table_f32_kernel(const float* __rest
     if (m >= M) return;
     const int c = blockIdx.x / Kb, kb = blockIdx.x % Kb;
     Columns<V_T, CPT> col;
-    col.load(W, ldw, c, m, M);
+    col.load(P, W, ldw, K, V, c, kb, m, M);
     const int k_end = min(16, K - kb * 16);
-#pragma unroll 4
-    for (int kk = 0; kk < k_end; ++kk) {
+#pragma unroll V_T ? 4 : 16
+    for (int kk = 0; kk < (V_T ? k_end : 16); ++kk) {
+        if (V_T == 0 && kk >= k_end) continue;
         float t[CPT];
-        col.entries(P, W, ldw, K, V, c, kb * 16 + kk, m, M, t);
+        col.entries(P, K, c, kb, kk, t);
         float* dst = T + ((size_t)c * K + kb * 16 + kk) * M + m;
         if constexpr (CPT == 4) *reinterpret_cast<f32x4*>(dst) = f32x4{t[0], t[1], t[2], t[3]}; else *dst = t[0];
     }

@@ -14,6 +14,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("C,K,V,M,strided", [
     (3, 16, 1, 1024, False), (2, 5, 2, 1028, False), (2, 16, 4, 1023, False), (2, 16, 8, 1024, True), (1, 8, 9, 1300, False),
     (2, 17, 16, 1032, False), (1, 33, 32, 4100, False), (3, 16, 3, 1024, False), (2, 16, 16, 4096, False), (5, 7, 9, 63, False),
+    # a run-time V: 16 sums a thread, blocks of centroids that are not full
+    (2, 33, 12, 100, False), (1, 16, 64, 1000, True), (3, 5, 6, 70, False), (1, 17, 5, 65, False),
 ])
 def test_table_shares(C, K, V, M, strided):
     import paper_2302_03213_amd as lut
