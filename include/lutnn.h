@@ -235,6 +235,25 @@ LUTNN_API lutnn_status lutnn_linear_tree(const lutnn_layer* layer, const lutnn_t
                                          void* stream);
 
 /*
+ * lutnn_linear and lutnn_linear_tree as the library runs them fastest when the scratch is its own to lay out: the outputs
+ * are those of variant AUTO (an fp32 table's sums may be taken in another order).  Besides AUTO's choices, the one-launch
+ * kernel also takes INT4 tables and rows of any width.
+ *
+ *   scratch  device memory of at least lutnn_linear_scratch_bytes bytes, 16-byte aligned, contents unspecified
+ *            before and after; may be NULL where that is 0
+ * Errors: as lutnn_linear and lutnn_linear_tree with AUTO; E_SHAPE for a scratch that is too small.
+ */
+LUTNN_API lutnn_status lutnn_linear_scratch(const lutnn_layer* layer, const float* X, int64_t N, int64_t ldx, float* Y,
+                                            int64_t ldy, void* scratch, size_t scratch_bytes, void* stream);
+LUTNN_API lutnn_status lutnn_linear_tree_scratch(const lutnn_layer* layer, const lutnn_tree* tree, const float* X,
+                                                 int64_t N, int64_t ldx, float* Y, int64_t ldy, void* scratch,
+                                                 size_t scratch_bytes, void* stream);
+
+/* Host: bytes of scratch lutnn_linear_scratch (tree = 0) or lutnn_linear_tree_scratch (tree = 1) needs; 0 where one launch
+ * needs none, and for invalid or empty shapes. */
+LUTNN_API size_t lutnn_linear_scratch_bytes(const lutnn_layer* layer, int64_t N, int32_t tree);
+
+/*
  * The hash encoder with deep trees (Sec. 7 evaluates a 12-level tree: 4096 buckets per codebook)
  * and the lookup behind it, with 16-bit indices.  Same definitions as lutnn_encode_tree,
  * lutnn_lookup and lutnn_linear_tree; what changes is the index width and the limits:

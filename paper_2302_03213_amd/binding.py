@@ -33,7 +33,7 @@ EXPORTS = ["lutnn_softpq_backward_static", "lutnn_set_tunable", "lutnn_encode_tr
            "lutnn_softpq_backward", "lutnn_softpq_backward_conv2d", "lutnn_linear_gradient", "lutnn_linear_gradient_preferred", "lutnn_softpq_workspace_bytes",
            "lutnn_encode_tree_conv2d", "lutnn_conv2d_tree", "lutnn_conv2d_rows", "lutnn_encode_conv2d", "lutnn_conv2d",
            "lutnn_auto_variant", "lutnn_linear_auto_variant", "lutnn_status_string", "lutnn_last_error", "lutnn_version",
-           "lutnn_probe_smfmac_stream"]
+           "lutnn_probe_smfmac_stream", "lutnn_linear_scratch", "lutnn_linear_tree_scratch", "lutnn_linear_scratch_bytes"]
 
 
 class LutnnError(RuntimeError):
@@ -95,6 +95,13 @@ def _load():
     lib.lutnn_linear_tree.restype = i32
     lib.lutnn_linear_tree.argtypes = [ctypes.POINTER(_CLayer), ctypes.POINTER(_CTree), vp, i64, i64, vp,
                                       i64, i32, vp, vp]
+    lib.lutnn_linear_scratch.restype = i32
+    lib.lutnn_linear_scratch.argtypes = [ctypes.POINTER(_CLayer), vp, i64, i64, vp, i64, vp, ctypes.c_size_t, vp]
+    lib.lutnn_linear_tree_scratch.restype = i32
+    lib.lutnn_linear_tree_scratch.argtypes = [ctypes.POINTER(_CLayer), ctypes.POINTER(_CTree), vp, i64, i64, vp, i64, vp,
+                                              ctypes.c_size_t, vp]
+    lib.lutnn_linear_scratch_bytes.restype = ctypes.c_size_t
+    lib.lutnn_linear_scratch_bytes.argtypes = [ctypes.POINTER(_CLayer), i64, i32]
     lib.lutnn_encode_tree16.restype = i32
     lib.lutnn_encode_tree16.argtypes = [ctypes.POINTER(_CTree), vp, i64, i64, vp, vp]
     lib.lutnn_lookup16.restype = i32
@@ -313,8 +320,15 @@ def linear_tree(layer, tree, X, variant="auto", out=None, idx_workspace=None):
         out = torch.empty((N, layer.M), dtype=torch.float32, device=X.device)
     assert out.dtype == torch.float32 and out.stride(1) == 1 and out.shape == (N, layer.M)
     v = _variant(variant)
-    if idx_workspace is None and not _one_launch(layer, N, v):
-        idx_workspace = torch.empty((N, layer.C), dtype=torch.uint8, device=X.device)
+    if idx_workspace is None:
+        if v == VARIANT_AUTO:
+            nbytes = LIB.lutnn_linear_scratch_bytes(layer.ref, N, 1)
+            scratch = torch.empty(nbytes, dtype=torch.uint8, device=X.device) if nbytes else None
+            _check(LIB.lutnn_linear_tree_scratch(layer.ref, tree.ref, _ptr(X), N, X.stride(0), _ptr(out), out.stride(0),
+                                                 _ptr(scratch), nbytes, _stream()))
+            return out
+        if v != VARIANT_FUSED:
+            idx_workspace = torch.empty((N, layer.C), dtype=torch.uint8, device=X.device)
     _check(LIB.lutnn_linear_tree(layer.ref, tree.ref, _ptr(X), N, X.stride(0),
                                  _ptr(out), out.stride(0), v, _ptr(idx_workspace), _stream()))
     return out
@@ -523,13 +537,6 @@ def conv2d_tree(layer, tree, inp, kernel, stride=1, pad=0, variant="auto", out=N
     return out
 
 
-def _one_launch(layer, N, variant):
-    """Whether the call runs as one launch, which has no use for an index workspace (lutnn_linear_auto_variant with
-    the alignment that torch's allocations have)."""
-    return variant == VARIANT_FUSED or (variant == VARIANT_AUTO and
-                                        LIB.lutnn_linear_auto_variant(layer.ref, 256, N) == VARIANT_FUSED)
-
-
 def auto_variant(layer, N, idx=None):
     """lutnn_auto_variant: name of the lookup variant that "auto" stands for at this shape."""
     code = LIB.lutnn_auto_variant(layer.ref, _ptr(idx), N)
@@ -551,8 +558,15 @@ def linear(layer, X, variant="auto", out=None, idx_workspace=None):
         out = torch.empty((N, layer.M), dtype=torch.float32, device=X.device)
     assert out.dtype == torch.float32 and out.stride(1) == 1 and out.shape == (N, layer.M)
     v = _variant(variant)
-    if idx_workspace is None and not _one_launch(layer, N, v):
-        idx_workspace = torch.empty((N, layer.C), dtype=torch.uint8, device=X.device)
+    if idx_workspace is None:
+        if v == VARIANT_AUTO:
+            nbytes = LIB.lutnn_linear_scratch_bytes(layer.ref, N, 0)
+            scratch = torch.empty(nbytes, dtype=torch.uint8, device=X.device) if nbytes else None
+            _check(LIB.lutnn_linear_scratch(layer.ref, _ptr(X), N, X.stride(0), _ptr(out), out.stride(0), _ptr(scratch),
+                                            nbytes, _stream()))
+            return out
+        if v != VARIANT_FUSED:
+            idx_workspace = torch.empty((N, layer.C), dtype=torch.uint8, device=X.device)
     _check(LIB.lutnn_linear(layer.ref, _ptr(X), N, X.stride(0), _ptr(out),
                             out.stride(0), v, _ptr(idx_workspace), _stream()))
     return out

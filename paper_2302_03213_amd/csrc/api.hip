@@ -96,7 +96,7 @@ int resolve_lookup_variant(const lutnn_layer* L, int variant, const uint8_t* idx
     if (is_int_table(L->table_dtype) && L->table_packed && L->K <= 16) {
         // small problems with few codebooks: rows gathered straight from L2 beat a matrix-core launch
         const bool sparse_ok = lutnn::smfmac_supported(L->C, L->K, idx);
-        if (lutnn::gather_preferred(L->table, L->table_dtype == LUTNN_TABLE_I4 ? 2 : 1, L->C, L->M, N, sparse_ok))
+        if (lutnn::gather_preferred(L->table, L->table_dtype == LUTNN_TABLE_I4 ? 2 : 1, L->C, L->K, L->M, N, sparse_ok))
             return LUTNN_VARIANT_LDS;
         // the sparse kernel at any N (its 128-row tiles spread even a single row's columns over the
         // chip and stream the table in parallel); the dense one where the sparse one cannot run
@@ -193,6 +193,20 @@ lutnn_status check_tree(const lutnn_tree* T, const float* X, int64_t N, int64_t 
                     (long long)T->C * T->V);
     if (!aligned(X, 4) || !aligned(T->split_dim, 4) || !aligned(T->threshold, 4))
         return fail(LUTNN_E_ALIGN, "X, split_dim and threshold must be 4-byte aligned");
+    return LUTNN_OK;
+}
+
+lutnn_status check_tree_matches(const lutnn_layer* layer, const lutnn_tree* tree) {
+    if (tree->C != layer->C || tree->V != layer->V || (1 << tree->levels) != layer->K)
+        return fail(LUTNN_E_SHAPE, "tree (C=%d V=%d levels=%d) does not match layer (C=%d V=%d K=%d)", tree->C,
+                    tree->V, tree->levels, layer->C, layer->V, layer->K);
+    return LUTNN_OK;
+}
+
+lutnn_status check_scratch(const void* scratch, size_t given, size_t needed) {
+    if (!scratch) return fail(LUTNN_E_NULL, "scratch is NULL");
+    if (given < needed) return fail(LUTNN_E_SHAPE, "scratch of %zu bytes is smaller than the %zu this shape needs", given, needed);
+    if (!aligned(scratch, 16)) return fail(LUTNN_E_ALIGN, "scratch must be 16-byte aligned");
     return LUTNN_OK;
 }
 
@@ -490,24 +504,31 @@ inline int small_table_kind(const lutnn_layer* L) {
     return L->table_dtype == LUTNN_TABLE_F32 ? 0 : L->table_dtype == LUTNN_TABLE_I8 ? 1 : 2;
 }
 
+// The layers for which the calls with a variant count the one-launch kernel among their forms: whole groups of four
+// columns, rows that tile a wavefront, aligned fp32 and INT8 tables.  (The kernel runs any width and type; the calls
+// without a variant use it there too.)
+bool one_launch_form(const lutnn_layer* L) {
+    const int kind = small_table_kind(L);
+    return kind != 2 && L->M % 4 == 0 && (L->M >= 256 || 64 % (L->M / 4) == 0) && aligned(L->table, kind == 0 ? 16 : 4) &&
+           lutnn::linear_small_supported(L->table, kind, L->C, L->K, L->V, L->M);
+}
+
 // The one-launch kernel is worth it where the lookup it replaces would be the gather anyway (the
 // indices it would see are 16-byte aligned in LDS, so the sparse kernel counts as available when
 // the shape allows it).
-bool small_preferred(const lutnn_layer* L, int64_t N) {
+bool small_preferred(const lutnn_layer* L, int64_t N, bool tree = false) {
     const int kind = small_table_kind(L);
-    if (kind == 2) return false;
     const bool sparse_ok = is_int_table(L->table_dtype) && L->table_packed && L->K <= 16 && L->C % 32 == 0;
     const bool matrix_ok = is_int_table(L->table_dtype) && L->table_packed && L->K <= 16;
-    const bool gather_wins = !matrix_ok || lutnn::gather_preferred(L->table, kind, L->C, L->M, N, sparse_ok);
-    return lutnn::linear_small_preferred(L->table, kind, L->C, L->K, L->V, L->M, N, gather_wins);
+    const bool gather_wins = !matrix_ok || lutnn::gather_preferred(L->table, kind, L->C, L->K, L->M, N, sparse_ok);
+    return lutnn::linear_small_preferred(L->table, kind, L->C, L->K, L->V, L->M, N, tree, gather_wins);
 }
 
 // Which of the two one-kernel forms FUSED runs: the one-launch kernel for small problems where it
 // is the faster one, or where the tile kernel cannot run at all; the switch LUTNN_FUSED_KERNEL =
 // small | tile pins the choice (tests that must reach both).
 bool fused_takes_small_kernel(const lutnn_layer* L, int64_t N) {
-    const int kind = small_table_kind(L);
-    const bool can_small = lutnn::linear_small_supported(L->table, kind, L->C, L->K, L->V, L->M);
+    const bool can_small = one_launch_form(L);
     const bool can_tile = lutnn::fused_supported(L->C, L->K, L->V, L->M, L->table_dtype) &&
                           (L->table_dtype == LUTNN_TABLE_F32 ? L->table != nullptr : L->table_packed != nullptr);
     const int pinned = lutnn::tunable(lutnn::kTuneFusedKernel);
@@ -517,6 +538,28 @@ bool fused_takes_small_kernel(const lutnn_layer* L, int64_t N) {
     return !can_tile || small_preferred(L, N);
 }
 
+lutnn_status check_fused(const lutnn_layer* L, const float* Y, int64_t ldy) {
+    if (!Y) return fail(LUTNN_E_NULL, "Y is NULL");
+    if (ldy < L->M) return fail(LUTNN_E_SHAPE, "ldy=%lld is smaller than M=%d", (long long)ldy, L->M);
+    if (!aligned(Y, 4)) return fail(LUTNN_E_ALIGN, "Y must be 4-byte aligned");
+    if (L->bias && !aligned(L->bias, 4)) return fail(LUTNN_E_ALIGN, "bias must be 4-byte aligned");
+    if (is_int_table(L->table_dtype) && !L->scale) return fail(LUTNN_E_NULL, "an integer table needs layer->scale");
+    return LUTNN_OK;
+}
+
+lutnn_status one_launch(const lutnn_layer* L, const float* X, int64_t N, int64_t ldx, float* Y, int64_t ldy, hipStream_t s) {
+    return hip_result(lutnn::launch_linear_small(L->centroids, L->table, small_table_kind(L), L->scale, L->bias, L->C, L->K,
+                                                 L->V, L->M, X, N, ldx, Y, ldy, s),
+                      "one-launch linear");
+}
+
+lutnn_status one_launch_tree(const lutnn_layer* L, const lutnn_tree* T, const float* X, int64_t N, int64_t ldx, float* Y,
+                             int64_t ldy, hipStream_t s) {
+    return hip_result(lutnn::launch_linear_small_tree(T->split_dim, T->threshold, T->levels, L->table, small_table_kind(L),
+                                                      L->scale, L->bias, L->C, L->V, L->M, X, N, ldx, Y, ldy, s),
+                      "one-launch linear (hash encoder)");
+}
+
 // What lutnn_linear runs for `variant`.  AUTO: one launch where the problem is small enough that
 // the second launch would be the larger part of the time; else encode once, then the fastest
 // lookup - over conv-like, BERT-like and FC shapes the two launches are never slower than the tile
@@ -524,11 +567,10 @@ bool fused_takes_small_kernel(const lutnn_layer* L, int64_t N) {
 // table per row block).  Without a workspace for the indices a fused kernel is the only choice.
 int resolve_linear_variant(const lutnn_layer* L, int variant, const uint8_t* idx_workspace, int64_t N) {
     if (variant != LUTNN_VARIANT_AUTO) return variant;
-    if (small_preferred(L, N)) return LUTNN_VARIANT_FUSED;
+    if (one_launch_form(L) && small_preferred(L, N)) return LUTNN_VARIANT_FUSED;
     const bool tile_ok = lutnn::fused_supported(L->C, L->K, L->V, L->M, L->table_dtype) &&
                          (L->table_dtype == LUTNN_TABLE_F32 ? L->table != nullptr : L->table_packed != nullptr);
-    const bool small_ok = lutnn::linear_small_supported(L->table, small_table_kind(L), L->C, L->K, L->V, L->M);
-    if ((tile_ok || small_ok) && !idx_workspace) return LUTNN_VARIANT_FUSED;
+    if ((tile_ok || one_launch_form(L)) && !idx_workspace) return LUTNN_VARIANT_FUSED;
     return resolve_lookup_variant(L, LUTNN_VARIANT_AUTO, idx_workspace, N);
 }
 
@@ -545,23 +587,8 @@ lutnn_status lutnn_linear(const lutnn_layer* layer, const float* X, int64_t N, i
     const int v = resolve_linear_variant(L, variant, idx_workspace, N);
 
     if (v == LUTNN_VARIANT_FUSED) {
-        if (!Y) return fail(LUTNN_E_NULL, "Y is NULL");
-        if (ldy < L->M) return fail(LUTNN_E_SHAPE, "ldy=%lld is smaller than M=%d", (long long)ldy, L->M);
-        if (!aligned(Y, 4)) return fail(LUTNN_E_ALIGN, "Y must be 4-byte aligned");
-        if (L->bias && !aligned(L->bias, 4)) return fail(LUTNN_E_ALIGN, "bias must be 4-byte aligned");
-        if (is_int_table(L->table_dtype) && !L->scale)
-            return fail(LUTNN_E_NULL, "an integer table needs layer->scale");
-        if (fused_takes_small_kernel(L, N)) {
-            if (L->table_dtype == LUTNN_TABLE_I8)
-                return hip_result(lutnn::launch_linear_small_i8(L->centroids, static_cast<const int8_t*>(L->table),
-                                                                L->scale, L->bias, L->C, L->K, L->V, L->M, X, N,
-                                                                ldx, Y, ldy, s),
-                                  "one-launch linear");
-            return hip_result(lutnn::launch_linear_small_f32(L->centroids, static_cast<const float*>(L->table),
-                                                             L->bias, L->C, L->K, L->V, L->M, X, N, ldx, Y, ldy,
-                                                             s),
-                              "one-launch linear");
-        }
+        if (lutnn_status st = check_fused(L, Y, ldy)) return st;
+        if (fused_takes_small_kernel(L, N)) return one_launch(L, X, N, ldx, Y, ldy, s);
         if (!lutnn::fused_supported(L->C, L->K, L->V, L->M, L->table_dtype))
             return fail(LUTNN_E_UNSUPPORTED, "no fused kernel for C=%d K=%d V=%d M=%d dtype=%d", L->C, L->K,
                         L->V, L->M, L->table_dtype);
@@ -595,37 +622,19 @@ lutnn_status lutnn_linear_tree(const lutnn_layer* layer, const lutnn_tree* tree,
                                uint8_t* idx_workspace, void* stream) {
     if (lutnn_status st = check_layer(layer)) return st;
     if (lutnn_status st = check_tree(tree, X, N, ldx)) return st;
-    if (tree->C != layer->C || tree->V != layer->V || (1 << tree->levels) != layer->K)
-        return fail(LUTNN_E_SHAPE, "tree (C=%d V=%d levels=%d) does not match layer (C=%d V=%d K=%d)", tree->C,
-                    tree->V, tree->levels, layer->C, layer->V, layer->K);
+    if (lutnn_status st = check_tree_matches(layer, tree)) return st;
     if (N == 0) return LUTNN_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
     // One launch (the tree walk, then the gather, in one kernel) where FUSED asks for it or where
     // AUTO would take it with the distance encoder: the rule prices launches and table reads, and
     // a walk costs less than the search it replaces.
-    const bool can_small =
-        lutnn::linear_small_supported(layer->table, small_table_kind(layer), layer->C, layer->K, layer->V, layer->M);
+    const bool can_small = one_launch_form(layer);
     if (variant == LUTNN_VARIANT_FUSED && !can_small)
         return fail(LUTNN_E_UNSUPPORTED, "no one-launch kernel with the hash encoder for C=%d K=%d V=%d M=%d dtype=%d",
                     layer->C, layer->K, layer->V, layer->M, layer->table_dtype);
-    if (variant == LUTNN_VARIANT_FUSED || (variant == LUTNN_VARIANT_AUTO && small_preferred(layer, N))) {
-        if (!Y) return fail(LUTNN_E_NULL, "Y is NULL");
-        if (ldy < layer->M) return fail(LUTNN_E_SHAPE, "ldy=%lld is smaller than M=%d", (long long)ldy, layer->M);
-        if (!aligned(Y, 4)) return fail(LUTNN_E_ALIGN, "Y must be 4-byte aligned");
-        if (layer->bias && !aligned(layer->bias, 4)) return fail(LUTNN_E_ALIGN, "bias must be 4-byte aligned");
-        if (layer->table_dtype == LUTNN_TABLE_I8) {
-            if (!layer->scale) return fail(LUTNN_E_NULL, "an integer table needs layer->scale");
-            return hip_result(lutnn::launch_linear_small_tree_i8(
-                                  tree->split_dim, tree->threshold, tree->levels,
-                                  static_cast<const int8_t*>(layer->table), layer->scale, layer->bias, layer->C,
-                                  layer->V, layer->M, X, N, ldx, Y, ldy, s),
-                              "one-launch linear (hash encoder)");
-        }
-        return hip_result(lutnn::launch_linear_small_tree_f32(
-                              tree->split_dim, tree->threshold, tree->levels,
-                              static_cast<const float*>(layer->table), layer->bias, layer->C, layer->V, layer->M, X,
-                              N, ldx, Y, ldy, s),
-                          "one-launch linear (hash encoder)");
+    if (variant == LUTNN_VARIANT_FUSED || (variant == LUTNN_VARIANT_AUTO && can_small && small_preferred(layer, N, true))) {
+        if (lutnn_status st = check_fused(layer, Y, ldy)) return st;
+        return one_launch_tree(layer, tree, X, N, ldx, Y, ldy, s);
     }
     if (!idx_workspace) return fail(LUTNN_E_NULL, "idx_workspace is NULL");
     const int v = resolve_lookup_variant(layer, variant, idx_workspace, N);
@@ -636,6 +645,41 @@ lutnn_status lutnn_linear_tree(const lutnn_layer* layer, const lutnn_tree* tree,
                                      "tree encode launch"))
         return st;
     return do_lookup(layer, v, idx_workspace, N, Y, ldy, s);
+}
+
+size_t lutnn_linear_scratch_bytes(const lutnn_layer* layer, int64_t N, int32_t tree) {
+    if (check_layer(layer) != LUTNN_OK || N <= 0 || N >= kMaxRows || small_preferred(layer, N, tree != 0)) return 0;
+    return (size_t)N * layer->C;
+}
+
+lutnn_status lutnn_linear_scratch(const lutnn_layer* layer, const float* X, int64_t N, int64_t ldx, float* Y, int64_t ldy,
+                                  void* scratch, size_t scratch_bytes, void* stream) {
+    if (lutnn_status st = check_layer(layer)) return st;
+    if (N == 0) return LUTNN_OK;
+    if (lutnn_status st = check_encode(layer, X, N, ldx)) return st;
+    if (small_preferred(layer, N)) {
+        if (lutnn_status st = check_fused(layer, Y, ldy)) return st;
+        return one_launch(layer, X, N, ldx, Y, ldy, static_cast<hipStream_t>(stream));
+    }
+    if (lutnn_status st = check_scratch(scratch, scratch_bytes, lutnn_linear_scratch_bytes(layer, N, 0))) return st;
+    const int v = resolve_lookup_variant(layer, LUTNN_VARIANT_AUTO, static_cast<uint8_t*>(scratch), N);
+    return lutnn_linear(layer, X, N, ldx, Y, ldy, v, static_cast<uint8_t*>(scratch), stream);
+}
+
+lutnn_status lutnn_linear_tree_scratch(const lutnn_layer* layer, const lutnn_tree* tree, const float* X, int64_t N,
+                                       int64_t ldx, float* Y, int64_t ldy, void* scratch, size_t scratch_bytes,
+                                       void* stream) {
+    if (lutnn_status st = check_layer(layer)) return st;
+    if (lutnn_status st = check_tree(tree, X, N, ldx)) return st;
+    if (lutnn_status st = check_tree_matches(layer, tree)) return st;
+    if (N == 0) return LUTNN_OK;
+    if (small_preferred(layer, N, true)) {
+        if (lutnn_status st = check_fused(layer, Y, ldy)) return st;
+        return one_launch_tree(layer, tree, X, N, ldx, Y, ldy, static_cast<hipStream_t>(stream));
+    }
+    if (lutnn_status st = check_scratch(scratch, scratch_bytes, lutnn_linear_scratch_bytes(layer, N, 1))) return st;
+    const int v = resolve_lookup_variant(layer, LUTNN_VARIANT_AUTO, static_cast<uint8_t*>(scratch), N);
+    return lutnn_linear_tree(layer, tree, X, N, ldx, Y, ldy, v, static_cast<uint8_t*>(scratch), stream);
 }
 
 lutnn_status lutnn_encode_tree16(const lutnn_tree* tree, const float* X, int64_t N, int64_t ldx,
@@ -685,9 +729,7 @@ lutnn_status lutnn_linear_tree16(const lutnn_layer* layer, const lutnn_tree* tre
                                  int64_t ldx, float* Y, int64_t ldy, uint16_t* idx_workspace, void* stream) {
     if (lutnn_status st = check_layer(layer, kMaxK16)) return st;
     if (lutnn_status st = check_tree(tree, X, N, ldx, 12)) return st;
-    if (tree->C != layer->C || tree->V != layer->V || (1 << tree->levels) != layer->K)
-        return fail(LUTNN_E_SHAPE, "tree (C=%d V=%d levels=%d) does not match layer (C=%d V=%d K=%d)", tree->C,
-                    tree->V, tree->levels, layer->C, layer->V, layer->K);
+    if (lutnn_status st = check_tree_matches(layer, tree)) return st;
     if (N == 0) return LUTNN_OK;
     if (!idx_workspace) return fail(LUTNN_E_NULL, "idx_workspace is NULL");
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -782,9 +824,7 @@ lutnn_status lutnn_conv2d_tree(const lutnn_layer* layer, const lutnn_tree* tree,
                                uint8_t* idx_workspace, void* stream) {
     if (lutnn_status st = check_layer(layer)) return st;
     if (lutnn_status st = check_tree_shape(tree)) return st;
-    if (tree->C != layer->C || tree->V != layer->V || (1 << tree->levels) != layer->K)
-        return fail(LUTNN_E_SHAPE, "tree (C=%d V=%d levels=%d) does not match layer (C=%d V=%d K=%d)", tree->C,
-                    tree->V, tree->levels, layer->C, layer->V, layer->K);
+    if (lutnn_status st = check_tree_matches(layer, tree)) return st;
     lutnn::ConvGeom g;
     int64_t N = 0;
     if (lutnn_status st = check_conv(layer, geom, B, &g, &N)) return st;

@@ -1,7 +1,18 @@
 // One output row's share of the table read and accumulation (arXiv 2302.03213, Eq. 4) when the
-// table rows are read straight from global memory: a lane owns four consecutive columns and adds
-// the selected row of every codebook, in codebook order, sixteen loads in flight at a time.
-// Shared by the stand-alone gather kernel and the one-launch kernel for small problems.
+// table rows are read straight from global memory: a lane owns four consecutive columns (eight of a
+// 4-bit table) and adds the selected row of every codebook, in codebook order, sixteen loads in
+// flight at a time.  Shared by the stand-alone gather kernels and the one-launch kernel for small problems.
+//
+// Any width and any alignment: the hardware reads a dword or four from any byte (dword) address, so rows that
+// start anywhere are read like aligned ones, and the last lane of a row takes the row's last group of
+// columns, which may overlap its neighbour's (both then store the same values).  A wavefront that shares a row
+// of indices reads them as dwords too, wherever they start.
+//
+// What bounds it: the chain of loads where rows are few, the rate of the table's reads where they are many.  Whole calls,
+// before (staged through LDS where the width was no multiple of four, one load at a time where the number of codebooks was
+// none) and with this: 106 rows x 512 codebooks, M = 157, fp32 1016 -> 27 us; 30 x 413, M = 1146, INT8 89 -> 8; 67 x 17 of
+// 64 table rows, M = 148, INT4 88 -> 8; 4096 x 96 of 4096 table rows (16-bit indices, four loads in flight before), M =
+// 768, INT8 89 -> 63.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -10,171 +21,198 @@
 
 namespace lutnn {
 
-//   T       table, fp32 or int8, [C][K][M]; M % 4 == 0 and T aligned for a four-column load
-//   irow    this row's C index bytes (global memory or LDS); IDX_DWORD: 4-byte aligned, read
-//           four codebooks at a time
-//   m       first of the lane's four columns (< M)
-//   yrow    &Y[row][0]
-//   UNIFORM the whole wavefront works on the same row: index words are made wave-uniform
-template <typename TT, bool IDX_DWORD, bool UNIFORM>
-__device__ __forceinline__ void gather_row(const TT* __restrict__ T, const float* __restrict__ scale,
-                                           const float* __restrict__ bias, int C, int K, int M,
-                                           const uint8_t* __restrict__ irow, int m, float* __restrict__ yrow) {
-    constexpr bool I8 = sizeof(TT) == 1;
-    typedef typename std::conditional<I8, uint32_t, float4>::type Vec;  // four columns
-    auto uni = [](uint32_t x) { return UNIFORM ? (uint32_t)__builtin_amdgcn_readfirstlane(x) : x; };
-    const TT* __restrict__ tcol = T + m;
-
-    float fa[4] = {0.f, 0.f, 0.f, 0.f};
-    int32_t ia[4] = {0, 0, 0, 0};
-    auto accumulate = [&](const Vec& v) {
-        if constexpr (I8) {
-            ia[0] += (int32_t)(int8_t)(v & 0xffu);
-            ia[1] += (int32_t)(int8_t)((v >> 8) & 0xffu);
-            ia[2] += (int32_t)(int8_t)((v >> 16) & 0xffu);
-            ia[3] += (int32_t)v >> 24;
-        } else {
-            fa[0] += v.x;
-            fa[1] += v.y;
-            fa[2] += v.z;
-            fa[3] += v.w;
-        }
-    };
-    auto add = [&](int c, int k) {
-        k = k < K ? k : K - 1;
-        accumulate(*reinterpret_cast<const Vec*>(tcol + ((size_t)c * K + k) * M));
-    };
-    int c = 0;
-    if (IDX_DWORD) {
-        // sixteen table rows in flight at a time (added in codebook order all the same)
-        for (; c + 16 <= C; c += 16) {
-            uint32_t word[4];
+// What a lane reads of a table row, by the table's type.
+struct TableF32 {
+    using Entry = float;
+    using Acc = float;
+    static constexpr int kCols = 4;
+    typedef float Vec __attribute__((ext_vector_type(4), aligned(4)));
+    __host__ __device__ static int row_entries(int M) { return M; }
+    __host__ __device__ static int last_group(int M) { return M - 4; }
+    __device__ static int offset(int m) { return m; }
+    __device__ __forceinline__ static void add(Acc (&a)[4], Vec v) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) word[q] = uni(*reinterpret_cast<const uint32_t*>(irow + c + 4 * q));
-            Vec v[16];
-#pragma unroll
-            for (int b = 0; b < 16; ++b) {
-                int k = (int)((word[b >> 2] >> (8 * (b & 3))) & 0xffu);
-                k = k < K ? k : K - 1;
-                v[b] = *reinterpret_cast<const Vec*>(tcol + ((size_t)(c + b) * K + k) * M);
-            }
-#pragma unroll
-            for (int b = 0; b < 16; ++b) accumulate(v[b]);
-        }
-        for (; c + 4 <= C; c += 4) {
-            const uint32_t word = uni(*reinterpret_cast<const uint32_t*>(irow + c));
-#pragma unroll
-            for (int b = 0; b < 4; ++b) add(c + b, (int)((word >> (8 * b)) & 0xffu));
-        }
+        for (int j = 0; j < 4; ++j) a[j] += v[j];
     }
-    for (; c < C; ++c) add(c, (int)uni((uint32_t)irow[c]));
-
-    float* __restrict__ y = yrow + m;
-    float4 out;
-    if constexpr (I8) {
-        const float s = *scale;
-        if (bias) {
-            out = make_float4(__fmaf_rn((float)ia[0], s, bias[m]), __fmaf_rn((float)ia[1], s, bias[m + 1]),
-                              __fmaf_rn((float)ia[2], s, bias[m + 2]), __fmaf_rn((float)ia[3], s, bias[m + 3]));
-        } else {
-            out = make_float4(__fmul_rn((float)ia[0], s), __fmul_rn((float)ia[1], s),
-                              __fmul_rn((float)ia[2], s), __fmul_rn((float)ia[3], s));
-        }
-    } else {
-        out = bias ? make_float4(fa[0] + bias[m], fa[1] + bias[m + 1], fa[2] + bias[m + 2], fa[3] + bias[m + 3])
-                   : make_float4(fa[0], fa[1], fa[2], fa[3]);
+};
+struct TableI8 {
+    using Entry = int8_t;
+    using Acc = int32_t;
+    static constexpr int kCols = 4;
+    typedef uint32_t Vec __attribute__((aligned(1)));
+    __host__ __device__ static int row_entries(int M) { return M; }
+    __host__ __device__ static int last_group(int M) { return M - 4; }
+    __device__ static int offset(int m) { return m; }
+    __device__ __forceinline__ static void add(Acc (&a)[4], uint32_t v) {
+        a[0] += (int32_t)(int8_t)(v & 0xffu);
+        a[1] += (int32_t)(int8_t)((v >> 8) & 0xffu);
+        a[2] += (int32_t)(int8_t)((v >> 16) & 0xffu);
+        a[3] += (int32_t)v >> 24;
     }
-    y[0] = out.x;
-    y[1] = out.y;
-    y[2] = out.z;
-    y[3] = out.w;
+};
+struct TableI4 {  // rows of ceil(M / 2) bytes, even column in the low nibble
+    using Entry = uint8_t;
+    using Acc = int32_t;
+    static constexpr int kCols = 8;
+    typedef uint32_t Vec __attribute__((aligned(1)));
+    __host__ __device__ static int row_entries(int M) { return (M + 1) / 2; }
+    __host__ __device__ static int last_group(int M) { return 2 * ((M + 1) / 2 - 4); }
+    __device__ static int offset(int m) { return m / 2; }
+    __device__ __forceinline__ static void add(Acc (&a)[8], uint32_t v) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) a[j] += (int32_t)(v << (28 - 4 * j)) >> 28;  // nibble j, sign extended
+    }
+};
+// A row has at least one whole group of columns.
+template <class Table>
+inline bool gather_supported(int M) {
+    return Table::last_group(M) >= 0;
 }
 
-// The same for a handful of rows: the SPLIT wavefronts of a workgroup share one (row, 256 columns)
+// Adds the rows that irow[c], c in [c, c_end), select to `a`, in that order.
+//   tcol     the lane's columns of table row 0
+//   irow     index bytes (or 16-bit indices) in global memory or LDS; DWORD: irow + c is 4-byte aligned
+//   UNIFORM  the whole wavefront works on the same row: index words are made wave-uniform
+template <class Table, class Index, bool DWORD, bool UNIFORM>
+__device__ __forceinline__ void gather_range(const typename Table::Entry* __restrict__ tcol, int C, int K, int M,
+                                             const Index* __restrict__ irow, int c, int c_end,
+                                             typename Table::Acc (&a)[Table::kCols]) {
+    using Vec = typename Table::Vec;
+    constexpr int kBatch = 16, kPer = 4 / sizeof(Index), kWords = kBatch / kPer;
+    constexpr uint32_t kMask = sizeof(Index) == 1 ? 0xffu : 0xffffu;
+    auto uni = [](uint32_t x) { return UNIFORM ? (uint32_t)__builtin_amdgcn_readfirstlane(x) : x; };
+    auto word_at = [&](int c0) {
+        typedef uint32_t AnyByte __attribute__((aligned(1)));
+        if constexpr (DWORD) return *reinterpret_cast<const uint32_t*>(irow + c0);
+        return (uint32_t)*reinterpret_cast<const AnyByte*>(irow + c0);
+    };
+    const uint32_t stride = (uint32_t)Table::row_entries(M);
+    auto row = [&](int c0, uint32_t word, int b) -> const Vec& {
+        uint32_t k = (word >> (8 * sizeof(Index) * (b % kPer))) & kMask;
+        k = k < (uint32_t)K ? k : (uint32_t)(K - 1);
+        return *reinterpret_cast<const Vec*>(tcol + ((size_t)(c0 + b) * (size_t)(stride * (uint64_t)K) + (uint64_t)k * stride));
+    };
+    // sixteen table rows in flight at a time (added in codebook order all the same), and behind them the next
+    // sixteen indices: with few wavefronts the loop is a latency chain, and every wait of its own counts
+    uint32_t next[kWords];
+    if (c + kBatch <= c_end) {
+#pragma unroll
+        for (int q = 0; q < kWords; ++q) next[q] = word_at(c + q * kPer);
+    }
+    for (; c + kBatch <= c_end; c += kBatch) {
+        uint32_t word[kWords];
+#pragma unroll
+        for (int q = 0; q < kWords; ++q) word[q] = uni(next[q]);
+        Vec v[kBatch];
+#pragma unroll
+        for (int b = 0; b < kBatch; ++b) v[b] = row(c, word[b / kPer], b);
+        if (c + 2 * kBatch <= c_end) {
+#pragma unroll
+            for (int q = 0; q < kWords; ++q) next[q] = word_at(c + kBatch + q * kPer);
+        }
+#pragma unroll
+        for (int b = 0; b < kBatch; ++b) Table::add(a, v[b]);
+    }
+    // the rest: eight, four and up to three more, all in flight at once
+    const int left = max(c_end - c, 0);  // nothing at all for the last wavefronts of a split row
+    Vec v8[8], v4[4], v1[3];
+    const int c4 = c + (left & 8), c1 = c4 + (left & 4);
+    if (left & 8) {
+        uint32_t word[8 / kPer];
+#pragma unroll
+        for (int q = 0; q < 8 / kPer; ++q) word[q] = uni(word_at(c + q * kPer));
+#pragma unroll
+        for (int b = 0; b < 8; ++b) v8[b] = row(c, word[b / kPer], b);
+    }
+    if (left & 4) {
+        uint32_t word[4 / kPer];
+#pragma unroll
+        for (int q = 0; q < 4 / kPer; ++q) word[q] = uni(word_at(c4 + q * kPer));
+#pragma unroll
+        for (int b = 0; b < 4; ++b) v4[b] = row(c4, word[b / kPer], b);
+    }
+#pragma unroll
+    for (int b = 0; b < 3; ++b)
+        if (b < (left & 3)) v1[b] = row(c1 + b, uni((uint32_t)irow[c1 + b]), 0);
+    if (left & 8) {
+#pragma unroll
+        for (int b = 0; b < 8; ++b) Table::add(a, v8[b]);
+    }
+    if (left & 4) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) Table::add(a, v4[b]);
+    }
+#pragma unroll
+    for (int b = 0; b < 3; ++b)
+        if (b < (left & 3)) Table::add(a, v1[b]);
+}
+
+// Dequantises (r = s*q, Sec. 3.3), adds the bias and stores the lane's columns m ...
+template <class Table>
+__device__ __forceinline__ void store_columns_of_row(const typename Table::Acc (&a)[Table::kCols],
+                                                     const float* __restrict__ scale, const float* __restrict__ bias,
+                                                     int m, int M, float* __restrict__ yrow) {
+    float s = 1.f;
+    if constexpr (!std::is_same<Table, TableF32>::value) s = *scale;
+    float out[Table::kCols];
+#pragma unroll
+    for (int j = 0; j < Table::kCols; ++j) {
+        const bool inside = Table::kCols == 4 || m + j < M;  // an odd M leaves half a byte at the end of a 4-bit row
+        const float b = bias && inside ? bias[m + j] : 0.f;
+        if constexpr (std::is_same<Table, TableF32>::value)
+            out[j] = bias ? a[j] + b : a[j];
+        else
+            out[j] = bias ? __fmaf_rn((float)a[j], s, b) : __fmul_rn((float)a[j], s);
+    }
+#pragma unroll
+    for (int j = 0; j < Table::kCols; ++j)
+        if (Table::kCols == 4 || m + j < M) yrow[m + j] = out[j];
+}
+
+//   T       table, [C][K] rows; gather_supported(M)
+//   irow    this row's C indices; DWORD: 4-byte aligned
+//   m       first of the lane's columns (< M, a multiple of kCols)
+//   yrow    &Y[row][0]
+template <class Table, class Index, bool DWORD, bool UNIFORM>
+__device__ __forceinline__ void gather_row(const typename Table::Entry* __restrict__ T, const float* __restrict__ scale,
+                                           const float* __restrict__ bias, int C, int K, int M,
+                                           const Index* __restrict__ irow, int m, float* __restrict__ yrow) {
+    m = min(m, Table::last_group(M));
+    typename Table::Acc a[Table::kCols] = {};
+    gather_range<Table, Index, DWORD, UNIFORM>(T + Table::offset(m), C, K, M, irow, 0, C, a);
+    store_columns_of_row<Table>(a, scale, bias, m, M, yrow);
+}
+
+// The same for a handful of rows: the SPLIT wavefronts of a workgroup share one row and 64 * kCols columns
 // and take a contiguous range of `per_wave` codebooks each (a multiple of 4); the partial sums meet
 // in LDS and wavefront 0 adds them in range order (exact for integer tables, a fixed order for fp32
 // ones).  Every thread of the workgroup must call it (it holds a barrier); m may lie past M.
-template <typename TT, bool IDX_DWORD, int SPLIT>
-__device__ __forceinline__ void gather_row_split(const TT* __restrict__ T, const float* __restrict__ scale,
-                                                 const float* __restrict__ bias, int C, int K, int M,
-                                                 const uint8_t* __restrict__ irow, int m,
+template <class Table, class Index, bool DWORD, int SPLIT>
+__device__ __forceinline__ void gather_row_split(const typename Table::Entry* __restrict__ T,
+                                                 const float* __restrict__ scale, const float* __restrict__ bias, int C,
+                                                 int K, int M, const Index* __restrict__ irow, int m,
                                                  float* __restrict__ yrow, int per_wave) {
-    constexpr bool I8 = sizeof(TT) == 1;
-    typedef typename std::conditional<I8, uint32_t, float4>::type Vec;  // four columns
-    typedef typename std::conditional<I8, int32_t, float>::type Acc;
-    __shared__ Acc part[SPLIT][4][64];
+    using Acc = typename Table::Acc;
+    constexpr int kCols = Table::kCols;
+    __shared__ Acc part[SPLIT][kCols][64];
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const bool col_ok = m < M;  // M % 4 == 0: a lane's four columns are all inside or all outside
-    const TT* __restrict__ tcol = T + (col_ok ? m : 0);
+    const bool col_ok = m < M;
+    m = min(m, Table::last_group(M));
 
-    Acc a[4] = {0, 0, 0, 0};
-    auto accumulate = [&](const Vec& v) {
-        if constexpr (I8) {
-            a[0] += (int32_t)(int8_t)(v & 0xffu);
-            a[1] += (int32_t)(int8_t)((v >> 8) & 0xffu);
-            a[2] += (int32_t)(int8_t)((v >> 16) & 0xffu);
-            a[3] += (int32_t)v >> 24;
-        } else {
-            a[0] += v.x;
-            a[1] += v.y;
-            a[2] += v.z;
-            a[3] += v.w;
-        }
-    };
-    auto add = [&](int c, int k) {
-        k = k < K ? k : K - 1;
-        accumulate(*reinterpret_cast<const Vec*>(tcol + ((size_t)c * K + k) * M));
-    };
-    // codebooks [c, c_end) of this wavefront; per_wave is a multiple of 4, so dword index loads stay aligned
-    int c = w * per_wave;
-    const int c_end = min(C, c + per_wave);
-    if (IDX_DWORD) {
-        // sixteen table rows in flight at a time: with so few wavefronts the loop is a latency chain,
-        // and a wait per group of four codebooks would be most of the kernel
-        for (; c + 16 <= c_end; c += 16) {
-            uint32_t word[4];
+    Acc a[kCols] = {};
+    gather_range<Table, Index, DWORD, true>(T + Table::offset(m), C, K, M, irow, w * per_wave, min(C, (w + 1) * per_wave), a);
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                word[q] = (uint32_t)__builtin_amdgcn_readfirstlane(*reinterpret_cast<const uint32_t*>(irow + c + 4 * q));
-            Vec v[16];
-#pragma unroll
-            for (int b = 0; b < 16; ++b) {
-                int k = (int)((word[b >> 2] >> (8 * (b & 3))) & 0xffu);
-                k = k < K ? k : K - 1;
-                v[b] = *reinterpret_cast<const Vec*>(tcol + ((size_t)(c + b) * K + k) * M);
-            }
-#pragma unroll
-            for (int b = 0; b < 16; ++b) accumulate(v[b]);
-        }
-        for (; c + 4 <= c_end; c += 4) {
-            const uint32_t word =
-                (uint32_t)__builtin_amdgcn_readfirstlane(*reinterpret_cast<const uint32_t*>(irow + c));
-#pragma unroll
-            for (int b = 0; b < 4; ++b) add(c + b, (int)((word >> (8 * b)) & 0xffu));
-        }
-    }
-    for (; c < c_end; ++c) add(c, (int)__builtin_amdgcn_readfirstlane((uint32_t)irow[c]));
-#pragma unroll
-    for (int j = 0; j < 4; ++j) part[w][j][lane] = a[j];
+    for (int j = 0; j < kCols; ++j) part[w][j][lane] = a[j];
     __syncthreads();
     if (w != 0 || !col_ok) return;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < kCols; ++j) {
         Acc sum = part[0][j][lane];
         for (int ww = 1; ww < SPLIT; ++ww) sum += part[ww][j][lane];
         a[j] = sum;
     }
-    float* __restrict__ y = yrow + m;
-    if constexpr (I8) {
-        const float s = *scale;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            y[j] = bias ? __fmaf_rn((float)a[j], s, bias[m + j]) : __fmul_rn((float)a[j], s);
-    } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) y[j] = bias ? a[j] + bias[m + j] : a[j];
-    }
+    store_columns_of_row<Table>(a, scale, bias, m, M, yrow);
 }
 
 }  // namespace lutnn

@@ -7,8 +7,7 @@
 // cost.  Here a workgroup owns R rows and up to 1024 output columns: it first encodes its rows
 // against all C codebooks (one thread per (row, codebook), the direct-form search of the encoder),
 // leaves the C index bytes of each row in LDS, and after one barrier its wavefronts gather and add
-// the selected table rows straight from L2 exactly as the stand-alone gather kernel does (a lane
-// owns four columns, sixteen loads in flight, codebook order).  Workgroups that share rows but
+// the selected table rows straight from L2 exactly as the stand-alone gather kernel does (gather_row.h).  Workgroups that share rows but
 // not columns repeat the encoding - cheap while rows x codebooks is small, which is the
 // condition under which this kernel is chosen.
 //
@@ -27,7 +26,6 @@ namespace {
 
 constexpr int kSmallThreads = 256;
 constexpr int kSmallWaves = 4;
-constexpr int kChunkCols = 256;  // columns a wavefront covers: 64 lanes x 4
 
 // Step 1 of the operator for ONE sub-vector, as a value the kernels below are compiled around:
 // the arg-min of Eq. 2 ...
@@ -123,14 +121,15 @@ __device__ __forceinline__ void encode_rows_to_lds(const float* __restrict__ X, 
 }
 
 //   R                rows per workgroup
-//   col_groups       workgroups per row group; each takes chunks_per_group runs of 256 columns
-//   lpr              lanes per row when M < 256 (M / 4), else 64
+//   col_groups       workgroups per row group; each takes chunks_per_group runs of 64 * kCols columns
+//   lpr              lanes per row when a row is narrower than a wavefront, else 64
 //   Cpad             C rounded up to 4: byte stride of a row's indices in LDS
-template <int V, typename ENC, typename TT>
+template <int V, typename ENC, class Table>
 __global__ __launch_bounds__(kSmallThreads) void linear_small_kernel(
-    const float* __restrict__ X, int64_t ldx, const ENC enc, const TT* __restrict__ T,
+    const float* __restrict__ X, int64_t ldx, const ENC enc, const typename Table::Entry* __restrict__ T,
     const float* __restrict__ scale, const float* __restrict__ bias, int C, int K_rt, int M, int64_t N,
     float* __restrict__ Y, int64_t ldy, int R, int col_groups, int chunks_per_group, int lpr, int Cpad) {
+    constexpr int kChunk = 64 * Table::kCols;
     extern __shared__ uint32_t sidx_words[];
     uint8_t* __restrict__ sidx = reinterpret_cast<uint8_t*>(sidx_words);  // [R][Cpad]
     const int K = ENC::kK ? ENC::kK : K_rt;
@@ -146,12 +145,12 @@ __global__ __launch_bounds__(kSmallThreads) void linear_small_kernel(
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (lpr >= 64) {
         const int chunk0 = cg * chunks_per_group;
-        const int chunks_here = min(chunks_per_group, (M + kChunkCols - 1) / kChunkCols - chunk0);
+        const int chunks_here = min(chunks_per_group, (M + kChunk - 1) / kChunk - chunk0);
         for (int item = w; item < rows_here * chunks_here; item += kSmallWaves) {
             const int r = item / chunks_here;
-            const int m = (chunk0 + item - r * chunks_here) * kChunkCols + lane * 4;
-            if (m < M)  // M % 4 == 0: a lane's four columns are all inside or all outside
-                gather_row<TT, true, true>(T, scale, bias, C, K, M, sidx + r * Cpad, m, Y + (r0 + r) * ldy);
+            const int m = ((chunk0 + item - r * chunks_here) * 64 + lane) * Table::kCols;
+            if (m < M)
+                gather_row<Table, uint8_t, true, true>(T, scale, bias, C, K, M, sidx + r * Cpad, m, Y + (r0 + r) * ldy);
         }
     } else {
         const int rows_per_wave = 64 / lpr;
@@ -159,18 +158,18 @@ __global__ __launch_bounds__(kSmallThreads) void linear_small_kernel(
         for (int first = w * rows_per_wave; first < rows_here; first += kSmallWaves * rows_per_wave) {
             const int r = first + sub;
             if (sub < rows_per_wave && r < rows_here)
-                gather_row<TT, true, false>(T, scale, bias, C, K, M, sidx + r * Cpad, (lane - sub * lpr) * 4,
-                                            Y + (r0 + r) * ldy);
+                gather_row<Table, uint8_t, true, false>(T, scale, bias, C, K, M, sidx + r * Cpad,
+                                                        (lane - sub * lpr) * Table::kCols, Y + (r0 + r) * ldy);
         }
     }
 }
 
-// The same for a handful of rows on a layer with many codebooks: one workgroup per (row, 256
+// The same for a handful of rows on a layer with many codebooks: one workgroup per (row, 64 * kCols
 // columns), its SPLIT wavefronts first encode the row between them (each workgroup of the row
 // repeats that), then share out the codebooks of the table read as the split gather kernel does.
-template <int V, typename ENC, typename TT, int SPLIT>
+template <int V, typename ENC, class Table, int SPLIT>
 __global__ __launch_bounds__(64 * SPLIT) void linear_split_kernel(
-    const float* __restrict__ X, int64_t ldx, const ENC enc, const TT* __restrict__ T,
+    const float* __restrict__ X, int64_t ldx, const ENC enc, const typename Table::Entry* __restrict__ T,
     const float* __restrict__ scale, const float* __restrict__ bias, int C, int K_rt, int M,
     float* __restrict__ Y, int64_t ldy, int col_chunks, int per_wave) {
     extern __shared__ uint32_t sidx_words[];
@@ -179,15 +178,17 @@ __global__ __launch_bounds__(64 * SPLIT) void linear_split_kernel(
     const int64_t row = blockIdx.x / col_chunks;  // < N by construction of the grid
     encode_rows_to_lds<V>(X + row * ldx, ldx, 1, enc, C, sidx, 0, 64 * SPLIT);
     __syncthreads();
-    const int m = (int)(blockIdx.x % col_chunks) * kChunkCols + (threadIdx.x & 63) * 4;
-    gather_row_split<TT, true, SPLIT>(T, scale, bias, C, K, M, sidx, m, Y + row * ldy, per_wave);
+    const int m = ((int)(blockIdx.x % col_chunks) * 64 + (threadIdx.x & 63)) * Table::kCols;
+    gather_row_split<Table, uint8_t, true, SPLIT>(T, scale, bias, C, K, M, sidx, m, Y + row * ldy, per_wave);
 }
 
-// Few (row, 256 columns) pairs and enough codebooks to share out: the split form.
+inline int row_chunks(int M, int cols) { return (M + 64 * cols - 1) / (64 * cols); }  // wavefronts across a row
+
+// Few (row, chunk of columns) pairs and enough codebooks to share out: the split form.
 constexpr int64_t kSplitMaxItems = 2049;
 constexpr int kSplitMinCodebooks = 64;
-inline bool split_form(int C, int M, int64_t N) {
-    return M >= kChunkCols && C >= kSplitMinCodebooks && N * ((M + kChunkCols - 1) / kChunkCols) < kSplitMaxItems;
+inline bool split_form(int C, int M, int64_t N, int cols) {
+    return M >= 64 * cols && C >= kSplitMinCodebooks && N * row_chunks(M, cols) < kSplitMaxItems;
 }
 
 struct SmallPlan {
@@ -196,49 +197,52 @@ struct SmallPlan {
     size_t shmem;
 };
 
-SmallPlan make_plan(int C, int M, int64_t N) {
+SmallPlan make_plan(int C, int M, int64_t N, int cols) {
     SmallPlan p;
     p.Cpad = (C + 3) & ~3;
-    if (M >= kChunkCols) {
-        const int chunks = (M + kChunkCols - 1) / kChunkCols;
+    p.lpr = (M + cols - 1) / cols;
+    if (p.lpr >= 64) {
+        const int chunks = row_chunks(M, cols);
         p.lpr = 64;
         p.chunks_per_group = std::min(chunks, kSmallWaves);
         p.col_groups = (chunks + p.chunks_per_group - 1) / p.chunks_per_group;
-        // at least one (row, 256 columns) item per wavefront
+        // at least one (row, chunk of columns) item per wavefront
         p.R = p.chunks_per_group >= 4 ? 1 : p.chunks_per_group >= 2 ? 2 : 4;
     } else {
-        p.lpr = M / 4;
         p.chunks_per_group = 1;
         p.col_groups = 1;
         p.R = kSmallWaves * (64 / p.lpr);
     }
+    // one (row, codebook) per thread where that is possible: a second round of searches costs more than the wavefronts
+    // left without a row to gather (16 rows of 64 codebooks, V = 4: 11 -> 7 us, V = 32: 62 -> 20)
+    p.R = std::max(1, std::min(p.R, kSmallThreads / C));
     p.blocks = ((N + p.R - 1) / p.R) * p.col_groups;
     p.shmem = (size_t)p.R * p.Cpad;
     return p;
 }
 
 // One launch with the encoder `enc` in front of the table read.
-template <int V, typename ENC, typename TT>
-hipError_t launch_enc(const ENC& enc, const TT* T, const float* scale, const float* bias, int C, int K, int M,
+template <int V, class Table, typename ENC>
+hipError_t launch_enc(const ENC& enc, const typename Table::Entry* T, const float* scale, const float* bias, int C, int K, int M,
                       const float* X, int64_t N, int64_t ldx, float* Y, int64_t ldy, hipStream_t s) {
-    if (split_form(C, M, N)) {
-        const int col_chunks = (M + kChunkCols - 1) / kChunkCols;
+    if (split_form(C, M, N, Table::kCols)) {
+        const int col_chunks = row_chunks(M, Table::kCols);
         const dim3 grid((unsigned)(N * col_chunks));
         const size_t shmem = (size_t)((C + 3) & ~3);
         if (C >= 256) {  // sixteen codebooks or more per wavefront: one full batch of loads each
             constexpr int SPLIT = 16;
-            hipLaunchKernelGGL((linear_split_kernel<V, ENC, TT, SPLIT>), grid, dim3(64 * SPLIT), shmem, s, X, ldx,
+            hipLaunchKernelGGL((linear_split_kernel<V, ENC, Table, SPLIT>), grid, dim3(64 * SPLIT), shmem, s, X, ldx,
                                enc, T, scale, bias, C, K, M, Y, ldy, col_chunks, ((C + SPLIT - 1) / SPLIT + 3) & ~3);
         } else {
             constexpr int SPLIT = 4;
-            hipLaunchKernelGGL((linear_split_kernel<V, ENC, TT, SPLIT>), grid, dim3(64 * SPLIT), shmem, s, X, ldx,
+            hipLaunchKernelGGL((linear_split_kernel<V, ENC, Table, SPLIT>), grid, dim3(64 * SPLIT), shmem, s, X, ldx,
                                enc, T, scale, bias, C, K, M, Y, ldy, col_chunks, ((C + SPLIT - 1) / SPLIT + 3) & ~3);
         }
         return hipGetLastError();
     }
-    const SmallPlan p = make_plan(C, M, N);
+    const SmallPlan p = make_plan(C, M, N, Table::kCols);
     if (p.blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((linear_small_kernel<V, ENC, TT>), dim3((unsigned)p.blocks), dim3(kSmallThreads), p.shmem, s,
+    hipLaunchKernelGGL((linear_small_kernel<V, ENC, Table>), dim3((unsigned)p.blocks), dim3(kSmallThreads), p.shmem, s,
                        X, ldx, enc, T, scale, bias, C, K, M, N, Y, ldy, p.R, p.col_groups, p.chunks_per_group,
                        p.lpr, p.Cpad);
     return hipGetLastError();
@@ -260,90 +264,88 @@ hipError_t with_subvector_length(int V, F&& f) {
     }
 }
 
-template <typename TT>
-hipError_t launch_t(const float* P, const TT* T, const float* scale, const float* bias, int C, int K, int V,
+template <class Table>
+hipError_t launch_t(const float* P, const void* table, const float* scale, const float* bias, int C, int K, int V,
                     int M, const float* X, int64_t N, int64_t ldx, float* Y, int64_t ldy, hipStream_t s) {
+    const auto* T = static_cast<const typename Table::Entry*>(table);
     return with_subvector_length(V, [&](auto v) {
         constexpr int VV = decltype(v)::value;
         if (K == 16)
-            return launch_enc<VV>(DistanceSearch<VV, 16>{P, K}, T, scale, bias, C, K, M, X, N, ldx, Y, ldy, s);
+            return launch_enc<VV, Table>(DistanceSearch<VV, 16>{P, K}, T, scale, bias, C, K, M, X, N, ldx, Y, ldy, s);
         if (K == 8)
-            return launch_enc<VV>(DistanceSearch<VV, 8>{P, K}, T, scale, bias, C, K, M, X, N, ldx, Y, ldy, s);
-        return launch_enc<VV>(DistanceSearch<VV, 0>{P, K}, T, scale, bias, C, K, M, X, N, ldx, Y, ldy, s);
+            return launch_enc<VV, Table>(DistanceSearch<VV, 8>{P, K}, T, scale, bias, C, K, M, X, N, ldx, Y, ldy, s);
+        return launch_enc<VV, Table>(DistanceSearch<VV, 0>{P, K}, T, scale, bias, C, K, M, X, N, ldx, Y, ldy, s);
     });
 }
 
-template <typename TT>
-hipError_t launch_tree_t(const int32_t* split_dim, const float* threshold, int levels, const TT* T,
+template <class Table>
+hipError_t launch_tree_t(const int32_t* split_dim, const float* threshold, int levels, const void* table,
                          const float* scale, const float* bias, int C, int V, int M, const float* X, int64_t N,
                          int64_t ldx, float* Y, int64_t ldy, hipStream_t s) {
+    const auto* T = static_cast<const typename Table::Entry*>(table);
     const int K = 1 << levels;
     return with_subvector_length(V, [&](auto v) {
         constexpr int VV = decltype(v)::value;
         if (levels == 4)
-            return launch_enc<VV>(TreeWalk<VV, 4>{split_dim, threshold, levels}, T, scale, bias, C, K, M, X, N,
-                                  ldx, Y, ldy, s);
-        return launch_enc<VV>(TreeWalk<VV, 0>{split_dim, threshold, levels}, T, scale, bias, C, K, M, X, N, ldx,
-                              Y, ldy, s);
+            return launch_enc<VV, Table>(TreeWalk<VV, 4>{split_dim, threshold, levels}, T, scale, bias, C, K, M, X, N,
+                                         ldx, Y, ldy, s);
+        return launch_enc<VV, Table>(TreeWalk<VV, 0>{split_dim, threshold, levels}, T, scale, bias, C, K, M, X, N, ldx,
+                                     Y, ldy, s);
     });
 }
 
+inline int cols_of(int table_kind) { return table_kind == 2 ? TableI4::kCols : TableI8::kCols; }
+
 }  // namespace
 
-// Shapes the kernel can run: fp32 or INT8 table in its plain layout, whole groups of four columns,
-// table aligned for a four-column load, a sub-vector length with an unrolled search.
+// Shapes the kernel can run: a table in its plain layout with at least one lane's columns per row, a sub-vector
+// length with an unrolled search.
 bool linear_small_supported(const void* T, int table_kind, int C, int K, int V, int M) {
-    if (!T || (table_kind != 0 && table_kind != 1)) return false;
+    if (!T) return false;
     if (!(V == 1 || V == 2 || V == 3 || V == 4 || V == 8 || V == 9 || V == 16 || V == 32)) return false;
-    if (M % 4 != 0 || K > 256) return false;
-    if (M < kChunkCols && 64 % (M / 4) != 0) return false;  // rows narrower than a wavefront must tile it
-    if (make_plan(C, M, 1).shmem > 32 * 1024 || C > 32768) return false;  // index bytes must fit LDS
-    const uintptr_t align = table_kind == 0 ? 15 : 3;
-    return (reinterpret_cast<uintptr_t>(T) & align) == 0;
+    if (!(table_kind == 2 ? gather_supported<TableI4>(M) : gather_supported<TableI8>(M)) || K > 256) return false;
+    if (make_plan(C, M, 1, cols_of(table_kind)).shmem > 32 * 1024 || C > 32768) return false;  // index bytes must fit LDS
+    return table_kind != 0 || (reinterpret_cast<uintptr_t>(T) & 3) == 0;
 }
 
 // ... and the shapes on which it beats encode + lookup.  Only where the lookup would be the gather
 // anyway (`gather_wins`: the library's own pricing of the gather against the matrix cores), and
-// where the encoding that every workgroup repeats stays cheap: a workgroup reads all C*K*V
-// centroid values (each thread its own 64*V bytes), which costs more than the launch it saves from
-// about 128 KiB on (sweeps over V = 2, 4, 16, C = 64 ... 2048, M = 256 ... 4096, 1 ... 64 rows: the
-// one-launch form wins up to C*V of 2048-3072 and loses beyond), and all workgroups together should
-// read less than 32 MiB of them; the rows form also wants a short chain of codebooks per row.
-bool linear_small_preferred(const void* T, int table_kind, int C, int K, int V, int M, int64_t N,
+// where the encoding that every workgroup repeats stays cheap.  A round of 256 searches takes 0.45 (1 + V) us with K = 16
+// (each thread reads its own 64 V bytes of centroids), a round of walks about one, beside the 4.2 us of a launch; the two
+// launches take 8 to 9 us and 3 more of the host (sweep over V = 2 ... 32, C = 8 ... 128, 1 ... 1024 rows of 64
+// and 128 columns).  In the split form all workgroups together should also read less than 32 MiB of centroids (sweeps over
+// V = 2, 4, 16, C = 64 ... 2048, M = 256 ... 4096, 1 ... 64 rows: it wins up to C*V of 2048-3072); the rows form wants a
+// short chain of codebooks per row.
+bool linear_small_preferred(const void* T, int table_kind, int C, int K, int V, int M, int64_t N, bool tree,
                             bool gather_wins) {
     if (!gather_wins || !linear_small_supported(T, table_kind, C, K, V, M)) return false;
     if ((int64_t)C * V > 3072) return false;
+    const int cols = cols_of(table_kind);
     const double centroid_bytes = (double)C * K * V * 4;
-    if (split_form(C, M, N))
-        return (double)N * ((M + kChunkCols - 1) / kChunkCols) * centroid_bytes < 33554432.0;
-    const SmallPlan p = make_plan(C, M, N);
+    if (split_form(C, M, N, cols)) return (double)N * row_chunks(M, cols) * centroid_bytes < 33554432.0;
+    const SmallPlan p = make_plan(C, M, N, cols);
+    const double round_us = tree ? 1.0 : 0.45 * (1 + V) * K / 16;
+    if (4.2 + round_us * (double)std::min<int64_t>(p.R, N) * C / kSmallThreads > 10.5) return false;
     return C <= 128 && (double)N * C * p.col_groups <= 32768.0;
 }
 
-hipError_t launch_linear_small_f32(const float* P, const float* T, const float* bias, int C, int K, int V,
-                                   int M, const float* X, int64_t N, int64_t ldx, float* Y, int64_t ldy,
-                                   hipStream_t s) {
-    return launch_t<float>(P, T, nullptr, bias, C, K, V, M, X, N, ldx, Y, ldy, s);
-}
-
-hipError_t launch_linear_small_i8(const float* P, const int8_t* T, const float* scale, const float* bias, int C,
-                                  int K, int V, int M, const float* X, int64_t N, int64_t ldx, float* Y,
-                                  int64_t ldy, hipStream_t s) {
-    return launch_t<int8_t>(P, T, scale, bias, C, K, V, M, X, N, ldx, Y, ldy, s);
+hipError_t launch_linear_small(const float* P, const void* T, int table_kind, const float* scale, const float* bias,
+                               int C, int K, int V, int M, const float* X, int64_t N, int64_t ldx, float* Y,
+                               int64_t ldy, hipStream_t s) {
+    if (table_kind == 0) return launch_t<TableF32>(P, T, scale, bias, C, K, V, M, X, N, ldx, Y, ldy, s);
+    if (table_kind == 1) return launch_t<TableI8>(P, T, scale, bias, C, K, V, M, X, N, ldx, Y, ldy, s);
+    return launch_t<TableI4>(P, T, scale, bias, C, K, V, M, X, N, ldx, Y, ldy, s);
 }
 
 // The same kernels with the hash encoder in front (K = 2^levels table rows per codebook).
-hipError_t launch_linear_small_tree_f32(const int32_t* split_dim, const float* threshold, int levels,
-                                        const float* T, const float* bias, int C, int V, int M, const float* X,
-                                        int64_t N, int64_t ldx, float* Y, int64_t ldy, hipStream_t s) {
-    return launch_tree_t<float>(split_dim, threshold, levels, T, nullptr, bias, C, V, M, X, N, ldx, Y, ldy, s);
-}
-
-hipError_t launch_linear_small_tree_i8(const int32_t* split_dim, const float* threshold, int levels,
-                                       const int8_t* T, const float* scale, const float* bias, int C, int V,
-                                       int M, const float* X, int64_t N, int64_t ldx, float* Y, int64_t ldy,
-                                       hipStream_t s) {
-    return launch_tree_t<int8_t>(split_dim, threshold, levels, T, scale, bias, C, V, M, X, N, ldx, Y, ldy, s);
+hipError_t launch_linear_small_tree(const int32_t* split_dim, const float* threshold, int levels, const void* T,
+                                    int table_kind, const float* scale, const float* bias, int C, int V, int M,
+                                    const float* X, int64_t N, int64_t ldx, float* Y, int64_t ldy, hipStream_t s) {
+    if (table_kind == 0)
+        return launch_tree_t<TableF32>(split_dim, threshold, levels, T, scale, bias, C, V, M, X, N, ldx, Y, ldy, s);
+    if (table_kind == 1)
+        return launch_tree_t<TableI8>(split_dim, threshold, levels, T, scale, bias, C, V, M, X, N, ldx, Y, ldy, s);
+    return launch_tree_t<TableI4>(split_dim, threshold, levels, T, scale, bias, C, V, M, X, N, ldx, Y, ldy, s);
 }
 
 }  // namespace lutnn

@@ -18,7 +18,7 @@
 // result is the exact integer sum.
 #include <type_traits>
 
-#include "gather_row.h"
+#include "gather_launch.h"
 #include "lutnn_kernels.h"
 
 namespace lutnn {
@@ -247,271 +247,8 @@ __global__ __launch_bounds__(kThreads) void lookup_lds_f32_kernel(
     }
 }
 
-// ------------------------------------------------------------------------------- any K: no LDS
-// One thread per (row, column); the table is read straight from global memory (L2).  Used when a
-// codebook's K x MT slab does not fit the LDS staging buffer.
-template <typename TT>
-__global__ __launch_bounds__(kThreads) void lookup_global_kernel(
-    const TT* __restrict__ T, const float* __restrict__ scale, const float* __restrict__ bias, int C,
-    int K, int M, const uint8_t* __restrict__ idx, int64_t N, float* __restrict__ Y, int64_t ldy) {
-    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i >= N * (int64_t)M) return;
-    const int64_t n = i / M;
-    const int m = (int)(i % M);
-    if constexpr (sizeof(TT) == 1) {
-        int32_t acc = 0;
-        for (int c = 0; c < C; ++c) {
-            int k = idx[n * C + c];
-            k = k < K ? k : K - 1;
-            acc += (int32_t)T[((size_t)c * K + k) * M + m];
-        }
-        const float s = *scale;
-        Y[n * ldy + m] = bias ? __fmaf_rn((float)acc, s, bias[m]) : __fmul_rn((float)acc, s);
-    } else {
-        float acc = 0.f;
-        for (int c = 0; c < C; ++c) {
-            int k = idx[n * C + c];
-            k = k < K ? k : K - 1;
-            acc += T[((size_t)c * K + k) * M + m];
-        }
-        Y[n * ldy + m] = bias ? acc + bias[m] : acc;
-    }
-}
-
-// ------------------------------------------------------------------------- few rows: no staging
-// Staging a K x MT slab per codebook pays off when many rows of a workgroup read it.  With few
-// rows (a batch of a few hundred) the staged grid cannot even fill the chip, and the slab is read
-// from L2 by every row tile anyway.  Here one wavefront owns one row and a run of 256 columns,
-// each lane four consecutive columns, and reads the selected table row straight from global
-// memory (one 4- or 16-byte load per lane and codebook, the wave's loads are contiguous).  The
-// index is wave-uniform (scalar load, four codebooks per dword) and the loads of several
-// codebooks are in flight at once.  Sums run over the codebooks in order, as in the staged
-// kernels.  Needs M % 4 == 0 and a table aligned for the vector load.
-constexpr int kGatherCols = 256;
-
-// UNIFORM: a wavefront works on one row (M >= 256: scalar index loads).  Otherwise rows are
-// narrower than a wavefront: `lpr` lanes per row, 64 / lpr rows per wavefront, per-lane index loads.
-template <typename TT, bool IDX_DWORD, bool UNIFORM>
-__global__ __launch_bounds__(kThreads) void lookup_gather_kernel(
-    const TT* __restrict__ T, const float* __restrict__ scale, const float* __restrict__ bias, int C,
-    int K, int M, const uint8_t* __restrict__ idx, int64_t N, float* __restrict__ Y, int64_t ldy,
-    int col_chunks, int lpr) {
-    const int lane = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t gw = (int64_t)blockIdx.x * kWaves + w;
-    int64_t row;
-    int m;
-    if (UNIFORM) {
-        row = gw / col_chunks;
-        m = (int)(gw % col_chunks) * kGatherCols + lane * 4;
-    } else {
-        const int sub = lane / lpr;
-        if (sub >= 64 / lpr) return;
-        row = gw * (64 / lpr) + sub;
-        m = (lane - sub * lpr) * 4;
-    }
-    if (row >= N) return;
-    if (m >= M) return;  // M % 4 == 0: a lane's four columns are all inside or all outside
-    gather_row<TT, IDX_DWORD, UNIFORM>(T, scale, bias, C, K, M, idx + row * C, m, Y + row * ldy);
-}
-
-// The same gather for a handful of rows (batch-1 inference, the paper's own setting): with so few
-// wavefronts the per-row chain of C loads and additions is pure latency, so the SPLIT wavefronts of
-// a workgroup share one (row, 256 columns) and take a contiguous range of codebooks each; the
-// partial sums meet in LDS and wavefront 0 adds them in range order (exact for integer tables, a
-// fixed order for fp32 ones).  M % 4 == 0, table aligned for the vector load, M >= 256.
-template <typename TT, bool IDX_DWORD, int SPLIT>
-__global__ __launch_bounds__(64 * SPLIT) void lookup_gather_split_kernel(
-    const TT* __restrict__ T, const float* __restrict__ scale, const float* __restrict__ bias, int C,
-    int K, int M, const uint8_t* __restrict__ idx, int64_t N, float* __restrict__ Y, int64_t ldy,
-    int col_chunks, int per_wave) {
-    const int lane = threadIdx.x & 63;
-    const int64_t row = blockIdx.x / col_chunks;  // < N by construction of the grid
-    const int m = (int)(blockIdx.x % col_chunks) * kGatherCols + lane * 4;
-    gather_row_split<TT, IDX_DWORD, SPLIT>(T, scale, bias, C, K, M, idx + row * C, m, Y + row * ldy, per_wave);
-}
-
-// Fewer (row, 256-column chunk) pairs than this and at least this many codebooks: the split form
-// (measured at C = 1024, M = 4096: faster than one wavefront per pair up to about 160 rows).
-constexpr int64_t kSplitMaxWaves = 2049;
-constexpr int kSplitMinCodebooks = 64;
-
 // The staged kernels need at least this many workgroups to be worth their staging.
 constexpr int64_t kMinStagedBlocks = 512;
-
-template <typename TT>
-bool gather_ok(const TT* T, int M, int64_t staged_blocks) {
-    return staged_blocks < kMinStagedBlocks && M % 4 == 0 &&
-           (reinterpret_cast<uintptr_t>(T) & (4 * sizeof(TT) - 1)) == 0;
-}
-
-inline bool gather_i4_ok(const uint8_t* T, int M, int64_t staged_blocks) {
-    return staged_blocks < kMinStagedBlocks && M % 8 == 0 && (reinterpret_cast<uintptr_t>(T) & 3) == 0;
-}
-
-template <typename TT>
-hipError_t launch_gather(const TT* T, const float* scale, const float* bias, int C, int K, int M,
-                         const uint8_t* idx, int64_t N, float* Y, int64_t ldy, hipStream_t s) {
-    const bool idx_dword = (C % 4 == 0) && ((reinterpret_cast<uintptr_t>(idx) & 3) == 0);
-    const int lpr = M / 4;  // lanes per row when a row is narrower than a wavefront
-    if (lpr >= 64) {
-        const int col_chunks = (M + kGatherCols - 1) / kGatherCols;
-        if (N * col_chunks < kSplitMaxWaves && C >= kSplitMinCodebooks) {
-            const dim3 grid((unsigned)(N * col_chunks));
-#define LUTNN_LAUNCH_SPLIT(DW, SPLIT)                                                                        \
-    hipLaunchKernelGGL((lookup_gather_split_kernel<TT, DW, SPLIT>), grid, dim3(64 * SPLIT), 0, s, T, scale,  \
-                       bias, C, K, M, idx, N, Y, ldy, col_chunks, ((C + SPLIT - 1) / SPLIT + 3) & ~3)
-            if (C >= 512) {
-                if (idx_dword) LUTNN_LAUNCH_SPLIT(true, 16); else LUTNN_LAUNCH_SPLIT(false, 16);
-            } else {
-                if (idx_dword) LUTNN_LAUNCH_SPLIT(true, 4); else LUTNN_LAUNCH_SPLIT(false, 4);
-            }
-#undef LUTNN_LAUNCH_SPLIT
-            return hipGetLastError();
-        }
-        const int64_t blocks = (N * col_chunks + kWaves - 1) / kWaves;
-        if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-        if (idx_dword)
-            hipLaunchKernelGGL((lookup_gather_kernel<TT, true, true>), dim3((unsigned)blocks),
-                               dim3(kThreads), 0, s, T, scale, bias, C, K, M, idx, N, Y, ldy, col_chunks, lpr);
-        else
-            hipLaunchKernelGGL((lookup_gather_kernel<TT, false, true>), dim3((unsigned)blocks),
-                               dim3(kThreads), 0, s, T, scale, bias, C, K, M, idx, N, Y, ldy, col_chunks, lpr);
-    } else {
-        const int64_t rows_per_block = (int64_t)(64 / lpr) * kWaves;
-        const int64_t blocks = (N + rows_per_block - 1) / rows_per_block;
-        if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-        if (idx_dword)
-            hipLaunchKernelGGL((lookup_gather_kernel<TT, true, false>), dim3((unsigned)blocks),
-                               dim3(kThreads), 0, s, T, scale, bias, C, K, M, idx, N, Y, ldy, 1, lpr);
-        else
-            hipLaunchKernelGGL((lookup_gather_kernel<TT, false, false>), dim3((unsigned)blocks),
-                               dim3(kThreads), 0, s, T, scale, bias, C, K, M, idx, N, Y, ldy, 1, lpr);
-    }
-    return hipGetLastError();
-}
-
-// 4-bit table, any K, any M: one thread per (row, column), nibbles read from global memory.
-__global__ __launch_bounds__(kThreads) void lookup_global_i4_kernel(
-    const uint8_t* __restrict__ T, const float* __restrict__ scale, const float* __restrict__ bias,
-    int C, int K, int M, const uint8_t* __restrict__ idx, int64_t N, float* __restrict__ Y,
-    int64_t ldy) {
-    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i >= N * (int64_t)M) return;
-    const int64_t n = i / M;
-    const int m = (int)(i % M);
-    const int Mb = (M + 1) / 2;
-    int32_t acc = 0;
-    for (int c = 0; c < C; ++c) {
-        int k = idx[n * C + c];
-        k = k < K ? k : K - 1;
-        const uint32_t two = T[((size_t)c * K + k) * Mb + (m >> 1)];
-        const uint32_t nib = (m & 1) ? two >> 4 : two & 0xfu;
-        acc += (int32_t)((nib ^ 8u) - 8u);
-    }
-    const float s = *scale;
-    Y[n * ldy + m] = bias ? __fmaf_rn((float)acc, s, bias[m]) : __fmul_rn((float)acc, s);
-}
-
-// 4-bit table, few rows: as lookup_gather_kernel, a lane takes eight columns (one dword of the
-// table row), a wavefront 512.  Needs M % 8 == 0 and a 4-byte aligned table.
-constexpr int kGatherColsI4 = 512;
-
-template <bool IDX_DWORD, bool UNIFORM>
-__global__ __launch_bounds__(kThreads) void lookup_gather_i4_kernel(
-    const uint8_t* __restrict__ T, const float* __restrict__ scale, const float* __restrict__ bias,
-    int C, int K, int M, const uint8_t* __restrict__ idx, int64_t N, float* __restrict__ Y,
-    int64_t ldy, int col_chunks, int lpr) {
-    const int lane = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t gw = (int64_t)blockIdx.x * kWaves + w;
-    int64_t row;
-    int m;
-    if (UNIFORM) {
-        row = gw / col_chunks;
-        m = (int)(gw % col_chunks) * kGatherColsI4 + lane * 8;
-    } else {  // rows narrower than a wavefront: lpr lanes per row
-        const int sub = lane / lpr;
-        if (sub >= 64 / lpr) return;
-        row = gw * (64 / lpr) + sub;
-        m = (lane - sub * lpr) * 8;
-    }
-    if (row >= N) return;
-    if (m >= M) return;  // M % 8 == 0: a lane's eight columns are all inside or all outside
-    auto uni = [](uint32_t x) { return UNIFORM ? (uint32_t)__builtin_amdgcn_readfirstlane(x) : x; };
-    const uint8_t* __restrict__ irow = idx + row * C;
-    const uint8_t* __restrict__ tcol = T + m / 2;
-    const size_t Mb = (size_t)M / 2;
-    int32_t a[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    auto add = [&](int c, int k) {
-        k = k < K ? k : K - 1;
-        const uint32_t v = *reinterpret_cast<const uint32_t*>(tcol + ((size_t)c * K + k) * Mb);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) a[j] += (int32_t)(v << (28 - 4 * j)) >> 28;  // nibble j, sign extended
-    };
-    int c = 0;
-    if (IDX_DWORD) {
-        for (; c + 4 <= C; c += 4) {
-            const uint32_t word = uni(*reinterpret_cast<const uint32_t*>(irow + c));
-#pragma unroll
-            for (int b = 0; b < 4; ++b) add(c + b, (int)((word >> (8 * b)) & 0xffu));
-        }
-    }
-    for (; c < C; ++c) add(c, (int)uni((uint32_t)irow[c]));
-    const float s = *scale;
-    float* __restrict__ y = Y + row * ldy + m;
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-        y[j] = bias ? __fmaf_rn((float)a[j], s, bias[m + j]) : __fmul_rn((float)a[j], s);
-}
-
-// The split form of the 4-bit gather for a handful of rows (see lookup_gather_split_kernel): one
-// (row, 512 columns) per workgroup, its wavefronts each a range of the codebooks.  M % 8 == 0, M >= 512.
-template <bool IDX_DWORD, int SPLIT>
-__global__ __launch_bounds__(64 * SPLIT) void lookup_gather_i4_split_kernel(
-    const uint8_t* __restrict__ T, const float* __restrict__ scale, const float* __restrict__ bias,
-    int C, int K, int M, const uint8_t* __restrict__ idx, float* __restrict__ Y, int64_t ldy,
-    int col_chunks, int per_wave) {
-    __shared__ int32_t part[SPLIT][8][64];
-    const int lane = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t row = blockIdx.x / col_chunks;  // < N by construction of the grid
-    const int m = (int)(blockIdx.x % col_chunks) * kGatherColsI4 + lane * 8;
-    const bool col_ok = m < M;  // M % 8 == 0: a lane's eight columns are all inside or all outside
-    const uint8_t* __restrict__ irow = idx + row * C;
-    const uint8_t* __restrict__ tcol = T + (col_ok ? m / 2 : 0);
-    const size_t Mb = (size_t)M / 2;
-    int32_t a[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    auto add = [&](int c, int k) {
-        k = k < K ? k : K - 1;
-        const uint32_t v = *reinterpret_cast<const uint32_t*>(tcol + ((size_t)c * K + k) * Mb);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) a[j] += (int32_t)(v << (28 - 4 * j)) >> 28;  // nibble j, sign extended
-    };
-    int c = w * per_wave;  // per_wave is a multiple of 4: dword index loads stay aligned
-    const int c_end = min(C, c + per_wave);
-    if (IDX_DWORD) {
-        for (; c + 4 <= c_end; c += 4) {
-            const uint32_t word =
-                (uint32_t)__builtin_amdgcn_readfirstlane(*reinterpret_cast<const uint32_t*>(irow + c));
-#pragma unroll
-            for (int b = 0; b < 4; ++b) add(c + b, (int)((word >> (8 * b)) & 0xffu));
-        }
-    }
-    for (; c < c_end; ++c) add(c, (int)__builtin_amdgcn_readfirstlane((uint32_t)irow[c]));
-#pragma unroll
-    for (int j = 0; j < 8; ++j) part[w][j][lane] = a[j];
-    __syncthreads();
-    if (w != 0 || !col_ok) return;
-    const float s = *scale;
-    float* __restrict__ y = Y + row * ldy + m;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        int32_t sum = part[0][j][lane];
-        for (int ww = 1; ww < SPLIT; ++ww) sum += part[ww][j][lane];
-        y[j] = bias ? __fmaf_rn((float)sum, s, bias[m + j]) : __fmul_rn((float)sum, s);
-    }
-}
 
 constexpr int kLdsBudget = 64 * 1024;
 
@@ -519,25 +256,69 @@ inline bool idx_dword_ok(const uint8_t* idx, int C) {
     return (C % 4 == 0) && ((reinterpret_cast<uintptr_t>(idx) & 3) == 0);
 }
 
-}  // namespace
+// The staged kernels' tile: columns, rows, LDS bytes of a staged column (4-bit entries are widened to bytes).
+template <class Table>
+struct Staged {
+    static constexpr bool kF32 = std::is_same<Table, TableF32>::value;
+    static constexpr int kTileCols = kF32 ? kColsF32 : kColsI8, kColBytes = kF32 ? 4 : 1;
+    static constexpr int kTileRows = (kF32 ? kRowsPerWaveF32 : kRowsPerWaveI8) * kWaves;
+    static int64_t blocks(int64_t N, int M) {
+        return ((N + kTileRows - 1) / kTileRows) * ((M + kTileCols - 1) / kTileCols);
+    }
+};
 
-// True when the gather variant would read the table straight from L2 (no staging) and the whole
-// problem is small enough for that to beat the matrix-core kernels, whose tiles and pipeline fill
-// are wasted on it (measured cross-over: about 3e7 table entries) ...
-bool gather_preferred(const void* T, int table_kind, int C, int M, int64_t N, bool sparse_ok) {
-    if (!T) return false;
-    const bool f32 = table_kind == 0;
-    const int64_t rows_per_block = f32 ? kRowsPerWaveF32 * kWaves : kRowsPerWaveI8 * kWaves;
-    const int cols_per_block = f32 ? kColsF32 : kColsI8;
-    const int64_t staged_blocks =
-        ((N + rows_per_block - 1) / rows_per_block) * ((M + cols_per_block - 1) / cols_per_block);
-    const bool direct = table_kind == 0   ? gather_ok(static_cast<const float*>(T), M, staged_blocks)
-                        : table_kind == 1 ? gather_ok(static_cast<const int8_t*>(T), M, staged_blocks)
-                                          : gather_i4_ok(static_cast<const uint8_t*>(T), M, staged_blocks);
-    if (!direct) return false;
+// Table rows read straight from global memory: where the staged grid would be small, and where four codebooks' slabs do
+// not fit its LDS (K > 64; one thread per output, the other choice there, reads a byte where this reads a dword).
+template <class Table>
+bool gather_ok(int64_t N, int K, int M) {
+    using S = Staged<Table>;
+    return gather_supported<Table>(M) &&
+           (S::blocks(N, M) < kMinStagedBlocks || (int64_t)4 * K * S::kTileCols * S::kColBytes > kLdsBudget);
+}
+
+template <class Table>
+hipError_t launch_lookup_lds(const typename Table::Entry* T, const float* scale, const float* bias, int C, int K, int M,
+                             const uint8_t* idx, int64_t N, float* Y, int64_t ldy, hipStream_t s) {
+    using S = Staged<Table>;
+    if (gather_ok<Table>(N, K, M)) return launch_gather<Table, uint8_t>(T, scale, bias, C, K, M, idx, N, Y, ldy, s);
+    const int64_t per_codebook = (int64_t)K * S::kTileCols * S::kColBytes;  // LDS bytes per staged codebook
+    if (4 * per_codebook > kLdsBudget) return launch_global<Table, uint8_t>(T, scale, bias, C, K, M, idx, N, Y, ldy, s);
+    int CC = (int)(kLdsBudget / 2 / per_codebook) & ~3;  // aim for 32 KiB so two workgroups share a CU
+    if (CC < 4) CC = 4;
+    if (CC > 16) CC = 16;
+    const int col_tiles = (M + S::kTileCols - 1) / S::kTileCols;
+    const int64_t blocks = S::blocks(N, M);
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    const size_t shmem = (size_t)(CC * per_codebook);
+    const dim3 grid((unsigned)blocks), block(kThreads);
+    const bool dw = idx_dword_ok(idx, C);
+    if constexpr (S::kF32) {
+        if (dw)
+            hipLaunchKernelGGL((lookup_lds_f32_kernel<true>), grid, block, shmem, s, T, bias, C, K, M, idx, N, Y, ldy, CC,
+                               col_tiles);
+        else
+            hipLaunchKernelGGL((lookup_lds_f32_kernel<false>), grid, block, shmem, s, T, bias, C, K, M, idx, N, Y, ldy, CC,
+                               col_tiles);
+    } else {
+        constexpr int BITS = std::is_same<Table, TableI4>::value ? 4 : 8;
+        const int vec16 = BITS == 8 && (M % 16 == 0) && ((reinterpret_cast<uintptr_t>(T) & 15) == 0);
+        const int8_t* Tb = reinterpret_cast<const int8_t*>(T);
+        if (dw)
+            hipLaunchKernelGGL((lookup_lds_i8_kernel<true, BITS>), grid, block, shmem, s, Tb, scale, bias, C, K, M, idx, N,
+                               Y, ldy, CC, col_tiles, vec16);
+        else
+            hipLaunchKernelGGL((lookup_lds_i8_kernel<false, BITS>), grid, block, shmem, s, Tb, scale, bias, C, K, M, idx, N,
+                               Y, ldy, CC, col_tiles, vec16);
+    }
+    return hipGetLastError();
+}
+
+template <class Table>
+bool gather_preferred_t(int C, int K, int M, int64_t N, bool sparse_ok) {
+    if (!gather_ok<Table>(N, K, M)) return false;
     // a few rows: the split gather reads N rows' worth of table entries, the matrix cores the whole
     // table; measured cross-over at config 5's width between 32 and 48 rows (K = 16)
-    const int chunk = table_kind == 2 ? kGatherColsI4 : kGatherCols;  // columns per wavefront
+    constexpr int chunk = 64 * Table::kCols;  // columns per wavefront
     const int64_t col_chunks = (M + chunk - 1) / chunk;
     if (M >= chunk && C >= kSplitMinCodebooks && N <= 32 && N * col_chunks < kSplitMaxWaves) return true;
     // Otherwise price both (ms per call, fitted to sweeps of 32-2048 rows over seventeen layer
@@ -554,36 +335,24 @@ bool gather_preferred(const void* T, int table_kind, int C, int M, int64_t N, bo
     return t_gather < t_matrix;
 }
 
+}  // namespace
+
+// True when the gather variant would read the table straight from L2 (no staging) and the whole
+// problem is small enough for that to beat the matrix-core kernels, whose tiles and pipeline fill
+// are wasted on it (measured cross-over: about 3e7 table entries).
+bool gather_preferred(const void* T, int table_kind, int C, int K, int M, int64_t N, bool sparse_ok) {
+    if (!T) return false;
+    return table_kind == 0   ? gather_preferred_t<TableF32>(C, K, M, N, sparse_ok)
+           : table_kind == 1 ? gather_preferred_t<TableI8>(C, K, M, N, sparse_ok)
+                             : gather_preferred_t<TableI4>(C, K, M, N, sparse_ok);
+}
+
 hipError_t launch_lookup_lds_i8(const int8_t* T, const float* scale, const float* bias, int C, int K,
                                 int M, const uint8_t* idx, int64_t N, float* Y, int64_t ldy,
                                 hipStream_t s) {
     if (rows_kernel_preferred(N, M, K, false))
         return launch_lookup_rows_i8(T, 8, scale, bias, C, K, M, idx, N, Y, ldy, s);
-    const int per_codebook = K * kColsI8;  // LDS bytes per staged codebook
-    if (4 * per_codebook > kLdsBudget) {
-        const int64_t blocks = (N * (int64_t)M + kThreads - 1) / kThreads;
-        if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((lookup_global_kernel<int8_t>), dim3((unsigned)blocks), dim3(kThreads), 0, s,
-                           T, scale, bias, C, K, M, idx, N, Y, ldy);
-        return hipGetLastError();
-    }
-    int CC = (kLdsBudget / 2 / per_codebook) & ~3;  // aim for 32 KiB so two workgroups share a CU
-    if (CC < 4) CC = 4;
-    if (CC > 16) CC = 16;
-    const int col_tiles = (M + kColsI8 - 1) / kColsI8;
-    const int64_t row_tiles = (N + kRowsPerWaveI8 * kWaves - 1) / (kRowsPerWaveI8 * kWaves);
-    const int64_t blocks = row_tiles * col_tiles;
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    if (gather_ok(T, M, blocks)) return launch_gather(T, scale, bias, C, K, M, idx, N, Y, ldy, s);
-    const int vec16 = (M % 16 == 0) && ((reinterpret_cast<uintptr_t>(T) & 15) == 0);
-    const size_t shmem = (size_t)CC * per_codebook;
-    if (idx_dword_ok(idx, C))
-        hipLaunchKernelGGL((lookup_lds_i8_kernel<true>), dim3((unsigned)blocks), dim3(kThreads), shmem,
-                           s, T, scale, bias, C, K, M, idx, N, Y, ldy, CC, col_tiles, vec16);
-    else
-        hipLaunchKernelGGL((lookup_lds_i8_kernel<false>), dim3((unsigned)blocks), dim3(kThreads), shmem,
-                           s, T, scale, bias, C, K, M, idx, N, Y, ldy, CC, col_tiles, vec16);
-    return hipGetLastError();
+    return launch_lookup_lds<TableI8>(T, scale, bias, C, K, M, idx, N, Y, ldy, s);
 }
 
 hipError_t launch_lookup_lds_i4(const uint8_t* T, const float* scale, const float* bias, int C, int K,
@@ -591,99 +360,13 @@ hipError_t launch_lookup_lds_i4(const uint8_t* T, const float* scale, const floa
                                 hipStream_t s) {
     if (rows_kernel_preferred(N, M, K, false))
         return launch_lookup_rows_i8(T, 4, scale, bias, C, K, M, idx, N, Y, ldy, s);
-    const int per_codebook = K * kColsI8;  // LDS bytes per staged codebook (entries widened to bytes)
-    if (4 * per_codebook > kLdsBudget) {
-        const int64_t blocks = (N * (int64_t)M + kThreads - 1) / kThreads;
-        if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(lookup_global_i4_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, s, T, scale,
-                           bias, C, K, M, idx, N, Y, ldy);
-        return hipGetLastError();
-    }
-    int CC = (kLdsBudget / 2 / per_codebook) & ~3;
-    if (CC < 4) CC = 4;
-    if (CC > 16) CC = 16;
-    const int col_tiles = (M + kColsI8 - 1) / kColsI8;
-    const int64_t row_tiles = (N + kRowsPerWaveI8 * kWaves - 1) / (kRowsPerWaveI8 * kWaves);
-    const int64_t blocks = row_tiles * col_tiles;
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    const bool idx_dword = idx_dword_ok(idx, C);
-    if (gather_i4_ok(T, M, blocks)) {
-        const int lpr = M / 8;
-        if (lpr >= 64) {
-            const int col_chunks = (M + kGatherColsI4 - 1) / kGatherColsI4;
-            if (N * col_chunks < kSplitMaxWaves && C >= kSplitMinCodebooks) {
-                const dim3 grid((unsigned)(N * col_chunks));
-#define LUTNN_LAUNCH_SPLIT_I4(DW, SPLIT)                                                                      \
-    hipLaunchKernelGGL((lookup_gather_i4_split_kernel<DW, SPLIT>), grid, dim3(64 * SPLIT), 0, s, T, scale, bias, \
-                       C, K, M, idx, Y, ldy, col_chunks, ((C + SPLIT - 1) / SPLIT + 3) & ~3)
-                if (C >= 512) {
-                    if (idx_dword) LUTNN_LAUNCH_SPLIT_I4(true, 16); else LUTNN_LAUNCH_SPLIT_I4(false, 16);
-                } else {
-                    if (idx_dword) LUTNN_LAUNCH_SPLIT_I4(true, 4); else LUTNN_LAUNCH_SPLIT_I4(false, 4);
-                }
-#undef LUTNN_LAUNCH_SPLIT_I4
-                return hipGetLastError();
-            }
-            const int64_t gblocks = (N * col_chunks + kWaves - 1) / kWaves;
-            if (gblocks > 0x7fffffffLL) return hipErrorInvalidValue;
-            if (idx_dword)
-                hipLaunchKernelGGL((lookup_gather_i4_kernel<true, true>), dim3((unsigned)gblocks),
-                                   dim3(kThreads), 0, s, T, scale, bias, C, K, M, idx, N, Y, ldy, col_chunks, lpr);
-            else
-                hipLaunchKernelGGL((lookup_gather_i4_kernel<false, true>), dim3((unsigned)gblocks),
-                                   dim3(kThreads), 0, s, T, scale, bias, C, K, M, idx, N, Y, ldy, col_chunks, lpr);
-        } else {
-            const int64_t rows_per_block = (int64_t)(64 / lpr) * kWaves;
-            const int64_t gblocks = (N + rows_per_block - 1) / rows_per_block;
-            if (gblocks > 0x7fffffffLL) return hipErrorInvalidValue;
-            if (idx_dword)
-                hipLaunchKernelGGL((lookup_gather_i4_kernel<true, false>), dim3((unsigned)gblocks),
-                                   dim3(kThreads), 0, s, T, scale, bias, C, K, M, idx, N, Y, ldy, 1, lpr);
-            else
-                hipLaunchKernelGGL((lookup_gather_i4_kernel<false, false>), dim3((unsigned)gblocks),
-                                   dim3(kThreads), 0, s, T, scale, bias, C, K, M, idx, N, Y, ldy, 1, lpr);
-        }
-        return hipGetLastError();
-    }
-    const size_t shmem = (size_t)CC * per_codebook;
-    const int8_t* Tb = reinterpret_cast<const int8_t*>(T);
-    if (idx_dword)
-        hipLaunchKernelGGL((lookup_lds_i8_kernel<true, 4>), dim3((unsigned)blocks), dim3(kThreads), shmem,
-                           s, Tb, scale, bias, C, K, M, idx, N, Y, ldy, CC, col_tiles, 0);
-    else
-        hipLaunchKernelGGL((lookup_lds_i8_kernel<false, 4>), dim3((unsigned)blocks), dim3(kThreads), shmem,
-                           s, Tb, scale, bias, C, K, M, idx, N, Y, ldy, CC, col_tiles, 0);
-    return hipGetLastError();
+    return launch_lookup_lds<TableI4>(T, scale, bias, C, K, M, idx, N, Y, ldy, s);
 }
 
 hipError_t launch_lookup_lds_f32(const float* T, const float* bias, int C, int K, int M,
                                  const uint8_t* idx, int64_t N, float* Y, int64_t ldy, hipStream_t s) {
     if (rows_kernel_preferred(N, M, K, true)) return launch_lookup_rows_f32(T, bias, C, K, M, idx, N, Y, ldy, s);
-    const int per_codebook = K * kColsF32 * 4;
-    if (4 * per_codebook > kLdsBudget) {
-        const int64_t blocks = (N * (int64_t)M + kThreads - 1) / kThreads;
-        if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((lookup_global_kernel<float>), dim3((unsigned)blocks), dim3(kThreads), 0, s, T,
-                           (const float*)nullptr, bias, C, K, M, idx, N, Y, ldy);
-        return hipGetLastError();
-    }
-    int CC = (kLdsBudget / 2 / per_codebook) & ~3;
-    if (CC < 4) CC = 4;
-    if (CC > 16) CC = 16;
-    const int col_tiles = (M + kColsF32 - 1) / kColsF32;
-    const int64_t row_tiles = (N + kRowsPerWaveF32 * kWaves - 1) / (kRowsPerWaveF32 * kWaves);
-    const int64_t blocks = row_tiles * col_tiles;
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    if (gather_ok(T, M, blocks))
-        return launch_gather(T, (const float*)nullptr, bias, C, K, M, idx, N, Y, ldy, s);
-    const size_t shmem = (size_t)CC * per_codebook;
-    if (idx_dword_ok(idx, C))
-        hipLaunchKernelGGL((lookup_lds_f32_kernel<true>), dim3((unsigned)blocks), dim3(kThreads), shmem,
-                           s, T, bias, C, K, M, idx, N, Y, ldy, CC, col_tiles);
-    else
-        hipLaunchKernelGGL((lookup_lds_f32_kernel<false>), dim3((unsigned)blocks), dim3(kThreads), shmem,
-                           s, T, bias, C, K, M, idx, N, Y, ldy, CC, col_tiles);
-    return hipGetLastError();
+    return launch_lookup_lds<TableF32>(T, nullptr, bias, C, K, M, idx, N, Y, ldy, s);
 }
 
 }  // namespace lutnn

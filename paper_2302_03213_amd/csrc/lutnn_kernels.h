@@ -138,7 +138,7 @@ hipError_t launch_lookup_rows_f32(const float* T, const float* bias, int C, int 
                                   const uint8_t* idx, int64_t N, float* Y, int64_t ldy, hipStream_t s);
 
 // table_kind: 0 fp32, 1 int8, 2 int4 (nibble pairs)
-bool gather_preferred(const void* T, int table_kind, int C, int M, int64_t N, bool sparse_ok);
+bool gather_preferred(const void* T, int table_kind, int C, int K, int M, int64_t N, bool sparse_ok);
 
 // Eq. 4, one-hot MFMA variant (INT8).
 hipError_t launch_lookup_mfma_i8(const int8_t* packed, const float* scale, const float* bias, int C,
@@ -160,24 +160,18 @@ hipError_t launch_linear_fused_f32(const float* P, const float* T, const float* 
                                    int V, int M, const float* X, int64_t N, int64_t ldx, float* Y,
                                    int64_t ldy, hipStream_t s);
 
-// Eq. 2 + Eq. 4 in one launch for small problems, reading the plain table (table_kind 0 fp32, 1 int8).
+// Eq. 2 + Eq. 4 in one launch for small problems, reading the plain table (table_kind 0 fp32, 1 int8, 2 int4).
 bool linear_small_supported(const void* T, int table_kind, int C, int K, int V, int M);
-bool linear_small_preferred(const void* T, int table_kind, int C, int K, int V, int M, int64_t N,
+// preferred: `tree` with the hash encoder as step 1
+bool linear_small_preferred(const void* T, int table_kind, int C, int K, int V, int M, int64_t N, bool tree,
                             bool gather_wins);
-hipError_t launch_linear_small_f32(const float* P, const float* T, const float* bias, int C, int K, int V,
-                                   int M, const float* X, int64_t N, int64_t ldx, float* Y, int64_t ldy,
-                                   hipStream_t s);
-hipError_t launch_linear_small_i8(const float* P, const int8_t* T, const float* scale, const float* bias, int C,
-                                  int K, int V, int M, const float* X, int64_t N, int64_t ldx, float* Y,
-                                  int64_t ldy, hipStream_t s);
+hipError_t launch_linear_small(const float* P, const void* T, int table_kind, const float* scale, const float* bias,
+                               int C, int K, int V, int M, const float* X, int64_t N, int64_t ldx, float* Y,
+                               int64_t ldy, hipStream_t s);
 // ... and with the hash encoder (Sec. 2) as step 1: the trees' K = 2^levels.
-hipError_t launch_linear_small_tree_f32(const int32_t* split_dim, const float* threshold, int levels,
-                                        const float* T, const float* bias, int C, int V, int M, const float* X,
-                                        int64_t N, int64_t ldx, float* Y, int64_t ldy, hipStream_t s);
-hipError_t launch_linear_small_tree_i8(const int32_t* split_dim, const float* threshold, int levels,
-                                       const int8_t* T, const float* scale, const float* bias, int C, int V,
-                                       int M, const float* X, int64_t N, int64_t ldx, float* Y, int64_t ldy,
-                                       hipStream_t s);
+hipError_t launch_linear_small_tree(const int32_t* split_dim, const float* threshold, int levels, const void* T,
+                                    int table_kind, const float* scale, const float* bias, int C, int V, int M,
+                                    const float* X, int64_t N, int64_t ldx, float* Y, int64_t ldy, hipStream_t s);
 
 // probe_smfmac.hip: sink holds 256 * compute_units() ints
 hipError_t launch_probe_smfmac_stream(int operands, int iterations, int32_t* sink, hipStream_t s);
