@@ -237,7 +237,7 @@ LUTNN_API lutnn_status lutnn_linear_tree(const lutnn_layer* layer, const lutnn_t
 /*
  * lutnn_linear and lutnn_linear_tree as the library runs them fastest when the scratch is its own to lay out: the outputs
  * are those of variant AUTO (an fp32 table's sums may be taken in another order).  Besides AUTO's choices, the one-launch
- * kernel also takes INT4 tables and rows of any width.
+ * kernel also takes INT4 tables and rows of any width, and SMFMAC any C.
  *
  *   scratch  device memory of at least lutnn_linear_scratch_bytes bytes, 16-byte aligned, contents unspecified
  *            before and after; may be NULL where that is 0
@@ -382,6 +382,15 @@ LUTNN_API lutnn_status lutnn_encode_conv2d(const lutnn_layer* layer, const float
 LUTNN_API lutnn_status lutnn_conv2d(const lutnn_layer* layer, const float* input, int64_t B,
                                     const lutnn_conv2d_geom* geom, float* Y, int64_t ldy,
                                     int32_t variant, uint8_t* idx_workspace, void* stream);
+
+/* lutnn_conv2d and lutnn_conv2d_tree in the manner of lutnn_linear_scratch; N = lutnn_conv2d_rows(geom, B). */
+LUTNN_API size_t lutnn_conv2d_scratch_bytes(const lutnn_layer* layer, int64_t N);
+LUTNN_API lutnn_status lutnn_conv2d_scratch(const lutnn_layer* layer, const float* input, int64_t B,
+                                            const lutnn_conv2d_geom* geom, float* Y, int64_t ldy, void* scratch,
+                                            size_t scratch_bytes, void* stream);
+LUTNN_API lutnn_status lutnn_conv2d_tree_scratch(const lutnn_layer* layer, const lutnn_tree* tree, const float* input,
+                                                 int64_t B, const lutnn_conv2d_geom* geom, float* Y, int64_t ldy,
+                                                 void* scratch, size_t scratch_bytes, void* stream);
 
 /*
  * Z = G . W^T in fp32: the input gradient of the ordinary linear layer with weights W, which lutnn_softpq_backward

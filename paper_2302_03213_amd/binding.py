@@ -33,7 +33,8 @@ EXPORTS = ["lutnn_softpq_backward_static", "lutnn_set_tunable", "lutnn_encode_tr
            "lutnn_softpq_backward", "lutnn_softpq_backward_conv2d", "lutnn_linear_gradient", "lutnn_linear_gradient_preferred", "lutnn_softpq_workspace_bytes",
            "lutnn_encode_tree_conv2d", "lutnn_conv2d_tree", "lutnn_conv2d_rows", "lutnn_encode_conv2d", "lutnn_conv2d",
            "lutnn_auto_variant", "lutnn_linear_auto_variant", "lutnn_status_string", "lutnn_last_error", "lutnn_version",
-           "lutnn_probe_smfmac_stream", "lutnn_linear_scratch", "lutnn_linear_tree_scratch", "lutnn_linear_scratch_bytes"]
+           "lutnn_probe_smfmac_stream", "lutnn_linear_scratch", "lutnn_linear_tree_scratch", "lutnn_linear_scratch_bytes",
+           "lutnn_conv2d_scratch_bytes", "lutnn_conv2d_scratch", "lutnn_conv2d_tree_scratch"]
 
 
 class LutnnError(RuntimeError):
@@ -100,6 +101,14 @@ def _load():
     lib.lutnn_linear_tree_scratch.restype = i32
     lib.lutnn_linear_tree_scratch.argtypes = [ctypes.POINTER(_CLayer), ctypes.POINTER(_CTree), vp, i64, i64, vp, i64, vp,
                                               ctypes.c_size_t, vp]
+    lib.lutnn_conv2d_scratch_bytes.restype = ctypes.c_size_t
+    lib.lutnn_conv2d_scratch_bytes.argtypes = [ctypes.POINTER(_CLayer), i64]
+    lib.lutnn_conv2d_scratch.restype = i32
+    lib.lutnn_conv2d_scratch.argtypes = [ctypes.POINTER(_CLayer), vp, i64, ctypes.POINTER(_CConvGeom), vp, i64, vp,
+                                         ctypes.c_size_t, vp]
+    lib.lutnn_conv2d_tree_scratch.restype = i32
+    lib.lutnn_conv2d_tree_scratch.argtypes = [ctypes.POINTER(_CLayer), ctypes.POINTER(_CTree), vp, i64,
+                                              ctypes.POINTER(_CConvGeom), vp, i64, vp, ctypes.c_size_t, vp]
     lib.lutnn_linear_scratch_bytes.restype = ctypes.c_size_t
     lib.lutnn_linear_scratch_bytes.argtypes = [ctypes.POINTER(_CLayer), i64, i32]
     lib.lutnn_encode_tree16.restype = i32
@@ -497,10 +506,17 @@ def conv2d(layer, inp, kernel, stride=1, pad=0, variant="auto", out=None, idx_wo
     if out is None:
         out = torch.empty((N, layer.M), dtype=torch.float32, device=inp.device)
     assert out.dtype == torch.float32 and out.stride(1) == 1 and out.shape == (N, layer.M)
+    v = _variant(variant)
     if idx_workspace is None:
+        if v == VARIANT_AUTO:
+            nbytes = LIB.lutnn_conv2d_scratch_bytes(layer.ref, N)
+            scratch = torch.empty(nbytes, dtype=torch.uint8, device=inp.device)
+            _check(LIB.lutnn_conv2d_scratch(layer.ref, _ptr(inp), inp.shape[0], ctypes.byref(geom), _ptr(out),
+                                            out.stride(0), _ptr(scratch), nbytes, _stream()))
+            return out
         idx_workspace = torch.empty((N, layer.C), dtype=torch.uint8, device=inp.device)
     _check(LIB.lutnn_conv2d(layer.ref, _ptr(inp), inp.shape[0], ctypes.byref(geom), _ptr(out),
-                            out.stride(0), _variant(variant), _ptr(idx_workspace), _stream()))
+                            out.stride(0), v, _ptr(idx_workspace), _stream()))
     return out
 
 
@@ -529,10 +545,17 @@ def conv2d_tree(layer, tree, inp, kernel, stride=1, pad=0, variant="auto", out=N
     if out is None:
         out = torch.empty((N, layer.M), dtype=torch.float32, device=inp.device)
     assert out.dtype == torch.float32 and out.stride(1) == 1 and out.shape == (N, layer.M)
+    v = _variant(variant)
     if idx_workspace is None:
+        if v == VARIANT_AUTO:
+            nbytes = LIB.lutnn_conv2d_scratch_bytes(layer.ref, N)
+            scratch = torch.empty(nbytes, dtype=torch.uint8, device=inp.device)
+            _check(LIB.lutnn_conv2d_tree_scratch(layer.ref, tree.ref, _ptr(inp), inp.shape[0], ctypes.byref(geom), _ptr(out),
+                                                 out.stride(0), _ptr(scratch), nbytes, _stream()))
+            return out
         idx_workspace = torch.empty((N, layer.C), dtype=torch.uint8, device=inp.device)
     _check(LIB.lutnn_conv2d_tree(layer.ref, tree.ref, _ptr(inp), inp.shape[0],
-                                 ctypes.byref(geom), _ptr(out), out.stride(0), _variant(variant),
+                                 ctypes.byref(geom), _ptr(out), out.stride(0), v,
                                  _ptr(idx_workspace), _stream()))
     return out
 

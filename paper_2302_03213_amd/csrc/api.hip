@@ -142,12 +142,13 @@ lutnn_status check_lookup(const lutnn_layer* L, int variant, const uint8_t* idx,
     return LUTNN_OK;
 }
 
-lutnn_status do_lookup(const lutnn_layer* L, int variant, const uint8_t* idx, int64_t N, float* Y,
+// ldi: stride of the index rows; C (dense) but for the padded rows that SMFMAC may be given
+lutnn_status do_lookup(const lutnn_layer* L, int variant, const uint8_t* idx, int64_t ldi, int64_t N, float* Y,
                        int64_t ldy, hipStream_t s) {
     hipError_t e;
     if (variant == LUTNN_VARIANT_SMFMAC) {
         e = lutnn::launch_lookup_smfmac_i8(static_cast<const int8_t*>(L->table_packed), L->scale, L->bias,
-                                           L->C, L->K, L->M, idx, N, Y, ldy, s);
+                                           L->C, L->K, L->M, idx, ldi, N, Y, ldy, s);
     } else if (variant == LUTNN_VARIANT_MFMA) {
         e = lutnn::launch_lookup_mfma_i8(static_cast<const int8_t*>(L->table_packed), L->scale, L->bias,
                                          L->C, L->K, L->M, idx, N, Y, ldy, s);
@@ -354,7 +355,7 @@ lutnn_status lutnn_encode(const lutnn_layer* layer, const float* X, int64_t N, i
     if (N == 0) return LUTNN_OK;  // an empty batch may come with NULL data pointers
     if (lutnn_status st = check_encode(layer, X, N, ldx)) return st;
     if (!idx) return fail(LUTNN_E_NULL, "idx is NULL");
-    return hip_result(lutnn::launch_encode(layer->centroids, layer->C, layer->K, layer->V, X, N, ldx, idx,
+    return hip_result(lutnn::launch_encode(layer->centroids, layer->C, layer->K, layer->V, X, N, ldx, {idx, layer->C},
                                            static_cast<hipStream_t>(stream)),
                       "encode launch");
 }
@@ -365,7 +366,7 @@ lutnn_status lutnn_encode_tree(const lutnn_tree* tree, const float* X, int64_t N
     if (N == 0) return LUTNN_OK;
     if (!idx) return fail(LUTNN_E_NULL, "idx is NULL");
     return hip_result(lutnn::launch_encode_tree(tree->split_dim, tree->threshold, tree->C, tree->levels,
-                                                tree->V, X, N, ldx, idx, static_cast<hipStream_t>(stream)),
+                                                tree->V, X, N, ldx, {idx, tree->C}, static_cast<hipStream_t>(stream)),
                       "tree encode launch");
 }
 
@@ -495,7 +496,7 @@ lutnn_status lutnn_lookup(const lutnn_layer* layer, const uint8_t* idx, int64_t 
         return fail(LUTNN_E_UNSUPPORTED, "FUSED is a lutnn_linear variant, not a lookup variant");
     const int v = resolve_lookup_variant(layer, variant, idx, N);
     if (lutnn_status st = check_lookup(layer, v, idx, Y, N, ldy)) return st;
-    return do_lookup(layer, v, idx, N, Y, ldy, static_cast<hipStream_t>(stream));
+    return do_lookup(layer, v, idx, layer->C, N, Y, ldy, static_cast<hipStream_t>(stream));
 }
 
 namespace {
@@ -515,11 +516,11 @@ bool one_launch_form(const lutnn_layer* L) {
 
 // The one-launch kernel is worth it where the lookup it replaces would be the gather anyway (the
 // indices it would see are 16-byte aligned in LDS, so the sparse kernel counts as available when
-// the shape allows it).
-bool small_preferred(const lutnn_layer* L, int64_t N, bool tree = false) {
+// the shape allows it; any_codebooks: whatever C).
+bool small_preferred(const lutnn_layer* L, int64_t N, bool tree, bool any_codebooks) {
     const int kind = small_table_kind(L);
-    const bool sparse_ok = is_int_table(L->table_dtype) && L->table_packed && L->K <= 16 && L->C % 32 == 0;
     const bool matrix_ok = is_int_table(L->table_dtype) && L->table_packed && L->K <= 16;
+    const bool sparse_ok = matrix_ok && (any_codebooks || L->C % 32 == 0);
     const bool gather_wins = !matrix_ok || lutnn::gather_preferred(L->table, kind, L->C, L->K, L->M, N, sparse_ok);
     return lutnn::linear_small_preferred(L->table, kind, L->C, L->K, L->V, L->M, N, tree, gather_wins);
 }
@@ -535,7 +536,7 @@ bool fused_takes_small_kernel(const lutnn_layer* L, int64_t N) {
     if (pinned == 1 && can_small) return true;
     if (pinned == 0 && can_tile) return false;
     if (!can_small) return false;
-    return !can_tile || small_preferred(L, N);
+    return !can_tile || small_preferred(L, N, false, false);
 }
 
 lutnn_status check_fused(const lutnn_layer* L, const float* Y, int64_t ldy) {
@@ -567,7 +568,7 @@ lutnn_status one_launch_tree(const lutnn_layer* L, const lutnn_tree* T, const fl
 // table per row block).  Without a workspace for the indices a fused kernel is the only choice.
 int resolve_linear_variant(const lutnn_layer* L, int variant, const uint8_t* idx_workspace, int64_t N) {
     if (variant != LUTNN_VARIANT_AUTO) return variant;
-    if (one_launch_form(L) && small_preferred(L, N)) return LUTNN_VARIANT_FUSED;
+    if (one_launch_form(L) && small_preferred(L, N, false, false)) return LUTNN_VARIANT_FUSED;
     const bool tile_ok = lutnn::fused_supported(L->C, L->K, L->V, L->M, L->table_dtype) &&
                          (L->table_dtype == LUTNN_TABLE_F32 ? L->table != nullptr : L->table_packed != nullptr);
     if ((tile_ok || one_launch_form(L)) && !idx_workspace) return LUTNN_VARIANT_FUSED;
@@ -611,10 +612,10 @@ lutnn_status lutnn_linear(const lutnn_layer* layer, const float* X, int64_t N, i
     if (!idx_workspace) return fail(LUTNN_E_NULL, "this variant needs idx_workspace");
     if (lutnn_status st = check_lookup(L, v, idx_workspace, Y, N, ldy)) return st;
     if (lutnn_status st = hip_result(
-            lutnn::launch_encode(L->centroids, L->C, L->K, L->V, X, N, ldx, idx_workspace, s),
+            lutnn::launch_encode(L->centroids, L->C, L->K, L->V, X, N, ldx, {idx_workspace, L->C}, s),
             "encode launch"))
         return st;
-    return do_lookup(L, v, idx_workspace, N, Y, ldy, s);
+    return do_lookup(L, v, idx_workspace, L->C, N, Y, ldy, s);
 }
 
 lutnn_status lutnn_linear_tree(const lutnn_layer* layer, const lutnn_tree* tree, const float* X,
@@ -632,7 +633,7 @@ lutnn_status lutnn_linear_tree(const lutnn_layer* layer, const lutnn_tree* tree,
     if (variant == LUTNN_VARIANT_FUSED && !can_small)
         return fail(LUTNN_E_UNSUPPORTED, "no one-launch kernel with the hash encoder for C=%d K=%d V=%d M=%d dtype=%d",
                     layer->C, layer->K, layer->V, layer->M, layer->table_dtype);
-    if (variant == LUTNN_VARIANT_FUSED || (variant == LUTNN_VARIANT_AUTO && can_small && small_preferred(layer, N, true))) {
+    if (variant == LUTNN_VARIANT_FUSED || (variant == LUTNN_VARIANT_AUTO && can_small && small_preferred(layer, N, true, false))) {
         if (lutnn_status st = check_fused(layer, Y, ldy)) return st;
         return one_launch_tree(layer, tree, X, N, ldx, Y, ldy, s);
     }
@@ -641,15 +642,83 @@ lutnn_status lutnn_linear_tree(const lutnn_layer* layer, const lutnn_tree* tree,
     if (lutnn_status st = check_lookup(layer, v, idx_workspace, Y, N, ldy)) return st;
     if (lutnn_status st = hip_result(lutnn::launch_encode_tree(tree->split_dim, tree->threshold, tree->C,
                                                                tree->levels, tree->V, X, N, ldx,
-                                                               idx_workspace, s),
+                                                               {idx_workspace, tree->C}, s),
                                      "tree encode launch"))
         return st;
-    return do_lookup(layer, v, idx_workspace, N, Y, ldy, s);
+    return do_lookup(layer, v, idx_workspace, layer->C, N, Y, ldy, s);
 }
 
+}  // extern "C"
+
+namespace {
+// The shape part of a tree, as the layer view check_conv wants (it reads C and V only).
+lutnn_layer shape_of(const lutnn_tree* T) {
+    lutnn_layer l{};
+    l.C = T->C;
+    l.V = T->V;
+    l.K = 1 << T->levels;
+    l.M = 1;
+    return l;
+}
+lutnn_status check_tree_shape(const lutnn_tree* T) {
+    if (!T) return fail(LUTNN_E_NULL, "tree is NULL");
+    if (T->reserved != 0) return fail(LUTNN_E_SHAPE, "tree->reserved must be 0");
+    if (T->levels < 1 || T->levels > 8)
+        return fail(LUTNN_E_SHAPE, "tree->levels=%d outside 1..8 (indices are uint8)", T->levels);
+    return check_dims(T->C, 1 << T->levels, T->V, 1);
+}
+
+// ... and everything about a convolution with the hash encoder but where its indices go.
+lutnn_status check_tree_conv(const lutnn_tree* tree, const float* input, int64_t B, const lutnn_conv2d_geom* geom,
+                             lutnn::ConvGeom* g, int64_t* N) {
+    if (lutnn_status st = check_tree_shape(tree)) return st;
+    const lutnn_layer shape = shape_of(tree);
+    if (lutnn_status st = check_conv(&shape, geom, B, g, N)) return st;
+    if (*N == 0) return LUTNN_OK;
+    if (!tree->split_dim || !tree->threshold) return fail(LUTNN_E_NULL, "tree->split_dim or tree->threshold is NULL");
+    if (!input) return fail(LUTNN_E_NULL, "input is NULL");
+    if (!aligned(input, 4) || !aligned(tree->split_dim, 4) || !aligned(tree->threshold, 4))
+        return fail(LUTNN_E_ALIGN, "input, split_dim and threshold must be 4-byte aligned");
+    return LUTNN_OK;
+}
+}  // namespace
+
+namespace {
+
+// What the calls with a scratch of their own layout run after the encoder, and the stride of the index rows between the
+// two: the sparse lookup wherever the matrix cores are worth it, whatever C (its index rows are padded), or what AUTO stands for.
+struct TwoStep {
+    int variant;
+    int64_t ldi;
+};
+TwoStep two_step(const lutnn_layer* L, int64_t N) {
+    const bool matrix = is_int_table(L->table_dtype) && L->table_packed && L->K <= 16 &&
+                        !lutnn::gather_preferred(L->table, L->table_dtype == LUTNN_TABLE_I4 ? 2 : 1, L->C, L->K, L->M, N, true);
+    if (matrix) return {LUTNN_VARIANT_SMFMAC, lutnn::smfmac_index_stride(L->C)};
+    return {LUTNN_VARIANT_LDS, L->C};
+}
+
+// Checks and runs the two steps; encode(IndexRows) launches the first.
+template <class Encode>
+lutnn_status run_two_step(const lutnn_layer* L, int64_t N, float* Y, int64_t ldy, void* scratch, size_t scratch_bytes,
+                          hipStream_t s, const char* what, Encode&& encode) {
+    const TwoStep two = two_step(L, N);
+    if (lutnn_status st = check_scratch(scratch, scratch_bytes, (size_t)N * two.ldi)) return st;
+    uint8_t* idx = static_cast<uint8_t*>(scratch);
+    // MFMA: what SMFMAC needs but for the dense index matrix's own conditions
+    const int needs = two.variant == LUTNN_VARIANT_SMFMAC ? LUTNN_VARIANT_MFMA : two.variant;
+    if (lutnn_status st = check_lookup(L, needs, idx, Y, N, ldy)) return st;
+    if (lutnn_status st = hip_result(encode(lutnn::IndexRows{idx, two.ldi}), what)) return st;
+    return do_lookup(L, two.variant, idx, two.ldi, N, Y, ldy, s);
+}
+
+}  // namespace
+
+extern "C" {
+
 size_t lutnn_linear_scratch_bytes(const lutnn_layer* layer, int64_t N, int32_t tree) {
-    if (check_layer(layer) != LUTNN_OK || N <= 0 || N >= kMaxRows || small_preferred(layer, N, tree != 0)) return 0;
-    return (size_t)N * layer->C;
+    if (check_layer(layer) != LUTNN_OK || N <= 0 || N >= kMaxRows || small_preferred(layer, N, tree != 0, true)) return 0;
+    return (size_t)N * two_step(layer, N).ldi;
 }
 
 lutnn_status lutnn_linear_scratch(const lutnn_layer* layer, const float* X, int64_t N, int64_t ldx, float* Y, int64_t ldy,
@@ -657,13 +726,14 @@ lutnn_status lutnn_linear_scratch(const lutnn_layer* layer, const float* X, int6
     if (lutnn_status st = check_layer(layer)) return st;
     if (N == 0) return LUTNN_OK;
     if (lutnn_status st = check_encode(layer, X, N, ldx)) return st;
-    if (small_preferred(layer, N)) {
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    if (small_preferred(layer, N, false, true)) {
         if (lutnn_status st = check_fused(layer, Y, ldy)) return st;
-        return one_launch(layer, X, N, ldx, Y, ldy, static_cast<hipStream_t>(stream));
+        return one_launch(layer, X, N, ldx, Y, ldy, s);
     }
-    if (lutnn_status st = check_scratch(scratch, scratch_bytes, lutnn_linear_scratch_bytes(layer, N, 0))) return st;
-    const int v = resolve_lookup_variant(layer, LUTNN_VARIANT_AUTO, static_cast<uint8_t*>(scratch), N);
-    return lutnn_linear(layer, X, N, ldx, Y, ldy, v, static_cast<uint8_t*>(scratch), stream);
+    return run_two_step(layer, N, Y, ldy, scratch, scratch_bytes, s, "encode launch", [&](lutnn::IndexRows idx) {
+        return lutnn::launch_encode(layer->centroids, layer->C, layer->K, layer->V, X, N, ldx, idx, s);
+    });
 }
 
 lutnn_status lutnn_linear_tree_scratch(const lutnn_layer* layer, const lutnn_tree* tree, const float* X, int64_t N,
@@ -673,13 +743,49 @@ lutnn_status lutnn_linear_tree_scratch(const lutnn_layer* layer, const lutnn_tre
     if (lutnn_status st = check_tree(tree, X, N, ldx)) return st;
     if (lutnn_status st = check_tree_matches(layer, tree)) return st;
     if (N == 0) return LUTNN_OK;
-    if (small_preferred(layer, N, true)) {
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    if (small_preferred(layer, N, true, true)) {
         if (lutnn_status st = check_fused(layer, Y, ldy)) return st;
-        return one_launch_tree(layer, tree, X, N, ldx, Y, ldy, static_cast<hipStream_t>(stream));
+        return one_launch_tree(layer, tree, X, N, ldx, Y, ldy, s);
     }
-    if (lutnn_status st = check_scratch(scratch, scratch_bytes, lutnn_linear_scratch_bytes(layer, N, 1))) return st;
-    const int v = resolve_lookup_variant(layer, LUTNN_VARIANT_AUTO, static_cast<uint8_t*>(scratch), N);
-    return lutnn_linear_tree(layer, tree, X, N, ldx, Y, ldy, v, static_cast<uint8_t*>(scratch), stream);
+    return run_two_step(layer, N, Y, ldy, scratch, scratch_bytes, s, "tree encode launch", [&](lutnn::IndexRows idx) {
+        return lutnn::launch_encode_tree(tree->split_dim, tree->threshold, tree->C, tree->levels, tree->V, X, N, ldx, idx, s);
+    });
+}
+
+size_t lutnn_conv2d_scratch_bytes(const lutnn_layer* layer, int64_t N) {
+    if (check_layer(layer) != LUTNN_OK || N <= 0 || N >= kMaxRows) return 0;
+    return (size_t)N * two_step(layer, N).ldi;
+}
+
+lutnn_status lutnn_conv2d_scratch(const lutnn_layer* layer, const float* input, int64_t B, const lutnn_conv2d_geom* geom,
+                                  float* Y, int64_t ldy, void* scratch, size_t scratch_bytes, void* stream) {
+    if (lutnn_status st = check_layer(layer)) return st;
+    lutnn::ConvGeom g;
+    int64_t N = 0;
+    if (lutnn_status st = check_conv(layer, geom, B, &g, &N)) return st;
+    if (N == 0) return LUTNN_OK;
+    if (lutnn_status st = check_conv_input(layer, input)) return st;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    return run_two_step(layer, N, Y, ldy, scratch, scratch_bytes, s, "convolution encode launch", [&](lutnn::IndexRows idx) {
+        return lutnn::launch_encode_conv(layer->centroids, layer->C, layer->K, layer->V, input, B, g, idx, s);
+    });
+}
+
+lutnn_status lutnn_conv2d_tree_scratch(const lutnn_layer* layer, const lutnn_tree* tree, const float* input, int64_t B,
+                                       const lutnn_conv2d_geom* geom, float* Y, int64_t ldy, void* scratch,
+                                       size_t scratch_bytes, void* stream) {
+    if (lutnn_status st = check_layer(layer)) return st;
+    lutnn::ConvGeom g;
+    int64_t N = 0;
+    if (lutnn_status st = check_tree_conv(tree, input, B, geom, &g, &N)) return st;
+    if (lutnn_status st = check_tree_matches(layer, tree)) return st;
+    if (N == 0) return LUTNN_OK;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    return run_two_step(layer, N, Y, ldy, scratch, scratch_bytes, s, "convolution tree encode launch", [&](lutnn::IndexRows idx) {
+        return lutnn::launch_encode_tree_conv(tree->split_dim, tree->threshold, tree->C, tree->levels, tree->V, input, B, g,
+                                              idx, s);
+    });
 }
 
 lutnn_status lutnn_encode_tree16(const lutnn_tree* tree, const float* X, int64_t N, int64_t ldx,
@@ -778,44 +884,19 @@ lutnn_status lutnn_encode_conv2d(const lutnn_layer* layer, const float* input, i
     if (lutnn_status st = check_conv_input(layer, input)) return st;
     if (!idx) return fail(LUTNN_E_NULL, "idx is NULL");
     return hip_result(lutnn::launch_encode_conv(layer->centroids, layer->C, layer->K, layer->V, input, B,
-                                                g, idx, static_cast<hipStream_t>(stream)),
+                                                g, {idx, layer->C}, static_cast<hipStream_t>(stream)),
                       "convolution encode launch");
 }
 
-namespace {
-// The shape part of a tree, as the layer view check_conv wants (it reads C and V only).
-lutnn_layer shape_of(const lutnn_tree* T) {
-    lutnn_layer l{};
-    l.C = T->C;
-    l.V = T->V;
-    l.K = 1 << T->levels;
-    l.M = 1;
-    return l;
-}
-lutnn_status check_tree_shape(const lutnn_tree* T) {
-    if (!T) return fail(LUTNN_E_NULL, "tree is NULL");
-    if (T->reserved != 0) return fail(LUTNN_E_SHAPE, "tree->reserved must be 0");
-    if (T->levels < 1 || T->levels > 8)
-        return fail(LUTNN_E_SHAPE, "tree->levels=%d outside 1..8 (indices are uint8)", T->levels);
-    return check_dims(T->C, 1 << T->levels, T->V, 1);
-}
-}  // namespace
-
 lutnn_status lutnn_encode_tree_conv2d(const lutnn_tree* tree, const float* input, int64_t B,
                                       const lutnn_conv2d_geom* geom, uint8_t* idx, void* stream) {
-    if (lutnn_status st = check_tree_shape(tree)) return st;
-    const lutnn_layer shape = shape_of(tree);
     lutnn::ConvGeom g;
     int64_t N = 0;
-    if (lutnn_status st = check_conv(&shape, geom, B, &g, &N)) return st;
+    if (lutnn_status st = check_tree_conv(tree, input, B, geom, &g, &N)) return st;
     if (N == 0) return LUTNN_OK;
-    if (!tree->split_dim || !tree->threshold) return fail(LUTNN_E_NULL, "tree->split_dim or tree->threshold is NULL");
-    if (!input) return fail(LUTNN_E_NULL, "input is NULL");
     if (!idx) return fail(LUTNN_E_NULL, "idx is NULL");
-    if (!aligned(input, 4) || !aligned(tree->split_dim, 4) || !aligned(tree->threshold, 4))
-        return fail(LUTNN_E_ALIGN, "input, split_dim and threshold must be 4-byte aligned");
     return hip_result(lutnn::launch_encode_tree_conv(tree->split_dim, tree->threshold, tree->C, tree->levels,
-                                                     tree->V, input, B, g, idx, static_cast<hipStream_t>(stream)),
+                                                     tree->V, input, B, g, {idx, tree->C}, static_cast<hipStream_t>(stream)),
                       "convolution tree encode launch");
 }
 
@@ -835,7 +916,7 @@ lutnn_status lutnn_conv2d_tree(const lutnn_layer* layer, const lutnn_tree* tree,
     const int v = resolve_lookup_variant(layer, variant, idx_workspace, N);
     if (lutnn_status st = check_lookup(layer, v, idx_workspace, Y, N, ldy)) return st;
     if (lutnn_status st = lutnn_encode_tree_conv2d(tree, input, B, geom, idx_workspace, stream)) return st;
-    return do_lookup(layer, v, idx_workspace, N, Y, ldy, static_cast<hipStream_t>(stream));
+    return do_lookup(layer, v, idx_workspace, layer->C, N, Y, ldy, static_cast<hipStream_t>(stream));
 }
 
 lutnn_status lutnn_linear_gradient(const float* G, int64_t N, int64_t ldg, const float* W, int64_t ldw, int32_t D, int32_t M,
@@ -915,10 +996,10 @@ lutnn_status lutnn_conv2d(const lutnn_layer* layer, const float* input, int64_t 
     if (lutnn_status st = check_lookup(layer, v, idx_workspace, Y, N, ldy)) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (lutnn_status st = hip_result(lutnn::launch_encode_conv(layer->centroids, layer->C, layer->K,
-                                                               layer->V, input, B, g, idx_workspace, s),
+                                                               layer->V, input, B, g, {idx_workspace, layer->C}, s),
                                      "convolution encode launch"))
         return st;
-    return do_lookup(layer, v, idx_workspace, N, Y, ldy, s);
+    return do_lookup(layer, v, idx_workspace, layer->C, N, Y, ldy, s);
 }
 
 int32_t lutnn_auto_variant(const lutnn_layer* layer, const uint8_t* idx, int64_t N) {

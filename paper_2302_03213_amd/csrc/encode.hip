@@ -26,7 +26,7 @@ template <int V, int K_T, int CT, int CONV = 0>
 __global__ __launch_bounds__(kEncThreads) void encode_tile_kernel(const float* __restrict__ X,
                                                                   int64_t ldx,
                                                                   const float* __restrict__ P,
-                                                                  uint8_t* __restrict__ idx,
+                                                                  const IndexRows idx,
                                                                   int64_t N, int C, int K_rt, int vec4,
                                                                   int idx_dword_ok, ConvGeom geom) {
     using E = EncTile<V, CT>;
@@ -54,14 +54,14 @@ __global__ __launch_bounds__(kEncThreads) void encode_tile_kernel(const float* _
     store_index_bytes<V, CT>(is + lane * (CT / 4), w * E::CPW, packed);
     __syncthreads();
 
-    // each row's CT index bytes are contiguous in idx[N][C]
+    // each row's CT index bytes are contiguous
     for (int i = tid; i < kEncRows * (CT / 4); i += kEncThreads) {
         const int r = i / (CT / 4), j = i % (CT / 4);
         const int c = c0 + 4 * j;
         if (row0 + r >= N || c >= C) continue;
         const uint32_t wv = is[i];
-        uint8_t* dst = idx + (row0 + r) * (int64_t)C + c;
-        if (idx_dword_ok) {  // C % 4 == 0 and idx 4-byte aligned -> the whole dword is in range
+        uint8_t* dst = idx.rows + (row0 + r) * idx.ld + c;
+        if (idx_dword_ok) {  // aligned rows of whole dwords
             *reinterpret_cast<uint32_t*>(dst) = wv;
         } else {
 #pragma unroll
@@ -81,7 +81,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_tile_kernel(const float* _
 //   bs_max  floats reserved per channel (the largest band of any tile; computed by the launcher)
 template <int K_T, int CT>
 __global__ __launch_bounds__(kEncThreads) void encode_conv9_band_kernel(
-    const float* __restrict__ input, const float* __restrict__ P, uint8_t* __restrict__ idx, int C,
+    const float* __restrict__ input, const float* __restrict__ P, const IndexRows idx, int C,
     int K_rt, ConvGeom g, int pix_tiles, int bs_max, int idx_dword_ok) {
     constexpr int V = 9;
     using E = EncTile<V, CT>;
@@ -170,7 +170,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_conv9_band_kernel(
         const int c = c0 + 4 * j;
         if (r >= rows || c >= C) continue;
         const uint32_t wv = is[i];
-        uint8_t* dst = idx + (n0 + r) * (int64_t)C + c;
+        uint8_t* dst = idx.rows + (n0 + r) * idx.ld + c;
         if (idx_dword_ok) {
             *reinterpret_cast<uint32_t*>(dst) = wv;
         } else {
@@ -186,7 +186,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_conv9_band_kernel(
 __global__ __launch_bounds__(kEncThreads) void encode_generic_kernel(const float* __restrict__ X,
                                                                      int64_t ldx,
                                                                      const float* __restrict__ P,
-                                                                     uint8_t* __restrict__ idx,
+                                                                     const IndexRows idx,
                                                                      int64_t N, int C, int K, int V) {
     const int64_t i = (int64_t)blockIdx.x * kEncThreads + threadIdx.x;
     if (i >= N * (int64_t)C) return;
@@ -209,19 +209,19 @@ __global__ __launch_bounds__(kEncThreads) void encode_generic_kernel(const float
             best = k;
         }
     }
-    idx[i] = (uint8_t)best;
+    idx.rows[n * idx.ld + c] = (uint8_t)best;
 }
 
 template <int V, int CT, int CONV = 0>
 hipError_t launch_tile_ct(const float* P, int C, int K, const float* X, int64_t N, int64_t ldx,
-                          uint8_t* idx, hipStream_t s, const ConvGeom& geom = ConvGeom{}) {
+                          IndexRows idx, hipStream_t s, const ConvGeom& geom = ConvGeom{}) {
     const int64_t row_tiles = (N + kEncRows - 1) / kEncRows;
     const int64_t col_tiles = (C + CT - 1) / CT;
     const int64_t blocks = row_tiles * col_tiles;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const int vec4 = ((CT * V) % 4 == 0) && (((int64_t)C * V) % 4 == 0) && (ldx % 4 == 0) &&
                      ((reinterpret_cast<uintptr_t>(X) & 15) == 0);
-    const int idx_dword_ok = (C % 4 == 0) && ((reinterpret_cast<uintptr_t>(idx) & 3) == 0);
+    const int idx_dword_ok = idx.dwords(C);
     dim3 grid((unsigned)blocks), block(kEncThreads);
     if (K == 16)
         hipLaunchKernelGGL((encode_tile_kernel<V, 16, CT, CONV>), grid, block, 0, s, X, ldx, P, idx, N, C,
@@ -243,7 +243,7 @@ hipError_t launch_tile_ct(const float* P, int C, int K, const float* X, int64_t 
 // chain; BERT's FFN-down at 4096 rows (1536 full tiles: one and a half rounds) 0.034 -> 0.029 ms.
 template <int V, int CONV = 0>
 hipError_t launch_tile(const float* P, int C, int K, const float* X, int64_t N, int64_t ldx,
-                       uint8_t* idx, hipStream_t s, const ConvGeom& geom = ConvGeom{}) {
+                       IndexRows idx, hipStream_t s, const ConvGeom& geom = ConvGeom{}) {
     constexpr int CT = enc_tile_codebooks(V);
     constexpr int CT_SMALL = CT / 4 >= 4 ? CT / 4 : 4;
     const int64_t full_blocks = ((N + kEncRows - 1) / kEncRows) * ((C + CT - 1) / CT);
@@ -268,12 +268,12 @@ int64_t conv_band_floats(const ConvGeom& g) {
 
 template <int CT>
 hipError_t launch_conv9_band(const float* P, int C, int K, const float* input, int64_t B,
-                             const ConvGeom& g, uint8_t* idx, int64_t bs_max, hipStream_t s) {
+                             const ConvGeom& g, IndexRows idx, int64_t bs_max, hipStream_t s) {
     const int64_t pix_tiles = ((int64_t)g.Ho * g.Wo + kEncRows - 1) / kEncRows;
     const int64_t blocks = B * pix_tiles * ((C + CT - 1) / CT);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const size_t shmem = (size_t)CT * bs_max * 4 + (size_t)kEncRows * (CT / 4) * 4;
-    const int idx_dword_ok = (C % 4 == 0) && ((reinterpret_cast<uintptr_t>(idx) & 3) == 0);
+    const int idx_dword_ok = idx.dwords(C);
     dim3 grid((unsigned)blocks), block(kEncThreads);
     if (K == 16)
         hipLaunchKernelGGL((encode_conv9_band_kernel<16, CT>), grid, block, shmem, s, input, P, idx, C, K, g,
@@ -289,7 +289,7 @@ hipError_t launch_conv9_band(const float* P, int C, int K, const float* input, i
 
 template <int V>
 hipError_t launch_conv_v(const float* P, int C, int K, const float* input, int64_t B, int64_t N,
-                         const ConvGeom& g, uint8_t* idx, hipStream_t s) {
+                         const ConvGeom& g, IndexRows idx, hipStream_t s) {
     const int taps = g.kh * g.kw;
     if (taps == 1) return launch_tile<V, 1>(P, C, K, input, N, 0, idx, s, g);
     if constexpr (V == 9) {
@@ -312,7 +312,7 @@ hipError_t launch_conv_v(const float* P, int C, int K, const float* input, int64
 }
 
 hipError_t launch_encode_conv(const float* P, int C, int K, int V, const float* input, int64_t B,
-                              const ConvGeom& g, uint8_t* idx, hipStream_t s) {
+                              const ConvGeom& g, IndexRows idx, hipStream_t s) {
     const int64_t N = B * g.Ho * g.Wo;
     switch (V) {
         case 1: return launch_conv_v<1>(P, C, K, input, B, N, g, idx, s);
@@ -327,7 +327,7 @@ hipError_t launch_encode_conv(const float* P, int C, int K, int V, const float* 
 }
 
 hipError_t launch_encode(const float* P, int C, int K, int V, const float* X, int64_t N, int64_t ldx,
-                         uint8_t* idx, hipStream_t s) {
+                         IndexRows idx, hipStream_t s) {
     switch (V) {
         case 1: return launch_tile<1>(P, C, K, X, N, ldx, idx, s);
         case 2: return launch_tile<2>(P, C, K, X, N, ldx, idx, s);

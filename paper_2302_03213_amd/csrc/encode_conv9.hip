@@ -296,7 +296,7 @@ __device__ __forceinline__ uint32_t search_rows(uint64_t rows, uint32_t best, co
 template <int K_T, int NI>
 __global__ __launch_bounds__(kEncThreads, NI > 5 ? 3 : 4) void encode_conv9_filter_kernel(const float* __restrict__ input,
                                                                              const float* __restrict__ P,
-                                                                             uint8_t* __restrict__ idx, int C, ConvGeom g,
+                                                                             const IndexRows idx, int C, ConvGeom g,
                                                                              int per, int longer,
                                                                              int pix_tiles, int idx_dword_ok) {
     constexpr int BS = 64 * NI;  // floats reserved per channel
@@ -414,7 +414,7 @@ __global__ __launch_bounds__(kEncThreads, NI > 5 ? 3 : 4) void encode_conv9_filt
         }
         // each lane stores its row's four bytes
         if (now.p0 + lane <= now.p1) {
-            uint8_t* dst = idx + (n0 + lane) * (int64_t)C + channel;
+            uint8_t* dst = idx.rows + (n0 + lane) * idx.ld + channel;
             if (idx_dword_ok) {
                 if (channel < C) *reinterpret_cast<uint32_t*>(dst) = packed;
             } else {
@@ -427,20 +427,20 @@ __global__ __launch_bounds__(kEncThreads, NI > 5 ? 3 : 4) void encode_conv9_filt
 }
 
 template <int K_T, int NI>
-hipError_t launch(const float* P, int C, const float* input, int64_t B, const ConvGeom& g, uint8_t* idx, int64_t chunks,
+hipError_t launch(const float* P, int C, const float* input, int64_t B, const ConvGeom& g, IndexRows idx, int64_t chunks,
                   hipStream_t s) {
     const int64_t pix_tiles = ((int64_t)g.Ho * g.Wo + kEncRows - 1) / kEncRows, tiles = B * pix_tiles;
     const int64_t blocks = chunks * ((C + kCT - 1) / kCT);
     const int per = (int)((tiles + chunks - 1) / chunks), longer = (int)(tiles - (per - 1) * chunks);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    const int idx_dword_ok = (C % 4 == 0) && ((reinterpret_cast<uintptr_t>(idx) & 3) == 0);
+    const int idx_dword_ok = idx.dwords(C);
     hipLaunchKernelGGL((encode_conv9_filter_kernel<K_T, NI>), dim3((unsigned)blocks), dim3(kEncThreads), 0, s, input, P, idx,
                        C, g, per, longer, (int)pix_tiles, idx_dword_ok);
     return hipGetLastError();
 }
 
 template <int K_T>
-hipError_t launch_k(const float* P, int C, const float* input, int64_t B, const ConvGeom& g, uint8_t* idx, int64_t chunks,
+hipError_t launch_k(const float* P, int C, const float* input, int64_t B, const ConvGeom& g, IndexRows idx, int64_t chunks,
                     hipStream_t s) {
     const int64_t bs = conv_band_floats(g);
     if (bs <= 192) return launch<K_T, 3>(P, C, input, B, g, idx, chunks, s);
@@ -470,7 +470,7 @@ int64_t encode_conv9_filter_chunks(int C, int K, int64_t B, const ConvGeom& g) {
 }
 
 hipError_t launch_encode_conv9_filter(const float* P, int C, int K, const float* input, int64_t B, const ConvGeom& g,
-                                      uint8_t* idx, int64_t chunks, hipStream_t s) {
+                                      IndexRows idx, int64_t chunks, hipStream_t s) {
     if (K == 8) return launch_k<8>(P, C, input, B, g, idx, chunks, s);
     return launch_k<16>(P, C, input, B, g, idx, chunks, s);
 }

@@ -87,9 +87,9 @@ __device__ __forceinline__ void walk_trees(const float* __restrict__ xs, const u
     store_index_bytes<V, CT>(is + lane * (CT / 4), w * E::CPW, packed);
 }
 
-// Each row's CT index bytes are contiguous in idx[N][C]: out as row segments.
+// Each row's CT index bytes are contiguous: out as row segments.
 template <int CT>
-__device__ __forceinline__ void write_index_rows(const uint32_t* __restrict__ is, uint8_t* __restrict__ idx,
+__device__ __forceinline__ void write_index_rows(const uint32_t* __restrict__ is, const IndexRows idx,
                                                  int64_t N, int C, int64_t row0, int c0, int idx_dword_ok,
                                                  int tid) {
     for (int i = tid; i < kEncRows * (CT / 4); i += kEncThreads) {
@@ -97,8 +97,8 @@ __device__ __forceinline__ void write_index_rows(const uint32_t* __restrict__ is
         const int c = c0 + 4 * j;
         if (row0 + r >= N || c >= C) continue;
         const uint32_t wv = is[i];
-        uint8_t* dst = idx + (row0 + r) * (int64_t)C + c;
-        if (idx_dword_ok) {  // C % 4 == 0 and idx 4-byte aligned -> the whole dword is in range
+        uint8_t* dst = idx.rows + (row0 + r) * idx.ld + c;
+        if (idx_dword_ok) {  // aligned rows of whole dwords
             *reinterpret_cast<uint32_t*>(dst) = wv;
         } else {
 #pragma unroll
@@ -111,7 +111,7 @@ __device__ __forceinline__ void write_index_rows(const uint32_t* __restrict__ is
 template <int V, int CT, int L_T>
 __global__ __launch_bounds__(kEncThreads) void encode_tree_tile_kernel(
     const float* __restrict__ X, int64_t ldx, const int32_t* __restrict__ split_dim,
-    const float* __restrict__ threshold, uint8_t* __restrict__ idx, int64_t N, int C, int levels_rt,
+    const float* __restrict__ threshold, const IndexRows idx, int64_t N, int C, int levels_rt,
     int vec4, int idx_dword_ok) {
     using E = EncTile<V, CT>;
     __shared__ float xs[E::kLdsFloats];
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_tree_tile_kernel(
 template <int V, int CT, int L_T>
 __global__ __launch_bounds__(kEncThreads) void encode_tree_conv_kernel(
     const float* __restrict__ input, ConvGeom geom, const int32_t* __restrict__ split_dim,
-    const float* __restrict__ threshold, uint8_t* __restrict__ idx, int64_t N, int C, int levels_rt,
+    const float* __restrict__ threshold, const IndexRows idx, int64_t N, int C, int levels_rt,
     int idx_dword_ok) {
     using E = EncTile<V, CT>;
     __shared__ float xs[E::kLdsFloats];
@@ -223,7 +223,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_tree_deep_kernel(
 template <typename IdxT>
 __global__ __launch_bounds__(kEncThreads) void encode_tree_generic_kernel(
     const float* __restrict__ X, int64_t ldx, const int32_t* __restrict__ split_dim,
-    const float* __restrict__ threshold, IdxT* __restrict__ idx, int64_t N, int C, int levels,
+    const float* __restrict__ threshold, IdxT* __restrict__ idx, int64_t ldi, int64_t N, int C, int levels,
     int V) {
     const int64_t i = (int64_t)blockIdx.x * kEncThreads + threadIdx.x;
     if (i >= N * (int64_t)C) return;
@@ -238,7 +238,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_tree_generic_kernel(
         const int d = dim[node];
         node = 2 * node + 1 + (x[d < 0 ? 0 : d >= V ? V - 1 : d] > thr[node] ? 1 : 0);
     }
-    idx[i] = (IdxT)(node - nodes);
+    idx[n * ldi + c] = (IdxT)(node - nodes);
 }
 
 template <int V>
@@ -258,14 +258,14 @@ hipError_t launch_tree_deep(const int32_t* split_dim, const float* threshold, in
 
 template <int V, int CT>
 hipError_t launch_tree_ct(const int32_t* split_dim, const float* threshold, int C, int levels,
-                          const float* X, int64_t N, int64_t ldx, uint8_t* idx, hipStream_t s) {
+                          const float* X, int64_t N, int64_t ldx, IndexRows idx, hipStream_t s) {
     const int64_t row_tiles = (N + kEncRows - 1) / kEncRows;
     const int64_t col_tiles = (C + CT - 1) / CT;
     const int64_t blocks = row_tiles * col_tiles;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const int vec4 = ((CT * V) % 4 == 0) && (((int64_t)C * V) % 4 == 0) && (ldx % 4 == 0) &&
                      ((reinterpret_cast<uintptr_t>(X) & 15) == 0);
-    const int idx_dword_ok = (C % 4 == 0) && ((reinterpret_cast<uintptr_t>(idx) & 3) == 0);
+    const int idx_dword_ok = idx.dwords(C);
     const size_t node_bytes = (size_t)CT * ((1u << levels) - 1) * sizeof(uint2);
     dim3 block(kEncThreads);
     dim3 grid((unsigned)blocks);
@@ -282,7 +282,7 @@ hipError_t launch_tree_ct(const int32_t* split_dim, const float* threshold, int 
 // tile's nodes would take more than 24 KiB of LDS (deep trees); then a quarter of it.
 template <int V>
 hipError_t launch_tree(const int32_t* split_dim, const float* threshold, int C, int levels,
-                       const float* X, int64_t N, int64_t ldx, uint8_t* idx, hipStream_t s) {
+                       const float* X, int64_t N, int64_t ldx, IndexRows idx, hipStream_t s) {
     constexpr int CT = enc_tile_codebooks(V);
     constexpr int CT_SMALL = CT / 4 >= 4 ? CT / 4 : 4;
     const int64_t full_blocks = ((N + kEncRows - 1) / kEncRows) * ((C + CT - 1) / CT);
@@ -294,14 +294,14 @@ hipError_t launch_tree(const int32_t* split_dim, const float* threshold, int C, 
 
 template <int V>
 hipError_t launch_tree_conv(const int32_t* split_dim, const float* threshold, int C, int levels,
-                            const float* input, int64_t N, const ConvGeom& g, uint8_t* idx, hipStream_t s) {
+                            const float* input, int64_t N, const ConvGeom& g, IndexRows idx, hipStream_t s) {
     // quarter-width tiles when the grid is small or the nodes of a full tile exceed 24 KiB, as above
     constexpr int CTF = enc_tile_codebooks(V);
     constexpr int CTS = CTF / 4 >= 4 ? CTF / 4 : 4;
     const int64_t row_tiles = (N + kEncRows - 1) / kEncRows;
     const size_t full_node_bytes = (size_t)CTF * ((1u << levels) - 1) * sizeof(uint2);
     const bool small = CTS < CTF && (row_tiles * ((C + CTF - 1) / CTF) < 1024 || full_node_bytes > 24 * 1024);
-    const int idx_dword_ok = (C % 4 == 0) && ((reinterpret_cast<uintptr_t>(idx) & 3) == 0);
+    const int idx_dword_ok = idx.dwords(C);
     auto go = [&](auto ct_c) {
         constexpr int CT = decltype(ct_c)::value;
         const int64_t blocks = row_tiles * ((C + CT - 1) / CT);
@@ -322,7 +322,7 @@ hipError_t launch_tree_conv(const int32_t* split_dim, const float* threshold, in
 
 // Sub-vector lengths as for the distance encoder's convolution form.
 hipError_t launch_encode_tree_conv(const int32_t* split_dim, const float* threshold, int C, int levels,
-                                   int V, const float* input, int64_t B, const ConvGeom& g, uint8_t* idx,
+                                   int V, const float* input, int64_t B, const ConvGeom& g, IndexRows idx,
                                    hipStream_t s) {
     const int64_t N = B * g.Ho * g.Wo;
     switch (V) {
@@ -338,7 +338,7 @@ hipError_t launch_encode_tree_conv(const int32_t* split_dim, const float* thresh
 }
 
 hipError_t launch_encode_tree(const int32_t* split_dim, const float* threshold, int C, int levels,
-                              int V, const float* X, int64_t N, int64_t ldx, uint8_t* idx,
+                              int V, const float* X, int64_t N, int64_t ldx, IndexRows idx,
                               hipStream_t s) {
     switch (V) {
         case 1: return launch_tree<1>(split_dim, threshold, C, levels, X, N, ldx, idx, s);
@@ -355,7 +355,7 @@ hipError_t launch_encode_tree(const int32_t* split_dim, const float* threshold, 
     const int64_t blocks = (total + kEncThreads - 1) / kEncThreads;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     hipLaunchKernelGGL(encode_tree_generic_kernel<uint8_t>, dim3((unsigned)blocks), dim3(kEncThreads), 0, s, X, ldx,
-                       split_dim, threshold, idx, N, C, levels, V);
+                       split_dim, threshold, idx.rows, idx.ld, N, C, levels, V);
     return hipGetLastError();
 }
 
@@ -378,7 +378,7 @@ hipError_t launch_encode_tree16(const int32_t* split_dim, const float* threshold
     const int64_t blocks = (total + kEncThreads - 1) / kEncThreads;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     hipLaunchKernelGGL(encode_tree_generic_kernel<uint16_t>, dim3((unsigned)blocks), dim3(kEncThreads), 0, s, X,
-                       ldx, split_dim, threshold, idx, N, C, levels, V);
+                       ldx, split_dim, threshold, idx, (int64_t)C, N, C, levels, V);
     return hipGetLastError();
 }
 

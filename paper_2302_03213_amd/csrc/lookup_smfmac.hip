@@ -47,7 +47,10 @@
 // stage stream - the last three stages of a tile already fetch the first three stages of the next
 // one, so there is no pipeline fill per tile.
 //
-// Needs C % 32 == 0 and a 16-byte aligned idx.
+// Index rows are 16-byte aligned and a multiple of 32 bytes apart.  Any C: the calls that lay out the index rows themselves
+// pad them, and the last super-stage reads rows of zeros past C.  Whole calls, before (the dense kernel, half the rate and
+// one super-stage of 8 codebooks ahead) and with this: 3001 rows x 75 codebooks, M = 1001 27.9 -> 14.8 us; 651 x 532, M = 971 46.7 ->
+// 23.5; 207 x 516, M = 3063 48.6 -> 24.6.
 #include <algorithm>
 #include <cstdlib>
 #include <type_traits>
@@ -62,6 +65,7 @@ typedef int v8i __attribute__((ext_vector_type(8)));
 
 constexpr int NBUF = 4;               // LDS ring depth, stages
 constexpr int SC = 16;                // codebooks per stage
+constexpr int kTail = 8;
 constexpr int KSTEPS = 4;             // MFMA steps per stage, 4 codebooks each
 
 // 64 lanes x 16 bytes global -> LDS at (lds_base + LDS_IMM) + 16 * lane; see dma16().  GOFF: a constant
@@ -78,6 +82,9 @@ __device__ __forceinline__ void dma16_at(uint32_t lds_base, const void* sbase, u
         : "memory", "m0", "scc");
 }
 
+// A table row of zeros, for the codebooks past C of the last super-stage.
+__device__ const uint4 kZeroRow[128] = {};
+
 // TM = 32-row blocks per wavefront, TN = 32-column tiles per wavefront (4, or 3): the workgroup tile
 // is 128*TM rows x 32*TN columns.  (4, 4) is the efficient shape; TM = 3, 2 and 1 exist so that
 // problems with few rows still spread over the chip, and TN = 3 (96 columns) for widths where it
@@ -87,14 +94,18 @@ __device__ __forceinline__ void dma16_at(uint32_t lds_base, const void* sbase, u
 // contracts C / splits consecutive codebooks and adds its int32 partial sums into Y with atomics; Y
 // then holds integers (zeroed beforehand, turned into the final floats by a separate pass).  For
 // problems with fewer tiles than compute units: more workgroups stream the table in parallel.
-template <int TM, int TN, bool SPLIT = false, bool STREAM = false>
+// TN_TAIL = TN, or 4 + kTail: C is no multiple of 32 (TAIL); the last super-stage's rows past C are rows of zeros, whatever
+// the index bytes there are.
+template <int TM, int TN_TAIL, bool SPLIT = false, bool STREAM = false>
 __global__ __launch_bounds__(kMfmaThreads, 1) void lookup_smfmac_i8_kernel(
     const uint4* __restrict__ packed, const float* __restrict__ scale, const float* __restrict__ bias,
-    int C, int M, int Mp, const uint8_t* __restrict__ idx, int64_t N, float* __restrict__ Y,
+    int C, int M, int Mp, const uint8_t* __restrict__ idx, int ldi, int64_t N, float* __restrict__ Y,
     int64_t ldy, int row_tiles, int64_t tiles, int splits, int row_group) {
+    constexpr int TN = TN_TAIL % kTail;
+    constexpr bool TAIL = TN_TAIL >= kTail;
     constexpr int WAVE_ROWS = TM * 32;
     constexpr int BM = 4 * WAVE_ROWS;  // rows per workgroup
-    static_assert(TN == 4 || (TN == 3 && TM == 4), "column tiles per wavefront");
+    static_assert(TN == 4 || (TN == 3 && TM == 4 && !TAIL), "column tiles per wavefront");
     constexpr int BN = 32 * TN;          // columns per workgroup
     constexpr int STAGE_VECS = SC * BN;  // uint4 per stage buffer (32 KiB at TN = 4)
     constexpr int B_LOADS = 2 * TN;      // table loads per wave per stage (1 KiB each)
@@ -125,10 +136,10 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void lookup_smfmac_i8_kernel(
     if (t >= xcd_end) return;
     bool has_next = t + wg_per_xcd < xcd_end;
 
-    // codebooks of this workgroup: all C, or share `t % splits` of them (C / splits % 32 == 0)
-    const int c_count = SPLIT ? C / splits : C;
-    const int c_begin = SPLIT ? (int)(t % splits) * c_count : 0;
-    const int supers = c_count / 32;  // C % 32 == 0
+    // super-stages of this workgroup: all of them, or share `t % splits`
+    const int supers_all = TAIL ? (C + 31) / 32 : C / 32;
+    const int supers = SPLIT ? supers_all / splits : supers_all;
+    const int c_begin = SPLIT ? (int)(t % splits) * supers * 32 : 0;
     const int stages = 2 * supers;
 
     // ---- the two streams.  Compute works on tile (ct_n0, ct_m0); the loads run three stages
@@ -142,6 +153,7 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void lookup_smfmac_i8_kernel(
     int64_t ct_m0, ft_m0;
     const char* bp;
     const uint8_t* ip;
+    int brow = 0;  // TAIL: the codebook that bp is at
     uint32_t fioff[TM];
     const uint32_t rs1 = (uint32_t)Mp * 16u;  // bytes from one codebook's row to the next
     const int row0 = 16 * (w >> 1) + 4 * (w & 1);
@@ -162,12 +174,13 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void lookup_smfmac_i8_kernel(
             ft_m0 = (tile % row_tiles) * BM;
         }
         bp = reinterpret_cast<const char*>(packed + ft_n0) + (size_t)(row0 + c_begin) * rs1;
-        ip = idx + ft_m0 * C + c_begin;
+        brow = row0 + c_begin;
+        ip = idx + ft_m0 * (TAIL ? ldi : C) + c_begin;
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             int64_t row = w * WAVE_ROWS + i * 32 + l32;
             if (ft_m0 + row >= N) row = N - 1 - ft_m0;
-            fioff[i] = (uint32_t)(row * C + 16 * h);
+            fioff[i] = (uint32_t)(row * (TAIL ? ldi : C) + 16 * h);
         }
     };
     aim_loads_at(t);
@@ -192,7 +205,10 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void lookup_smfmac_i8_kernel(
     const uint32_t lane16_mid = lane < 32 ? 1024u + lane * 16u : rs1 + (lane - 32) * 16u;
     auto load_b = [&](auto fb_c, auto q_c) {  // load q of the stage that goes to ring buffer FB
         constexpr int FB = decltype(fb_c)::value, Q = decltype(q_c)::value;
-        if constexpr (TN == 4) {
+        if constexpr (TAIL) {
+            const char* row = brow < C ? bp : reinterpret_cast<const char*>(kZeroRow);
+            dma16_at<(FB * STAGE_VECS + (Q >> 1) * BN + 64 * (Q & 1)) * 16>(ring_w, row, (Q & 1) ? lane16_hi : lane16);
+        } else if constexpr (TN == 4) {
             dma16_at<(FB * STAGE_VECS + (Q >> 1) * BN + 64 * (Q & 1)) * 16>(ring_w, bp, (Q & 1) ? lane16_hi : lane16);
         } else {
             constexpr int LDS = FB * STAGE_VECS * 16 + Q * 1024;
@@ -216,6 +232,11 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void lookup_smfmac_i8_kernel(
             bp += (sp_of_loaded_stage == 0) ? 5 * (size_t)rs1 : 21 * (size_t)rs1;
         else
             bp += (sp_of_loaded_stage == 0) ? 8 * (size_t)rs1 : 24 * (size_t)rs1;
+        if constexpr (TAIL) brow += sp_of_loaded_stage == 0 ? 5 : 21;
+    };
+    auto next_row = [&]() {
+        bp += rs1;
+        if constexpr (TAIL) ++brow;
     };
 
     v16i acc[TM][TN];
@@ -328,14 +349,14 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void lookup_smfmac_i8_kernel(
     auto load_stage = [&](auto fb_c) {
         load_b(fb_c, I0{});
         load_b(fb_c, I1{});
-        if constexpr (TN == 4) bp += rs1;
+        if constexpr (TN == 4) next_row();
         load_b(fb_c, std::integral_constant<int, 2>{});
         load_b(fb_c, std::integral_constant<int, 3>{});
-        if constexpr (TN == 4) bp += rs1;
+        if constexpr (TN == 4) next_row();
         load_b(fb_c, std::integral_constant<int, 4>{});
         load_b(fb_c, std::integral_constant<int, 5>{});
         if constexpr (TN == 4) {
-            bp += rs1;
+            next_row();
             load_b(fb_c, std::integral_constant<int, 6>{});
             load_b(fb_c, std::integral_constant<int, 7>{});
         }
@@ -465,7 +486,7 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void lookup_smfmac_i8_kernel(
                     }
                     if (q == S - 1) {
                         if (j + 1 < KSTEPS)
-                            bp += rs1;
+                            next_row();
                         else
                             next_stage_rows(SP ^ 1);  // stage s + 3 has the other parity
                     }
@@ -565,10 +586,16 @@ __global__ __launch_bounds__(256) void dequant_rows_kernel(float* __restrict__ Y
     *y = bias ? __fmaf_rn(a, *scale, bias[m]) : __fmul_rn(a, *scale);
 }
 
-template <int TM, int TN = 4>
-hipError_t launch_tm(const int8_t* packed, const float* scale, const float* bias, int C, int M,
-                     const uint8_t* idx, int64_t N, float* Y, int64_t ldy, hipStream_t s) {
-    constexpr int BM = 128 * TM, BN = 32 * TN;
+template <int TM, int TN_TAIL, bool SPLIT, bool STREAM, class... Args>
+void enqueue(int64_t blocks, hipStream_t s, Args... args) {
+    hipLaunchKernelGGL((lookup_smfmac_i8_kernel<TM, TN_TAIL, SPLIT, STREAM>), dim3((unsigned)blocks), dim3(kMfmaThreads), 0, s,
+                       args...);
+}
+
+template <int TM, int TN, bool TAIL>
+hipError_t launch_tail(const int8_t* packed, const float* scale, const float* bias, int C, int M, const uint8_t* idx,
+                       int64_t ldi, int64_t N, float* Y, int64_t ldy, hipStream_t s) {
+    constexpr int BM = 128 * TM, BN = 32 * TN, kAdd = TAIL ? kTail : 0;
     const int Mp = (int)packed_cols(M);
     const int64_t col_tiles = (M + BN - 1) / BN;  // the packed table is padded to 256 columns
     if (col_tiles * BN > Mp) return hipErrorInvalidValue;  // 96-column tiles past the padding
@@ -589,7 +616,7 @@ hipError_t launch_tm(const int8_t* packed, const float* scale, const float* bias
     // decision (sweeps, and tests that must reach both paths).
     const int kComputeUnits = compute_units();
     if (TN == 4 && tiles <= kComputeUnits / 2 && C >= 512) {
-        const int supers = C / 32;
+        const int supers = (C + 31) / 32;
         int splits = 1;
         for (int cand = (int)std::min<int64_t>(16, kComputeUnits / tiles); cand > 1; --cand)
             if (supers % cand == 0 && supers / cand >= 2) {
@@ -605,9 +632,8 @@ hipError_t launch_tm(const int8_t* packed, const float* scale, const float* bias
             const dim3 cells((unsigned)((M + 255) / 256), (unsigned)N);
             hipLaunchKernelGGL(zero_rows_kernel, cells, dim3(256), 0, s, Y, M, ldy);
             const int64_t units = tiles * splits;
-            hipLaunchKernelGGL((lookup_smfmac_i8_kernel<TM, 4, true>), dim3((unsigned)((units + 7) / 8 * 8)),
-                               dim3(kMfmaThreads), 0, s, reinterpret_cast<const uint4*>(packed), scale, bias, C, M,
-                               Mp, idx, N, Y, ldy, (int)row_tiles, units, splits, 0);
+            enqueue<TM, 4 + kAdd, true, false>((units + 7) / 8 * 8, s, reinterpret_cast<const uint4*>(packed), scale, bias, C,
+                                              M, Mp, idx, (int)ldi, N, Y, ldy, (int)row_tiles, units, splits, 0);
             hipLaunchKernelGGL(dequant_rows_kernel, cells, dim3(256), 0, s, Y, M, ldy, scale, bias);
             return hipGetLastError();
         }
@@ -623,18 +649,23 @@ hipError_t launch_tm(const int8_t* packed, const float* scale, const float* bias
     if (const int pinned = tunable(kTuneSmfmacRowGroup); pinned >= 0) row_group = pinned;
     // Stream several tiles per workgroup when the ring phase carries over from tile to tile:
     // one workgroup per compute unit (the kernel's LDS footprint allows only one anyway).
-    if (C % 64 == 0 && blocks > kComputeUnits) blocks = kComputeUnits;
+    if ((C + 31) / 32 % 2 == 0 && blocks > kComputeUnits) blocks = kComputeUnits;
     // an output of 128 MiB or more cannot stay in any cache: stream it (512-row tiles only, the
     // height such problems take)
     if (TM == 4 && TN == 4 && (double)N * M * 4 >= 134217728.0)
-        hipLaunchKernelGGL((lookup_smfmac_i8_kernel<TM, 4, false, TM == 4>), dim3((unsigned)blocks),
-                           dim3(kMfmaThreads), 0, s, reinterpret_cast<const uint4*>(packed), scale, bias, C, M, Mp,
-                           idx, N, Y, ldy, (int)row_tiles, tiles, 1, row_group);
+        enqueue<TM, 4 + kAdd, false, TM == 4>(blocks, s, reinterpret_cast<const uint4*>(packed), scale, bias, C, M, Mp, idx,
+                                             (int)ldi, N, Y, ldy, (int)row_tiles, tiles, 1, row_group);
     else
-        hipLaunchKernelGGL((lookup_smfmac_i8_kernel<TM, TN, false>), dim3((unsigned)blocks), dim3(kMfmaThreads), 0, s,
-                           reinterpret_cast<const uint4*>(packed), scale, bias, C, M, Mp, idx, N, Y, ldy,
-                           (int)row_tiles, tiles, 1, row_group);
+        enqueue<TM, TN + kAdd, false, false>(blocks, s, reinterpret_cast<const uint4*>(packed), scale, bias, C, M, Mp, idx,
+                                            (int)ldi, N, Y, ldy, (int)row_tiles, tiles, 1, row_group);
     return hipGetLastError();
+}
+
+template <int TM, int TN = 4>
+hipError_t launch_tm(const int8_t* packed, const float* scale, const float* bias, int C, int M, const uint8_t* idx,
+                     int64_t ldi, int64_t N, float* Y, int64_t ldy, hipStream_t s) {
+    if (C % 32 == 0) return launch_tail<TM, TN, false>(packed, scale, bias, C, M, idx, ldi, N, Y, ldy, s);
+    return launch_tail<TM, 4, true>(packed, scale, bias, C, M, idx, ldi, N, Y, ldy, s);
 }
 
 }  // namespace
@@ -644,9 +675,9 @@ bool smfmac_supported(int C, int K, const uint8_t* idx) {
 }
 
 hipError_t launch_lookup_smfmac_i8(const int8_t* packed, const float* scale, const float* bias, int C,
-                                   int K, int M, const uint8_t* idx, int64_t N, float* Y, int64_t ldy,
+                                   int K, int M, const uint8_t* idx, int64_t ldi, int64_t N, float* Y, int64_t ldy,
                                    hipStream_t s) {
-    if (!smfmac_supported(C, K, idx)) return hipErrorInvalidValue;
+    if (K > 16 || ldi % 32 != 0 || ldi < C || ldi > (1 << 22) || (reinterpret_cast<uintptr_t>(idx) & 15) != 0) return hipErrorInvalidValue;
     // Tile height.  512 rows amortise the table slab best, but the tiles have to cover the chip:
     // price each height as (rounds of 256 workgroups) x (measured time of one tile relative to
     // the 512-row tile: 0.8 for 384 rows, 0.56 for 256, 0.42 for 128 - the slab traffic does not
@@ -663,27 +694,32 @@ hipError_t launch_lookup_smfmac_i8(const int8_t* packed, const float* scale, con
     // ahead; at 16384 rows, where it needs a fourth round, 4 % behind - which the price reproduces).
     // LUTNN_SMFMAC_TILE_COLS = 96 | 128 pins the width of 512-row tiles.
     constexpr double kNarrowRel = 0.75;
-    const bool narrow_fits = (int64_t)(M + 95) / 96 * 96 <= (int64_t)packed_cols(M);
+    const bool narrow_fits = C % 32 == 0 && (int64_t)(M + 95) / 96 * 96 <= (int64_t)packed_cols(M);
     const int pinned_cols = tunable(kTuneSmfmacTileCols);
     // LUTNN_SMFMAC_TILE_ROWS = 128 | 256 | 384 | 512 pins the height (tuning sweeps, and tests that
     // must reach every instance whatever the prices below say); anything else is ignored.
     switch (tunable(kTuneSmfmacTileRows)) {
         case 512:
-            if (pinned_cols == 96 && narrow_fits) return launch_tm<4, 3>(packed, scale, bias, C, M, idx, N, Y, ldy, s);
-            return launch_tm<4>(packed, scale, bias, C, M, idx, N, Y, ldy, s);
-        case 384: return launch_tm<3>(packed, scale, bias, C, M, idx, N, Y, ldy, s);
-        case 256: return launch_tm<2>(packed, scale, bias, C, M, idx, N, Y, ldy, s);
-        case 128: return launch_tm<1>(packed, scale, bias, C, M, idx, N, Y, ldy, s);
+            if (pinned_cols == 96 && narrow_fits) return launch_tm<4, 3>(packed, scale, bias, C, M, idx, ldi, N, Y, ldy, s);
+            return launch_tm<4>(packed, scale, bias, C, M, idx, ldi, N, Y, ldy, s);
+        case 384: return launch_tm<3>(packed, scale, bias, C, M, idx, ldi, N, Y, ldy, s);
+        case 256: return launch_tm<2>(packed, scale, bias, C, M, idx, ldi, N, Y, ldy, s);
+        case 128: return launch_tm<1>(packed, scale, bias, C, M, idx, ldi, N, Y, ldy, s);
         default: break;
     }
-    const double c4 = cost(512, 1.0), c3 = cost(384, 0.8), c2 = cost(256, 0.56), c1 = cost(128, 0.42);
+    // With one or two super-stages a tile is mostly its own write, which lower tiles spread better: 4096 rows, M = 3072, 48
+    // codebooks 19.8 us with 512 rows and 16.7 with 128; 24 codebooks, M = 2304 14.3 and 13.5 with 384; 16384 rows, 20
+    // codebooks, M = 4096 79 and 63.  (The dense kernel, which such numbers of codebooks took: 23, 14.9 and 63.)
+    const bool one = C < 32, two = C > 32 && C < 64;
+    const double c4 = cost(512, 1.0), c3 = cost(384, one ? 0.62 : 0.8), c2 = cost(256, two ? 0.42 : 0.56),
+                 c1 = cost(128, two ? 0.27 : 0.42);
     const double best = std::min(std::min(c4, c3), std::min(c2, c1));
     if (narrow_fits && pinned_cols != 128 && (cost(512, kNarrowRel, 96) < best || (pinned_cols == 96 && c4 == best)))
-        return launch_tm<4, 3>(packed, scale, bias, C, M, idx, N, Y, ldy, s);
-    if (c4 == best) return launch_tm<4>(packed, scale, bias, C, M, idx, N, Y, ldy, s);
-    if (c3 == best) return launch_tm<3>(packed, scale, bias, C, M, idx, N, Y, ldy, s);
-    if (c2 == best) return launch_tm<2>(packed, scale, bias, C, M, idx, N, Y, ldy, s);
-    return launch_tm<1>(packed, scale, bias, C, M, idx, N, Y, ldy, s);
+        return launch_tm<4, 3>(packed, scale, bias, C, M, idx, ldi, N, Y, ldy, s);
+    if (c4 == best) return launch_tm<4>(packed, scale, bias, C, M, idx, ldi, N, Y, ldy, s);
+    if (c3 == best) return launch_tm<3>(packed, scale, bias, C, M, idx, ldi, N, Y, ldy, s);
+    if (c2 == best) return launch_tm<2>(packed, scale, bias, C, M, idx, ldi, N, Y, ldy, s);
+    return launch_tm<1>(packed, scale, bias, C, M, idx, ldi, N, Y, ldy, s);
 }
 
 }  // namespace lutnn

@@ -36,10 +36,21 @@ struct ConvGeom {
     int Cin, H, W, kh, kw, sh, sw, ph, pw, Ho, Wo;
 };
 
+// Where an encoder puts its indices: row n at rows + n * ld.  ld is C in the dense layout of the C ABI; the rows that the
+// sparse lookup reads for itself are padded to 32 bytes, their bytes past C unspecified.
+struct IndexRows {
+    uint8_t* rows;
+    int64_t ld;
+    // indices of four codebooks leave as one dword
+    bool dwords(int C) const {
+        return ld % 4 == 0 && ld >= ((C + 3) & ~3) && (reinterpret_cast<uintptr_t>(rows) & 3) == 0;
+    }
+};
+
 // Eq. 2 on the rows of that matrix, read from the NCHW input without materialising it.
 bool encode_conv_supported(int V);
 hipError_t launch_encode_conv(const float* P, int C, int K, int V, const float* input, int64_t B,
-                              const ConvGeom& g, uint8_t* idx, hipStream_t s);
+                              const ConvGeom& g, IndexRows idx, hipStream_t s);
 
 // A 3x3 convolution with V = 9, the matrix cores as a filter (encode_conv9.hip), over `chunks` chunks of pixel tiles:
 // encode_conv9_filter_chunks gives their number, 0 where the direct search is to be taken.  conv_band_floats: the
@@ -47,15 +58,15 @@ hipError_t launch_encode_conv(const float* P, int C, int K, int V, const float* 
 int64_t conv_band_floats(const ConvGeom& g);
 int64_t encode_conv9_filter_chunks(int C, int K, int64_t B, const ConvGeom& g);
 hipError_t launch_encode_conv9_filter(const float* P, int C, int K, const float* input, int64_t B, const ConvGeom& g,
-                                      uint8_t* idx, int64_t chunks, hipStream_t s);
+                                      IndexRows idx, int64_t chunks, hipStream_t s);
 
 // Eq. 2.
 hipError_t launch_encode(const float* P, int C, int K, int V, const float* X, int64_t N, int64_t ldx,
-                         uint8_t* idx, hipStream_t s);
+                         IndexRows idx, hipStream_t s);
 
 // Hash encoding (Sec. 2, Sec. 7): per codebook a heap-ordered threshold tree with `levels` levels.
 hipError_t launch_encode_tree(const int32_t* split_dim, const float* threshold, int C, int levels,
-                              int V, const float* X, int64_t N, int64_t ldx, uint8_t* idx,
+                              int V, const float* X, int64_t N, int64_t ldx, IndexRows idx,
                               hipStream_t s);
 
 // The same with 16-bit leaves, for trees of up to 12 levels (Sec. 7), and Eq. 4 on 16-bit indices
@@ -106,7 +117,7 @@ size_t softpq_matrix_workspace_bytes(int C, int K, int V, int64_t N);
 hipError_t launch_softpq_matrix(const SoftPqCall& a, hipStream_t s);
 
 hipError_t launch_encode_tree_conv(const int32_t* split_dim, const float* threshold, int C, int levels,
-                                   int V, const float* input, int64_t B, const ConvGeom& g, uint8_t* idx,
+                                   int V, const float* input, int64_t B, const ConvGeom& g, IndexRows idx,
                                    hipStream_t s);
 
 // Eq. 3 + Sec. 3.3.
@@ -145,10 +156,12 @@ hipError_t launch_lookup_mfma_i8(const int8_t* packed, const float* scale, const
                                  int K, int M, const uint8_t* idx, int64_t N, float* Y, int64_t ldy,
                                  hipStream_t s);
 
-// Eq. 4, one-hot contraction on the 2:4 structured-sparse matrix instructions (INT8).
-bool smfmac_supported(int C, int K, const uint8_t* idx);
+// Eq. 4, one-hot contraction on the 2:4 structured-sparse matrix instructions (INT8).  The index rows are 16-byte aligned,
+// their stride ldi a multiple of 32 and at least C.
+bool smfmac_supported(int C, int K, const uint8_t* idx);  // with a dense index matrix
+inline int64_t smfmac_index_stride(int C) { return ((int64_t)C + 31) / 32 * 32; }
 hipError_t launch_lookup_smfmac_i8(const int8_t* packed, const float* scale, const float* bias, int C,
-                                   int K, int M, const uint8_t* idx, int64_t N, float* Y, int64_t ldy,
+                                   int K, int M, const uint8_t* idx, int64_t ldi, int64_t N, float* Y, int64_t ldy,
                                    hipStream_t s);
 
 // Eq. 2 + Eq. 4 in one kernel.
