@@ -18,7 +18,7 @@ INCLUDE = os.path.join(ROOT, "include")
 OBJDIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "liblutnn.so")
 
-SOURCES = ["api.hip", "encode.hip", "encode_conv9.hip", "encode_tree.hip", "build_table.hip", "lookup_lds.hip", "lookup_rows.hip", "lookup_mfma.hip", "lookup_smfmac.hip", "lookup_wide.hip",
+SOURCES = ["api.hip", "encode.hip", "encode_conv9.hip", "encode_tree.hip", "build_table.hip", "lookup_lds.hip", "lookup_rows.hip", "lookup_mfma.hip", "lookup_smfmac.hip", "lookup_wide.hip", "lookup_matrix_f32.hip",
            "linear_fused.hip", "linear_small.hip", "softpq_backward.hip", "softpq_matrix.hip", "softpq_conv.hip", "matmul_split.hip", "probe_smfmac.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

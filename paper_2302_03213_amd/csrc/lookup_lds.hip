@@ -166,87 +166,6 @@ __global__ __launch_bounds__(kThreads) void lookup_lds_i8_kernel(
     }
 }
 
-// ------------------------------------------------------------------------------------------ FP32
-constexpr int kColsF32 = 128;  // MT: 64 lanes x 2 columns
-constexpr int kRowsPerWaveF32 = 8;
-
-template <bool IDX_DWORD>
-__global__ __launch_bounds__(kThreads) void lookup_lds_f32_kernel(
-    const float* __restrict__ T, const float* __restrict__ bias, int C, int K, int M,
-    const uint8_t* __restrict__ idx, int64_t N, float* __restrict__ Y, int64_t ldy, int CC,
-    int col_tiles) {
-    extern __shared__ uint32_t lds[];
-    float2* tab = reinterpret_cast<float2*>(lds);  // [CC][K][64] float2
-    constexpr int RW = kRowsPerWaveF32;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t row_tile = blockIdx.x / col_tiles;
-    const int n0 = (int)(blockIdx.x % col_tiles) * kColsF32;
-    const int64_t row0 = row_tile * (RW * kWaves) + (int64_t)w * RW;
-
-    float2 acc[RW];
-#pragma unroll
-    for (int r = 0; r < RW; ++r) acc[r] = make_float2(0.f, 0.f);
-
-    for (int c0 = 0; c0 < C; c0 += CC) {
-        __syncthreads();
-        const int elems = CC * K * 64;  // float2 elements
-        for (int i = tid; i < elems; i += kThreads) {
-            const int rowid = i >> 6, j = i & 63;
-            const int cl = rowid / K, k = rowid - cl * K;
-            const int c = c0 + cl;
-            const int m = n0 + 2 * j;
-            float2 v = make_float2(0.f, 0.f);
-            if (c < C) {
-                const float* src = T + ((size_t)c * K + k) * M + m;
-                if (m < M) v.x = src[0];
-                if (m + 1 < M) v.y = src[1];
-            }
-            tab[i] = v;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < RW; ++r) {
-            const int64_t row = row0 + r;
-            if (row < N) {
-                for (int cl4 = 0; cl4 < CC; cl4 += 4) {
-                    uint32_t word;
-                    if (IDX_DWORD) {
-                        word = (c0 + cl4 < C)
-                                   ? *reinterpret_cast<const uint32_t*>(idx + row * C + c0 + cl4)
-                                   : 0u;
-                    } else {
-                        word = 0;
-                        for (int b = 0; b < 4; ++b)
-                            if (c0 + cl4 + b < C)
-                                word |= (uint32_t)idx[row * C + c0 + cl4 + b] << (8 * b);
-                    }
-                    word = __builtin_amdgcn_readfirstlane(word);
-#pragma unroll
-                    for (int b = 0; b < 4; ++b) {
-                        int k = (word >> (8 * b)) & 0xff;
-                        k = k < K ? k : K - 1;
-                        const float2 x = tab[((cl4 + b) * K + k) * 64 + lane];
-                        acc[r].x += x.x;  // codebooks past C were staged as zeros
-                        acc[r].y += x.y;
-                    }
-                }
-            }
-        }
-    }
-
-    const int col = n0 + lane * 2;
-#pragma unroll
-    for (int r = 0; r < RW; ++r) {
-        const int64_t row = row0 + r;
-        if (row >= N) continue;
-        float* y = Y + row * ldy + col;
-        if (col < M) y[0] = bias ? acc[r].x + bias[col] : acc[r].x;
-        if (col + 1 < M) y[1] = bias ? acc[r].y + bias[col + 1] : acc[r].y;
-    }
-}
-
 // The staged kernels need at least this many workgroups to be worth their staging.
 constexpr int64_t kMinStagedBlocks = 512;
 
@@ -256,60 +175,44 @@ inline bool idx_dword_ok(const uint8_t* idx, int C) {
     return (C % 4 == 0) && ((reinterpret_cast<uintptr_t>(idx) & 3) == 0);
 }
 
-// The staged kernels' tile: columns, rows, LDS bytes of a staged column (4-bit entries are widened to bytes).
-template <class Table>
-struct Staged {
-    static constexpr bool kF32 = std::is_same<Table, TableF32>::value;
-    static constexpr int kTileCols = kF32 ? kColsF32 : kColsI8, kColBytes = kF32 ? 4 : 1;
-    static constexpr int kTileRows = (kF32 ? kRowsPerWaveF32 : kRowsPerWaveI8) * kWaves;
-    static int64_t blocks(int64_t N, int M) {
-        return ((N + kTileRows - 1) / kTileRows) * ((M + kTileCols - 1) / kTileCols);
-    }
-};
+inline int64_t staged_blocks(int64_t N, int M) {
+    return ((N + kRowsPerWaveI8 * kWaves - 1) / (kRowsPerWaveI8 * kWaves)) * ((M + kColsI8 - 1) / kColsI8);
+}
 
 // Table rows read straight from global memory: where the staged grid would be small, and where four codebooks' slabs do
-// not fit its LDS (K > 64; one thread per output, the other choice there, reads a byte where this reads a dword).
+// not fit its LDS (K > 64; one thread per output, the other choice there, reads a byte where this reads a dword).  fp32
+// tables always: staged, 32 rows to a slab, they were two to four times slower.
 template <class Table>
 bool gather_ok(int64_t N, int K, int M) {
-    using S = Staged<Table>;
-    return gather_supported<Table>(M) &&
-           (S::blocks(N, M) < kMinStagedBlocks || (int64_t)4 * K * S::kTileCols * S::kColBytes > kLdsBudget);
+    return gather_supported<Table>(M) && (std::is_same<Table, TableF32>::value || staged_blocks(N, M) < kMinStagedBlocks ||
+                                          (int64_t)4 * K * kColsI8 > kLdsBudget);
 }
 
 template <class Table>
 hipError_t launch_lookup_lds(const typename Table::Entry* T, const float* scale, const float* bias, int C, int K, int M,
                              const uint8_t* idx, int64_t N, float* Y, int64_t ldy, hipStream_t s) {
-    using S = Staged<Table>;
     if (gather_ok<Table>(N, K, M)) return launch_gather<Table, uint8_t>(T, scale, bias, C, K, M, idx, N, Y, ldy, s);
-    const int64_t per_codebook = (int64_t)K * S::kTileCols * S::kColBytes;  // LDS bytes per staged codebook
-    if (4 * per_codebook > kLdsBudget) return launch_global<Table, uint8_t>(T, scale, bias, C, K, M, idx, N, Y, ldy, s);
+    // LDS bytes per staged codebook (4-bit entries are widened to bytes)
+    const int64_t per_codebook = (int64_t)K * kColsI8;
+    if (std::is_same<Table, TableF32>::value || 4 * per_codebook > kLdsBudget)
+        return launch_global<Table, uint8_t>(T, scale, bias, C, K, M, idx, N, Y, ldy, s);
     int CC = (int)(kLdsBudget / 2 / per_codebook) & ~3;  // aim for 32 KiB so two workgroups share a CU
     if (CC < 4) CC = 4;
     if (CC > 16) CC = 16;
-    const int col_tiles = (M + S::kTileCols - 1) / S::kTileCols;
-    const int64_t blocks = S::blocks(N, M);
+    const int col_tiles = (M + kColsI8 - 1) / kColsI8;
+    const int64_t blocks = staged_blocks(N, M);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const size_t shmem = (size_t)(CC * per_codebook);
+    constexpr int BITS = std::is_same<Table, TableI4>::value ? 4 : 8;
+    const int vec16 = BITS == 8 && (M % 16 == 0) && ((reinterpret_cast<uintptr_t>(T) & 15) == 0);
+    const int8_t* Tb = reinterpret_cast<const int8_t*>(T);
     const dim3 grid((unsigned)blocks), block(kThreads);
-    const bool dw = idx_dword_ok(idx, C);
-    if constexpr (S::kF32) {
-        if (dw)
-            hipLaunchKernelGGL((lookup_lds_f32_kernel<true>), grid, block, shmem, s, T, bias, C, K, M, idx, N, Y, ldy, CC,
-                               col_tiles);
-        else
-            hipLaunchKernelGGL((lookup_lds_f32_kernel<false>), grid, block, shmem, s, T, bias, C, K, M, idx, N, Y, ldy, CC,
-                               col_tiles);
-    } else {
-        constexpr int BITS = std::is_same<Table, TableI4>::value ? 4 : 8;
-        const int vec16 = BITS == 8 && (M % 16 == 0) && ((reinterpret_cast<uintptr_t>(T) & 15) == 0);
-        const int8_t* Tb = reinterpret_cast<const int8_t*>(T);
-        if (dw)
-            hipLaunchKernelGGL((lookup_lds_i8_kernel<true, BITS>), grid, block, shmem, s, Tb, scale, bias, C, K, M, idx, N,
-                               Y, ldy, CC, col_tiles, vec16);
-        else
-            hipLaunchKernelGGL((lookup_lds_i8_kernel<false, BITS>), grid, block, shmem, s, Tb, scale, bias, C, K, M, idx, N,
-                               Y, ldy, CC, col_tiles, vec16);
-    }
+    if (idx_dword_ok(idx, C))
+        hipLaunchKernelGGL((lookup_lds_i8_kernel<true, BITS>), grid, block, shmem, s, Tb, scale, bias, C, K, M, idx, N, Y, ldy,
+                           CC, col_tiles, vec16);
+    else
+        hipLaunchKernelGGL((lookup_lds_i8_kernel<false, BITS>), grid, block, shmem, s, Tb, scale, bias, C, K, M, idx, N, Y, ldy,
+                           CC, col_tiles, vec16);
     return hipGetLastError();
 }
 
@@ -365,7 +268,13 @@ hipError_t launch_lookup_lds_i4(const uint8_t* T, const float* scale, const floa
 
 hipError_t launch_lookup_lds_f32(const float* T, const float* bias, int C, int K, int M,
                                  const uint8_t* idx, int64_t N, float* Y, int64_t ldy, hipStream_t s) {
-    if (rows_kernel_preferred(N, M, K, true)) return launch_lookup_rows_f32(T, bias, C, K, M, idx, N, Y, ldy, s);
+    // us of the three forms, fitted to sweeps of 100-14000 rows, 16-700 codebooks and 150-3072 columns
+    const double entries = (double)N * C * M;
+    const double matrix = lookup_matrix_f32_us(C, K, M, N);
+    const double rows = rows_kernel_preferred(N, M, K, true) ? 10.0 + 7e-8 * entries + 1.5e-6 * (double)N * M : 1e30;
+    const double gather = 4.0 + 3e-7 * entries;
+    if (matrix < rows && matrix < gather) return launch_lookup_matrix_f32(T, bias, C, K, M, idx, N, Y, ldy, s);
+    if (rows < 1e30) return launch_lookup_rows_f32(T, bias, C, K, M, idx, N, Y, ldy, s);
     return launch_lookup_lds<TableF32>(T, nullptr, bias, C, K, M, idx, N, Y, ldy, s);
 }
 

@@ -1,0 +1,86 @@
+"""GPU parity of the unquantised lookup on the matrix cores (arXiv 2302.03213, Eq. 4) at the edges of its tiles and stages,
+and with table entries whose parts need care.  Exact 64-bit sums: the error of C terms stays within C half ulps of the sum
+of their magnitudes, as an fp32 chain's does."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import dev, host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lut():
+    import paper_2302_03213_amd as lut_mod
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return lut_mod
+
+
+def run(lut, T, idx, bias, offset=0):
+    C, K, M = T.shape
+    flat = torch.empty(T.size + offset, device="cuda")
+    flat[offset:] = torch.from_numpy(T.reshape(-1))
+    layer = lut.LutLayer(torch.zeros((C, K, 4), device="cuda"), flat[offset:].view(T.shape), lut.TABLE_F32, M, bias=dev(bias))
+    N = idx.shape[0]
+    i8 = torch.empty(idx.size + offset, dtype=torch.uint8, device="cuda")
+    i8[offset:] = torch.from_numpy(idx.reshape(-1))
+    out = torch.full((N, M + 3), -3.5, device="cuda")
+    lut.lookup(layer, i8[offset:].view(idx.shape), "lds", out=out[:, :M])
+    assert (host(out[:, M:]) == -3.5).all()
+    return host(out[:, :M])
+
+
+def sums(T, idx, bias):
+    """The 64-bit sums, their terms' magnitudes, and the fp32 chain."""
+    total = np.zeros((idx.shape[0], T.shape[2]))
+    size = np.zeros_like(total)
+    chain = np.zeros(total.shape, np.float32)
+    with np.errstate(over="ignore", invalid="ignore"):
+        for c in range(T.shape[0]):
+            term = T[c, np.minimum(idx[:, c], T.shape[1] - 1)]
+            total += term
+            size += np.abs(term.astype(np.float64))
+            chain += term
+        return (total, size, chain) if bias is None else (total + bias, size + np.abs(bias), chain + bias)
+
+
+# stages of four codebooks with one, two and three left, rows past a tile, widths that end in one; enough rows that the
+# kernel is the one taken
+SHAPES = [(20011, 7, 16, 401), (21000, 9, 8, 513), (20000, 10, 16, 640), (15000, 64, 16, 129), (9000, 130, 7, 190), (6500, 513, 16, 255),
+          (8193, 32, 16, 321)]
+
+
+@pytest.mark.parametrize("N,C,K,M", SHAPES)
+def test_edges(lut, N, C, K, M):
+    rng = np.random.default_rng(N + C)
+    T = rng.standard_normal((C, K, M)).astype(np.float32)
+    bias = rng.standard_normal(M).astype(np.float32) if C != 64 else None
+    idx = rng.integers(0, K + (C == 9), (N, C)).astype(np.uint8)  # with one past the table, which is its last row
+    total, size, chain = sums(T, idx, bias)
+    got = run(lut, T, idx, bias, offset=C % 2)
+    assert (np.abs(got - total) <= (C + 1) * 2.0 ** -24 * size).all()
+    if C >= 32:  # no less exact than the chain
+        assert np.linalg.norm(got - total) <= 1.02 * np.linalg.norm(chain - total)
+
+
+@pytest.mark.parametrize("scale", [1e-38, 1e-30, 1e28])
+def test_small_and_large_entries(lut, scale):
+    rng = np.random.default_rng(1)
+    T = (rng.standard_normal((33, 16, 200)) * scale).astype(np.float32)
+    idx = rng.integers(0, 16, (10000, 33)).astype(np.uint8)
+    total, size, _ = sums(T, idx, None)
+    assert (np.abs(run(lut, T, idx, None) - total) <= 34 * (2.0 ** -24 * size + 2.0 ** -149)).all()
+
+
+def test_entries_that_are_not_finite_and_overflow(lut):
+    rng = np.random.default_rng(2)
+    T = rng.standard_normal((40, 16, 200)).astype(np.float32)
+    T[3, 5, 7], T[4, 2, 70], T[11, 15, 199], T[12, 0, 100], T[13, 0, 100] = np.inf, -np.inf, np.nan, 3e38, 3e38
+    idx = rng.integers(0, 16, (10000, 40)).astype(np.uint8)
+    bias = rng.standard_normal(200).astype(np.float32)
+    total, size, chain = sums(T, idx, bias)
+    got = run(lut, T, idx, bias)
+    fine = np.isfinite(chain)
+    np.testing.assert_array_equal(got[~fine], chain[~fine])
+    assert (np.abs(got - total)[fine] <= 41 * 2.0 ** -24 * size[fine]).all()
