@@ -1,6 +1,6 @@
 """Thin ctypes binding of liblutnn.so (C ABI in include/lutnn.h).
 
-Argument marshalling only: every step of the operator runs in the HIP kernels.  PyTorch is used
+Argument marshalling only (the calls made per step have it in C++, csrc/torch_calls.cpp): every step of the operator runs in the HIP kernels.  PyTorch is used
 for device memory and streams.  There is no CPU fallback: if the shared library cannot be loaded
 the import of this module fails.
 
@@ -8,6 +8,8 @@ Names and notation follow arXiv 2302.03213: N rows, D = C*V inputs, K centroids 
 M outputs; codebooks P[C][K][V], weights W[D][M] (Table 1), table T[C][K][M] (Eq. 3).
 """
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
@@ -72,8 +74,8 @@ def _is_current(path):
 
 def _load():
     path = _build.LIB
-    if not os.path.exists(path) or not _is_current(path):
-        _build.build()  # raises if hipcc is missing or the compile fails
+    if not all(os.path.exists(p) and _is_current(p) for p in (path, _build.TORCH_CALLS)):
+        _build.build()  # raises if a compiler is missing or the compile fails
     lib = ctypes.CDLL(path)
     missing = [name for name in EXPORTS if not hasattr(lib, name)]
     if missing:
@@ -161,13 +163,28 @@ def _load():
     return lib
 
 
+def _load_torch_calls():
+    loader = importlib.machinery.ExtensionFileLoader("torch_calls", _build.TORCH_CALLS)
+    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("torch_calls", loader))
+    loader.exec_module(module)
+    return module
+
+
 LIB = _load()
+_calls = _load_torch_calls()
 
 
 def _check(status):
     if status != 0:
         raise LutnnError(status, LIB.lutnn_status_string(status).decode(),
                          LIB.lutnn_last_error().decode())
+
+
+def _result(got):
+    """What a native call gave: its outputs, or a status."""
+    if got.__class__ is int:
+        _check(got)
+    return got
 
 
 def _stream():
@@ -236,6 +253,7 @@ class LutLayer:
         self.c = _CLayer(self.C, self.K, self.V, self.M, self.table_dtype, 0, _ptr(centroids),
                          _ptr(table), _ptr(packed), _ptr(scale), _ptr(bias))
         self.ref = ctypes.byref(self.c)
+        self.address = ctypes.addressof(self.c)
 
     @property
     def D(self):
@@ -244,6 +262,11 @@ class LutLayer:
 
 def build_table(centroids, W, table_dtype, bias=None, packed=True):
     """lutnn_build_table: Eq. 3 (+ Sec. 3.3 for INT8 / INT4).  centroids [C,K,V], W [D,M] on the GPU."""
+    if packed:
+        got = _calls.build_table(centroids, W, table_dtype)
+        if got is not None:
+            table, pk, scale = _result(got)
+            return LutLayer(centroids, table, table_dtype, W.shape[1], pk, scale, bias)
     assert centroids.is_cuda and W.is_cuda and centroids.dtype == torch.float32
     assert centroids.is_contiguous() and W.dtype == torch.float32 and W.stride(1) == 1
     C, K, V = centroids.shape
@@ -308,6 +331,7 @@ class LutTree:
         self.threshold = threshold.contiguous()
         self.c = _CTree(self.C, self.V, levels, 0, self.split_dim.data_ptr(), self.threshold.data_ptr())
         self.ref = ctypes.byref(self.c)
+        self.address = ctypes.addressof(self.c)
 
 
 def encode_tree(tree, X, out=None):
@@ -323,6 +347,10 @@ def encode_tree(tree, X, out=None):
 
 def linear_tree(layer, tree, X, variant="auto", out=None, idx_workspace=None):
     """lutnn_linear_tree: hash encoding, then the table lookup of Eq. 4."""
+    if out is None and idx_workspace is None and variant in ("auto", VARIANT_AUTO):
+        got = _calls.linear(layer.address, tree.address, X)
+        if got is not None:
+            return _result(got)
     assert X.is_cuda and X.dtype == torch.float32 and X.stride(1) == 1
     N = X.shape[0]
     if out is None:
@@ -369,6 +397,10 @@ def lookup16(layer, idx, out=None):
 
 def linear_tree16(layer, tree, X, out=None, idx_workspace=None):
     """lutnn_linear_tree16: deep-tree hash encoding, then the 16-bit index lookup."""
+    if out is None and idx_workspace is None:
+        got = _calls.linear_tree16(layer.address, tree.address, X)
+        if got is not None:
+            return _result(got)
     assert X.is_cuda and X.dtype == torch.float32 and X.stride(1) == 1
     N = X.shape[0]
     if out is None:
@@ -402,6 +434,30 @@ def linear_gradient_preferred(G, W):
     (lutnn_linear_gradient_preferred)."""
     return bool(LIB.lutnn_linear_gradient_preferred(_ptr(G), G.shape[0], G.stride(0), _ptr(W), W.stride(0), W.shape[0],
                                                     W.shape[1]))
+
+
+def _softpq_gradients(centroids, M, temperature, X, Z, need_dx):
+    """softpq_backward from the centroids alone."""
+    got = _calls.softpq_backward(centroids, M, temperature, X, Z, need_dx)
+    if got is not None:
+        return _result(got)
+    return softpq_backward(LutLayer(centroids.detach().contiguous(), None, TABLE_F32, M), temperature, X.detach(), Z, need_dx)
+
+
+def _softpq_gradients_conv2d(centroids, temperature, inp, W, G, kernel, stride, pad, need_dx):
+    got = _calls.softpq_backward_conv2d(centroids, temperature, inp, W, G, need_dx, kernel, stride, pad)
+    if got is not None:
+        return _result(got)
+    layer = LutLayer(centroids.detach().contiguous(), None, TABLE_F32, W.shape[1])
+    return softpq_backward_conv2d(layer, temperature, inp.detach().contiguous(), W, G, kernel, stride, pad, need_dx)
+
+
+def _input_gradient(G, W):
+    """Z = G @ W^T by whichever is faster (linear_gradient_preferred)."""
+    Z = _calls.linear_gradient(G, W)
+    if Z is None:
+        Z = linear_gradient(G, W) if linear_gradient_preferred(G, W) else False
+    return G @ W.t() if Z is False else _result(Z)
 
 
 def softpq_backward(layer, temperature, X, Z, need_dx=True, workspace=None):
@@ -498,6 +554,10 @@ def encode_conv2d(layer, inp, kernel, stride=1, pad=0, out=None):
 
 def conv2d(layer, inp, kernel, stride=1, pad=0, variant="auto", out=None, idx_workspace=None):
     """lutnn_conv2d: the convolution, Y [B*Ho*Wo, M] (output pixels by output channels)."""
+    if out is None and idx_workspace is None and variant in ("auto", VARIANT_AUTO):
+        got = _calls.conv2d(layer.address, inp, kernel, stride, pad)
+        if got is not None:
+            return _result(got)
     assert inp.is_cuda and inp.dtype == torch.float32 and inp.is_contiguous() and inp.dim() == 4
     geom = conv_geom(inp, kernel, stride, pad)
     N = conv2d_rows(geom, inp.shape[0])
@@ -575,6 +635,10 @@ def linear_auto_variant(layer, N, idx_workspace=None):
 
 def linear(layer, X, variant="auto", out=None, idx_workspace=None):
     """lutnn_linear: the whole operator, Y ~= X @ W (+ bias)."""
+    if out is None and idx_workspace is None and variant in ("auto", VARIANT_AUTO):
+        got = _calls.linear(layer.address, X)
+        if got is not None:
+            return _result(got)
     assert X.is_cuda and X.dtype == torch.float32 and X.stride(1) == 1
     N = X.shape[0]
     if out is None:

@@ -1,4 +1,4 @@
-"""Compile liblutnn.so (HIP, gfx950 only) in-tree with hipcc.
+"""Compile liblutnn.so (HIP, gfx950 only) in-tree with hipcc, and torch_calls.so (host code) with g++.
 
     python -m paper_2302_03213_amd.build
 
@@ -7,9 +7,11 @@ next to this file so that it travels with the source tree.
 """
 import concurrent.futures
 import hashlib
+import importlib.util
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -17,6 +19,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 OBJDIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "liblutnn.so")
+TORCH_CALLS = os.path.join(PKG, "torch_calls.so")  # csrc/torch_calls.cpp: host code on torch's C++ tensors
 
 SOURCES = ["api.hip", "encode.hip", "encode_conv9.hip", "encode_tree.hip", "build_table.hip", "lookup_lds.hip", "lookup_rows.hip", "lookup_mfma.hip", "lookup_smfmac.hip", "lookup_wide.hip", "lookup_matrix_f32.hip",
            "linear_fused.hip", "linear_small.hip", "softpq_backward.hip", "softpq_matrix.hip", "softpq_conv.hip", "matmul_split.hip", "probe_smfmac.hip"]
@@ -36,7 +39,7 @@ def source_hash():
     """12 hex digits over every file the library is compiled from (csrc/*, include/lutnn.h); the
     library reports it through lutnn_version() so that the loader can tell a stale binary."""
     h = hashlib.sha256()
-    files = [os.path.join(CSRC, f) for f in sorted(os.listdir(CSRC)) if f.endswith((".hip", ".h"))]
+    files = [os.path.join(CSRC, f) for f in sorted(os.listdir(CSRC)) if f.endswith((".hip", ".h", ".cpp"))]
     for path in files + headers():
         h.update(os.path.basename(path).encode() + b"\0")
         with open(path, "rb") as f:
@@ -68,7 +71,21 @@ def build(verbose=False):
     objs = [o for o, _ in results]
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     subprocess.run(cmd, check=True)
+    _build_torch_calls()
     return LIB
+
+
+def _build_torch_calls():
+    torch = importlib.util.find_spec("torch").submodule_search_locations[0]
+    include, lib = os.path.join(torch, "include"), os.path.join(torch, "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           '-DLUTNN_SOURCE_HASH="%s"' % source_hash(), "-I", include, "-I", os.path.join(include, "torch", "csrc", "api", "include"),
+           "-I", os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"), "-I", sysconfig.get_paths()["include"], "-I", INCLUDE,
+           os.path.join(CSRC, "torch_calls.cpp"), "-o", TORCH_CALLS, "-L", PKG, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN",
+           "-L", lib, "-ltorch", "-ltorch_cpu", "-ltorch_hip", "-lc10", "-lc10_hip", "-ltorch_python"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for torch_calls.cpp:\n%s" % r.stderr)
 
 
 def headers():

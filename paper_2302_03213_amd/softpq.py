@@ -47,7 +47,7 @@ class _SoftPQLinearFn(torch.autograd.Function):
     def forward(ctx, X, centroids, temperature, W, bias, table_dtype, host_temperature):
         ctx.temperature = host_temperature
         layer = _b.build_table(centroids.detach(), W, table_dtype, bias=bias)
-        Y = _b.linear(layer, X.detach())
+        Y = _b.linear(layer, X)
         ctx.save_for_backward(X, centroids, temperature, W)
         ctx.has_bias = bias is not None
         ctx.table_dtype = table_dtype
@@ -58,11 +58,8 @@ class _SoftPQLinearFn(torch.autograd.Function):
         X, centroids, temperature, W = ctx.saved_tensors
         G = G.contiguous()
         # input gradient of the ordinary linear layer
-        Z = _b.linear_gradient(G, W) if _b.linear_gradient_preferred(G, W) else G @ W.t()
-        C, K, V = centroids.shape
-        layer = _b.LutLayer(centroids.detach().contiguous(), None, _b.TABLE_F32, W.shape[1])
-        dP, dX, dt = _b.softpq_backward(layer, ctx.temperature.get(), X.detach(), Z,
-                                        need_dx=ctx.needs_input_grad[0])
+        Z = _b._input_gradient(G, W)
+        dP, dX, dt = _b._softpq_gradients(centroids, W.shape[1], ctx.temperature.get(), X, Z, ctx.needs_input_grad[0])
         dbias = G.sum(dim=0) if ctx.has_bias and ctx.needs_input_grad[4] else None
         return dX, dP, dt.reshape(temperature.shape), None, dbias, None, None
 
@@ -94,10 +91,9 @@ class _SoftPQConv2dFn(torch.autograd.Function):
         ctx.temperature = host_temperature
         layer = _b.build_table(centroids.detach(), W, table_dtype, bias=bias)
         B, _, H, Wd = inp.shape
-        Y = _b.conv2d(layer, inp.detach().contiguous(), kernel, stride, pad)  # [B*Ho*Wo, M]
-        geom = _b.conv_geom(inp, kernel, stride, pad)
-        Ho = (H + 2 * geom.pad_h - geom.kh) // geom.stride_h + 1
-        Wo = (Wd + 2 * geom.pad_w - geom.kw) // geom.stride_w + 1
+        Y = _b.conv2d(layer, inp.contiguous(), kernel, stride, pad)  # [B*Ho*Wo, M]
+        (kh, kw), (sh, sw), (ph, pw) = _b._pair(kernel), _b._pair(stride), _b._pair(pad)
+        Ho, Wo = (H + 2 * ph - kh) // sh + 1, (Wd + 2 * pw - kw) // sw + 1
         ctx.save_for_backward(inp, centroids, temperature, W)
         ctx.has_bias = bias is not None
         ctx.conv = (kernel, stride, pad)
@@ -108,9 +104,8 @@ class _SoftPQConv2dFn(torch.autograd.Function):
         inp, centroids, temperature, W = ctx.saved_tensors
         kernel, stride, pad = ctx.conv
         G = G.contiguous()
-        layer = _b.LutLayer(centroids.detach().contiguous(), None, _b.TABLE_F32, W.shape[1])
-        dP, dinp, dt = _b.softpq_backward_conv2d(layer, ctx.temperature.get(), inp.detach().contiguous(), W, G, kernel,
-                                                 stride, pad, need_dx=ctx.needs_input_grad[0])
+        dP, dinp, dt = _b._softpq_gradients_conv2d(centroids, ctx.temperature.get(), inp, W, G, kernel, stride, pad,
+                                                   ctx.needs_input_grad[0])
         dbias = G.sum(dim=(0, 2, 3)) if ctx.has_bias and ctx.needs_input_grad[4] else None
         return dinp, dP, dt.reshape(temperature.shape), None, dbias, None, None, None, None, None
 

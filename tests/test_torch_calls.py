@@ -1,0 +1,54 @@
+"""The native calls behind binding.py's per-step functions take the plain case only and leave the rest, errors included, to
+the Python way (no GPU needed for what they refuse)."""
+import pytest
+import torch
+
+import paper_2302_03213_amd as lut
+from paper_2302_03213_amd import binding
+
+
+def layer():
+    return lut.LutLayer(torch.zeros((2, 16, 4)), torch.zeros((2, 16, 8)), lut.TABLE_F32, 8)
+
+
+def test_tensors_that_are_not_on_the_gpu_are_left_alone():
+    l, X = layer(), torch.zeros((3, 8))
+    calls = binding._calls
+    assert calls.linear(l.address, X) is None and calls.linear(l.address, l.address, X) is None
+    assert calls.linear(l.address, None) is None and calls.linear(l.address) is None
+    assert calls.linear_tree16(l.address, l.address, X) is None
+    assert calls.conv2d(l.address, torch.zeros((1, 2, 2, 2)), 1, 1, 0) is None
+    assert calls.build_table(torch.zeros((2, 16, 4)), torch.zeros((8, 8)), 0) is None
+    assert calls.linear_gradient(X, X) is None
+    assert calls.softpq_backward(torch.zeros((2, 16, 4)), 8, 1.0, X, X, True) is None
+    assert calls.softpq_backward_conv2d(torch.zeros((2, 16, 4)), 1.0, X, X, X, True, 1, 1, 0) is None
+    with pytest.raises(AssertionError):
+        lut.linear(l, X)
+    with pytest.raises(AssertionError):
+        lut.conv2d(l, torch.zeros((1, 2, 2, 2)), 1)
+
+
+@pytest.mark.gpu
+def test_what_was_refused_is_refused_and_forms_agree():
+    P, W = torch.randn((6, 16, 4), device="cuda"), torch.randn((24, 40), device="cuda")
+    l = lut.build_table(P, W, lut.TABLE_I8)
+    X = torch.randn((300, 24), device="cuda")
+    ws = torch.empty((300, 6), dtype=torch.uint8, device="cuda")
+    ref = lut.linear(l, X, idx_workspace=ws)
+    wide = torch.randn((300, 31), device="cuda")
+    wide[:, 3:27] = X
+    for x in (X, wide[:, 3:27], torch.nn.Parameter(X), X.clone().requires_grad_(True)):
+        got = lut.linear(l, x)
+        assert torch.equal(got, ref) and not got.requires_grad
+    for bad in (X.t(), X.double(), X.cpu(), X[0]):
+        with pytest.raises((AssertionError, IndexError)):
+            lut.linear(l, bad)
+    with pytest.raises(lut.LutnnError):
+        lut.linear(l, X[:, :20].contiguous())  # rows narrower than C * V
+    with pytest.raises(ValueError):
+        lut.build_table(P, W[:20], lut.TABLE_I8)
+    with pytest.raises(ValueError):
+        lut.conv2d(l, torch.randn((1, 24, 2, 2), device="cuda"), 5)
+    image = torch.randn((2, 24, 5, 5), device="cuda")
+    assert torch.equal(lut.conv2d(l, image, (1, 1), (2, 2), (0, 0)), lut.conv2d(l, image, 1, 2, 0))
+    assert lut.linear(l, X[:0]).shape == (0, 40)
