@@ -404,6 +404,19 @@ LUTNN_API lutnn_status lutnn_conv2d_tree_scratch(const lutnn_layer* layer, const
 LUTNN_API lutnn_status lutnn_linear_gradient(const float* G, int64_t N, int64_t ldg, const float* W, int64_t ldw,
                                              int32_t D, int32_t M, float* Z, int64_t ldz, void* stream);
 
+/*
+ * out[m] = sum of dL/dY over everything but the output column: the bias gradient.  fp32, in a fixed order.
+ *
+ *   G    inner = 1: [outer][M] fp32, row stride ldg >= M, M >= 4 (E_UNSUPPORTED below).  inner > 1: [outer][M][inner], dense
+ *        (a convolution's dL/dY, inner = Ho*Wo); ldg is not looked at
+ *   out  [M] fp32, overwritten
+ *   workspace  at least lutnn_bias_gradient_workspace_bytes(outer, M, inner) bytes, 4-byte aligned
+ * Errors: E_NULL, E_SHAPE, E_UNSUPPORTED, E_ALIGN, E_HIP.
+ */
+LUTNN_API lutnn_status lutnn_bias_gradient(const float* G, int64_t outer, int64_t ldg, int32_t M, int64_t inner, float* out,
+                                           void* workspace, size_t workspace_bytes, void* stream);
+LUTNN_API size_t lutnn_bias_gradient_workspace_bytes(int64_t outer, int32_t M, int64_t inner);
+
 /* Host: 1 where lutnn_linear_gradient is faster than a library's fp32 matrix product for these operands and no less exact,
  * 0 elsewhere (few tiles of a long sum, rows that are not whole 16-byte vectors, fewer than 16 terms) and for shapes it
  * refuses. */

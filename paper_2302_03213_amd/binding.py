@@ -36,7 +36,8 @@ EXPORTS = ["lutnn_softpq_backward_static", "lutnn_set_tunable", "lutnn_encode_tr
            "lutnn_encode_tree_conv2d", "lutnn_conv2d_tree", "lutnn_conv2d_rows", "lutnn_encode_conv2d", "lutnn_conv2d",
            "lutnn_auto_variant", "lutnn_linear_auto_variant", "lutnn_status_string", "lutnn_last_error", "lutnn_version",
            "lutnn_probe_smfmac_stream", "lutnn_linear_scratch", "lutnn_linear_tree_scratch", "lutnn_linear_scratch_bytes",
-           "lutnn_conv2d_scratch_bytes", "lutnn_conv2d_scratch", "lutnn_conv2d_tree_scratch"]
+           "lutnn_conv2d_scratch_bytes", "lutnn_conv2d_scratch", "lutnn_conv2d_tree_scratch", "lutnn_bias_gradient",
+           "lutnn_bias_gradient_workspace_bytes"]
 
 
 class LutnnError(RuntimeError):
@@ -98,6 +99,10 @@ def _load():
     lib.lutnn_linear_tree.restype = i32
     lib.lutnn_linear_tree.argtypes = [ctypes.POINTER(_CLayer), ctypes.POINTER(_CTree), vp, i64, i64, vp,
                                       i64, i32, vp, vp]
+    lib.lutnn_bias_gradient.restype = i32
+    lib.lutnn_bias_gradient.argtypes = [vp, i64, i64, i32, i64, vp, vp, ctypes.c_size_t, vp]
+    lib.lutnn_bias_gradient_workspace_bytes.restype = ctypes.c_size_t
+    lib.lutnn_bias_gradient_workspace_bytes.argtypes = [i64, i32, i64]
     lib.lutnn_linear_scratch.restype = i32
     lib.lutnn_linear_scratch.argtypes = [ctypes.POINTER(_CLayer), vp, i64, i64, vp, i64, vp, ctypes.c_size_t, vp]
     lib.lutnn_linear_tree_scratch.restype = i32
@@ -450,6 +455,13 @@ def _softpq_gradients_conv2d(centroids, temperature, inp, W, G, kernel, stride, 
         return _result(got)
     layer = LutLayer(centroids.detach().contiguous(), None, TABLE_F32, W.shape[1])
     return softpq_backward_conv2d(layer, temperature, inp.detach().contiguous(), W, G, kernel, stride, pad, need_dx)
+
+
+def _bias_gradient(G):
+    """G = dL/dY, [N, M] or [B, M, Ho, Wo], summed over all but M (lutnn_bias_gradient)."""
+    differentiated = G.requires_grad and torch.is_grad_enabled()  # a second derivative goes through torch's sum
+    got = None if differentiated else _calls.bias_gradient(G)
+    return G.sum(dim=(0,) + tuple(range(2, G.dim()))) if got is None else _result(got)
 
 
 def _input_gradient(G, W):

@@ -22,7 +22,7 @@ LIB = os.path.join(PKG, "liblutnn.so")
 TORCH_CALLS = os.path.join(PKG, "torch_calls.so")  # csrc/torch_calls.cpp: host code on torch's C++ tensors
 
 SOURCES = ["api.hip", "encode.hip", "encode_conv9.hip", "encode_tree.hip", "build_table.hip", "lookup_lds.hip", "lookup_rows.hip", "lookup_mfma.hip", "lookup_smfmac.hip", "lookup_wide.hip", "lookup_matrix_f32.hip",
-           "linear_fused.hip", "linear_small.hip", "softpq_backward.hip", "softpq_matrix.hip", "softpq_conv.hip", "matmul_split.hip", "probe_smfmac.hip"]
+           "linear_fused.hip", "linear_small.hip", "softpq_backward.hip", "softpq_matrix.hip", "softpq_conv.hip", "matmul_split.hip", "column_sums.hip", "probe_smfmac.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

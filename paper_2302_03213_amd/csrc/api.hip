@@ -941,6 +941,27 @@ int32_t lutnn_linear_gradient_preferred(const float* G, int64_t N, int64_t ldg, 
     return lutnn::matmul_split_preferred(G, N, ldg, W, ldw, D, M);
 }
 
+size_t lutnn_bias_gradient_workspace_bytes(int64_t outer, int32_t M, int64_t inner) {
+    if (outer <= 0 || M <= 0 || inner <= 0 || outer >= kMaxRows || inner >= kMaxRows) return 0;
+    return (size_t)lutnn::column_sums_partials(outer, M, inner) * sizeof(float);
+}
+
+lutnn_status lutnn_bias_gradient(const float* G, int64_t outer, int64_t ldg, int32_t M, int64_t inner, float* out,
+                                 void* workspace, size_t workspace_bytes, void* stream) {
+    if (M <= 0 || inner <= 0 || inner >= kMaxRows) return fail(LUTNN_E_SHAPE, "M=%d and inner=%lld must be positive", M, (long long)inner);
+    if (inner == 1 && M < 4) return fail(LUTNN_E_UNSUPPORTED, "rows of M=%d values: 4 at least", M);
+    if (outer < 0 || outer >= kMaxRows) return fail(LUTNN_E_SHAPE, "outer=%lld out of range", (long long)outer);
+    if (inner == 1 && ldg < M) return fail(LUTNN_E_SHAPE, "ldg=%lld is smaller than M=%d", (long long)ldg, M);
+    if (!out) return fail(LUTNN_E_NULL, "out is NULL");
+    if (outer > 0 && (!G || !workspace)) return fail(LUTNN_E_NULL, "G or workspace is NULL");
+    if (const size_t need = lutnn_bias_gradient_workspace_bytes(outer, M, inner); workspace_bytes < need)
+        return fail(LUTNN_E_SHAPE, "workspace of %zu bytes is smaller than the %zu this shape needs", workspace_bytes, need);
+    if (!aligned(G, 4) || !aligned(out, 4) || !aligned(workspace, 4)) return fail(LUTNN_E_ALIGN, "G, out and workspace must be 4-byte aligned");
+    return hip_result(lutnn::launch_column_sums(G, outer, ldg, M, inner, static_cast<float*>(workspace), out,
+                                                static_cast<hipStream_t>(stream)),
+                      "bias gradient launch");
+}
+
 lutnn_status lutnn_softpq_backward_conv2d(const lutnn_layer* layer, float temperature, const float* input, int64_t B,
                                           const lutnn_conv2d_geom* geom, const float* W, int64_t ldw, const float* G,
                                           float* Z, float* dP, float* dinput, float* dt, void* workspace,

@@ -104,6 +104,12 @@ bool matmul_split_preferred(const float* G, int64_t N, int64_t ldg, const float*
 hipError_t launch_matmul_split(const float* G, int64_t N, int64_t ldg, const float* W, int64_t ldw, int D, int M, float* Z,
                                int64_t ldz, hipStream_t s);
 
+// out[m] = sum_o sum_i G[o][m][i], o with stride ldg (inner = 1: rows, M >= 4) or dense (inner > 1); partial holds
+// column_sums_partials floats.
+int64_t column_sums_partials(int64_t outer, int M, int64_t inner);
+hipError_t launch_column_sums(const float* G, int64_t outer, int64_t ldg, int M, int64_t inner, float* partial, float* out,
+                              hipStream_t s);
+
 // Z[b][d][l] = sum_m W[d][m] G[b][m][l]: the im2col gradient of the ordinary convolution with weights W.
 hipError_t launch_conv_z(const float* W, int64_t ldw, const float* G, int64_t B, int D, int M, const ConvGeom& g, float* Z,
                          hipStream_t s);

@@ -235,11 +235,29 @@ PyObject* softpq_backward_conv2d(PyObject* const* args, Py_ssize_t n) {
     }));
 }
 
+// bias_gradient(G): [N, M] or [B, M, Ho, Wo] summed over all but M
+PyObject* bias_gradient(PyObject* const* args, Py_ssize_t n) {
+    if (n != 1 || !(rows(args[0]) || dense(args[0], 4))) return none();
+    const at::Tensor& G = THPVariable_Unpack(args[0]);
+    const int64_t M = G.size(1), inner = G.dim() == 4 ? G.size(2) * G.size(3) : 1;
+    // planes of one pixel are rows
+    if (M < (inner == 1 ? 4 : 1) || M > INT32_MAX || inner < 1) return none();
+    const at::Tensor out = empty({M}, G);
+    const int64_t bytes = (int64_t)lutnn_bias_gradient_workspace_bytes(G.size(0), (int32_t)M, inner);
+    const at::Tensor workspace = empty({std::max<int64_t>(bytes, 4)}, G, at::kByte);
+    void* s = stream();
+    return result(launch([&] {
+                      return lutnn_bias_gradient(data(G), G.size(0), G.stride(0), (int32_t)M, inner, data(out), data(workspace),
+                                                 workspace.numel(), s);
+                  }),
+                  out);
+}
+
 PyMethodDef kMethods[] = {
 #define LUTNN_METHOD(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(guarded<name>)), METH_FASTCALL, nullptr}
     LUTNN_METHOD(linear),          LUTNN_METHOD(linear_tree16),   LUTNN_METHOD(conv2d),
     LUTNN_METHOD(build_table),     LUTNN_METHOD(linear_gradient), LUTNN_METHOD(softpq_backward),
-    LUTNN_METHOD(softpq_backward_conv2d), {nullptr, nullptr, 0, nullptr}};
+    LUTNN_METHOD(softpq_backward_conv2d), LUTNN_METHOD(bias_gradient), {nullptr, nullptr, 0, nullptr}};
 
 PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "torch_calls", nullptr, -1, kMethods, nullptr, nullptr, nullptr, nullptr};
 

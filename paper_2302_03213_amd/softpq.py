@@ -60,7 +60,7 @@ class _SoftPQLinearFn(torch.autograd.Function):
         # input gradient of the ordinary linear layer
         Z = _b._input_gradient(G, W)
         dP, dX, dt = _b._softpq_gradients(centroids, W.shape[1], ctx.temperature.get(), X, Z, ctx.needs_input_grad[0])
-        dbias = G.sum(dim=0) if ctx.has_bias and ctx.needs_input_grad[4] else None
+        dbias = _b._bias_gradient(G) if ctx.has_bias and ctx.needs_input_grad[4] else None
         return dX, dP, dt.reshape(temperature.shape), None, dbias, None, None
 
 
@@ -106,7 +106,7 @@ class _SoftPQConv2dFn(torch.autograd.Function):
         G = G.contiguous()
         dP, dinp, dt = _b._softpq_gradients_conv2d(centroids, ctx.temperature.get(), inp, W, G, kernel, stride, pad,
                                                    ctx.needs_input_grad[0])
-        dbias = G.sum(dim=(0, 2, 3)) if ctx.has_bias and ctx.needs_input_grad[4] else None
+        dbias = _b._bias_gradient(G) if ctx.has_bias and ctx.needs_input_grad[4] else None
         return dinp, dP, dt.reshape(temperature.shape), None, dbias, None, None, None, None, None
 
 

@@ -1,0 +1,41 @@
+"""lutnn_bias_gradient against 64-bit sums, at the edges of its chunks and tiles: the error of n terms stays within log2(n) + 16
+half ulps of the sum of their magnitudes (chains of at most a few dozen additions, in a tree)."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def binding():
+    import paper_2302_03213_amd.binding as b
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return b
+
+
+def check(got, G, dims):
+    exact, size = G.double().sum(dim=dims), G.double().abs().sum(dim=dims)
+    assert got.shape == exact.shape and got.dtype == torch.float32
+    assert ((got.double() - exact).abs() <= 48 * 2.0 ** -24 * size).all()
+
+
+@pytest.mark.parametrize("N,M", [(1, 4), (31, 5), (33, 63), (64, 257), (1000, 255), (5000, 1030), (40000, 9), (129, 3072), (0, 12)])
+def test_rows(binding, N, M):
+    wide = torch.randn((N, M + 3), device="cuda")
+    for G in (wide[:, 3:], wide[:, :M].contiguous()):
+        check(binding._bias_gradient(G), G, 0)
+
+
+@pytest.mark.parametrize("B,M,H,W", [(1, 1, 7, 7), (5, 3, 1, 2), (33, 64, 14, 14), (2, 130, 56, 57), (3, 5, 1, 1), (0, 4, 3, 3)])
+def test_planes(binding, B, M, H, W):
+    G = torch.randn((B, M, H, W), device="cuda")
+    check(binding._bias_gradient(G), G, (0, 2, 3))
+
+
+def test_rows_too_narrow_and_second_derivatives_go_through_torch(binding):
+    G = torch.randn((50, 3), device="cuda")
+    check(binding._bias_gradient(G), G, 0)
+    G = torch.randn((50, 8), device="cuda", requires_grad=True)
+    assert binding._bias_gradient(G).requires_grad
+    with torch.no_grad():
+        assert not binding._bias_gradient(G).requires_grad
