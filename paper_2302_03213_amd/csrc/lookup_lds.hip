@@ -16,6 +16,7 @@
 // 256 biased bytes cannot overflow 16 bits (256*255 < 65536); the partial sums are widened to
 // int32 at least that often and the bias (128 per codebook) is removed in the epilogue, so the
 // result is the exact integer sum.
+#include <algorithm>
 #include <type_traits>
 
 #include "gather_launch.h"
@@ -272,7 +273,10 @@ hipError_t launch_lookup_lds_f32(const float* T, const float* bias, int C, int K
     const double entries = (double)N * C * M;
     const double matrix = lookup_matrix_f32_us(C, K, M, N);
     const double rows = rows_kernel_preferred(N, M, K, true) ? 10.0 + 7e-8 * entries + 1.5e-6 * (double)N * M : 1e30;
-    const double gather = 4.0 + 3e-7 * entries;
+    // ns an entry: a workgroup reads 1024 columns, and where a row has 1, 2, 4 or 8 of them an XCD's workgroups keep to the
+    // same columns, which its L2 then holds (300 rows x 512 codebooks, M = 4096 0.25; 400 x 192, M = 3072 0.41)
+    const int per_row = (M + 1023) / 1024;
+    const double gather = 4.0 + (per_row == 1 ? 2e-7 : 8 % per_row == 0 ? 2.4e-7 : 4e-7) * entries;
     if (matrix < rows && matrix < gather) return launch_lookup_matrix_f32(T, bias, C, K, M, idx, N, Y, ldy, s);
     if (rows < 1e30) return launch_lookup_rows_f32(T, bias, C, K, M, idx, N, Y, ldy, s);
     return launch_lookup_lds<TableF32>(T, nullptr, bias, C, K, M, idx, N, Y, ldy, s);
