@@ -45,7 +45,8 @@ float* data(PyObject* object) { return data(THPVariable_Unpack(object)); }
 PyObject* none() { Py_RETURN_NONE; }
 PyObject* result(int status, const at::Tensor& out) { return status ? PyLong_FromLong(status) : THPVariable_Wrap(out); }
 
-// Launches without the interpreter's lock, as ctypes does.
+// Launches without the interpreter's lock, as ctypes does.  The call is one of the C ABI's on pointers taken before: a
+// tensor's data may be refused with an exception, which must not leave here without the lock.
 template <class Call>
 int launch(Call&& call) {
     int status;
@@ -53,12 +54,14 @@ int launch(Call&& call) {
     Py_END_ALLOW_THREADS return status;
 }
 
-// An exception (out of memory, a mode that gives no data pointers): the long way meets the same, and reports it.
+// An exception (out of memory, a mode that gives no data pointers): the long way meets the same, and reports it.  One that
+// came out of Python (a dispatch mode's) is still set there.
 template <PyObject* (*Function)(PyObject* const*, Py_ssize_t)>
 PyObject* guarded(PyObject*, PyObject* const* args, Py_ssize_t n) {
     try {
         return Function(args, n);
     } catch (const std::exception&) {
+        PyErr_Clear();
         return none();
     }
 }
@@ -73,12 +76,12 @@ PyObject* linear(PyObject* const* args, Py_ssize_t n) {
     const at::Tensor out = empty({N, layer->M}, X);
     const size_t bytes = lutnn_linear_scratch_bytes(layer, N, tree != nullptr);
     const at::Tensor scratch = bytes ? empty({(int64_t)bytes}, X, at::kByte) : at::Tensor();
+    const int64_t ldx = X.stride(0), ldy = out.stride(0);
+    float *x = data(X), *y = data(out), *w = data(scratch);
     void* s = stream();
-    return result(launch([&] {
-                      return tree ? lutnn_linear_tree_scratch(layer, tree, data(X), N, X.stride(0), data(out), out.stride(0),
-                                                              data(scratch), bytes, s)
-                                  : lutnn_linear_scratch(layer, data(X), N, X.stride(0), data(out), out.stride(0),
-                                                         data(scratch), bytes, s);
+    return result(launch([=] {
+                      return tree ? lutnn_linear_tree_scratch(layer, tree, x, N, ldx, y, ldy, w, bytes, s)
+                                  : lutnn_linear_scratch(layer, x, N, ldx, y, ldy, w, bytes, s);
                   }),
                   out);
 }
@@ -86,15 +89,15 @@ PyObject* linear(PyObject* const* args, Py_ssize_t n) {
 PyObject* linear_tree16(PyObject* const* args, Py_ssize_t n) {
     if (n != 3 || !rows(args[2])) return none();
     const lutnn_layer* layer = layer_of(args[0]);
+    const lutnn_tree* tree = tree_of(args[1]);
     const at::Tensor& X = THPVariable_Unpack(args[2]);
     const int64_t N = X.size(0);
     const at::Tensor out = empty({N, layer->M}, X), idx = empty({N, layer->C}, X, at::kShort);
+    const int64_t ldx = X.stride(0), ldy = out.stride(0);
+    float *x = data(X), *y = data(out);
+    uint16_t* i = static_cast<uint16_t*>(idx.data_ptr());
     void* s = stream();
-    return result(launch([&] {
-                      return lutnn_linear_tree16(layer, tree_of(args[1]), data(X), N, X.stride(0), data(out), out.stride(0),
-                                                 static_cast<uint16_t*>(idx.data_ptr()), s);
-                  }),
-                  out);
+    return result(launch([=] { return lutnn_linear_tree16(layer, tree, x, N, ldx, y, ldy, i, s); }), out);
 }
 
 // Kernel, stride and padding as whole numbers.
@@ -123,12 +126,10 @@ PyObject* conv2d(PyObject* const* args, Py_ssize_t n) {
     const at::Tensor out = empty({N, layer->M}, inp);
     const size_t bytes = lutnn_conv2d_scratch_bytes(layer, N);
     const at::Tensor scratch = empty({(int64_t)bytes}, inp, at::kByte);
+    const int64_t B = inp.size(0), ldy = out.stride(0);
+    float *x = data(inp), *y = data(out), *w = data(scratch);
     void* s = stream();
-    return result(launch([&] {
-                      return lutnn_conv2d_scratch(layer, data(inp), inp.size(0), &g, data(out), out.stride(0),
-                                                  data(scratch), bytes, s);
-                  }),
-                  out);
+    return result(launch([=, &g] { return lutnn_conv2d_scratch(layer, x, B, &g, y, ldy, w, bytes, s); }), out);
 }
 
 // build_table(centroids, W, dtype): (table, packed or None, scale or None)
@@ -149,10 +150,11 @@ PyObject* build_table(PyObject* const* args, Py_ssize_t n) {
     } else {
         return none();
     }
+    const int64_t ldw = W.stride(0);
+    float *p = data(P), *w = data(W), *t = data(table), *pk = data(packed), *sc = data(scale);
     void* s = stream();
-    const int status = launch([&] {
-        return lutnn_build_table(data(P), data(W), W.stride(0), (int32_t)C, (int32_t)K, (int32_t)V, (int32_t)M, (int32_t)dtype,
-                                 data(table), data(packed), data(scale), s);
+    const int status = launch([=] {
+        return lutnn_build_table(p, w, ldw, (int32_t)C, (int32_t)K, (int32_t)V, (int32_t)M, (int32_t)dtype, t, pk, sc, s);
     });
     if (status) return PyLong_FromLong(status);
     return Py_BuildValue("NNN", THPVariable_Wrap(table), packed.defined() ? THPVariable_Wrap(packed) : none(),
@@ -165,14 +167,13 @@ PyObject* linear_gradient(PyObject* const* args, Py_ssize_t n) {
     const at::Tensor &G = THPVariable_Unpack(args[0]), &W = THPVariable_Unpack(args[1]);
     const int64_t N = G.size(0), D = W.size(0), M = W.size(1);
     if (G.size(1) != M || D > INT32_MAX || M > INT32_MAX) return none();
-    if (!lutnn_linear_gradient_preferred(data(G), N, G.stride(0), data(W), W.stride(0), (int32_t)D, (int32_t)M)) Py_RETURN_FALSE;
+    const int64_t ldg = G.stride(0), ldw = W.stride(0);
+    float *g = data(G), *w = data(W);
+    if (!lutnn_linear_gradient_preferred(g, N, ldg, w, ldw, (int32_t)D, (int32_t)M)) Py_RETURN_FALSE;
     const at::Tensor Z = empty({N, D}, G);
+    float* z = data(Z);
     void* s = stream();
-    return result(launch([&] {
-                      return lutnn_linear_gradient(data(G), N, G.stride(0), data(W), W.stride(0), (int32_t)D, (int32_t)M,
-                                                   data(Z), D, s);
-                  }),
-                  Z);
+    return result(launch([=] { return lutnn_linear_gradient(g, N, ldg, w, ldw, (int32_t)D, (int32_t)M, z, D, s); }), Z);
 }
 
 struct SoftPqOut {
@@ -206,11 +207,12 @@ PyObject* softpq_backward(PyObject* const* args, Py_ssize_t n) {
     const lutnn_layer layer = shape_of(P, PyLong_AsLong(args[1]));
     const double t = PyFloat_AsDouble(args[2]);
     const SoftPqOut out(P.size(0), P.size(1), P.size(2), X.size(0), X, args[5] == Py_True);
+    const int64_t N = X.size(0), ldx = X.stride(0), ldz = Z.stride(0), lddx = out.dX.defined() ? out.dX.stride(0) : 0;
+    const int64_t bytes = out.workspace.numel();
+    float *x = data(X), *z = data(Z), *dp = data(out.dP), *dx = data(out.dX), *dt = data(out.dt), *w = data(out.workspace);
     void* s = stream();
-    return out.result(launch([&] {
-        return lutnn_softpq_backward(&layer, (float)t, data(X), X.size(0), X.stride(0), data(Z), Z.stride(0), data(out.dP),
-                                     data(out.dX), out.dX.defined() ? out.dX.stride(0) : 0, data(out.dt),
-                                     data(out.workspace), out.workspace.numel(), s);
+    return out.result(launch([=, &layer] {
+        return lutnn_softpq_backward(&layer, (float)t, x, N, ldx, z, ldz, dp, dx, lddx, dt, w, bytes, s);
     }));
 }
 
@@ -227,11 +229,12 @@ PyObject* softpq_backward_conv2d(PyObject* const* args, Py_ssize_t n) {
     const double t = PyFloat_AsDouble(args[1]);
     const SoftPqOut out(P.size(0), P.size(1), P.size(2), N, inp, args[5] == Py_True);
     const at::Tensor Z = empty({N * D}, inp);
+    const int64_t B = inp.size(0), ldw = W.stride(0), bytes = out.workspace.numel();
+    float *x = data(inp), *w = data(W), *dy = data(G), *z = data(Z), *dp = data(out.dP), *dx = data(out.dX), *dt = data(out.dt);
+    float* ws = data(out.workspace);
     void* s = stream();
-    return out.result(launch([&] {
-        return lutnn_softpq_backward_conv2d(&layer, (float)t, data(inp), inp.size(0), &g, data(W), W.stride(0), data(G),
-                                            data(Z), data(out.dP), data(out.dX), data(out.dt), data(out.workspace),
-                                            out.workspace.numel(), s);
+    return out.result(launch([=, &layer, &g] {
+        return lutnn_softpq_backward_conv2d(&layer, (float)t, x, B, &g, w, ldw, dy, z, dp, dx, dt, ws, bytes, s);
     }));
 }
 
@@ -245,12 +248,10 @@ PyObject* bias_gradient(PyObject* const* args, Py_ssize_t n) {
     const at::Tensor out = empty({M}, G);
     const int64_t bytes = (int64_t)lutnn_bias_gradient_workspace_bytes(G.size(0), (int32_t)M, inner);
     const at::Tensor workspace = empty({std::max<int64_t>(bytes, 4)}, G, at::kByte);
+    const int64_t outer = G.size(0), ldg = G.stride(0), size = workspace.numel();
+    float *g = data(G), *y = data(out), *w = data(workspace);
     void* s = stream();
-    return result(launch([&] {
-                      return lutnn_bias_gradient(data(G), G.size(0), G.stride(0), (int32_t)M, inner, data(out), data(workspace),
-                                                 workspace.numel(), s);
-                  }),
-                  out);
+    return result(launch([=] { return lutnn_bias_gradient(g, outer, ldg, (int32_t)M, inner, y, w, size, s); }), out);
 }
 
 PyMethodDef kMethods[] = {

@@ -52,3 +52,27 @@ def test_what_was_refused_is_refused_and_forms_agree():
     image = torch.randn((2, 24, 5, 5), device="cuda")
     assert torch.equal(lut.conv2d(l, image, (1, 1), (2, 2), (0, 0)), lut.conv2d(l, image, 1, 2, 0))
     assert lut.linear(l, X[:0]).shape == (0, 40)
+
+
+@pytest.mark.gpu
+def test_where_tensors_give_no_pointers_the_python_way_reports_it():
+    """Under torch.func.grad the outputs are wrappers without storage; under a dispatch mode their allocation can fail in
+    Python: the exception leaves the native call with the interpreter's lock held and no error set."""
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    class Refuses(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            raise ValueError("refused")
+
+    l = lut.build_table(torch.randn((6, 16, 4), device="cuda"), torch.randn((24, 40), device="cuda"), lut.TABLE_I8)
+    X = torch.randn((300, 24), device="cuda")
+
+    def inside(z):
+        with pytest.raises(RuntimeError):
+            lut.linear(l, X)
+        return z.sum()
+
+    torch.func.grad(inside)(torch.ones(3, device="cuda"))
+    with Refuses(), pytest.raises(ValueError, match="refused"):
+        lut.linear(l, X)
+    assert lut.linear(l, X).shape == (300, 40)
