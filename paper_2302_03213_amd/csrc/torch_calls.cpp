@@ -248,7 +248,8 @@ PyObject* bias_gradient(PyObject* const* args, Py_ssize_t n) {
     const at::Tensor out = empty({M}, G);
     const int64_t bytes = (int64_t)lutnn_bias_gradient_workspace_bytes(G.size(0), (int32_t)M, inner);
     const at::Tensor workspace = empty({std::max<int64_t>(bytes, 4)}, G, at::kByte);
-    const int64_t outer = G.size(0), ldg = G.stride(0), size = workspace.numel();
+    // the stride of a single row is whatever it is: a dimension of size 1 is contiguous with any
+    const int64_t outer = G.size(0), ldg = outer > 1 ? G.stride(0) : M, size = workspace.numel();
     float *g = data(G), *y = data(out), *w = data(workspace);
     void* s = stream();
     return result(launch([=] { return lutnn_bias_gradient(g, outer, ldg, (int32_t)M, inner, y, w, size, s); }), out);

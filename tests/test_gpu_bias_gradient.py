@@ -39,3 +39,26 @@ def test_rows_too_narrow_and_second_derivatives_go_through_torch(binding):
     assert binding._bias_gradient(G).requires_grad
     with torch.no_grad():
         assert not binding._bias_gradient(G).requires_grad
+
+
+def transposed(M):
+    """[1, M] with strides (1, 1): contiguous, as a dimension of size 1 has any stride."""
+    G = torch.randn((M, 1), device="cuda").t()
+    assert G.is_contiguous() and G.stride() == (1, 1)
+    return G
+
+
+def test_the_stride_of_a_single_row_says_nothing(binding):
+    G = transposed(40)
+    check(binding._bias_gradient(G), G, 0)
+    G = G.as_strided((1, 40, 1, 1), (1, 1, 1, 1))
+    assert G.is_contiguous()
+    check(binding._bias_gradient(G), G, (0, 2, 3))
+
+
+def test_backward_of_one_row_whose_output_is_transposed():
+    from paper_2302_03213_amd.softpq import SoftPQLinear
+    layer = SoftPQLinear(torch.randn((6, 16, 4), device="cuda"), torch.randn((24, 40), device="cuda"), bias=torch.zeros(40, device="cuda"))
+    v = torch.randn((40, 1), device="cuda")
+    dbias, = torch.autograd.grad((layer(torch.randn((1, 24), device="cuda")).t() * v).sum(), layer.bias)
+    assert torch.equal(dbias, v[:, 0])
