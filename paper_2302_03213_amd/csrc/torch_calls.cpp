@@ -22,7 +22,8 @@ const lutnn_tree* tree_of(PyObject* address) { return static_cast<const lutnn_tr
 
 void* stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
-// An ordinary CUDA tensor of fp32 with `dims` dimensions: no subclass, no transform's wrapper.
+// An ordinary CUDA tensor of fp32 with `dims` dimensions: no subclass, no transform's wrapper, no forward-mode tangent (which
+// what the long way leaves to torch carries on).
 bool plain(PyObject* object, int64_t dims) {
     if (!THPVariable_CheckExact(object) && Py_TYPE(object) != reinterpret_cast<PyTypeObject*>(ParameterClass)) return false;
     const at::Tensor& t = THPVariable_Unpack(object);
@@ -31,7 +32,7 @@ bool plain(PyObject* object, int64_t dims) {
                                                    c10::DispatchKey::Functionalize, c10::DispatchKey::ZeroTensor,
                                                    c10::DispatchKey::Negative});
     return t.is_cuda() && t.scalar_type() == at::kFloat && t.dim() == dims && t.layout() == at::kStrided &&
-           !t.key_set().has_any(kWrapped);
+           !t.key_set().has_any(kWrapped) && !t._fw_grad(0).defined();
 }
 bool rows(PyObject* object) { return plain(object, 2) && THPVariable_Unpack(object).stride(1) == 1; }
 bool dense(PyObject* object, int64_t dims) { return plain(object, dims) && THPVariable_Unpack(object).is_contiguous(); }

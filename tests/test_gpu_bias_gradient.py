@@ -62,3 +62,17 @@ def test_backward_of_one_row_whose_output_is_transposed():
     v = torch.randn((40, 1), device="cuda")
     dbias, = torch.autograd.grad((layer(torch.randn((1, 24), device="cuda")).t() * v).sum(), layer.bias)
     assert torch.equal(dbias, v[:, 0])
+
+
+def test_forward_over_reverse_keeps_the_tangent(binding):
+    """dL/dY that carries a forward-mode tangent: the bias gradient's tangent is its sum."""
+    import torch.autograd.forward_ad as forward
+    from paper_2302_03213_amd.softpq import SoftPQLinear
+    layer = SoftPQLinear(torch.randn((6, 16, 4), device="cuda"), torch.randn((24, 40), device="cuda"), bias=torch.zeros(40, device="cuda"))
+    X, target, tangent = torch.randn((50, 24), device="cuda"), torch.randn((50, 40), device="cuda"), torch.randn((50, 40), device="cuda")
+    with forward.dual_level():
+        dual = forward.make_dual(target, tangent)
+        Y = layer(X)
+        got = forward.unpack_dual(torch.autograd.grad(((Y - dual) ** 2).sum(), layer.bias)[0])
+        check(got.primal, 2 * (Y.detach() - target), 0)
+        check(got.tangent, -2 * tangent, 0)
