@@ -405,7 +405,8 @@ LUTNN_API lutnn_status lutnn_linear_gradient(const float* G, int64_t N, int64_t 
                                              int32_t D, int32_t M, float* Z, int64_t ldz, void* stream);
 
 /*
- * out[m] = sum of dL/dY over everything but the output column: the bias gradient.  fp32, in a fixed order.
+ * out[m] = sum of dL/dY over everything but the output column: the bias gradient.  Summed in 64 bits
+ * in a fixed order and rounded once.
  *
  *   G    inner = 1: [outer][M] fp32, row stride ldg >= M, M >= 4 (E_UNSUPPORTED below).  inner > 1: [outer][M][inner], dense
  *        (a convolution's dL/dY, inner = Ho*Wo); ldg is not looked at

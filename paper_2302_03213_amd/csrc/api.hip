@@ -943,7 +943,7 @@ int32_t lutnn_linear_gradient_preferred(const float* G, int64_t N, int64_t ldg, 
 
 size_t lutnn_bias_gradient_workspace_bytes(int64_t outer, int32_t M, int64_t inner) {
     if (outer <= 0 || M <= 0 || inner <= 0 || outer >= kMaxRows || inner >= kMaxRows) return 0;
-    return (size_t)lutnn::column_sums_partials(outer, M, inner) * sizeof(float);
+    return lutnn::column_sums_workspace(outer, M, inner);
 }
 
 lutnn_status lutnn_bias_gradient(const float* G, int64_t outer, int64_t ldg, int32_t M, int64_t inner, float* out,
@@ -957,7 +957,7 @@ lutnn_status lutnn_bias_gradient(const float* G, int64_t outer, int64_t ldg, int
     if (const size_t need = lutnn_bias_gradient_workspace_bytes(outer, M, inner); workspace_bytes < need)
         return fail(LUTNN_E_SHAPE, "workspace of %zu bytes is smaller than the %zu this shape needs", workspace_bytes, need);
     if (!aligned(G, 4) || !aligned(out, 4) || !aligned(workspace, 4)) return fail(LUTNN_E_ALIGN, "G, out and workspace must be 4-byte aligned");
-    return hip_result(lutnn::launch_column_sums(G, outer, ldg, M, inner, static_cast<float*>(workspace), out,
+    return hip_result(lutnn::launch_column_sums(G, outer, ldg, M, inner, workspace, out,
                                                 static_cast<hipStream_t>(stream)),
                       "bias gradient launch");
 }

@@ -104,10 +104,10 @@ bool matmul_split_preferred(const float* G, int64_t N, int64_t ldg, const float*
 hipError_t launch_matmul_split(const float* G, int64_t N, int64_t ldg, const float* W, int64_t ldw, int D, int M, float* Z,
                                int64_t ldz, hipStream_t s);
 
-// out[m] = sum_o sum_i G[o][m][i], o with stride ldg (inner = 1: rows, M >= 4) or dense (inner > 1); partial holds
-// column_sums_partials floats.
-int64_t column_sums_partials(int64_t outer, int M, int64_t inner);
-hipError_t launch_column_sums(const float* G, int64_t outer, int64_t ldg, int M, int64_t inner, float* partial, float* out,
+// out[m] = sum_o sum_i G[o][m][i], o with stride ldg (inner = 1: rows, M >= 4) or dense (inner > 1); the workspace holds
+// column_sums_workspace bytes.
+size_t column_sums_workspace(int64_t outer, int M, int64_t inner);
+hipError_t launch_column_sums(const float* G, int64_t outer, int64_t ldg, int M, int64_t inner, void* workspace, float* out,
                               hipStream_t s);
 
 // Z[b][d][l] = sum_m W[d][m] G[b][m][l]: the im2col gradient of the ordinary convolution with weights W.

@@ -32,6 +32,17 @@ def test_planes(binding, B, M, H, W):
     check(binding._bias_gradient(G), G, (0, 2, 3))
 
 
+# few and large planes, many and small ones, rows in one workgroup or shared out: every sum is a 64-bit one, rounded once
+@pytest.mark.parametrize("shape", [(1, 3, 700, 701), (2, 1, 64, 32), (2, 1, 64, 33), (3, 70, 37, 41), (20000, 5, 1, 2), (9000, 33, 3, 1),
+                                   (40, 130, 7, 7), (256, 9), (257, 255), (700, 256), (100000, 5), (3000, 1030), (1, 7), (2, 259)])
+def test_one_rounding(binding, shape):
+    G = torch.randn(shape, device="cuda") + (0.25 if shape[0] % 2 else 0.0)
+    dims = (0,) + tuple(range(2, len(shape)))
+    D = G.cpu().double()
+    exact, size = D.sum(dim=dims), D.abs().sum(dim=dims)
+    assert ((binding._bias_gradient(G).cpu().double() - exact).abs() <= 2.0 ** -24 * exact.abs() + 2.0 ** -46 * size).all()
+
+
 def test_rows_too_narrow_and_second_derivatives_go_through_torch(binding):
     G = torch.randn((50, 3), device="cuda")
     check(binding._bias_gradient(G), G, 0)
