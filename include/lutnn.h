@@ -493,6 +493,7 @@ LUTNN_API const char* lutnn_last_error(void);
  *   "LUTNN_SMFMAC_TILE_ROWS"  "128" | "256" | "384" | "512"   tile height of the sparse matrix-core lookup
  *   "LUTNN_SMFMAC_ROW_GROUP"  "0" .. "64"               row tiles per group of its tile order (0 = plain)
  *   "LUTNN_SMFMAC_TILE_COLS"  "96" | "128"              width of its 512-row tiles
+ *   "LUTNN_LOOKUP_F32"        "gather" | "rows" | "matrix"   which form the LDS variant runs on an fp32 table
  * value NULL or "" returns the switch to "not pinned".  A pinned choice the shape cannot take is
  * ignored.  Process-wide and atomic: safe to call while other threads launch, which then see
  * either the old or the new value.

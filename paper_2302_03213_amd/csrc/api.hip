@@ -33,7 +33,7 @@ lutnn_status hip_result(hipError_t e, const char* what) {
 // ---- tuning switches (lutnn_kernels.h)
 const char* const kTunableNames[lutnn::kTuneCount] = {"LUTNN_FUSED_KERNEL", "LUTNN_SMFMAC_SPLIT",
                                                       "LUTNN_SMFMAC_TILE_ROWS", "LUTNN_SMFMAC_ROW_GROUP",
-                                                      "LUTNN_SMFMAC_TILE_COLS"};
+                                                      "LUTNN_SMFMAC_TILE_COLS", "LUTNN_LOOKUP_F32"};
 std::atomic<int> g_tunable[lutnn::kTuneCount];
 std::once_flag g_tunable_once;
 
@@ -43,6 +43,12 @@ int parse_tunable(int which, const char* text) {
     if (which == lutnn::kTuneFusedKernel) {
         if (std::strcmp(text, "small") == 0) return 1;
         if (std::strcmp(text, "tile") == 0) return 0;
+        return -1;
+    }
+    if (which == lutnn::kTuneLookupF32) {
+        const char* const forms[] = {"gather", "rows", "matrix"};
+        for (int i = 0; i < 3; ++i)
+            if (std::strcmp(text, forms[i]) == 0) return i;
         return -1;
     }
     char* end = nullptr;

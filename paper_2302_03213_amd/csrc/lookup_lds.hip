@@ -277,6 +277,10 @@ hipError_t launch_lookup_lds_f32(const float* T, const float* bias, int C, int K
     // same columns, which its L2 then holds (300 rows x 512 codebooks, M = 4096 0.25; 400 x 192, M = 3072 0.41)
     const int per_row = (M + 1023) / 1024;
     const double gather = 4.0 + (per_row == 1 ? 2e-7 : 8 % per_row == 0 ? 2.4e-7 : 4e-7) * entries;
+    const int pinned = tunable(kTuneLookupF32);
+    if (pinned == 0 && gather_supported<TableF32>(M)) return launch_lookup_lds<TableF32>(T, nullptr, bias, C, K, M, idx, N, Y, ldy, s);
+    if (pinned == 1 && rows_kernel_supported(K, true)) return launch_lookup_rows_f32(T, bias, C, K, M, idx, N, Y, ldy, s);
+    if (pinned == 2 && matrix < 1e30) return launch_lookup_matrix_f32(T, bias, C, K, M, idx, N, Y, ldy, s);
     if (matrix < rows && matrix < gather) return launch_lookup_matrix_f32(T, bias, C, K, M, idx, N, Y, ldy, s);
     if (rows < 1e30) return launch_lookup_rows_f32(T, bias, C, K, M, idx, N, Y, ldy, s);
     return launch_lookup_lds<TableF32>(T, nullptr, bias, C, K, M, idx, N, Y, ldy, s);

@@ -267,12 +267,17 @@ inline int stage_codebooks(size_t bytes_per_codebook) {
 
 }  // namespace
 
+// One codebook's slab fits the staging buffer.
+bool rows_kernel_supported(int K, bool f32) {
+    const int mt = f32 ? kRowsColsF32 : kRowsColsI8;
+    return (size_t)K * (mt * (f32 ? 4 : 1) + 16) <= (size_t)kRowsLdsBudget;
+}
+
 // The lane = row kernels pay when a workgroup's 256 rows are real rows and the grid still covers
 // the chip; below that the 64-row staged kernels (or the direct gather) are the better shape.
 bool rows_kernel_preferred(int64_t N, int M, int K, bool f32) {
+    if (!rows_kernel_supported(K, f32)) return false;
     const int mt = f32 ? kRowsColsF32 : kRowsColsI8;
-    const size_t per_codebook = (size_t)K * (mt * (f32 ? 4 : 1) + 16);
-    if (per_codebook > (size_t)kRowsLdsBudget) return false;
     const int64_t blocks = ((N + kRowsThreads - 1) / kRowsThreads) * ((M + mt - 1) / mt);
     // one workgroup per compute unit at least (measured on BERT- and conv-size layers: at 96
     // workgroups the 64-row kernel is 2.4x faster, from 288 on this one is 1.6x faster)

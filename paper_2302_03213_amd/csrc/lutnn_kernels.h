@@ -22,6 +22,7 @@ enum Tunable {
     kTuneSmfmacTileRows,    // LUTNN_SMFMAC_TILE_ROWS: 128 | 256 | 384 | 512
     kTuneSmfmacRowGroup,    // LUTNN_SMFMAC_ROW_GROUP: row tiles per group of the tile order, 0..64 (0 = plain)
     kTuneSmfmacTileCols,    // LUTNN_SMFMAC_TILE_COLS: 96 | 128, width of the 512-row tiles
+    kTuneLookupF32,         // LUTNN_LOOKUP_F32: 0 = "gather", 1 = "rows", 2 = "matrix"
     kTuneCount
 };
 int tunable(int which);
@@ -147,6 +148,7 @@ hipError_t launch_lookup_lds_i4(const uint8_t* T, const float* scale, const floa
                                 hipStream_t s);
 // Eq. 4, gather variant with lane = row (256 rows per workgroup share the staged slabs): the shape
 // for many rows.  bits = 8: T is [C][K][M] int8; bits = 4: [C][K][ceil(M/2)] nibble pairs.
+bool rows_kernel_supported(int K, bool f32);
 bool rows_kernel_preferred(int64_t N, int M, int K, bool f32);
 hipError_t launch_lookup_rows_i8(const void* T, int bits, const float* scale, const float* bias, int C,
                                  int K, int M, const uint8_t* idx, int64_t N, float* Y, int64_t ldy,

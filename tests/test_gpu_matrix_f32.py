@@ -17,7 +17,7 @@ def lut():
     return lut_mod
 
 
-def run(lut, T, idx, bias, offset=0):
+def run(lut, T, idx, bias, offset=0, form="matrix"):
     C, K, M = T.shape
     flat = torch.empty(T.size + offset, device="cuda")
     flat[offset:] = torch.from_numpy(T.reshape(-1))
@@ -26,7 +26,8 @@ def run(lut, T, idx, bias, offset=0):
     i8 = torch.empty(idx.size + offset, dtype=torch.uint8, device="cuda")
     i8[offset:] = torch.from_numpy(idx.reshape(-1))
     out = torch.full((N, M + 3), -3.5, device="cuda")
-    lut.lookup(layer, i8[offset:].view(idx.shape), "lds", out=out[:, :M])
+    with lut.tunables(LUTNN_LOOKUP_F32=form):
+        lut.lookup(layer, i8[offset:].view(idx.shape), "lds", out=out[:, :M])
     assert (host(out[:, M:]) == -3.5).all()
     return host(out[:, :M])
 
@@ -45,10 +46,11 @@ def sums(T, idx, bias):
         return (total, size, chain) if bias is None else (total + bias, size + np.abs(bias), chain + bias)
 
 
-# stages of four codebooks with one, two and three left, rows past a tile, widths that end in one; enough rows that the
-# kernel is the one taken
+# stages of four codebooks with one, two and three left, rows past a tile and fewer than one, widths that end in a tile, one
+# column tile as a convolution has
 SHAPES = [(3001, 7, 16, 3001), (3100, 9, 8, 3017), (3000, 10, 16, 3072), (1500, 64, 16, 2049), (1100, 130, 7, 2190),
-          (2000, 513, 16, 1200), (4097, 32, 16, 1100)]
+          (2000, 513, 16, 1200), (4097, 32, 16, 1100), (1, 16, 16, 1), (63, 17, 16, 65), (257, 18, 5, 63), (1000, 19, 16, 130),
+          (255, 33, 1, 4), (20000, 64, 16, 64), (9000, 16, 8, 32), (300, 512, 16, 200)]
 
 
 @pytest.mark.parametrize("N,C,K,M", SHAPES)
@@ -84,3 +86,19 @@ def test_entries_that_are_not_finite_and_overflow(lut):
     fine = np.isfinite(chain)
     np.testing.assert_array_equal(got[~fine], chain[~fine])
     assert (np.abs(got - total)[fine] <= 41 * 2.0 ** -24 * size[fine]).all()
+
+
+def test_the_switch_pins_the_form(lut):
+    """The three forms add in different orders; both chains give the same sums.  A form the shape cannot take is ignored."""
+    rng = np.random.default_rng(3)
+    T = rng.standard_normal((40, 16, 700)).astype(np.float32)
+    idx = rng.integers(0, 16, (2500, 40)).astype(np.uint8)
+    chain = sums(T, idx, None)[2]
+    np.testing.assert_array_equal(run(lut, T, idx, None, form="rows"), chain)
+    np.testing.assert_array_equal(run(lut, T, idx, None, form="gather"), chain)
+    assert (run(lut, T, idx, None, form="matrix") != chain).any()
+    T, idx = rng.standard_normal((5, 200, 3)).astype(np.float32), rng.integers(0, 200, (300, 5)).astype(np.uint8)
+    for form in ("rows", "gather", "matrix"):
+        np.testing.assert_array_equal(run(lut, T, idx, None, form=form), sums(T, idx, None)[2])
+    with pytest.raises(lut.LutnnError):
+        lut.set_tunable("LUTNN_LOOKUP_F32", "staged")
