@@ -4,8 +4,10 @@
 // The one-hot contraction of lookup_smfmac.hip with every table entry as the sum of three bf16 parts, which hold all of its
 // 24 significant bits (split_bf16.h); the one-hot operand is 1.0 or 0, so that the products are the parts themselves.
 // A slice of four codebooks is summed from zero, low parts first, and then added to the running sum in fp32: only the two
-// instructions with the high parts round at the size of the sum, and the error against 64-bit sums stays below that of the
-// fp32 chain.  Sums that are not finite (an infinite or huge entry, which has no parts and
+// instructions with the high parts round at the size of the sum.  Its error against 64-bit sums is 0.55 to 0.75 of the fp32
+// chain's from 16 codebooks on where the entries are of one size, and no larger where they spread over 2^40 (relative to the
+// sum of the terms' magnitudes: 0.93 at 16 codebooks, 0.83 at 32).  Of fewer codebooks such entries are summed less exactly
+// than by the chain (1.2 times its error at 4, 1.07 at 8), which they are left to.  Sums that are not finite (an infinite or huge entry, which has no parts and
 // reaches every row of its column) are formed again as that chain.
 //
 // What bounds it.  A table value read from LDS serves 64 rows here, where a gather reads it for one; the bound is
@@ -34,6 +36,7 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBM = 256, kBN = 64, kCB = 4;  // rows, columns, codebooks of a stage
 constexpr int kPerCU = 2;                    // workgroups per compute unit
+constexpr int kMinCodebooks = 16;            // precision: see above
 constexpr int kPlane = kCB * 2 * kBN;        // 16-byte units (8 k of one column) per part
 
 __global__ __launch_bounds__(kMfmaThreads, kPerCU) void lookup_matrix_f32_kernel(
@@ -67,7 +70,7 @@ __global__ __launch_bounds__(kMfmaThreads, kPerCU) void lookup_matrix_f32_kernel
             for (int k = 0; k < 8; ++k) value[j][k] = __float_as_uint((slab + (int64_t)min(kh + k, K - 1) * M)[col]);
         }
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {  // the last four where fewer are left (C >= 4)
+        for (int i = 0; i < 2; ++i) {  // the last four where fewer are left
             typedef uint32_t AnyByte __attribute__((aligned(1)));
             word[i] = *reinterpret_cast<const AnyByte*>(irow[i] + min(c0, C - 4));
         }
@@ -160,7 +163,7 @@ __global__ __launch_bounds__(kMfmaThreads, kPerCU) void lookup_matrix_f32_kernel
 }  // namespace
 
 double lookup_matrix_f32_us(int C, int K, int M, int64_t N) {
-    if (K > 16 || C < 4) return 1e30;
+    if (K > 16 || C < kMinCodebooks) return 1e30;
     const int64_t tiles = ((N + kBM - 1) / kBM) * ((M + kBN - 1) / kBN);
     return 8.0 + 0.33 * C * std::max(1.0, (double)tiles / compute_units()) + 1.0e-6 * (double)N * M;
 }
@@ -169,7 +172,7 @@ hipError_t launch_lookup_matrix_f32(const float* T, const float* bias, int C, in
                                     float* Y, int64_t ldy, hipStream_t s) {
     const int64_t row_tiles = (N + kBM - 1) / kBM, tiles = row_tiles * ((M + kBN - 1) / kBN);
     const int64_t blocks = (tiles + 7) / 8 * 8;
-    if (K > 16 || C < 4 || blocks > 0x7fffffffLL || row_tiles > 0x7fffffffLL) return hipErrorInvalidValue;
+    if (K > 16 || C < kMinCodebooks || blocks > 0x7fffffffLL || row_tiles > 0x7fffffffLL) return hipErrorInvalidValue;
     hipLaunchKernelGGL(lookup_matrix_f32_kernel, dim3((unsigned)blocks), dim3(kMfmaThreads), 0, s, T, bias, C, K, M, idx, N, Y,
                        ldy, (int)row_tiles, tiles);
     return hipGetLastError();
