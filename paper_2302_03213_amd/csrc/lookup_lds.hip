@@ -20,6 +20,7 @@
 #include <type_traits>
 
 #include "gather_launch.h"
+#include "lookup_f32_forms.h"
 #include "lutnn_kernels.h"
 
 namespace lutnn {
@@ -269,20 +270,14 @@ hipError_t launch_lookup_lds_i4(const uint8_t* T, const float* scale, const floa
 
 hipError_t launch_lookup_lds_f32(const float* T, const float* bias, int C, int K, int M,
                                  const uint8_t* idx, int64_t N, float* Y, int64_t ldy, hipStream_t s) {
-    // us of the three forms, fitted to sweeps of 100-14000 rows, 16-700 codebooks and 150-3072 columns
-    const double entries = (double)N * C * M;
-    const double matrix = lookup_matrix_f32_us(C, K, M, N);
-    const double rows = rows_kernel_preferred(N, M, K, true) ? 10.0 + 7e-8 * entries + 1.5e-6 * (double)N * M : 1e30;
-    // ns an entry: a workgroup reads 1024 columns, and where a row has 1, 2, 4 or 8 of them an XCD's workgroups keep to the
-    // same columns, which its L2 then holds (300 rows x 512 codebooks, M = 4096 0.25; 400 x 192, M = 3072 0.41)
-    const int per_row = (M + 1023) / 1024;
-    const double gather = 4.0 + (per_row == 1 ? 2e-7 : 8 % per_row == 0 ? 2.4e-7 : 4e-7) * entries;
+    const LookupF32Us us = lookup_f32_us(C, K, M, N, rows_kernel_preferred(N, M, K, true), compute_units());
+    LookupF32 form = us.least(N, M);
     const int pinned = tunable(kTuneLookupF32);
-    if (pinned == 0 && gather_supported<TableF32>(M)) return launch_lookup_lds<TableF32>(T, nullptr, bias, C, K, M, idx, N, Y, ldy, s);
-    if (pinned == 1 && rows_kernel_supported(K, true)) return launch_lookup_rows_f32(T, bias, C, K, M, idx, N, Y, ldy, s);
-    if (pinned == 2 && matrix < 1e30) return launch_lookup_matrix_f32(T, bias, C, K, M, idx, N, Y, ldy, s);
-    if (matrix < rows && matrix < gather) return launch_lookup_matrix_f32(T, bias, C, K, M, idx, N, Y, ldy, s);
-    if (rows < 1e30) return launch_lookup_rows_f32(T, bias, C, K, M, idx, N, Y, ldy, s);
+    if (pinned == 0) form = LookupF32::gather;
+    if (pinned == 1 && rows_kernel_supported(K, true)) form = LookupF32::rows;
+    if (pinned == 2 && us.matrix < LookupF32Us::kNever) form = LookupF32::matrix;
+    if (form == LookupF32::matrix) return launch_lookup_matrix_f32(T, bias, C, K, M, idx, N, Y, ldy, s);
+    if (form == LookupF32::rows) return launch_lookup_rows_f32(T, bias, C, K, M, idx, N, Y, ldy, s);
     return launch_lookup_lds<TableF32>(T, nullptr, bias, C, K, M, idx, N, Y, ldy, s);
 }
 

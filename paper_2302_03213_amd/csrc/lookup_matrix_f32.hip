@@ -162,12 +162,6 @@ __global__ __launch_bounds__(kMfmaThreads, kPerCU) void lookup_matrix_f32_kernel
 
 }  // namespace
 
-double lookup_matrix_f32_us(int C, int K, int M, int64_t N) {
-    if (K > 16 || C < kMinCodebooks) return 1e30;
-    const int64_t tiles = ((N + kBM - 1) / kBM) * ((M + kBN - 1) / kBN);
-    return 8.0 + 0.33 * C * std::max(1.0, (double)tiles / compute_units()) + 1.0e-6 * (double)N * M;
-}
-
 hipError_t launch_lookup_matrix_f32(const float* T, const float* bias, int C, int K, int M, const uint8_t* idx, int64_t N,
                                     float* Y, int64_t ldy, hipStream_t s) {
     const int64_t row_tiles = (N + kBM - 1) / kBM, tiles = row_tiles * ((M + kBN - 1) / kBN);

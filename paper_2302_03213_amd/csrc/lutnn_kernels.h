@@ -157,8 +157,6 @@ hipError_t launch_lookup_rows_f32(const float* T, const float* bias, int C, int 
                                   const uint8_t* idx, int64_t N, float* Y, int64_t ldy, hipStream_t s);
 
 // Eq. 4 for an unquantised table on the 2:4 structured-sparse matrix instructions, from bf16 parts (K <= 16, C >= 16).
-// _us: what it takes, far above any other form's time for shapes it does not run.
-double lookup_matrix_f32_us(int C, int K, int M, int64_t N);
 hipError_t launch_lookup_matrix_f32(const float* T, const float* bias, int C, int K, int M, const uint8_t* idx, int64_t N,
                                     float* Y, int64_t ldy, hipStream_t s);
 
