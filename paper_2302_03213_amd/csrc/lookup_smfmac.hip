@@ -707,14 +707,19 @@ hipError_t launch_lookup_smfmac_i8(const int8_t* packed, const float* scale, con
         case 128: return launch_tm<1>(packed, scale, bias, C, M, idx, ldi, N, Y, ldy, s);
         default: break;
     }
-    // With one or two super-stages a tile is mostly its own write, which lower tiles spread better: 4096 rows, M = 3072, 48
-    // codebooks 19.8 us with 512 rows and 16.7 with 128; 24 codebooks, M = 2304 14.3 and 13.5 with 384; 16384 rows, 20
-    // codebooks, M = 4096 79 and 63.  (The dense kernel, which such numbers of codebooks took: 23, 14.9 and 63.)
-    const bool one = C < 32, two = C > 32 && C < 64;
-    const double c4 = cost(512, 1.0), c3 = cost(384, one ? 0.62 : 0.8), c2 = cost(256, two ? 0.42 : 0.56),
-                 c1 = cost(128, two ? 0.27 : 0.42);
+    // With one or two super-stages a tile is mostly its fill and its write, of which lower tiles have less: prices fitted to all
+    // heights' times over 840 shapes (1500-200000 rows, 8-64 codebooks, 32-4096 columns; the tile chosen takes 1.005 times
+    // the fastest one's time on average, 1.016 before).  16384 rows x 64 codebooks, M = 2304 57 us with 512 rows and 42 with
+    // 256; 16384 x 32, M = 4096 84 and 65 with 384; 16384 x 24, M = 3072 56 and 51 with 256; 4096 x 48, M = 3072 24 and 22
+    // with 128.  One super-stage and one round of 512-row tiles: two rounds of lower ones save nothing (4096 x 24, M = 3072
+    // 20.3 and 20.7 with 256).
+    const int supers = (C + 31) / 32;
+    const double c4 = cost(512, 1.0);
+    const bool first = supers == 1, one = first && c4 > 1.0, two = supers == 2;
+    const double c3 = cost(384, one ? 0.52 : first ? 0.62 : 0.8), c2 = cost(256, one ? 0.38 : two ? 0.46 : 0.56),
+                 c1 = cost(128, one ? 0.31 : two ? 0.26 : 0.42), narrow = cost(512, one ? 0.6 : two ? 0.8 : kNarrowRel, 96);
     const double best = std::min(std::min(c4, c3), std::min(c2, c1));
-    if (narrow_fits && pinned_cols != 128 && (cost(512, kNarrowRel, 96) < best || (pinned_cols == 96 && c4 == best)))
+    if (narrow_fits && pinned_cols != 128 && (narrow < best || (pinned_cols == 96 && c4 == best)))
         return launch_tm<4, 3>(packed, scale, bias, C, M, idx, ldi, N, Y, ldy, s);
     if (c4 == best) return launch_tm<4>(packed, scale, bias, C, M, idx, ldi, N, Y, ldy, s);
     if (c3 == best) return launch_tm<3>(packed, scale, bias, C, M, idx, ldi, N, Y, ldy, s);
