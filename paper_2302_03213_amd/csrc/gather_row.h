@@ -169,6 +169,16 @@ __device__ __forceinline__ void store_columns_of_row(const typename Table::Acc (
         if (Table::kCols == 4 || m + j < M) yrow[m + j] = out[j];
 }
 
+// The same for column m alone.
+template <class Table>
+__device__ __forceinline__ float dequantised(typename Table::Acc sum, const float* __restrict__ scale,
+                                             const float* __restrict__ bias, int m) {
+    if constexpr (std::is_same<Table, TableF32>::value)
+        return bias ? sum + bias[m] : sum;
+    else
+        return bias ? __fmaf_rn((float)sum, *scale, bias[m]) : __fmul_rn((float)sum, *scale);
+}
+
 //   T       table, [C][K] rows; gather_supported(M)
 //   irow    this row's C indices; DWORD: 4-byte aligned
 //   m       first of the lane's columns (< M, a multiple of kCols)
@@ -185,8 +195,8 @@ __device__ __forceinline__ void gather_row(const typename Table::Entry* __restri
 
 // The same for a handful of rows: the SPLIT wavefronts of a workgroup share one row and 64 * kCols columns
 // and take a contiguous range of `per_wave` codebooks each (a multiple of 4); the partial sums meet
-// in LDS and wavefront 0 adds them in range order (exact for integer tables, a fixed order for fp32
-// ones).  Every thread of the workgroup must call it (it holds a barrier); m may lie past M.
+// in LDS and are added in range order (exact for integer tables, a fixed order for fp32
+// ones), a column of every lane to a wavefront.  Every thread of the workgroup must call it (it holds a barrier); m may lie past M.
 template <class Table, class Index, bool DWORD, int SPLIT>
 __device__ __forceinline__ void gather_row_split(const typename Table::Entry* __restrict__ T,
                                                  const float* __restrict__ scale, const float* __restrict__ bias, int C,
@@ -205,14 +215,14 @@ __device__ __forceinline__ void gather_row_split(const typename Table::Entry* __
 #pragma unroll
     for (int j = 0; j < kCols; ++j) part[w][j][lane] = a[j];
     __syncthreads();
-    if (w != 0 || !col_ok) return;
+    if (!col_ok) return;
 #pragma unroll
-    for (int j = 0; j < kCols; ++j) {
+    for (int j = w; j < kCols; j += SPLIT) {
         Acc sum = part[0][j][lane];
+#pragma unroll
         for (int ww = 1; ww < SPLIT; ++ww) sum += part[ww][j][lane];
-        a[j] = sum;
+        if (kCols == 4 || m + j < M) yrow[m + j] = dequantised<Table>(sum, scale, bias, m + j);
     }
-    store_columns_of_row<Table>(a, scale, bias, m, M, yrow);
 }
 
 }  // namespace lutnn

@@ -12,16 +12,19 @@ import pytest
 from paper_2302_03213_amd import build
 
 
-@pytest.fixture(scope="module")
-def isa(tmp_path_factory):
-    out = str(tmp_path_factory.mktemp("isa") / "lookup_smfmac.s")
+def assembly(folder, source):
+    out = str(folder / (source + ".s"))
     flags = [f for f in build.FLAGS if f not in ("-fPIC", "-fvisibility=hidden")]
-    cmd = [build.HIPCC] + flags + ["-S", "--cuda-device-only", "-o", out,
-                                   os.path.join(build.CSRC, "lookup_smfmac.hip")]
+    cmd = [build.HIPCC] + flags + ["-S", "--cuda-device-only", "-o", out, os.path.join(build.CSRC, source)]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
     with open(out) as f:
         return f.read().split("\n")
+
+
+@pytest.fixture(scope="module")
+def isa(tmp_path_factory):
+    return assembly(tmp_path_factory.mktemp("isa"), "lookup_smfmac.hip")
 
 
 def kernel_body(lines, mangled_args):
@@ -58,6 +61,14 @@ INSTANCES = {
     "256x128": "ILi2ELi4ELb0ELb0E",
     "128x128": "ILi1ELi4ELb0ELb0E",
     "512x128 split": "ILi4ELi4ELb1ELb0E",
+    # any number of codebooks: rows of zeros past the last one
+    "512x128 streamed, any C": "ILi4ELi12ELb0ELb1E",
+    "512x128, any C": "ILi4ELi12ELb0ELb0E",
+    "384x128, any C": "ILi3ELi12ELb0ELb0E",
+    "256x128, any C": "ILi2ELi12ELb0ELb0E",
+    "128x128, any C": "ILi1ELi12ELb0ELb0E",
+    "256x128 split, any C": "ILi2ELi12ELb1ELb0E",
+    "128x128 split, any C": "ILi1ELi12ELb1ELb0E",
 }
 
 
@@ -92,3 +103,9 @@ def test_steady_state_loop_of_the_benchmark_instance_keeps_its_instruction_budge
     assert n_mfma == 192, n_mfma
     assert n_dma == 32, n_dma   # 3 stages x 8 table loads + their share of the index loads
     assert n_valu <= 430, "%d vector instructions per 192 matrix instructions" % n_valu
+
+
+def test_gathers_keep_their_rows_in_registers(tmp_path):
+    """Sixteen table rows in flight and, in the split form, sixteen wavefronts' sums to add: nothing of it in scratch memory."""
+    sizes = [int(l.split(":")[1]) for l in assembly(tmp_path, "lookup_lds.hip") if l.startswith("; ScratchSize:")]
+    assert len(sizes) >= 24 and not any(sizes), sizes
