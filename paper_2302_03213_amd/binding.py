@@ -11,6 +11,7 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import warnings
 
 import torch
 
@@ -66,17 +67,19 @@ class _CTree(ctypes.Structure):
                 ("threshold", ctypes.c_void_p)]
 
 
-def _is_current(path):
-    """True if the library file was compiled from the sources as they are now: its version string
+def _is_current(path, wanted):
+    """True if the file is there and was compiled from the sources as they are now: its version string
     (lutnn_version()) ends in their hash.  Read from the file, so a stale library is never mapped."""
+    if not os.path.exists(path):
+        return False
     with open(path, "rb") as f:
-        return (b"+" + _build.source_hash().encode() + b"\0") in f.read()
+        return (b"+" + wanted.encode() + b"\0") in f.read()
 
 
 def _load():
     path = _build.LIB
-    if not all(os.path.exists(p) and _is_current(p) for p in (path, _build.TORCH_CALLS)):
-        _build.build()  # raises if a compiler is missing or the compile fails
+    if not _is_current(path, _build.source_hash()):
+        _build.build_library()  # raises if hipcc is missing or the compile fails
     lib = ctypes.CDLL(path)
     missing = [name for name in EXPORTS if not hasattr(lib, name)]
     if missing:
@@ -168,7 +171,20 @@ def _load():
     return lib
 
 
+class _NoCalls:
+    """In the native calls' place where they cannot be built: everything takes the Python way."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
 def _load_torch_calls():
+    if not _is_current(_build.TORCH_CALLS, _build.torch_calls_hash()):
+        try:
+            _build.build_torch_calls()
+        except (OSError, RuntimeError) as e:  # no C++ compiler, no Python headers: the kernels need neither
+            warnings.warn("torch_calls.so is not there for this torch and cannot be built; calls take 2-3 us longer: %s" % e)
+            return _NoCalls()
     loader = importlib.machinery.ExtensionFileLoader("torch_calls", _build.TORCH_CALLS)
     module = importlib.util.module_from_spec(importlib.util.spec_from_loader("torch_calls", loader))
     loader.exec_module(module)

@@ -9,8 +9,8 @@ import concurrent.futures
 import hashlib
 import importlib.util
 import os
+import shutil
 import subprocess
-import sys
 import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -47,6 +47,13 @@ def source_hash():
     return h.hexdigest()[:12]
 
 
+def torch_calls_hash():
+    """The same for torch_calls.so, which is bound to the interpreter and to torch's C++ classes as well."""
+    import torch
+    made_for = (source_hash(), torch.__version__, str(torch.version.git_version), str(sysconfig.get_config_var("SOABI")))
+    return hashlib.sha256("\0".join(made_for).encode()).hexdigest()[:12]
+
+
 def _compile(src):
     obj = os.path.join(OBJDIR, os.path.splitext(src)[0] + ".o")
     cmd = [HIPCC] + FLAGS + ["-c", os.path.join(CSRC, src), "-o", obj]
@@ -61,6 +68,12 @@ def _compile(src):
 
 
 def build(verbose=False):
+    build_library(verbose)
+    build_torch_calls()
+    return LIB
+
+
+def build_library(verbose=False):
     os.makedirs(OBJDIR, exist_ok=True)
     with concurrent.futures.ThreadPoolExecutor(max_workers=6) as ex:
         results = list(ex.map(_compile, SOURCES))
@@ -71,16 +84,24 @@ def build(verbose=False):
     objs = [o for o, _ in results]
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     subprocess.run(cmd, check=True)
-    _build_torch_calls()
-    return LIB
 
 
-def _build_torch_calls():
+def _rocm_include():
+    """Where the HIP headers of the compiler's installation are."""
+    hipcc = os.path.abspath(shutil.which(HIPCC) or HIPCC)
+    for path in (hipcc, os.path.realpath(hipcc)):
+        include = os.path.join(os.path.dirname(os.path.dirname(path)), "include")
+        if os.path.exists(os.path.join(include, "hip", "hip_runtime.h")):
+            return include
+    return "/opt/rocm/include"
+
+
+def build_torch_calls():
     torch = importlib.util.find_spec("torch").submodule_search_locations[0]
     include, lib = os.path.join(torch, "include"), os.path.join(torch, "lib")
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
-           '-DLUTNN_SOURCE_HASH="%s"' % source_hash(), "-I", include, "-I", os.path.join(include, "torch", "csrc", "api", "include"),
-           "-I", os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"), "-I", sysconfig.get_paths()["include"], "-I", INCLUDE,
+           '-DLUTNN_SOURCE_HASH="%s"' % torch_calls_hash(), "-I", include, "-I", os.path.join(include, "torch", "csrc", "api", "include"),
+           "-I", _rocm_include(), "-I", sysconfig.get_paths()["include"], "-I", INCLUDE,
            os.path.join(CSRC, "torch_calls.cpp"), "-o", TORCH_CALLS, "-L", PKG, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN",
            "-L", lib, "-ltorch", "-ltorch_cpu", "-ltorch_hip", "-lc10", "-lc10_hip", "-ltorch_python"]
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -266,7 +266,8 @@ PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "torch_calls", nullptr, -1, kMetho
 
 }  // namespace
 
-// Built from sources of this hash: the loader can tell a stale file by it, as it does the library's.
+// Built from sources, and for a torch and an interpreter, of this hash: the loader can tell a stale file by it, as it does
+// the library's.
 extern "C" __attribute__((used, visibility("default"))) const char lutnn_torch_calls_version[] = "+" LUTNN_SOURCE_HASH;
 
 PyMODINIT_FUNC PyInit_torch_calls() { return PyModule_Create(&kModule); }

@@ -1,5 +1,7 @@
 """The native calls behind binding.py's per-step functions take the plain case only and leave the rest, errors included, to
 the Python way (no GPU needed for what they refuse)."""
+import os
+
 import pytest
 import torch
 
@@ -26,6 +28,33 @@ def test_tensors_that_are_not_on_the_gpu_are_left_alone():
         lut.linear(l, X)
     with pytest.raises(AssertionError):
         lut.conv2d(l, torch.zeros((1, 2, 2, 2)), 1)
+
+
+def test_the_file_is_bound_to_torch_and_the_interpreter(monkeypatch):
+    build, is_current = binding._build, binding._is_current
+    made = build.torch_calls_hash()
+    assert is_current(build.TORCH_CALLS, made) and not is_current(build.TORCH_CALLS + ".gone", made)
+    monkeypatch.setattr(torch, "__version__", "2.11.0")
+    assert not is_current(build.TORCH_CALLS, build.torch_calls_hash())
+    monkeypatch.undo()
+    monkeypatch.setattr(build.sysconfig, "get_config_var", lambda name: "cpython-313-x86_64-linux-gnu")
+    assert not is_current(build.TORCH_CALLS, build.torch_calls_hash())
+
+
+def test_headers_are_found_for_a_compiler_on_the_path(monkeypatch):
+    monkeypatch.setenv("PATH", os.path.dirname(binding._build.HIPCC), prepend=os.pathsep)
+    monkeypatch.setattr(binding._build, "HIPCC", "hipcc")
+    assert os.path.exists(os.path.join(binding._build._rocm_include(), "hip", "hip_runtime.h"))
+
+
+def test_without_a_compiler_everything_takes_the_python_way(monkeypatch, tmp_path):
+    def fails():
+        raise RuntimeError("no g++")
+    monkeypatch.setattr(binding._build, "TORCH_CALLS", str(tmp_path / "torch_calls.so"))
+    monkeypatch.setattr(binding._build, "build_torch_calls", fails)
+    with pytest.warns(UserWarning, match="no g[+][+]"):
+        calls = binding._load_torch_calls()
+    assert calls.linear(1, 2) is None and calls.bias_gradient(3) is None
 
 
 @pytest.mark.gpu
