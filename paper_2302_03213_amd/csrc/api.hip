@@ -512,11 +512,13 @@ inline int small_table_kind(const lutnn_layer* L) {
 }
 
 // The layers for which the calls with a variant count the one-launch kernel among their forms: whole groups of four
-// columns, rows that tile a wavefront, aligned fp32 and INT8 tables.  (The kernel runs any width and type; the calls
-// without a variant use it there too.)
+// columns, rows that tile a wavefront, aligned fp32 and INT8 tables, and 32 KiB for the indices of as many rows as four
+// wavefronts hold.  (The kernel runs any width and type, and fewer rows at a time; the calls without a variant use it there
+// too.)
 bool one_launch_form(const lutnn_layer* L) {
     const int kind = small_table_kind(L);
-    return kind != 2 && L->M % 4 == 0 && (L->M >= 256 || 64 % (L->M / 4) == 0) && aligned(L->table, kind == 0 ? 16 : 4) &&
+    const int rows = L->M < 256 ? 4 * (256 / L->M) : L->M <= 256 ? 4 : L->M <= 768 ? 2 : 1;
+    return (int64_t)rows * ((L->C + 3) & ~3) <= 32 * 1024 && kind != 2 && L->M % 4 == 0 && (L->M >= 256 || 64 % (L->M / 4) == 0) && aligned(L->table, kind == 0 ? 16 : 4) &&
            lutnn::linear_small_supported(L->table, kind, L->C, L->K, L->V, L->M);
 }
 

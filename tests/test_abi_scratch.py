@@ -50,6 +50,22 @@ def test_what_is_refused():
     assert name(conv(layer(), None, 16, ctypes.byref(geom), Y, 1000, S, rows * 128, None)) == NULL
 
 
+def test_one_launch_with_a_variant_takes_the_layers_it_took():
+    """Long rows of indices for many narrow outputs: refused by the calls with a variant, run by those without."""
+    linear, tree_call = lut.LIB.lutnn_linear, lut.LIB.lutnn_linear_tree
+    FUSED, AUTO = lut.binding.VARIANT_FUSED, lut.binding.VARIANT_AUTO
+    for C, M in [(2799, 64), (318, 4), (516, 16), (8193, 256), (16500, 768)]:
+        l = layer(C=C, K=64, V=1, M=M, dtype=lut.TABLE_F32, packed=None)
+        assert name(linear(l, X, 3, C, Y, M, FUSED, S, None)) == UNSUPPORTED
+        assert name(linear(l, X, 3, C, Y, M, AUTO, None, None)) == NULL
+        assert lut.LIB.lutnn_linear_auto_variant(l, None, 3) == lut.binding.VARIANT_LDS
+        tree = lut.binding._CTree(C, 1, 6, 0, 0x80000, 0x90000)
+        assert name(tree_call(l, ctypes.byref(tree), X, 3, C, Y, M, FUSED, S, None)) == UNSUPPORTED
+    for C, M in [(2048, 64), (128, 4), (8192, 256), (16384, 768), (32768, 1024)]:
+        l = layer(C=C, K=64, V=1, M=M, dtype=lut.TABLE_F32, packed=None)
+        assert lut.LIB.lutnn_linear_auto_variant(l, None, 3) == FUSED
+
+
 @pytest.mark.parametrize("args,want", [((X, 100, 7, 8, 1, Y, S, 1 << 20, None), SHAPE), ((X, 100, 8, 3, 1, Y, S, 1 << 20, None), UNSUPPORTED),
                                        ((X, 100, 8, 8, 0, Y, S, 1 << 20, None), SHAPE), ((X, -1, 8, 8, 1, Y, S, 1 << 20, None), SHAPE),
                                        ((None, 100, 8, 8, 1, Y, S, 1 << 20, None), NULL), ((X, 100, 8, 8, 1, None, S, 1 << 20, None), NULL),
