@@ -69,7 +69,9 @@ typedef enum {
     LUTNN_VARIANT_FUSED = 3, /* lutnn_linear only: one kernel, indices never leave the chip          */
     LUTNN_VARIANT_SMFMAC = 4 /* as MFMA, on the 2:4 structured-sparse matrix instructions: a one-hot
                                 slice is 2:4 sparse by construction, so the result is identical at
-                                twice the matrix rate.  Needs C % 32 == 0, 16-byte aligned idx.
+                                twice the matrix rate.  Needs C % 32 == 0, 16-byte aligned idx
+                                (other C take MFMA here, and SMFMAC only in the calls that lay
+                                out their own scratch: lutnn_linear_scratch ...).
                                 The rows per workgroup tile and whether a tile's codebooks are
                                 shared out over several workgroups are priced by the library;
                                 lutnn_set_tunable pins either (results are the same)                */
@@ -473,10 +475,18 @@ LUTNN_API int32_t lutnn_auto_variant(const lutnn_layer* layer, const uint8_t* id
 /*
  * Host: the same for lutnn_linear(layer, X, N, ..., LUTNN_VARIANT_AUTO, idx_workspace, ...):
  * LUTNN_VARIANT_FUSED where one launch does both steps, else what lutnn_auto_variant returns for
- * the lookup that follows the encoding.  Returns -1 for a NULL layer.
+ * the lookup that follows the encoding.  Returns -1 for a NULL layer.  (The calls with a scratch
+ * of the library's own layout choose otherwise: lutnn_scratch_variant.)
  */
 LUTNN_API int32_t lutnn_linear_auto_variant(const lutnn_layer* layer, const uint8_t* idx_workspace,
                                             int64_t N);
+
+/*
+ * Host: the same for the calls with a scratch: lutnn_linear_scratch (call = 0), lutnn_linear_tree_scratch
+ * (1), lutnn_conv2d_scratch and lutnn_conv2d_tree_scratch (2).  LUTNN_VARIANT_FUSED where one launch
+ * does both steps, else the lookup behind the encoder: _SMFMAC or _LDS.  Returns -1 for what is refused.
+ */
+LUTNN_API int32_t lutnn_scratch_variant(const lutnn_layer* layer, int64_t N, int32_t call);
 
 /* Host: static name of a status code. */
 LUTNN_API const char* lutnn_status_string(int32_t status);

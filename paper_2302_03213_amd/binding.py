@@ -38,7 +38,7 @@ EXPORTS = ["lutnn_softpq_backward_static", "lutnn_set_tunable", "lutnn_encode_tr
            "lutnn_auto_variant", "lutnn_linear_auto_variant", "lutnn_status_string", "lutnn_last_error", "lutnn_version",
            "lutnn_probe_smfmac_stream", "lutnn_linear_scratch", "lutnn_linear_tree_scratch", "lutnn_linear_scratch_bytes",
            "lutnn_conv2d_scratch_bytes", "lutnn_conv2d_scratch", "lutnn_conv2d_tree_scratch", "lutnn_bias_gradient",
-           "lutnn_bias_gradient_workspace_bytes"]
+           "lutnn_bias_gradient_workspace_bytes", "lutnn_scratch_variant"]
 
 
 class LutnnError(RuntimeError):
@@ -158,6 +158,8 @@ def _load():
                                  i32, vp, vp]
     lib.lutnn_auto_variant.restype = i32
     lib.lutnn_auto_variant.argtypes = [ctypes.POINTER(_CLayer), vp, i64]
+    lib.lutnn_scratch_variant.restype = i32
+    lib.lutnn_scratch_variant.argtypes = [ctypes.POINTER(_CLayer), i64, i32]
     lib.lutnn_linear_auto_variant.restype = i32
     lib.lutnn_linear_auto_variant.argtypes = [ctypes.POINTER(_CLayer), vp, i64]
     lib.lutnn_status_string.restype = ctypes.c_char_p
@@ -649,16 +651,25 @@ def conv2d_tree(layer, tree, inp, kernel, stride=1, pad=0, variant="auto", out=N
 
 
 def auto_variant(layer, N, idx=None):
-    """lutnn_auto_variant: name of the lookup variant that "auto" stands for at this shape."""
+    """lutnn_auto_variant: name of the lookup variant that "auto" stands for at this shape: in lookup(layer, idx), and in
+    linear, linear_tree and conv2d with `idx` as their workspace.  Without one they run what scratch_variant names."""
     code = LIB.lutnn_auto_variant(layer.ref, _ptr(idx), N)
     return {v: k for k, v in VARIANTS.items()}[code]
 
 
 def linear_auto_variant(layer, N, idx_workspace=None):
     """lutnn_linear_auto_variant: name of what lutnn_linear runs for "auto" at this shape ("fused" =
-    one launch does both steps)."""
+    one launch does both steps): linear(layer, X, idx_workspace=...).  Without a workspace it runs what scratch_variant
+    names."""
     code = LIB.lutnn_linear_auto_variant(layer.ref, _ptr(idx_workspace), N)
     return {v: k for k, v in VARIANTS.items()}[code]
+
+
+def scratch_variant(layer, N, call="linear"):
+    """lutnn_scratch_variant: name of what "auto" without a workspace runs at this shape ("fused" = one launch does both
+    steps); call: "linear", "linear_tree" or "conv2d" (with either encoder)."""
+    code = LIB.lutnn_scratch_variant(layer.ref, N, ("linear", "linear_tree", "conv2d").index(call))
+    return {v: k for k, v in VARIANTS.items()}.get(code)
 
 
 def linear(layer, X, variant="auto", out=None, idx_workspace=None):

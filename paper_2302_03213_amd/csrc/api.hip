@@ -761,6 +761,12 @@ lutnn_status lutnn_linear_tree_scratch(const lutnn_layer* layer, const lutnn_tre
     });
 }
 
+int32_t lutnn_scratch_variant(const lutnn_layer* layer, int64_t N, int32_t call) {
+    if (check_layer(layer) != LUTNN_OK || N <= 0 || N >= kMaxRows || call < 0 || call > 2) return -1;
+    if (call < 2 && small_preferred(layer, N, call == 1, true)) return LUTNN_VARIANT_FUSED;
+    return two_step(layer, N).variant;
+}
+
 size_t lutnn_conv2d_scratch_bytes(const lutnn_layer* layer, int64_t N) {
     if (check_layer(layer) != LUTNN_OK || N <= 0 || N >= kMaxRows) return 0;
     return (size_t)N * two_step(layer, N).ldi;

@@ -29,6 +29,21 @@ def test_scratch_bytes():
     assert lut.LIB.lutnn_conv2d_scratch_bytes(layer(), 5000) == 5000 * 128
 
 
+def test_the_variant_that_runs():
+    """... agrees with the scratch that is asked for: none for one launch, padded index rows for the sparse lookup."""
+    f, bytes_of = lut.LIB.lutnn_scratch_variant, lut.LIB.lutnn_linear_scratch_bytes
+    FUSED, SMFMAC, LDS = lut.binding.VARIANT_FUSED, lut.binding.VARIANT_SMFMAC, lut.binding.VARIANT_LDS
+    assert f(layer(), 5000, 0) == f(layer(), 5000, 1) == f(layer(), 5000, 2) == SMFMAC  # any number of codebooks
+    assert f(layer(M=37, C=20), 8, 0) == f(layer(dtype=lut.TABLE_I4), 1, 1) == FUSED  # any width, INT4
+    assert f(layer(M=37, C=20), 8, 2) == f(layer(K=40, packed=None), 5000, 0) == LDS
+    for C in (20, 75, 128, 700):
+        for N in (1, 40, 1000, 9000):
+            for tree in (0, 1):
+                v, n = f(layer(C=C), N, tree), bytes_of(layer(C=C), N, tree)
+                assert n == {FUSED: 0, SMFMAC: N * ((C + 31) // 32 * 32), LDS: N * C}[v]
+    assert f(layer(), 0, 0) == f(None, 10, 0) == f(layer(C=0), 10, 0) == f(layer(), 10, 3) == -1
+
+
 def test_what_is_refused():
     call = lut.LIB.lutnn_linear_scratch
     n = 5000 * 128
