@@ -23,12 +23,14 @@ def check(got, G, dims):
 def test_rows(binding, N, M):
     wide = torch.randn((N, M + 3), device="cuda")
     for G in (wide[:, 3:], wide[:, :M].contiguous()):
+        assert binding._calls.bias_gradient(G) is not None
         check(binding._bias_gradient(G), G, 0)
 
 
 @pytest.mark.parametrize("B,M,H,W", [(1, 1, 7, 7), (5, 3, 1, 2), (33, 64, 14, 14), (2, 130, 56, 57), (3, 5, 1, 1), (0, 4, 3, 3)])
 def test_planes(binding, B, M, H, W):
     G = torch.randn((B, M, H, W), device="cuda")
+    assert binding._calls.bias_gradient(G) is not None
     check(binding._bias_gradient(G), G, (0, 2, 3))
 
 
@@ -38,6 +40,7 @@ def test_planes(binding, B, M, H, W):
 def test_one_rounding(binding, shape):
     G = torch.randn(shape, device="cuda") + (0.25 if shape[0] % 2 else 0.0)
     dims = (0,) + tuple(range(2, len(shape)))
+    assert binding._calls.bias_gradient(G) is not None
     D = G.cpu().double()
     exact, size = D.sum(dim=dims), D.abs().sum(dim=dims)
     assert ((binding._bias_gradient(G).cpu().double() - exact).abs() <= 2.0 ** -24 * exact.abs() + 2.0 ** -46 * size).all()

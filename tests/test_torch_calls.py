@@ -105,3 +105,86 @@ def test_where_tensors_give_no_pointers_the_python_way_reports_it():
     with Refuses(), pytest.raises(ValueError, match="refused"):
         lut.linear(l, X)
     assert lut.linear(l, X).shape == (300, 40)
+
+
+def small_layers():
+    """A layer per kind of call: (function of fresh inputs, its inputs)."""
+    from paper_2302_03213_amd.softpq import SoftPQConv2d, SoftPQLinear
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(4)
+
+    def normal(*shape):
+        return torch.randn(shape, generator=gen, device="cuda")
+
+    P, W = normal(12, 16, 4), normal(48, 40)
+    tables = [lut.build_table(P, W, t) for t in (lut.TABLE_F32, lut.TABLE_I8, lut.TABLE_I4)]
+    tree = lut.LutTree(torch.zeros((12, 15), dtype=torch.int32, device="cuda"), normal(12, 15), 4)
+    deep = lut.LutTree(torch.zeros((12, 1023), dtype=torch.int32, device="cuda"), normal(12, 1023), 4)
+    deep_table = lut.build_table(normal(12, 1024, 4), W, lut.TABLE_I8)
+
+    def step(layer, x):
+        x = x.detach().requires_grad_(True)
+        Y = layer(x)
+        return (Y.detach(),) + torch.autograd.grad(Y.square().sum(), (x, layer.centroids, layer.temperature, layer.bias))
+
+    linear, conv = SoftPQLinear(P, W, bias=normal(40)), SoftPQConv2d(P, W, 2, 1, 1, bias=normal(40))
+    return [(lambda x: [lut.linear(t, x) for t in tables], normal(300, 48)), (lambda x: lut.linear_tree(tables[1], tree, x), normal(2000, 48)),
+            (lambda x: lut.linear_tree16(deep_table, deep, x), normal(100, 48)), (lambda x: lut.conv2d(tables[1], x, 2, 1, 1), normal(3, 12, 9, 9)),
+            (lambda x: step(linear, x), normal(500, 48)), (lambda x: step(conv, x), normal(3, 12, 9, 9))]
+
+
+def flat(outputs):
+    return list(outputs) if isinstance(outputs, (list, tuple)) else [outputs]
+
+
+@pytest.mark.gpu
+def test_every_native_call_takes_the_plain_case_and_agrees_with_the_python_way(monkeypatch):
+    taken, native = set(), binding._calls
+
+    class Watched:
+        def __getattr__(self, name):
+            def call(*args):
+                got = getattr(native, name)(*args)
+                if got is not None:
+                    taken.add(name)
+                return got
+            return call
+
+    layers = small_layers()
+    monkeypatch.setattr(binding, "_calls", Watched())
+    got = [flat(f(x)) for f, x in layers]
+    assert taken == {"linear", "linear_tree16", "conv2d", "build_table", "linear_gradient", "softpq_backward",
+                     "softpq_backward_conv2d", "bias_gradient"}
+    monkeypatch.setattr(binding, "_calls", binding._NoCalls())
+    for (f, x), outputs in zip(layers, got):
+        for a, b in zip(outputs, flat(f(x))):
+            # torch's own sum stands for the bias gradient on the Python way
+            assert torch.equal(a, b) or (a.shape == (40,) and torch.allclose(a, b, rtol=1e-5, atol=1e-4))
+
+
+@pytest.mark.gpu
+def test_other_streams_and_threads():
+    """Each thread on a stream of its own: outputs and scratch come from that stream's memory."""
+    import threading
+    layers = small_layers()
+    wanted = [[t.clone() for t in flat(f(x))] for f, x in layers]
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(first):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            for i in range(40):
+                n = (first + i) % len(layers)
+                f, x = layers[n]
+                outputs = flat(f(x))
+                stream.synchronize()
+                if not all(torch.equal(a, b) for a, b in zip(outputs, wanted[n])):
+                    wrong.append(n)
+
+    threads = [threading.Thread(target=work, args=(n,)) for n in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
