@@ -326,6 +326,10 @@ bool linear_small_preferred(const void* T, int table_kind, int C, int K, int V, 
     const SmallPlan p = make_plan(C, M, N, cols);
     const double round_us = tree ? 1.0 : 0.45 * (1 + V) * K / 16;
     if (4.2 + round_us * (double)std::min<int64_t>(p.R, N) * C / kSmallThreads > 10.5) return false;
+    // ... and the searches that all workgroups repeat keep the vector units busy, a wavefront's 64 lanes full or not: 1369
+    // rows x 1 codebook of 256, V = 32, M = 4096 382 us, in two launches 72; 2847 x 1 of 64, V = 2, M = 3072 54 and 20
+    const double search_us = tree ? 0 : 4.9e-6 * p.blocks * ((std::min<int64_t>(p.R, N) * C + 63) / 64) * K * V;
+    if (search_us > 2.0) return false;
     return C <= 128 && (double)N * C * p.col_groups <= 32768.0;
 }
 

@@ -44,6 +44,15 @@ def test_the_variant_that_runs():
     assert f(layer(), 0, 0) == f(None, 10, 0) == f(layer(C=0), 10, 0) == f(layer(), 10, 3) == -1
 
 
+def test_one_launch_where_the_searches_are_few():
+    """Every workgroup repeats the searches of its rows: thousands of workgroups and long searches take two launches."""
+    f = lut.LIB.lutnn_scratch_variant
+    FUSED, LDS = lut.binding.VARIANT_FUSED, lut.binding.VARIANT_LDS
+    for C, K, V, M, N, want in [(1, 256, 32, 4096, 1369, LDS), (3, 256, 32, 4096, 1038, LDS), (1, 64, 2, 3072, 2847, LDS), (1, 256, 2, 256, 200, FUSED),
+                                (6, 16, 8, 4096, 300, FUSED), (20, 100, 2, 128, 15, FUSED)]:
+        assert f(layer(C=C, K=K, V=V, M=M, dtype=lut.TABLE_F32, packed=None), N, 0) == want, (C, K, V, M, N)
+
+
 def test_what_is_refused():
     call = lut.LIB.lutnn_linear_scratch
     n = 5000 * 128
