@@ -235,7 +235,9 @@ bool gather_preferred_t(int C, int K, int M, int64_t N, bool sparse_ok) {
     // gather only wins below ~5.6e7 entries.
     const double entries = (double)N * C * M;
     if (C >= 512 && sparse_ok) return entries <= 5.6e7;
-    const double t_gather = 0.0038 + 8.9e-11 * entries;
+    // (Outputs cost the gather more than the matrix forms, which have whole tiles to write: 1311 rows x 2 codebooks, M =
+    // 3436, INT4 18.5 us and 11.9, whole calls.)
+    const double t_gather = 0.0038 + 8.9e-11 * entries + (std::is_same<Table, TableI4>::value ? 1.9e-9 : 5e-10) * (double)N * M;
     const double t_matrix = sparse_ok ? 0.0065 + 1.6e-5 * C : 0.0062 + 1.2e-4 * C;
     return t_gather < t_matrix;
 }

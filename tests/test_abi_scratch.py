@@ -53,6 +53,14 @@ def test_one_launch_where_the_searches_are_few():
         assert f(layer(C=C, K=K, V=V, M=M, dtype=lut.TABLE_F32, packed=None), N, 0) == want, (C, K, V, M, N)
 
 
+def test_few_codebooks_and_many_outputs_take_the_matrix_form():
+    f, MFMA = lut.LIB.lutnn_scratch_variant, lut.binding.VARIANT_MFMA
+    for C, M, N, dtype in [(2, 3436, 1311, lut.TABLE_I4), (1, 2368, 1323, lut.TABLE_I4), (4, 2944, 1282, lut.TABLE_I4), (3, 234, 17210, lut.TABLE_I4)]:
+        assert f(layer(C=C, V=2, M=M, dtype=dtype), N, 2) == MFMA, (C, M, N)
+    for C, M, N, dtype in [(64, 64, 3136, lut.TABLE_I8), (2, 300, 200, lut.TABLE_I4), (20, 128, 5000, lut.TABLE_I8)]:
+        assert f(layer(C=C, V=2, M=M, dtype=dtype), N, 2) == lut.binding.VARIANT_LDS, (C, M, N)
+
+
 def test_what_is_refused():
     call = lut.LIB.lutnn_linear_scratch
     n = 5000 * 128
