@@ -21,15 +21,31 @@ __global__ __launch_bounds__(kGatherThreads) void lookup_global_kernel(
     const int64_t n = i / M;
     const int m = (int)(i % M);
     typename Table::Acc acc = 0;
-    for (int c = 0; c < C; ++c) {
-        int k = idx[n * C + c];
+    const Index* __restrict__ irow = idx + n * C;
+    const auto entry = [&](int c, int k) {
         k = k < K ? k : K - 1;
-        const typename Table::Entry e = T[((size_t)c * K + k) * Table::row_entries(M) + Table::offset(m)];
+        return T[((size_t)c * K + k) * Table::row_entries(M) + Table::offset(m)];
+    };
+    const auto add = [&](typename Table::Entry e) {
         if constexpr (std::is_same<Table, TableI4>::value)
             acc += (int32_t)((((m & 1) ? e >> 4 : e & 0xf) ^ 8) - 8);
         else
             acc += (typename Table::Acc)e;
+    };
+    // eight codebooks' indices in flight, then their entries, added in codebook order
+    constexpr int kBatch = 8;
+    int c = 0;
+    for (; c + kBatch <= C; c += kBatch) {
+        int k[kBatch];
+        typename Table::Entry e[kBatch];
+#pragma unroll
+        for (int b = 0; b < kBatch; ++b) k[b] = irow[c + b];
+#pragma unroll
+        for (int b = 0; b < kBatch; ++b) e[b] = entry(c + b, k[b]);
+#pragma unroll
+        for (int b = 0; b < kBatch; ++b) add(e[b]);
     }
+    for (; c < C; ++c) add(entry(c, irow[c]));
     if constexpr (std::is_same<Table, TableF32>::value)
         Y[n * ldy + m] = bias ? acc + bias[m] : acc;
     else

@@ -35,7 +35,7 @@ inline LookupF32Us lookup_f32_us(int C, int K, int M, int64_t N, bool rows_ok, i
     // The gather reads every entry from L2, or from behind it where the table is larger than 4 MB: up to 0.5 ps more per entry.
     // A row of 8, 16 or 32 wavefronts keeps an XCD's workgroups to a half, a quarter or an eighth of the columns, and the
     // misses of its L2 are fewer (300 rows x 512 codebooks, M = 4096 180 us; 400 x 192, M = 3072, twice the time an entry).
-    // Rows of fewer than four columns have a thread per output in its place, which reads the row's indices byte by byte.
+    // Rows of fewer than four columns have a thread per output in its place, eight codebooks in flight.
     if (M >= 4) {
         const int across = (M + 255) / 256;
         const bool shared = across == 8 || across == 16 || across == 32;
@@ -43,7 +43,7 @@ inline LookupF32Us lookup_f32_us(int C, int K, int M, int64_t N, bool rows_ok, i
         const double per_entry = shared ? 0.115 + 0.052 * std::clamp(behind - 1.5, 0.0, 4.5) : 0.14 + 0.082 * std::clamp(behind - 1.8, 0.0, 4.5);
         us.gather = 5 + per_entry * entries + 0.75 * outputs;
     } else {
-        us.gather = 5 + 0.18 * C + 1.5e-6 * (double)N * C * (1 + M) * std::sqrt(C / 64.0);
+        us.gather = 5 + 0.05 * C + 1e-6 * (double)N * C * (0.2 + 0.45 * M);
     }
 
     // Lane = row: four workgroups of a compute unit stage their slabs side by side, and widths that are no multiple of four

@@ -53,7 +53,7 @@ MEASURED = [(16384, 4, 16, 1024, "gather"),    # 23, 48, -
             (3260, 96, 16, 1647, "matrix"),    # 164, 121, 61
             (18236, 567, 8, 384, "matrix"),    # 697, 481, 283
             (5204, 133, 16, 3200, "matrix"),   # 985, 309, 195
-            (300000, 256, 16, 3, "matrix"),    # 567, 379, 329
+            (300000, 256, 16, 3, "gather"),    # 139, 379, 329
             (2000000, 1, 16, 1, "gather")]     # 6, 47, -
 
 
