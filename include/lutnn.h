@@ -484,7 +484,8 @@ LUTNN_API int32_t lutnn_linear_auto_variant(const lutnn_layer* layer, const uint
 /*
  * Host: the same for the calls with a scratch: lutnn_linear_scratch (call = 0), lutnn_linear_tree_scratch
  * (1), lutnn_conv2d_scratch and lutnn_conv2d_tree_scratch (2).  LUTNN_VARIANT_FUSED where one launch
- * does both steps, else the lookup behind the encoder: _SMFMAC or _LDS.  Returns -1 for what is refused.
+ * does both steps, else the lookup behind the encoder: _SMFMAC, _MFMA (eight codebooks or fewer) or _LDS.
+ * Returns -1 for what is refused.
  */
 LUTNN_API int32_t lutnn_scratch_variant(const lutnn_layer* layer, int64_t N, int32_t call);
 

@@ -522,13 +522,18 @@ bool one_launch_form(const lutnn_layer* L) {
            lutnn::linear_small_supported(L->table, kind, L->C, L->K, L->V, L->M);
 }
 
+// Any number of codebooks can take the sparse kernel behind an encoder that pads its index rows; but it walks 32 of them at a
+// time, rows of zeros included, where the dense one walks eight (9805 rows x 2 codebooks, M = 2692 37 us and 25; 11744 x 7,
+// M = 1280 26 and 19; from nine on the sparse one is as fast or faster).
+bool sparse_worthwhile(int C) { return C > 8; }
+
 // The one-launch kernel is worth it where the lookup it replaces would be the gather anyway (the
 // indices it would see are 16-byte aligned in LDS, so the sparse kernel counts as available when
 // the shape allows it; any_codebooks: whatever C).
 bool small_preferred(const lutnn_layer* L, int64_t N, bool tree, bool any_codebooks) {
     const int kind = small_table_kind(L);
     const bool matrix_ok = is_int_table(L->table_dtype) && L->table_packed && L->K <= 16;
-    const bool sparse_ok = matrix_ok && (any_codebooks || L->C % 32 == 0);
+    const bool sparse_ok = matrix_ok && (any_codebooks ? sparse_worthwhile(L->C) : L->C % 32 == 0);
     const bool gather_wins = !matrix_ok || lutnn::gather_preferred(L->table, kind, L->C, L->K, L->M, N, sparse_ok);
     return lutnn::linear_small_preferred(L->table, kind, L->C, L->K, L->V, L->M, N, tree, gather_wins);
 }
@@ -693,17 +698,21 @@ lutnn_status check_tree_conv(const lutnn_tree* tree, const float* input, int64_t
 
 namespace {
 
-// What the calls with a scratch of their own layout run after the encoder, and the stride of the index rows between the
-// two: the sparse lookup wherever the matrix cores are worth it, whatever C (its index rows are padded), or what AUTO stands for.
+// What the calls with a scratch of their own layout run after the encoder, the stride of the index rows between the
+// two, and the bytes of scratch that a row is given: the sparse lookup wherever the matrix cores are worth it, whatever C
+// (its index rows are padded), or what AUTO stands for.
 struct TwoStep {
     int variant;
-    int64_t ldi;
+    int64_t ldi, row_bytes;
 };
 TwoStep two_step(const lutnn_layer* L, int64_t N) {
     const bool matrix = is_int_table(L->table_dtype) && L->table_packed && L->K <= 16 &&
-                        !lutnn::gather_preferred(L->table, L->table_dtype == LUTNN_TABLE_I4 ? 2 : 1, L->C, L->K, L->M, N, true);
-    if (matrix) return {LUTNN_VARIANT_SMFMAC, lutnn::smfmac_index_stride(L->C)};
-    return {LUTNN_VARIANT_LDS, L->C};
+                        !lutnn::gather_preferred(L->table, L->table_dtype == LUTNN_TABLE_I4 ? 2 : 1, L->C, L->K, L->M, N,
+                                                 sparse_worthwhile(L->C));
+    const int64_t padded = lutnn::smfmac_index_stride(L->C);
+    if (matrix && sparse_worthwhile(L->C)) return {LUTNN_VARIANT_SMFMAC, padded, padded};
+    if (matrix) return {LUTNN_VARIANT_MFMA, L->C, padded};
+    return {LUTNN_VARIANT_LDS, L->C, L->C};
 }
 
 // Checks and runs the two steps; encode(IndexRows) launches the first.
@@ -711,7 +720,7 @@ template <class Encode>
 lutnn_status run_two_step(const lutnn_layer* L, int64_t N, float* Y, int64_t ldy, void* scratch, size_t scratch_bytes,
                           hipStream_t s, const char* what, Encode&& encode) {
     const TwoStep two = two_step(L, N);
-    if (lutnn_status st = check_scratch(scratch, scratch_bytes, (size_t)N * two.ldi)) return st;
+    if (lutnn_status st = check_scratch(scratch, scratch_bytes, (size_t)N * two.row_bytes)) return st;
     uint8_t* idx = static_cast<uint8_t*>(scratch);
     // MFMA: what SMFMAC needs but for the dense index matrix's own conditions
     const int needs = two.variant == LUTNN_VARIANT_SMFMAC ? LUTNN_VARIANT_MFMA : two.variant;
@@ -726,7 +735,7 @@ extern "C" {
 
 size_t lutnn_linear_scratch_bytes(const lutnn_layer* layer, int64_t N, int32_t tree) {
     if (check_layer(layer) != LUTNN_OK || N <= 0 || N >= kMaxRows || small_preferred(layer, N, tree != 0, true)) return 0;
-    return (size_t)N * two_step(layer, N).ldi;
+    return (size_t)N * two_step(layer, N).row_bytes;
 }
 
 lutnn_status lutnn_linear_scratch(const lutnn_layer* layer, const float* X, int64_t N, int64_t ldx, float* Y, int64_t ldy,
@@ -769,7 +778,7 @@ int32_t lutnn_scratch_variant(const lutnn_layer* layer, int64_t N, int32_t call)
 
 size_t lutnn_conv2d_scratch_bytes(const lutnn_layer* layer, int64_t N) {
     if (check_layer(layer) != LUTNN_OK || N <= 0 || N >= kMaxRows) return 0;
-    return (size_t)N * two_step(layer, N).ldi;
+    return (size_t)N * two_step(layer, N).row_bytes;
 }
 
 lutnn_status lutnn_conv2d_scratch(const lutnn_layer* layer, const float* input, int64_t B, const lutnn_conv2d_geom* geom,

@@ -41,6 +41,8 @@ def test_the_variant_that_runs():
             for tree in (0, 1):
                 v, n = f(layer(C=C), N, tree), bytes_of(layer(C=C), N, tree)
                 assert n == {FUSED: 0, SMFMAC: N * ((C + 31) // 32 * 32), LDS: N * C}[v]
+    MFMA = lut.binding.VARIANT_MFMA
+    assert [f(layer(C=C), 20000, call) for call in (0, 1, 2) for C in (1, 8, 9)] == [MFMA, MFMA, SMFMAC] * 3
     assert f(layer(), 0, 0) == f(None, 10, 0) == f(layer(C=0), 10, 0) == f(layer(), 10, 3) == -1
 
 
