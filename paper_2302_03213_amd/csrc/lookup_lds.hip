@@ -227,7 +227,8 @@ bool gather_preferred_t(int C, int K, int M, int64_t N, bool sparse_ok) {
     const int64_t col_chunks = (M + chunk - 1) / chunk;
     if (M >= chunk && C >= kSplitMinCodebooks && N <= 32 && N * col_chunks < kSplitMaxWaves) return true;
     // Otherwise price both (ms per call, fitted to sweeps of 32-2048 rows over seventeen layer
-    // shapes; the rule picks the faster form or ties on all of them).  The gather costs its
+    // shapes, and of 2-60000 rows of 1-700 codebooks and 4-4096 columns: the form taken needs 1.001 to 1.016 times the faster one's
+    // time on average).  The gather costs its
     // N*C*M entry reads; a matrix-core launch costs its pipeline fill and the serial walk over the
     // codebooks - far longer per codebook on the dense kernel, which runs where the sparse one
     // cannot (C % 32 != 0 or unaligned indices).  From 512 codebooks on the sparse kernel shares
@@ -238,7 +239,7 @@ bool gather_preferred_t(int C, int K, int M, int64_t N, bool sparse_ok) {
     // (Outputs cost the gather more than the matrix forms, which have whole tiles to write: 1311 rows x 2 codebooks, M =
     // 3436, INT4 18.5 us and 11.9, whole calls.)
     const double t_gather = 0.0038 + 8.9e-11 * entries + (std::is_same<Table, TableI4>::value ? 1.9e-9 : 5e-10) * (double)N * M;
-    const double t_matrix = sparse_ok ? 0.0065 + 1.6e-5 * C : 0.0062 + 1.2e-4 * C;
+    const double t_matrix = sparse_ok ? 0.0065 + 1.6e-5 * C : 0.0074 + 1.42e-4 * C + 2.2e-11 * entries;
     return t_gather < t_matrix;
 }
 
