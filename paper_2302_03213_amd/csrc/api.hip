@@ -725,7 +725,7 @@ lutnn_status run_two_step(const lutnn_layer* L, int64_t N, float* Y, int64_t ldy
     // MFMA: what SMFMAC needs but for the dense index matrix's own conditions
     const int needs = two.variant == LUTNN_VARIANT_SMFMAC ? LUTNN_VARIANT_MFMA : two.variant;
     if (lutnn_status st = check_lookup(L, needs, idx, Y, N, ldy)) return st;
-    if (lutnn_status st = hip_result(encode(lutnn::IndexRows{idx, two.ldi}), what)) return st;
+    if (lutnn_status st = hip_result(encode(lutnn::IndexRows{idx, (int)two.ldi}), what)) return st;
     return do_lookup(L, two.variant, idx, two.ldi, N, Y, ldy, s);
 }
 

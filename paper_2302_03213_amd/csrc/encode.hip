@@ -60,7 +60,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_tile_kernel(const float* _
         const int c = c0 + 4 * j;
         if (row0 + r >= N || c >= C) continue;
         const uint32_t wv = is[i];
-        uint8_t* dst = idx.rows + (row0 + r) * idx.ld + c;
+        uint8_t* dst = idx.rows + (row0 + r) * (int64_t)idx.ld + c;
         if (idx_dword_ok) {  // aligned rows of whole dwords
             *reinterpret_cast<uint32_t*>(dst) = wv;
         } else {
@@ -170,7 +170,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_conv9_band_kernel(
         const int c = c0 + 4 * j;
         if (r >= rows || c >= C) continue;
         const uint32_t wv = is[i];
-        uint8_t* dst = idx.rows + (n0 + r) * idx.ld + c;
+        uint8_t* dst = idx.rows + (n0 + r) * (int64_t)idx.ld + c;
         if (idx_dword_ok) {
             *reinterpret_cast<uint32_t*>(dst) = wv;
         } else {
@@ -209,7 +209,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_generic_kernel(const float
             best = k;
         }
     }
-    idx.rows[n * idx.ld + c] = (uint8_t)best;
+    idx.rows[n * (int64_t)idx.ld + c] = (uint8_t)best;
 }
 
 template <int V, int CT, int CONV = 0>

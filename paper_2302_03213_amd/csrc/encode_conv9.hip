@@ -414,7 +414,7 @@ __global__ __launch_bounds__(kEncThreads, NI > 5 ? 3 : 4) void encode_conv9_filt
         }
         // each lane stores its row's four bytes
         if (now.p0 + lane <= now.p1) {
-            uint8_t* dst = idx.rows + (n0 + lane) * idx.ld + channel;
+            uint8_t* dst = idx.rows + (n0 + lane) * (int64_t)idx.ld + channel;
             if (idx_dword_ok) {
                 if (channel < C) *reinterpret_cast<uint32_t*>(dst) = packed;
             } else {

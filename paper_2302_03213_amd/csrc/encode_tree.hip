@@ -97,7 +97,7 @@ __device__ __forceinline__ void write_index_rows(const uint32_t* __restrict__ is
         const int c = c0 + 4 * j;
         if (row0 + r >= N || c >= C) continue;
         const uint32_t wv = is[i];
-        uint8_t* dst = idx.rows + (row0 + r) * idx.ld + c;
+        uint8_t* dst = idx.rows + (row0 + r) * (int64_t)idx.ld + c;
         if (idx_dword_ok) {  // aligned rows of whole dwords
             *reinterpret_cast<uint32_t*>(dst) = wv;
         } else {

@@ -41,7 +41,7 @@ struct ConvGeom {
 // sparse lookup reads for itself are padded to 32 bytes, their bytes past C unspecified.
 struct IndexRows {
     uint8_t* rows;
-    int64_t ld;
+    int ld;
     // indices of four codebooks leave as one dword
     bool dwords(int C) const {
         return ld % 4 == 0 && ld >= ((C + 3) & ~3) && (reinterpret_cast<uintptr_t>(rows) & 3) == 0;
