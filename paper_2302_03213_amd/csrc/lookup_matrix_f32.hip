@@ -14,8 +14,8 @@
 // the vector instructions that cut the table and build the one-hot operand (about 300 per wavefront and stage) beside 24
 // matrix instructions: 1.4 us a stage and workgroup, which is no less with two workgroups on the compute unit.  Against the
 // other forms (rows read from L2 by every row; staged in LDS for 256 rows), lookup alone: 1000 rows x 192 codebooks, M = 3072
-// 398 -> 84 us; 4096 x 192, M = 768 374 -> 85; 14000 x 64, M = 150 121 -> 35; 14000 x 16, M = 3072 145 -> 98.  At 4096 x 192,
-// M = 3072 the staged form is as fast (189 and 192).  The table is cut where it is staged, so no second copy of it exists.
+// 81 us (253 and 161); 4096 x 192, M = 768 81 (118 and 138); 4096 x 192, M = 3072 172 (1064 and 185); 4096 x 700, M = 768 262
+// (622 and 581).  Few columns leave the gather ahead: 14000 x 64, M = 150 34 (30).  The table is cut where it is staged, so no second copy of it exists.
 //
 // Layout (lane = 32 h + l): A values 0-3 are k 8h .. 8h+7 of the first codebook of a pair, values 4-7 those of the second,
 // two stored values to four k, their positions in bits 2t of the index word; B, column l, is all 16 k of codebook h.
